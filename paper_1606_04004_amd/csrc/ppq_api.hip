@@ -118,7 +118,7 @@ struct ppq_ctx {
     // built operator (device)
     double *T64[MAXD]{};   // real factor per DVR dimension (kinetic), nb x nb
     float *T32[MAXD]{};
-    float *T32p[MAXD]{};   // factors zero-padded to 64 x 64 (matrix-core tiles)
+    float *T32p[MAXD]{};   // factors zero-padded to 64 x 64, column-major (matrix-core tiles)
     double *T64p[MAXD]{};
     double2 *H64p[MAXD]{};
     float2 *H32p[MAXD]{};
@@ -656,14 +656,17 @@ void build_operator(ppq_ctx *c)
     dfree(c->pot_tabs);
     const int D = c->g.D;
     hipStream_t s = c->stream;
-    auto pad_upload = [&](const std::vector<cd> &h, int n, int b, double2 **d64, float2 **d32) {
+    // transpose: column-major (matrix-core tiles, whose lanes read down a column)
+    auto pad_upload = [&](const std::vector<cd> &h, int n, int b, double2 **d64, float2 **d32,
+                          bool transpose = false) {
         std::vector<double2> P((size_t)b * b, make_double2(0.0, 0.0));
         std::vector<float2> Pf((size_t)b * b, make_float2(0.f, 0.f));
         for (int i = 0; i < n; ++i)
             for (int j = 0; j < n; ++j) {
                 cd v = h[(size_t)i * n + j];
-                P[(size_t)i * b + j] = make_double2(v.real(), v.imag());
-                Pf[(size_t)i * b + j] = make_float2((float)v.real(), (float)v.imag());
+                const size_t at = transpose ? (size_t)j * b + i : (size_t)i * b + j;
+                P[at] = make_double2(v.real(), v.imag());
+                Pf[at] = make_float2((float)v.real(), (float)v.imag());
             }
         *d64 = upload(P, s);
         *d32 = upload(Pf, s);
@@ -754,8 +757,8 @@ void build_operator(ppq_ctx *c)
             std::vector<double> D64((size_t)64 * 64, 0.0);
             for (int i = 0; i < n; ++i)
                 for (int j = 0; j < n; ++j) {
-                    P64[(size_t)i * 64 + j] = (float)T[(size_t)i * n + j];
-                    D64[(size_t)i * 64 + j] = T[(size_t)i * n + j];
+                    P64[(size_t)j * 64 + i] = (float)T[(size_t)i * n + j];
+                    D64[(size_t)j * 64 + i] = T[(size_t)i * n + j];
                 }
             c->T32p[k] = upload(P64, s);
             c->T64p[k] = upload(D64, s);
@@ -943,7 +946,7 @@ void build_operator(ppq_ctx *c)
             int n = c->g.n[k];
             std::vector<cd> ht = similarity(L[k], Hk[k], n);
             pad_upload(ht, n, c->nb[k], &c->H64[k], &c->H32[k]);
-            if (n <= NMAX_MASK) pad_upload(ht, n, 64, &c->H64p[k], &c->H32p[k]);
+            if (n <= NMAX_MASK) pad_upload(ht, n, 64, &c->H64p[k], &c->H32p[k], true);
         }
     }
     // dense factors of the product terms, unpadded (nb x nb) and as 64 x 64
@@ -957,7 +960,7 @@ void build_operator(ppq_ctx *c)
         c->F32.push_back(d32);
         d64 = nullptr;
         d32 = nullptr;
-        if (n <= NMAX_MASK) pad_upload(fmats[i], n, 64, &d64, &d32);
+        if (n <= NMAX_MASK) pad_upload(fmats[i], n, 64, &d64, &d32, true);
         c->F64p.push_back(d64);
         c->F32p.push_back(d32);
     }

@@ -205,7 +205,7 @@ int hpsi_acc_f32(const FiberPass &fp, const float *T, const float2 *x, float2 *y
 constexpr int64_t DOT_BLOCKS_MAX = (int64_t)RED_BLOCKS * PSTRIDE_H;
 // Krylov reduction of nb per-block partials of one value (mode RED_H1 or RED_DELAY)
 void finalize_dot(const double2 *partial, int nb, KState *ks, int j, int m, int mode, hipStream_t s);
-// matrix-core forms (v_mfma_*_16x16x4); T64 / H64 are h zero-padded to 64 x 64
+// matrix-core forms (v_mfma_*_16x16x4); T64 / H64 are h zero-padded to 64 x 64, column-major
 void hpsi_mfma_f32(const FiberPass &fp, const float *T64, const float2 *x, const float *V, float2 *y, bool first,
                    const int *skip_if, int skip_j, hipStream_t s);
 void hpsi_mfma_f64(const FiberPass &fp, const double *T64, const double2 *x, const double *V, double2 *y, bool first,
@@ -323,7 +323,7 @@ struct CInput32 {
 };
 void hpsi_cplx_f32(const FiberPass &fp, const float2 *H, const CInput32 &in, float2 *y, bool accumulate,
                    const float *V, const int *skip_if, int skip_j, hipStream_t s);
-// complex factors on the matrix cores: y (= or +=) h (sum_i c_i x_i), h padded to 64 x 64
+// complex factors on the matrix cores: y (= or +=) h (sum_i c_i x_i), h padded to 64 x 64, column-major
 void hpsi_cmfma_f64(const FiberPass &fp, const double2 *H64, const CInput &in, double2 *y, bool accumulate,
                     const int *skip_if, int skip_j, hipStream_t s);
 void hpsi_cmfma_f32(const FiberPass &fp, const float2 *H64, const CInput32 &in, float2 *y, bool accumulate,
