@@ -228,7 +228,6 @@ struct ppq_ctx {
     std::vector<void *> zbuf;  // intermediates of product terms
     KState *ks = nullptr;
     double2 *partial = nullptr;
-    unsigned *counter = nullptr;
 
     // reference packet
     bool has_ref = false;
@@ -1305,7 +1304,7 @@ double2 *fused_dot_partial(const ppq_ctx *c)
 {
     if (!c->dot_want || c->g.D < 2) return nullptr;
     const int64_t nb = (c->nf[0] + 255) / 256;
-    return nb <= DOT_BLOCKS_MAX ? c->partial : nullptr;
+    return nb <= DOT_BLOCKS_MAX ? c->partial + KRY_DOTS : nullptr;
 }
 
 // y = P H_1 P x: the one-dimensional factors and the diagonal potential
@@ -1681,13 +1680,13 @@ void mark(ppq_ctx *c, int phase)
 // Lanczos/Arnoldi basis of `src` (FP64 master vector on the current set) in
 // Vb with the small matrix and norm in ks; m H-applications, CGS2.
 // tol > 0: the order is chosen per step by the error estimate (the adjoint's
-// recorded steps use the full order)
+// recorded steps use the full order).
+// expv: also the coefficients of exp(-i H dt) src, and a full-order step's last
+// vector stays provisional in memory with its correction folded into them;
+// without it every basis vector is left corrected (the adjoint reads the basis).
 template <class C>
-// fix_last: leave every basis vector corrected in memory (the adjoint reads the
-// basis); otherwise a full-order step's last vector stays provisional and
-// lanczos_coef folds its correction into the coefficients.
 void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, double dt = 0.0, double tol = 0.0,
-                  bool fix_last = true)
+                  bool expv = false)
 {
     hipStream_t s = c->stream;
     const int64_t n = c->nact;
@@ -1695,42 +1694,26 @@ void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, doub
     C *w = (C *)c->wk;
     const int *meff = &ks->meff;
     const bool herm = c->hermitian;
-    norm0<C>(src, n, c->partial, c->counter, ks, m, dt, tol, s);
-    normalise_from_master<C>(src, n, ks, Vb, s);
-    if (herm) {
-        // Lanczos with the second Gram-Schmidt pass of each vector applied in
-        // the next step's sweep: H is applied to the provisional q_j in slot
-        // j, <q_j|H q_j> comes from the product's last pass where it can,
-        // and one sweep per step corrects v_j and forms q_{j+1}
-        for (int j = 0; j < m; ++j) {
-            C *qj = Vb + (int64_t)j * ld;
-            mark(c, PPQ_PHASE_HPSI);
-            c->dot_want = true;
-            apply_internal(c, qj, w, meff, j);
-            c->dot_want = false;
-            const int fused = c->dot_nb;
-            mark(c, PPQ_PHASE_KRYLOV);
-            if (fused) finalize_dot(c->partial, fused, ks, j, m, RED_DELAY, s);
-            else cgs_dots<C>(qj, ld, 1, w, n, c->partial, c->counter, ks, j, m, j, s, RED_DELAY);
-            if (j == m - 1) {
-                if (j > 0 && fix_last) lanczos_fix<C>(Vb, ld, n, ks, j, s);
-                break;
-            }
-            lanczos_sweep<C>(Vb, ld, w, n, c->partial, c->counter, ks, j, m, s);
-        }
-        return;
-    }
-    // Arnoldi with the same delayed second pass: H is applied to the
-    // provisional q_j, the first-pass column of H v_j follows from the Arnoldi
-    // relation, and one sweep corrects v_j and forms q_{j+1}
+    kry_start<C>(src, n, c->partial, ks, m, dt, tol, Vb, s);
+    // The second Gram-Schmidt pass of each vector is applied in the next step's
+    // sweep: H acts on the provisional q_j in slot j, <q_j|H q_j> comes from the
+    // product's last pass where it can, and one sweep per step corrects v_j and
+    // forms q_{j+1}
     for (int j = 0; j < m; ++j) {
-        const C *qj = Vb + (int64_t)j * ld;
+        C *qj = Vb + (int64_t)j * ld;
         mark(c, PPQ_PHASE_HPSI);
+        c->dot_want = herm;
         apply_internal(c, qj, w, meff, j);
+        c->dot_want = false;
+        int nbd = c->dot_nb;
         mark(c, PPQ_PHASE_KRYLOV);
-        const bool last = (j == m - 1);
-        arnoldi_step<C>(Vb, ld, w, n, c->partial, c->counter, ks, j, m, last, s);
-        if (last && j > 0 && fix_last) lanczos_fix<C>(Vb, ld, n, ks, j, s);
+        if (nbd == 0) nbd = kry_dots<C>(Vb, ld, w, n, c->partial, ks, j, !herm, s);
+        if (j < m - 1) {
+            kry_sweep<C>(Vb, ld, w, n, c->partial, nbd, ks, j, !herm, s);
+            continue;
+        }
+        kry_close(ks, m, c->partial, n, nbd, dt, herm, expv, expv, s);
+        if (!expv && j > 0) kry_fix_last<C>(Vb, ld, n, ks, j, s);
     }
 }
 
@@ -1739,9 +1722,7 @@ void step_impl(ppq_ctx *c, double dt, int m, double tol)
 {
     mark(c, PPQ_PHASE_KRYLOV);
     C *Vb = (C *)c->Vk;
-    krylov_build<C>(c, c->psi[c->cur], Vb, c->ks, m, dt, tol, false);
-    krylov_expv(c->ks, m, dt, c->hermitian ? 1 : 0, c->stream);
-    lanczos_coef(c->ks, m, c->stream);
+    krylov_build<C>(c, c->psi[c->cur], Vb, c->ks, m, dt, tol, true);
     lincomb<C>(Vb, c->cap, c->psi[c->cur], c->nact, c->ks, c->psi_tmp, c->stream);
     std::swap(c->psi[c->cur], c->psi_tmp);
 }
@@ -1930,11 +1911,11 @@ void energy_into(ppq_ctx *c, int64_t r)
         // FP32 form: H acts on the FP32 copy; the inner product is accumulated in FP64
         float2 *x32 = (float2 *)c->Vk;
         KState *ks = c->ks;
-        norm0<float2>(c->psi[c->cur], c->nact, c->partial, c->counter, ks, 1, 0.0, 0.0, c->stream);
-        normalise_from_master<float2>(c->psi[c->cur], c->nact, ks, x32, c->stream);
+        kry_start<float2>(c->psi[c->cur], c->nact, c->partial, ks, 1, 0.0, 0.0, x32, c->stream);
         apply_internal(c, x32, c->wk, nullptr, 0);
-        cgs_dots<float2>(x32, c->cap, 1, (const float2 *)c->wk, c->nact, c->partial, c->counter, ks, 0, 1, 0,
-                         c->stream);
+        const int nbd = kry_dots<float2>(x32, c->cap, (const float2 *)c->wk, c->nact, c->partial, ks, 0, false,
+                                         c->stream);
+        kry_close(ks, 1, c->partial, c->nact, nbd, 0.0, true, false, false, c->stream);
         copy_alpha0(ks, rec + PPQ_OBS_ENERGY, c->stream);
         return;
     }
@@ -2213,7 +2194,7 @@ void adjoint_backward(ppq_ctx *c, double2 C_N)
                     adj_accumulate(c->partial, c->nparam, make_double2(0.0, -h), c->dC, s);
                 }
                 // lambda = exp(+i H h) mu
-                krylov_expv(c->ks_b, m, -h, 1, s);
+                kry_close(c->ks_b, m, c->partial, nn, 0, -h, true, true, false, s);
                 lincomb<C>((const C *)c->Wk, c->cap, c->mu, nn, c->ks_b, c->lam, s);
                 if (j > 0) std::swap(c->mu, c->lam);
             }
@@ -2335,9 +2316,7 @@ int ppq_create(ppq_ctx **out, int device, void *hip_stream, int precision)
         void *p = nullptr;
         ck(hipMalloc(&p, sizeof(KState)), "kstate");
         c->ks = (KState *)p;
-        c->partial = dalloc<double2>((int64_t)RED_BLOCKS * PSTRIDE_H);
-        c->counter = dalloc<unsigned>(4);
-        ck(hipMemset(c->counter, 0, 4 * sizeof(unsigned)), "counter");
+        c->partial = dalloc<double2>(PARTIAL_VALUES);
         c->small = dalloc<uint32_t>(4 * MAXD);  // fiber counts, scan totals, block counters
         c->count = dalloc<unsigned long long>(2);
         ck(hipHostMalloc((void **)&c->h_small, sizeof(uint32_t) * 4 * MAXD, hipHostMallocDefault), "pinned");
@@ -2369,7 +2348,6 @@ void ppq_destroy(ppq_ctx *c)
     dfree(c->kbm);
     dfree(c->ks);
     dfree(c->partial);
-    dfree(c->counter);
     for (auto &p : c->full) dfree(p);
     dfree(c->sub_meff);
     if (c->h_sub_meff) (void)hipHostFree(c->h_sub_meff);
@@ -3325,8 +3303,7 @@ int ppq_time_apply(ppq_ctx *c, int nrep, double *ms_median, double *ms_mean)
         ensure_krylov(c, std::max(c->kv_m, 1));
         const void *x = c->psi[c->cur];
         if (c->precision == PPQ_FP32) {
-            norm0<float2>(c->psi[c->cur], c->nact, c->partial, c->counter, c->ks, 1, 0.0, 0.0, c->stream);
-            normalise_from_master<float2>(c->psi[c->cur], c->nact, c->ks, (float2 *)c->Vk, c->stream);
+            kry_start<float2>(c->psi[c->cur], c->nact, c->partial, c->ks, 1, 0.0, 0.0, (float2 *)c->Vk, c->stream);
             x = c->Vk;
         }
         apply_internal(c, x, c->wk, nullptr, 0);

@@ -53,9 +53,8 @@ struct KState {
     double2 h1[MAXM * MAXM];   // Hessenberg, first Gram-Schmidt pass  [i*MAXM + j]
     double2 h2[MAXM * MAXM];   // second pass
     double2 y[MAXM];           // coefficients of the propagated vector
-    double2 cc[MAXM];          // delayed correction: H v_j = (H q_j - sum_k cc_k v_k) / beta_{j-1}
-    double inv_b;              // 1 / beta_{j-1} for the provisional q_j
-    double est;                // error estimate of the current order: n0 dt^k/k! prod beta_i
+    double inv_b;              // 1 / beta_{j-1} of the last order's provisional vector
+    double est[MAXM + 1];      // error estimate of order k: n0 dt^k/k! prod beta_i
     double kdt, ktol;          // step and order tolerance of this step (ktol 0: full order)
     int meff;                  // Krylov dimension actually built
     int pad;
@@ -201,10 +200,8 @@ int hpsi_acc_f64(const FiberPass &fp, const double *T, const double2 *x, double2
                  hipStream_t s, double2 *dotp = nullptr);
 int hpsi_acc_f32(const FiberPass &fp, const float *T, const float2 *x, float2 *y, const int *skip_if, int skip_j,
                  hipStream_t s, double2 *dotp = nullptr);
-// blocks of a fused <x|y> the shared partial buffer holds (RED_BLOCKS * PSTRIDE_H)
-constexpr int64_t DOT_BLOCKS_MAX = (int64_t)RED_BLOCKS * PSTRIDE_H;
-// Krylov reduction of nb per-block partials of one value (mode RED_H1 or RED_DELAY)
-void finalize_dot(const double2 *partial, int nb, KState *ks, int j, int m, int mode, hipStream_t s);
+// blocks of a fused <x|y> the next kernel's prologue sums
+constexpr int64_t DOT_BLOCKS_MAX = 4096;
 // matrix-core forms (v_mfma_*_16x16x4); T64 / H64 are h zero-padded to 64 x 64, column-major
 void hpsi_mfma_f32(const FiberPass &fp, const float *T64, const float2 *x, const float *V, float2 *y, bool first,
                    const int *skip_if, int skip_j, hipStream_t s);
@@ -342,48 +339,41 @@ void diag_scale(const uint32_t *keys, const C *x, int64_t n, const GridDesc &g, 
                 unsigned use, double2 w, C *y, bool acc, const int *skip_if, int skip_j, hipStream_t s);
 
 // Krylov vector kernels. V_i = Vb + i*ld (elements); C is double2 or float2.
-// Reductions write per-block partials; one finalising block sums them in a
-// fixed order (run-to-run deterministic) and updates KState.
-// RED_H1: first-pass dots into h1[.][j] (alpha_j from the diagonal one).
-// RED_BETA: second-pass dots into h2[.][j], then beta_j from the last value,
-// |q_{j+1}|^2, less their squares, and the order's error estimate.
-// RED_DELAY: Hermitian step with delayed correction, r[0] = <q_j|H q_j> of the
-// provisional vector; sets alpha_j, cc and inv_b (see k_lanczos_sweep).
-// RED_ADELAY: the same for an Arnoldi step, r[i] = <v_i|H q_j> (i < j) and
-// r[j] = <q_j|H q_j>; sets the first-pass column h1[.][j], cc and inv_b.
-enum ReduceMode { RED_NORM0 = 0, RED_H1 = 1, RED_BETA = 2, RED_DELAY = 3, RED_ADELAY = 4 };
+// Reductions write per-block partials, which the next kernel sums in a fixed
+// order in its prologue (run-to-run deterministic) and stores in KState (see
+// ppq_krylov.hip).  partial: two alternating areas of KRY_SLOTS values for the
+// sweeps, then KRY_DOTS_VALUES for the dots of a product.
+constexpr int KRY_BLOCKS = 512;      // blocks of a sweep or dot kernel at most
+constexpr int KRY_SLOTS = MAXM + 2;
+constexpr int64_t KRY_DOTS = (int64_t)2 * KRY_SLOTS * RED_BLOCKS;
+constexpr int64_t KRY_DOTS_VALUES = (int64_t)MAXM * RED_BLOCKS;
+constexpr int64_t PARTIAL_VALUES = KRY_DOTS + KRY_DOTS_VALUES;
+static_assert(PARTIAL_VALUES >= (int64_t)RED_BLOCKS * PSTRIDE_H, "partial sums of the other reductions");
+int kry_blocks(int64_t n);  // blocks of the Krylov kernels for n points
+// v0 = psi / |psi| and the start of KState (order limit m, |dt|, tolerance)
 template <class C>
-void norm0(const double2 *psi, int64_t n, double2 *partial, unsigned *counter, KState *ks, int m, double dt,
-           double tol, hipStream_t s);
+void kry_start(const double2 *psi, int64_t n, double2 *partial, KState *ks, int m, double dt, double tol, C *v0,
+               hipStream_t s);
+// Step j: the dots of z = H q_j (q_j in slot j) where the product has not left
+// them itself, <q_j|z> (Arnoldi: <v_i|z>, i < j, before it); returns the number
+// of blocks.  Then the sweep (see k_sweep), given the dots' block count.
 template <class C>
-void cgs_dots(const C *Vb, int64_t ld, int nv, const C *w, int64_t n, double2 *partial, unsigned *counter, KState *ks,
-              int j, int m, int ioff, hipStream_t s, int mode = RED_H1);
-// Hermitian Lanczos step j with the second Gram-Schmidt pass delayed by one
-// step (see k_lanczos_sweep): corrects v_j in its slot, writes the provisional
-// q_{j+1} to slot j+1 and reduces <v_i|q_{j+1}> (i <= j) and |q_{j+1}|^2
-// into h2[.][j] and beta_j.  lanczos_fix corrects the last vector alone.
+int kry_dots(const C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, const KState *ks, int j, bool arnoldi,
+             hipStream_t s);
 template <class C>
-void lanczos_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, unsigned *counter, KState *ks, int j,
-                   int m, hipStream_t s);
+void kry_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, int nbd, KState *ks, int j, bool arnoldi,
+               hipStream_t s);
+// corrects the last vector (slot j > 0) of a step that ran to its full order
 template <class C>
-void lanczos_fix(C *Vb, int64_t ld, int64_t n, const KState *ks, int j, hipStream_t s);
-// Arnoldi step j with the second pass delayed: the dots <v_i|z> (i < j) and
-// <q_j|z> of z = H q_j (RED_ADELAY), then one sweep that corrects v_j, forms
-// q_{j+1} = H v_j - sum_{i<=j} h1_ij v_i and reduces its second-pass dots and
-// norm (RED_BETA); `last`: the first reduction only (the step's last column)
-template <class C>
-void arnoldi_step(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, unsigned *counter, KState *ks, int j,
-                  int m, bool last, hipStream_t s);
-// after the exponential: fold the last vector's pending correction into the
-// coefficients y of a step that ran to its full order m (for a recombination
-// that reads the provisional last vector)
-void lanczos_coef(KState *ks, int m, hipStream_t s);
-template <class C>
-void normalise_from_master(const double2 *psi, int64_t n, KState *ks, C *v0, hipStream_t s);
+void kry_fix_last(C *Vb, int64_t ld, int64_t n, const KState *ks, int j, hipStream_t s);
+// Ends a step: the scalars of order m - 1 from its dots (nbd > 0), the
+// exponential's coefficients (expv), the last vector's pending correction folded
+// into them (fold; for a recombination that reads the provisional last vector).
+void kry_close(KState *ks, int m, const double2 *partial, int64_t n, int nbd, double dt, bool hermitian, bool expv,
+               bool fold, hipStream_t s);
 template <class C>
 void lincomb(const C *Vb, int64_t ld, const double2 *psi_master, int64_t n, const KState *ks, double2 *psi_out,
              hipStream_t s);
-void krylov_expv(KState *ks, int m, double dt, int hermitian, hipStream_t s);
 
 // observables
 void obs_partial(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, const double2 *bra,

@@ -3,26 +3,11 @@
 // The fiber contraction kernels live in ppq_hpsi.hip.
 #include <algorithm>
 
-#include "ppq_internal.hpp"
+#include "ppq_device.hpp"
 
 namespace ppq {
 
 namespace {
-
-constexpr int TB = 256;  // threads per block for streaming kernels
-constexpr int PSTRIDE = 36;  // partial sums per block (Krylov values, adjoint parameters)
-// Per-block partial sums are stored value-major, [value][block]: the one-block
-// final reductions then read every value's partials as contiguous runs, one
-// 1 KB line group per wavefront load, instead of one cache line per lane.
-__device__ inline int64_t pidx(int64_t b, int i) { return (int64_t)i * RED_BLOCKS + b; }
-
-__device__ inline int64_t gid() { return (int64_t)blockIdx.x * blockDim.x + threadIdx.x; }
-
-inline unsigned nblocks(int64_t n, int tb = TB)
-{
-    int64_t b = (n + tb - 1) / tb;
-    return (unsigned)(b < 1 ? 1 : b);
-}
 
 // complex product without contraction: (ac - bd) + i(ad + bc)
 __device__ inline double2 cmul_rn(double2 a, double2 b)
@@ -1026,638 +1011,6 @@ __global__ __launch_bounds__(TB) void k_missing(const T *V, int64_t n, uint32_t 
 }
 
 // ---- Krylov vectors ---------------------------------------------------------------
-__device__ inline double2 ld2(const double2 *p, int64_t i) { return p[i]; }
-__device__ inline double2 ld2(const float2 *p, int64_t i)
-{
-    float2 v = p[i];
-    return make_double2((double)v.x, (double)v.y);
-}
-__device__ inline void st2(double2 *p, int64_t i, double2 v) { p[i] = v; }
-__device__ inline void st2(float2 *p, int64_t i, double2 v) { p[i] = make_float2((float)v.x, (float)v.y); }
-// Streaming forms for the Krylov basis: the sweeps and the recombination
-// stream every earlier basis vector (more than the last-level cache holds),
-// so their loads and the corrected vectors' stores carry the non-temporal
-// hint and leave the cache to the product's tables and vectors.
-typedef double nt_d2 __attribute__((ext_vector_type(2)));
-typedef float nt_f2 __attribute__((ext_vector_type(2)));
-__device__ inline double2 ld2nt(const double2 *p, int64_t i)
-{
-    const nt_d2 v = __builtin_nontemporal_load(reinterpret_cast<const nt_d2 *>(p) + i);
-    return make_double2(v.x, v.y);
-}
-__device__ inline double2 ld2nt(const float2 *p, int64_t i)
-{
-    const nt_f2 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f2 *>(p) + i);
-    return make_double2((double)v.x, (double)v.y);
-}
-__device__ inline void st2nt(double2 *p, int64_t i, double2 v)
-{
-    const nt_d2 w = {v.x, v.y};
-    __builtin_nontemporal_store(w, reinterpret_cast<nt_d2 *>(p) + i);
-}
-__device__ inline void st2nt(float2 *p, int64_t i, double2 v)
-{
-    const nt_f2 w = {(float)v.x, (float)v.y};
-    __builtin_nontemporal_store(w, reinterpret_cast<nt_f2 *>(p) + i);
-}
-// the value a store of v into a C vector holds, without reading it back
-__device__ inline double2 stored(const double2 *, double2 v) { return v; }
-__device__ inline double2 stored(const float2 *, double2 v) { return make_double2((float)v.x, (float)v.y); }
-
-// conj(a) * b accumulated
-__device__ inline void cdot_acc(double2 &acc, double2 a, double2 b)
-{
-    acc.x = fma(a.x, b.x, fma(a.y, b.y, acc.x));
-    acc.y = fma(a.x, b.y, fma(-a.y, b.x, acc.y));
-}
-
-template <int NV>
-__device__ inline void block_reduce_store(double2 (&acc)[NV], double2 *partial)
-{
-    __shared__ double2 red[TB / 64][NV];
-    int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double2 v = acc[i];
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) {
-            v.x += __shfl_xor(v.x, s, 64);
-            v.y += __shfl_xor(v.y, s, 64);
-        }
-        if (lane == 0) red[w][i] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < NV) {
-        double2 s = red[0][threadIdx.x];
-        for (int ww = 1; ww < TB / 64; ++ww) {
-            s.x += red[ww][threadIdx.x].x;
-            s.y += red[ww][threadIdx.x].y;
-        }
-        partial[pidx(blockIdx.x, threadIdx.x)] = s;
-    }
-}
-
-// Final reduction of the per-block partials [value][block] by one block: every
-// value at once, each thread a fixed subset of blocks, then a fixed tree
-// (run-to-run deterministic); then the finaliser `mode` updates KState.
-// (A separate launch: a device-scope fence per block to let the last block
-// finish the sum would write back the L2 of every XCD.)
-template <int NV>
-__global__ __launch_bounds__(TB) void k_finalize(const double2 *partial, int nb, KState *ks, int j, int mode, int m,
-                                                 int ioff, int nvals, double dt, double tol)
-{
-    if (mode != RED_NORM0 && j >= ks->meff) return;
-    // the partials were just written from every XCD: issue all of this
-    // thread's loads before summing them (blocks t, t + TB, ... in order)
-    double2 tot[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) tot[i] = make_double2(0.0, 0.0);
-    constexpr int PER = RED_BLOCKS / TB;
-    static_assert(RED_BLOCKS % TB == 0, "partials per thread");
-    if (nb == RED_BLOCKS) {
-        double2 v[PER][NV];
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-#pragma unroll
-            for (int i = 0; i < NV; ++i) v[u][i] = partial[pidx(threadIdx.x + u * TB, i)];
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                tot[i].x += v[u][i].x;
-                tot[i].y += v[u][i].y;
-            }
-    } else {
-        for (int b = threadIdx.x; b < nb; b += TB) {
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                double2 v = partial[pidx(b, i)];
-                tot[i].x += v.x;
-                tot[i].y += v.y;
-            }
-        }
-    }
-    __shared__ double2 vals[TB / 64][NV];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double2 v = tot[i];
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) {
-            v.x += __shfl_xor(v.x, s, 64);
-            v.y += __shfl_xor(v.y, s, 64);
-        }
-        if (lane == 0) vals[wv][i] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    // Every loop over r runs to the compile-time NV with a predicate: an index
-    // known only at run time would put r in scratch memory.
-    double2 r[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        r[i] = vals[0][i];
-#pragma unroll
-        for (int w2 = 1; w2 < TB / 64; ++w2) {
-            r[i].x += vals[w2][i].x;
-            r[i].y += vals[w2][i].y;
-        }
-    }
-    if (mode == RED_NORM0) {
-        ks->n0 = sqrt(r[0].x);
-        ks->meff = m;
-        ks->est = ks->n0;
-        ks->kdt = fabs(dt);  // the estimate is a magnitude: |dt|^k
-        ks->ktol = tol;
-    } else if (mode == RED_H1) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            if (i < nvals) {
-                ks->h1[(i + ioff) * MAXM + j] = r[i];
-                if (i + ioff == j) ks->alpha[j] = r[i].x;
-            }
-        }
-    } else if (mode == RED_DELAY) {
-        // The provisional q_j = beta_{j-1} v_j + sum_{i<j} h_i v_i with
-        // h_i = h2[i][j-1] (the second pass's coefficients, not yet applied).
-        // From mu = <q_j|H q_j>, using H v_i = beta_i v_{i+1} + alpha_i v_i +
-        // beta_{i-1} v_{i-1} for i < j (all terms beyond O(h^2) kept):
-        //   g_i = <v_i|H q_j> = beta_i <v_{i+1}|q_j> + alpha_i h_i + beta_{i-1} h_{i-1}
-        //   alpha_j = (mu - 2 Re sum conj(h_i) g_i + sum conj(h_i) T_ik h_k) / beta_{j-1}^2
-        //   cc_k = sum_{i<j} T_ki h_i  (k <= j), so H v_j = (H q_j - sum cc_k v_k) / beta_{j-1}
-        // (the step's scalars are loaded at once and cc is summed in registers:
-        // loops run to MAXM with a predicate, so nothing goes to scratch)
-        const double2 mu = r[0];
-        double2 cc[MAXM];
-#pragma unroll
-        for (int k = 0; k < MAXM; ++k) cc[k] = make_double2(0.0, 0.0);
-        if (j == 0) {
-            ks->alpha[0] = mu.x;
-            ks->inv_b = 1.0;
-        } else {
-            const double b = ks->beta[j - 1];
-            const double2 *hh = ks->h2 + (j - 1);  // hh[i * MAXM] = h_i
-            double2 h[MAXM];
-            double al[MAXM], be[MAXM];
-#pragma unroll
-            for (int i = 0; i < MAXM; ++i) {
-                h[i] = i < j ? hh[i * MAXM] : make_double2(0.0, 0.0);
-                al[i] = i < j ? ks->alpha[i] : 0.0;
-                be[i] = i < j ? ks->beta[i] : 0.0;
-            }
-            double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-            for (int i = 0; i < MAXM; ++i) {
-                if (i < j) {
-                    const double2 hi = h[i];
-                    const double2 hn = (i + 1 < j) ? h[(i + 1) % MAXM] : make_double2(b, 0.0);
-                    const double2 hp = (i >= 1) ? h[(i + MAXM - 1) % MAXM] : make_double2(0.0, 0.0);
-                    const double bp = (i >= 1) ? be[(i + MAXM - 1) % MAXM] : 0.0;
-                    const double2 g = make_double2(be[i] * hn.x + al[i] * hi.x + bp * hp.x,
-                                                   be[i] * hn.y + al[i] * hi.y + bp * hp.y);
-                    s1 += hi.x * g.x + hi.y * g.y;  // Re(conj(h_i) g_i)
-                    s2 += al[i] * (hi.x * hi.x + hi.y * hi.y);
-                    if (i + 1 < j) s2 += 2.0 * be[i] * (hi.x * hn.x + hi.y * hn.y);
-                    // cc_k = alpha_k h_k + beta_k h_{k+1} + beta_{k-1} h_{k-1}, gathered per h_i
-                    cc[i].x += al[i] * hi.x;
-                    cc[i].y += al[i] * hi.y;
-                    if (i + 1 < MAXM) {
-                        cc[(i + 1) % MAXM].x += be[i] * hi.x;
-                        cc[(i + 1) % MAXM].y += be[i] * hi.y;
-                    }
-                    if (i >= 1) {
-                        cc[(i + MAXM - 1) % MAXM].x += bp * hi.x;
-                        cc[(i + MAXM - 1) % MAXM].y += bp * hi.y;
-                    }
-                }
-            }
-            ks->alpha[j] = (mu.x - 2.0 * s1 + s2) / (b * b);
-            ks->inv_b = 1.0 / b;
-        }
-#pragma unroll
-        for (int k = 0; k < MAXM; ++k) ks->cc[k] = cc[k];
-    } else if (mode == RED_ADELAY) {
-        // Arnoldi: q_j = beta_{j-1} v_j + sum_{i<j} h_i v_i (h_i = h2[i][j-1]);
-        // H v_i = sum_{k<=i+1} H_ki v_k with H_ki = h1 + h2 (k <= i), beta_i (k = i+1):
-        //   cc_k = sum_{i<j} H_ki h_i, so H v_j = (z - sum_{k<=j} cc_k v_k) / beta_{j-1}
-        //   <v_j|z> = (<q_j|z> - sum_{i<j} conj(h_i) <v_i|z>) / beta_{j-1}
-        //   h1_ij = <v_i|H v_j> = (<v_i|z> - cc_i) / beta_{j-1}   (i <= j)
-        // column j's second-pass terms come from this step's sweep (RED_BETA);
-        // a step's last column keeps only its first pass
-        // (cc is summed in registers; loops run to MAXM with a predicate)
-        double2 cc[MAXM];
-#pragma unroll
-        for (int k = 0; k < MAXM; ++k) {
-            cc[k] = make_double2(0.0, 0.0);
-            ks->h2[k * MAXM + j] = make_double2(0.0, 0.0);
-        }
-        if (j == 0) {
-            ks->h1[0] = r[0];
-            ks->alpha[0] = r[0].x;
-            ks->inv_b = 1.0;
-        } else {
-            const double b = ks->beta[j - 1], ib = 1.0 / b;
-            const double2 *hh = ks->h2 + (j - 1);
-#pragma unroll
-            for (int i = 0; i < MAXM; ++i) {
-                if (i < j) {
-                    const double2 hi = hh[i * MAXM];
-#pragma unroll
-                    for (int k = 0; k <= i; ++k) {
-                        const double2 a1 = ks->h1[k * MAXM + i], a2 = ks->h2[k * MAXM + i];
-                        const double2 hk = make_double2(a1.x + a2.x, a1.y + a2.y);
-                        cc[k].x += hk.x * hi.x - hk.y * hi.y;
-                        cc[k].y += hk.x * hi.y + hk.y * hi.x;
-                    }
-                    if (i + 1 < MAXM) {
-                        const double bi = ks->beta[i];
-                        cc[(i + 1) % MAXM].x += bi * hi.x;
-                        cc[(i + 1) % MAXM].y += bi * hi.y;
-                    }
-                }
-            }
-            // <v_j|z>, r[i] = <v_i|z> for i < j, r[j] = <q_j|z> (loops to NV with a predicate)
-            double2 vz = make_double2(0.0, 0.0);
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                if (i < j) {
-                    const double2 hi = hh[i * MAXM];
-                    vz.x += hi.x * r[i].x + hi.y * r[i].y;  // conj(h_i) r_i
-                    vz.y += hi.x * r[i].y - hi.y * r[i].x;
-                } else if (i == j) {
-                    vz = make_double2((r[i].x - vz.x) * ib, (r[i].y - vz.y) * ib);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                if (i < j) {
-                    ks->h1[i * MAXM + j] = make_double2((r[i].x - cc[i % MAXM].x) * ib, (r[i].y - cc[i % MAXM].y) * ib);
-                } else if (i == j) {
-                    const double2 g = make_double2((vz.x - cc[i % MAXM].x) * ib, (vz.y - cc[i % MAXM].y) * ib);
-                    ks->h1[j * MAXM + j] = g;
-                    ks->alpha[j] = g.x;
-                }
-            }
-            ks->inv_b = ib;
-        }
-#pragma unroll
-        for (int k = 0; k < MAXM; ++k) ks->cc[k] = cc[k];
-    } else {  // RED_BETA: h2[.][j] and beta_j from |q_{j+1}|^2 - sum |h2_i|^2
-        const int nh = nvals - 1;
-        double hh = 0.0, last = 0.0;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            if (i < nh) {
-                ks->h2[i * MAXM + j] = r[i];
-                hh += r[i].x * r[i].x + r[i].y * r[i].y;
-            } else if (i == nh) {
-                last = r[i].x;
-            }
-        }
-        double b2 = last - hh;
-        double b = sqrt(b2 > 0.0 ? b2 : 0.0);
-        ks->beta[j] = b;
-        if (j < m - 1) {
-            if (b < 1e-13) {
-                ks->meff = j + 1;
-            } else {
-                // Park and Light's estimate of the order-(j+1) step: the
-                // first Taylor term the Krylov space leaves out; with a
-                // tolerance, the step stops at the first order within it
-                const double est = ks->est * ks->kdt * b / (double)(j + 1);
-                ks->est = est;
-                if (ks->ktol > 0.0 && est <= ks->ktol) ks->meff = j + 1;
-            }
-        }
-    }
-}
-
-template <class C>
-__global__ __launch_bounds__(TB) void k_norm0(const double2 *psi, int64_t n, double2 *partial, unsigned *counter,
-                                              KState *ks, int m)
-{
-    double2 acc[1] = {make_double2(0.0, 0.0)};
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        double2 a = psi[p];
-        acc[0].x = fma(a.x, a.x, fma(a.y, a.y, acc[0].x));
-    }
-    block_reduce_store<1>(acc, partial);
-}
-
-template <class C, int NV>
-__global__ __launch_bounds__(TB) void k_cgs_dots(const C *Vb, int64_t ld, const C *w, int64_t n, double2 *partial,
-                                                 unsigned *counter, KState *ks, int j, int m, int ioff)
-{
-    if (j >= ks->meff) return;
-    double2 acc[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) acc[i] = make_double2(0.0, 0.0);
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        double2 wv = ld2(w, p);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) cdot_acc(acc[i], ld2(Vb, (int64_t)i * ld + p), wv);
-    }
-    block_reduce_store<NV>(acc, partial);
-}
-
-// Hermitian Lanczos step j with the second Gram-Schmidt pass of each vector
-// delayed to the next step's sweep.  Slot j holds the provisional
-// q_j = beta_{j-1} v_j + sum_{i<j} h_i v_i (first pass only, unnormalised) and
-// z = H q_j; with h_i = h2[i][j-1] and alpha_j, cc from RED_DELAY, one pass
-//   v_j     = (q_j - sum_{i<j} h_i v_i) / beta_{j-1}           -> slot j
-//   H v_j   = (z - sum_{k<j} cc_k v_k - cc_j v_j) / beta_{j-1}
-//   q_{j+1} = H v_j - alpha_j v_j - beta_{j-1} v_{j-1}          -> slot j+1
-// with the partial sums of <v_i|q_{j+1}> (i <= j) and |q_{j+1}|^2: the next
-// second pass's coefficients and, after RED_BETA, beta_j.  In exact arithmetic
-// h = 0 and this is the three-term recurrence; with rounding it applies the
-// same second projection as two separate sweeps would, one step later.
-template <class C, int NV>
-__global__ __launch_bounds__(TB) void k_lanczos_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial,
-                                                      unsigned *counter, KState *ks, int j)
-{
-    if (j >= ks->meff) return;
-    constexpr int NH = NV > 0 ? NV : 1;
-    double2 hq[NH], cc[NV + 1];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) hq[i] = ks->h2[i * MAXM + (j - 1)];
-#pragma unroll
-    for (int k = 0; k <= NV; ++k) cc[k] = ks->cc[k];
-    const double ib = ks->inv_b, al = ks->alpha[j], bm = NV > 0 ? ks->beta[j - 1] : 0.0;
-    C *qs = Vb + (int64_t)j * ld;
-    C *qn = Vb + (int64_t)(j + 1) * ld;
-    double2 acc[NV + 2];
-#pragma unroll
-    for (int i = 0; i < NV + 2; ++i) acc[i] = make_double2(0.0, 0.0);
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        double2 qv = ld2nt(qs, p), hv = ld2nt(z, p);
-        double2 vv[NH];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            vv[i] = ld2nt(Vb, (int64_t)i * ld + p);
-            qv.x -= hq[i].x * vv[i].x - hq[i].y * vv[i].y;
-            qv.y -= hq[i].x * vv[i].y + hq[i].y * vv[i].x;
-            hv.x -= cc[i].x * vv[i].x - cc[i].y * vv[i].y;
-            hv.y -= cc[i].x * vv[i].y + cc[i].y * vv[i].x;
-        }
-        st2nt(qs, p, make_double2(qv.x * ib, qv.y * ib));
-        const double2 vj = stored(qs, make_double2(qv.x * ib, qv.y * ib));
-        hv.x -= cc[NV].x * vj.x - cc[NV].y * vj.y;
-        hv.y -= cc[NV].x * vj.y + cc[NV].y * vj.x;
-        double2 wp = make_double2(hv.x * ib - al * vj.x, hv.y * ib - al * vj.y);
-        if (NV > 0) {
-            wp.x -= bm * vv[NV - 1].x;
-            wp.y -= bm * vv[NV - 1].y;
-        }
-        st2(qn, p, wp);
-        const double2 ws = stored(qn, wp);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) cdot_acc(acc[i], vv[i], ws);
-        cdot_acc(acc[NV], vj, ws);
-        acc[NV + 1].x = fma(ws.x, ws.x, fma(ws.y, ws.y, acc[NV + 1].x));
-    }
-    block_reduce_store<NV + 2>(acc, partial);
-}
-
-// Arnoldi step j, first reduction: <v_i|z> for i < j and <q_j|z> (slot j
-// holds the provisional q_j, z = H q_j).
-template <class C, int NV>
-__global__ __launch_bounds__(TB) void k_arnoldi_dots(const C *Vb, int64_t ld, const C *z, int64_t n,
-                                                     double2 *partial, unsigned *counter, KState *ks, int j)
-{
-    if (j >= ks->meff) return;
-    const C *qs = Vb + (int64_t)j * ld;
-    double2 acc[NV + 1];
-#pragma unroll
-    for (int i = 0; i <= NV; ++i) acc[i] = make_double2(0.0, 0.0);
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        const double2 zv = ld2(z, p);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) cdot_acc(acc[i], ld2nt(Vb, (int64_t)i * ld + p), zv);
-        cdot_acc(acc[NV], ld2(qs, p), zv);
-    }
-    block_reduce_store<NV + 1>(acc, partial);
-}
-
-// Arnoldi step j, the sweep: with h_i = h2[i][j-1], cc, inv_b and the
-// first-pass column h1[.][j] from RED_ADELAY,
-//   v_j     = (q_j - sum_{i<j} h_i v_i) / beta_{j-1}           -> slot j
-//   H v_j   = (z - sum_{k<=j} cc_k v_k) / beta_{j-1}
-//   q_{j+1} = H v_j - sum_{i<=j} h1_ij v_i                       -> slot j+1
-// and the partial sums of <v_i|q_{j+1}> (i <= j) and |q_{j+1}|^2.
-template <class C, int NV>
-__global__ __launch_bounds__(TB) void k_arnoldi_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial,
-                                                      unsigned *counter, KState *ks, int j)
-{
-    if (j >= ks->meff) return;
-    constexpr int NH = NV > 0 ? NV : 1;
-    double2 hq[NH], cc[NV + 1], g1[NV + 1];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) hq[i] = ks->h2[i * MAXM + (j - 1)];
-#pragma unroll
-    for (int k = 0; k <= NV; ++k) {
-        cc[k] = ks->cc[k];
-        g1[k] = ks->h1[k * MAXM + j];
-    }
-    const double ib = ks->inv_b;
-    C *qs = Vb + (int64_t)j * ld;
-    C *qn = Vb + (int64_t)(j + 1) * ld;
-    double2 acc[NV + 2];
-#pragma unroll
-    for (int i = 0; i < NV + 2; ++i) acc[i] = make_double2(0.0, 0.0);
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        double2 qv = ld2nt(qs, p), hv = ld2nt(z, p);
-        double2 vv[NH];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            vv[i] = ld2nt(Vb, (int64_t)i * ld + p);
-            qv.x -= hq[i].x * vv[i].x - hq[i].y * vv[i].y;
-            qv.y -= hq[i].x * vv[i].y + hq[i].y * vv[i].x;
-            hv.x -= cc[i].x * vv[i].x - cc[i].y * vv[i].y;
-            hv.y -= cc[i].x * vv[i].y + cc[i].y * vv[i].x;
-        }
-        st2nt(qs, p, make_double2(qv.x * ib, qv.y * ib));
-        const double2 vj = stored(qs, make_double2(qv.x * ib, qv.y * ib));
-        hv.x -= cc[NV].x * vj.x - cc[NV].y * vj.y;
-        hv.y -= cc[NV].x * vj.y + cc[NV].y * vj.x;
-        double2 wp = make_double2(hv.x * ib, hv.y * ib);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            wp.x -= g1[i].x * vv[i].x - g1[i].y * vv[i].y;
-            wp.y -= g1[i].x * vv[i].y + g1[i].y * vv[i].x;
-        }
-        wp.x -= g1[NV].x * vj.x - g1[NV].y * vj.y;
-        wp.y -= g1[NV].x * vj.y + g1[NV].y * vj.x;
-        st2(qn, p, wp);
-        const double2 ws = stored(qn, wp);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) cdot_acc(acc[i], vv[i], ws);
-        cdot_acc(acc[NV], vj, ws);
-        acc[NV + 1].x = fma(ws.x, ws.x, fma(ws.y, ws.y, acc[NV + 1].x));
-    }
-    block_reduce_store<NV + 2>(acc, partial);
-}
-
-// v_j = (q_j - sum_{i<j} h_i v_i) / beta_{j-1} in slot j: the last vector of a
-// step that ran to its full order (no later sweep corrects it).
-template <class C, int NV>
-__global__ __launch_bounds__(TB) void k_lanczos_fix(C *Vb, int64_t ld, int64_t n, const KState *ks, int j)
-{
-    if (j >= ks->meff) return;
-    double2 hq[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) hq[i] = ks->h2[i * MAXM + (j - 1)];
-    const double ib = ks->inv_b;
-    C *qs = Vb + (int64_t)j * ld;
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        double2 qv = ld2(qs, p);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const double2 v = ld2nt(Vb, (int64_t)i * ld + p);
-            qv.x -= hq[i].x * v.x - hq[i].y * v.y;
-            qv.y -= hq[i].x * v.y + hq[i].y * v.x;
-        }
-        st2(qs, p, make_double2(qv.x * ib, qv.y * ib));
-    }
-}
-
-// A step that ran to its full order m leaves its last vector provisional:
-// v_L = (q_L - sum_{i<L} h_i v_i) / beta_{L-1}, L = m - 1.  The propagated
-// vector sum_k y_k v_k is then sum_{k<L} (y_k - y_L h_k / beta_{L-1}) v_k +
-// (y_L / beta_{L-1}) q_L: the coefficients absorb the correction.
-__global__ void k_lanczos_coef(KState *ks, int m)
-{
-    if (threadIdx.x != 0 || ks->meff != m || m < 2) return;
-    const int L = m - 1;
-    const double2 yl = ks->y[L];
-    const double ib = ks->inv_b;
-    for (int k = 0; k < L; ++k) {
-        const double2 h = ks->h2[k * MAXM + (L - 1)];
-        ks->y[k].x -= ib * (yl.x * h.x - yl.y * h.y);
-        ks->y[k].y -= ib * (yl.x * h.y + yl.y * h.x);
-    }
-    ks->y[L] = make_double2(yl.x * ib, yl.y * ib);
-}
-
-template <class C>
-__global__ void k_normalise(const double2 *psi, int64_t n, const KState *ks, C *v0)
-{
-    double s = 1.0 / ks->n0;
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * blockDim.x) {
-        double2 a = ld2nt(psi, p);
-        st2(v0, p, make_double2(a.x * s, a.y * s));
-    }
-}
-
-template <class C>
-__global__ void k_lincomb(const C *Vb, int64_t ld, const double2 *psi_master, int64_t n, const KState *ks,
-                          double2 *out)
-{
-    int meff = ks->meff;
-    double2 y[MAXM];
-#pragma unroll
-    for (int i = 0; i < MAXM; ++i) y[i] = ks->y[i];
-    double inv_n0 = 1.0 / ks->n0;
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * blockDim.x) {
-        // j = 0 from the FP64 master copy (exact v_0 direction, its last use), j >= 1 from the basis
-        double2 v = ld2nt(psi_master, p);
-        v.x *= inv_n0;
-        v.y *= inv_n0;
-        double2 acc = make_double2(y[0].x * v.x - y[0].y * v.y, y[0].x * v.y + y[0].y * v.x);
-#pragma unroll
-        for (int i = 1; i < MAXM; ++i) {
-            if (i < meff) {
-                double2 b = ld2nt(Vb, (int64_t)i * ld + p);
-                acc.x += y[i].x * b.x - y[i].y * b.y;
-                acc.y += y[i].x * b.y + y[i].y * b.x;
-            }
-        }
-        out[p] = acc;
-    }
-}
-
-__device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-
-// y = n0 * exp(-i dt Hk) e_1 for the meff x meff Krylov matrix, by scaling and
-// squaring of a truncated Taylor series; one workgroup of 256 lanes, lane
-// (r, c) owns entry (r, c) of the 16 x 16 matrices.
-__global__ __launch_bounds__(256) void k_krylov_expv(KState *ks, double dt, int hermitian)
-{
-    __shared__ double2 A[MAXM][MAXM], P[MAXM][MAXM], E[MAXM][MAXM];
-    __shared__ double rown[MAXM];
-    __shared__ int s_sq;
-    int meff = ks->meff;
-    int r = threadIdx.x / MAXM, c = threadIdx.x % MAXM;
-    double2 h = make_double2(0.0, 0.0);
-    if (r < meff && c < meff) {
-        if (hermitian) {
-            if (r == c) h = make_double2(ks->alpha[r], 0.0);
-            else if (r == c + 1) h = make_double2(ks->beta[c], 0.0);
-            else if (c == r + 1) h = make_double2(ks->beta[r], 0.0);
-        } else {
-            if (r <= c) {
-                double2 a = ks->h1[r * MAXM + c], b = ks->h2[r * MAXM + c];
-                h = make_double2(a.x + b.x, a.y + b.y);
-            } else if (r == c + 1) {
-                h = make_double2(ks->beta[c], 0.0);
-            }
-        }
-    }
-    // A = -i dt H
-    A[r][c] = make_double2(dt * h.y, -dt * h.x);
-    __syncthreads();
-    if (threadIdx.x < MAXM) {
-        double s = 0.0;
-        for (int cc = 0; cc < MAXM; ++cc)
-            s += sqrt(A[threadIdx.x][cc].x * A[threadIdx.x][cc].x + A[threadIdx.x][cc].y * A[threadIdx.x][cc].y);
-        rown[threadIdx.x] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double nrm = 0.0;
-        for (int i = 0; i < MAXM; ++i) nrm = rown[i] > nrm ? rown[i] : nrm;
-        int sq = 0;
-        while (nrm > 0.125) {
-            nrm *= 0.5;
-            ++sq;
-        }
-        s_sq = sq;
-    }
-    __syncthreads();
-    int sq = s_sq;
-    double scale = ldexp(1.0, -sq);
-    A[r][c] = make_double2(A[r][c].x * scale, A[r][c].y * scale);
-    P[r][c] = make_double2(r == c ? 1.0 : 0.0, 0.0);
-    E[r][c] = P[r][c];
-    __syncthreads();
-    for (int kt = 1; kt <= 18; ++kt) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int l = 0; l < MAXM; ++l) {
-            double2 t = cmul(P[r][l], A[l][c]);
-            acc.x += t.x;
-            acc.y += t.y;
-        }
-        __syncthreads();
-        P[r][c] = make_double2(acc.x / kt, acc.y / kt);
-        E[r][c] = make_double2(E[r][c].x + acc.x / kt, E[r][c].y + acc.y / kt);
-        __syncthreads();
-    }
-    for (int q = 0; q < sq; ++q) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int l = 0; l < MAXM; ++l) {
-            double2 t = cmul(E[r][l], E[l][c]);
-            acc.x += t.x;
-            acc.y += t.y;
-        }
-        __syncthreads();
-        E[r][c] = acc;
-        __syncthreads();
-    }
-    if (c == 0 && r < MAXM) {
-        double n0 = ks->n0;
-        ks->y[r] = (r < meff) ? make_double2(n0 * E[r][0].x, n0 * E[r][0].y) : make_double2(0.0, 0.0);
-    }
-}
-
 __global__ __launch_bounds__(TB) void k_dot_partial(const double2 *a, const double2 *b, int64_t n,
                                                     double2 *partial)
 {
@@ -2400,163 +1753,6 @@ static unsigned red_blocks(int64_t n)
     return (unsigned)(b < 1 ? 1 : b);
 }
 
-#define PPQ_NV_SWITCH(nv, CALL) \
-    switch (nv) {               \
-    case 1: CALL(1); break;     \
-    case 2: CALL(2); break;     \
-    case 3: CALL(3); break;     \
-    case 4: CALL(4); break;     \
-    case 5: CALL(5); break;     \
-    case 6: CALL(6); break;     \
-    case 7: CALL(7); break;     \
-    case 8: CALL(8); break;     \
-    case 9: CALL(9); break;     \
-    case 10: CALL(10); break;   \
-    case 11: CALL(11); break;   \
-    case 12: CALL(12); break;   \
-    case 13: CALL(13); break;   \
-    case 14: CALL(14); break;   \
-    case 15: CALL(15); break;   \
-    case 16: CALL(16); break;   \
-    default: break;             \
-    }
-
-template <class C>
-void norm0(const double2 *psi, int64_t n, double2 *partial, unsigned *counter, KState *ks, int m, double dt,
-           double tol, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_norm0<C>, dim3(RED_BLOCKS), dim3(TB), 0, s, psi, n, partial, counter, ks, m);
-    hipLaunchKernelGGL(k_finalize<1>, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, ks, 0, (int)RED_NORM0, m, 0, 1,
-                       dt, tol);
-}
-template <class C>
-void cgs_dots(const C *Vb, int64_t ld, int nv, const C *w, int64_t n, double2 *partial, unsigned *counter, KState *ks,
-              int j, int m, int ioff, hipStream_t s, int mode)
-{
-#define CALL(NV)                                                                                                  \
-    hipLaunchKernelGGL((k_cgs_dots<C, NV>), dim3(RED_BLOCKS), dim3(TB), 0, s, Vb, ld, w, n, partial, counter, ks, j, \
-                       m, ioff);                                                                              \
-    hipLaunchKernelGGL(k_finalize<NV>, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, ks, j, mode, m, ioff, NV, 0.0, \
-                       0.0)
-    PPQ_NV_SWITCH(nv, CALL)
-#undef CALL
-}
-void finalize_dot(const double2 *partial, int nb, KState *ks, int j, int m, int mode, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_finalize<1>, dim3(1), dim3(TB), 0, s, partial, nb, ks, j, mode, m, j, 1, 0.0, 0.0);
-}
-template <class C>
-void lanczos_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, unsigned *counter, KState *ks, int j,
-                   int m, hipStream_t s)
-{
-#define CALL(NV)                                                                                                    \
-    hipLaunchKernelGGL((k_lanczos_sweep<C, NV>), dim3(RED_BLOCKS), dim3(TB), 0, s, Vb, ld, z, n, partial, counter, \
-                       ks, j);                                                                                   \
-    hipLaunchKernelGGL(k_finalize<NV + 2>, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, ks, j, (int)RED_BETA, m, 0, \
-                       NV + 2, 0.0, 0.0)
-    switch (j) {
-    case 0: CALL(0); break;
-    case 1: CALL(1); break;
-    case 2: CALL(2); break;
-    case 3: CALL(3); break;
-    case 4: CALL(4); break;
-    case 5: CALL(5); break;
-    case 6: CALL(6); break;
-    case 7: CALL(7); break;
-    case 8: CALL(8); break;
-    case 9: CALL(9); break;
-    case 10: CALL(10); break;
-    case 11: CALL(11); break;
-    case 12: CALL(12); break;
-    case 13: CALL(13); break;
-    case 14: CALL(14); break;
-    default: break;
-    }
-#undef CALL
-}
-template <class C>
-void arnoldi_step(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, unsigned *counter, KState *ks, int j,
-                  int m, bool last, hipStream_t s)
-{
-#define CALL(NV)                                                                                                   \
-    hipLaunchKernelGGL((k_arnoldi_dots<C, NV>), dim3(RED_BLOCKS), dim3(TB), 0, s, Vb, ld, z, n, partial, counter, \
-                       ks, j);                                                                                  \
-    hipLaunchKernelGGL(k_finalize<NV + 1>, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, ks, j, (int)RED_ADELAY, m, \
-                       0, NV + 1, 0.0, 0.0);                                                                    \
-    if (!last) {                                                                                               \
-        hipLaunchKernelGGL((k_arnoldi_sweep<C, NV>), dim3(RED_BLOCKS), dim3(TB), 0, s, Vb, ld, z, n, partial,   \
-                           counter, ks, j);                                                                     \
-        hipLaunchKernelGGL(k_finalize<NV + 2>, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, ks, j, (int)RED_BETA, \
-                           m, 0, NV + 2, 0.0, 0.0);                                                            \
-    }
-    switch (j) {
-    case 0: CALL(0); break;
-    case 1: CALL(1); break;
-    case 2: CALL(2); break;
-    case 3: CALL(3); break;
-    case 4: CALL(4); break;
-    case 5: CALL(5); break;
-    case 6: CALL(6); break;
-    case 7: CALL(7); break;
-    case 8: CALL(8); break;
-    case 9: CALL(9); break;
-    case 10: CALL(10); break;
-    case 11: CALL(11); break;
-    case 12: CALL(12); break;
-    case 13: CALL(13); break;
-    case 14: CALL(14); break;
-    case 15: CALL(15); break;
-    default: break;
-    }
-#undef CALL
-}
-void lanczos_coef(KState *ks, int m, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_lanczos_coef, dim3(1), dim3(64), 0, s, ks, m);
-}
-template <class C>
-void lanczos_fix(C *Vb, int64_t ld, int64_t n, const KState *ks, int j, hipStream_t s)
-{
-    unsigned b = red_blocks(n) * 4;
-#define CALL(NV) hipLaunchKernelGGL((k_lanczos_fix<C, NV>), dim3(b), dim3(TB), 0, s, Vb, ld, n, ks, j)
-    PPQ_NV_SWITCH(j, CALL)
-#undef CALL
-}
-template <class C>
-void normalise_from_master(const double2 *psi, int64_t n, KState *ks, C *v0, hipStream_t s)
-{
-    unsigned b = red_blocks(n) * 4;
-    hipLaunchKernelGGL(k_normalise<C>, dim3(b), dim3(TB), 0, s, psi, n, ks, v0);
-}
-template <class C>
-void lincomb(const C *Vb, int64_t ld, const double2 *psi_master, int64_t n, const KState *ks, double2 *psi_out,
-             hipStream_t s)
-{
-    unsigned b = red_blocks(n) * 4;
-    hipLaunchKernelGGL(k_lincomb<C>, dim3(b), dim3(TB), 0, s, Vb, ld, psi_master, n, ks, psi_out);
-}
-
-#define PPQ_INST(C)                                                                                               \
-    template void norm0<C>(const double2 *, int64_t, double2 *, unsigned *, KState *, int, double, double,        \
-                           hipStream_t);                                                                         \
-    template void cgs_dots<C>(const C *, int64_t, int, const C *, int64_t, double2 *, unsigned *, KState *, int,  \
-                              int, int, hipStream_t, int);                                                      \
-    template void lanczos_sweep<C>(C *, int64_t, const C *, int64_t, double2 *, unsigned *, KState *, int, int,   \
-                                   hipStream_t);                                                                \
-    template void lanczos_fix<C>(C *, int64_t, int64_t, const KState *, int, hipStream_t);                        \
-    template void arnoldi_step<C>(C *, int64_t, const C *, int64_t, double2 *, unsigned *, KState *, int, int,    \
-                                  bool, hipStream_t);                                                           \
-    template void normalise_from_master<C>(const double2 *, int64_t, KState *, C *, hipStream_t);                 \
-    template void lincomb<C>(const C *, int64_t, const double2 *, int64_t, const KState *, double2 *, hipStream_t);
-PPQ_INST(double2)
-PPQ_INST(float2)
-#undef PPQ_INST
-
-void krylov_expv(KState *ks, int m, double dt, int hermitian, hipStream_t s)
-{
-    (void)m;
-    hipLaunchKernelGGL(k_krylov_expv, dim3(1), dim3(256), 0, s, ks, dt, hermitian);
-}
 void dot_partial(const double2 *a, const double2 *b, int64_t n, double2 *partial, hipStream_t s)
 {
     hipLaunchKernelGGL(k_dot_partial, dim3(RED_BLOCKS), dim3(TB), 0, s, a, b, n, partial);
