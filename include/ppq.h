@@ -51,6 +51,12 @@
  *   PPQ_ACC_STAGE=1  lane-per-fiber passes (but the one with the fused
  *               <x|y>) read the permutation from each wavefront's copy of its
  *               rank range in LDS instead of scattered global loads.
+ *   PPQ_GRID=0 / 2  products of the default layout on fiber tables always /
+ *               on grid vectors wherever they fit (grids of at most 2^23
+ *               functions); 1 (default) chooses by the set's size and the
+ *               operator's factors.  On grid vectors every factor reads its
+ *               fibers from a vector over the whole grid, in one launch per
+ *               factor depth, and no fiber tables are built.
  *   PPQ_DILATE=1 / 2  adaption's dilation per function (atomics) / word by
  *               word from the bitmap of the functions kept (the +-1 stencil
  *               on DVR axes only); 0 (default) chooses by the grid-to-set

@@ -201,6 +201,21 @@ struct ppq_ctx {
     uint32_t *pair_task = nullptr;  // task starts of the current set
     int64_t pair_cap = 0;
 
+    // products on grid vectors (small sets on grids that fit; see use_grid)
+    int grid_switch = 1;         // 0: never, 1: by the sizes, 2: wherever they fit (PPQ_GRID)
+    bool grid_mode = false;      // the current set's products run on grid vectors
+    bool grid_clean = false;     // the grid vectors are zero outside the current set
+    bool grid_used = false;      // ... and hold values on it
+    bool grid_planned = false;   // stages match the operator and the grid vectors
+    void *xg = nullptr;          // grid vector of a product's input
+    std::vector<void *> zg;      // grid vectors of the products' intermediates
+    std::vector<GridStage<double>> gst64;
+    std::vector<GridStage<float>> gst32;
+    void *gst_dev = nullptr;     // device copies of the stages, fine slices then coarse ones
+    void *GT[MAXD]{};            // one-dimensional factors, column-major, in the context's precision
+    std::vector<void *> GF;      // dense factors of product terms, likewise
+    bool fibers_valid = false;   // the fiber tables match the set
+
     // <x|y> of a product fused into its last pass (Hermitian Krylov steps)
     bool dot_want = false;  // the caller asks for it
     int dot_nb = 0;         // blocks whose partials the last product stored (0: not fused)
@@ -360,7 +375,17 @@ void free_state_buffers(ppq_ctx *c)
     c->plane_mode = false;
     dfree(c->pair_task);
     c->pair_cap = 0;
+    c->fibers_valid = false;
     c->cap = 0;
+}
+
+void free_grid_vectors(ppq_ctx *c)
+{
+    dfree(c->xg);
+    for (auto &z : c->zg) dfree(z);
+    c->zg.clear();
+    c->grid_clean = false;
+    c->grid_planned = false;
 }
 
 void free_krylov(ppq_ctx *c)
@@ -384,7 +409,11 @@ void free_operator(ppq_ctx *c)
         dfree(c->H32p[k]);
         dfree(c->H64[k]);
         dfree(c->H32[k]);
+        dfree(c->GT[k]);
     }
+    for (auto &p : c->GF) dfree(p);
+    c->GF.clear();
+    c->grid_planned = false;
     for (auto &p : c->F64) dfree(p);
     for (auto &p : c->F32) dfree(p);
     for (auto &p : c->F64p) dfree(p);
@@ -636,7 +665,11 @@ void build_operator(ppq_ctx *c)
         dfree(c->H32p[k]);
         dfree(c->H64[k]);
         dfree(c->H32[k]);
+        dfree(c->GT[k]);
     }
+    for (auto &p : c->GF) dfree(p);
+    c->GF.clear();
+    c->grid_planned = false;
     for (auto &p : c->F64) dfree(p);
     for (auto &p : c->F32) dfree(p);
     for (auto &p : c->F64p) dfree(p);
@@ -669,6 +702,21 @@ void build_operator(ppq_ctx *c)
             }
         *d64 = upload(P, s);
         *d32 = upload(Pf, s);
+    };
+    // column-major copy of the context's precision, for the products on grid vectors
+    auto grid_upload = [&](const std::vector<cd> &h, int n, int b) -> void * {
+        if (c->precision == PPQ_FP64) {
+            std::vector<double2> P((size_t)b * b, make_double2(0.0, 0.0));
+            for (int i = 0; i < n; ++i)
+                for (int j = 0; j < n; ++j)
+                    P[(size_t)j * b + i] = make_double2(h[(size_t)i * n + j].real(), h[(size_t)i * n + j].imag());
+            return upload(P, s);
+        }
+        std::vector<float2> P((size_t)b * b, make_float2(0.f, 0.f));
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j)
+                P[(size_t)j * b + i] = make_float2((float)h[(size_t)i * n + j].real(), (float)h[(size_t)i * n + j].imag());
+        return upload(P, s);
     };
     // distinct dense factors of product terms, keyed by (dim, matrix), as they
     // act on the coefficients (transformed on lattice dimensions)
@@ -751,6 +799,13 @@ void build_operator(ppq_ctx *c)
                 }
             c->T64[k] = upload(P, s);
             c->T32[k] = upload(Pf, s);
+            for (int i = 0; i < n; ++i)
+                for (int j = 0; j < n; ++j) {
+                    P[(size_t)j * b + i] = T[(size_t)i * n + j];
+                    Pf[(size_t)j * b + i] = (float)T[(size_t)i * n + j];
+                }
+            if (c->precision == PPQ_FP64) c->GT[k] = upload(P, s);
+            else c->GT[k] = upload(Pf, s);
             if (n > NMAX_MASK) continue;  // long dimensions take no matrix-core tiles
             std::vector<float> P64((size_t)64 * 64, 0.0f);
             std::vector<double> D64((size_t)64 * 64, 0.0);
@@ -945,6 +1000,7 @@ void build_operator(ppq_ctx *c)
             int n = c->g.n[k];
             std::vector<cd> ht = similarity(L[k], Hk[k], n);
             pad_upload(ht, n, c->nb[k], &c->H64[k], &c->H32[k]);
+            c->GT[k] = grid_upload(ht, n, c->nb[k]);
             if (n <= NMAX_MASK) pad_upload(ht, n, 64, &c->H64p[k], &c->H32p[k], true);
         }
     }
@@ -955,6 +1011,7 @@ void build_operator(ppq_ctx *c)
         double2 *d64;
         float2 *d32;
         pad_upload(fmats[i], n, c->nb[k], &d64, &d32);
+        c->GF.push_back(grid_upload(fmats[i], n, c->nb[k]));
         c->F64.push_back(d64);
         c->F32.push_back(d32);
         d64 = nullptr;
@@ -1129,10 +1186,307 @@ PlanePass plane_pass_of(const ppq_ctx *c, int i)
     return pp;
 }
 
-void build_derived(ppq_ctx *c)
+// ---- products on grid vectors -------------------------------------------------
+constexpr int64_t GRID_TOTAL_MAX = int64_t(1) << 23;  // largest grid (functions)
+constexpr int64_t GRID_BYTES_MAX = int64_t(1) << 30;  // all grid vectors of a context
+constexpr int64_t GRID_REAL_MAX = int64_t(1) << 24;   // digits summed in one product (see use_grid)
+constexpr int64_t GRID_CPLX_MAX = int64_t(1) << 25;
+
+// Factors of one product with their depth: those that act on the product's
+// input are at depth 0, those on the results of depth d at d + 1.
+struct GridFactor {
+    int depth, kind, k;
+    const void *H, *H2;
+    int nin;
+    int in[4];         // intermediates read (-1: the input)
+    double cre[4], cim[4];
+    int dst, dst2;     // 0: y, i + 1: intermediate i
+    unsigned use;
+    const double *diag;
+    bool scaled;
+};
+
+// The factors of the operator (built) and the number of intermediates; H
+// pointers are those of GT and GF.
+std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
 {
-    if (c->derived_valid) return;
-    build_operator(c);
+    std::vector<GridFactor> fs;
+    const int D = c->g.D;
+    auto plain = [](int depth, int kind, int k, const void *H, int in, int dst) {
+        GridFactor f{};
+        f.depth = depth;
+        f.kind = kind;
+        f.k = k;
+        f.H = H;
+        f.nin = 1;
+        f.in[0] = in;
+        f.cre[0] = 1.0;
+        f.dst = dst;
+        f.dst2 = -1;
+        return f;
+    };
+    for (int k = 0; k < D; ++k) fs.push_back(plain(0, c->any_lattice ? GRID_CPLX : GRID_REAL, k, c->GT[k], -1, 0));
+    int z = 0;
+    // two-factor terms: each distinct inner factor once (with the dimension's own
+    // factor where there is one to share the input), each outer factor on a
+    // weighted sum of up to four inner results
+    std::vector<int> inner, outer;
+    for (const PairTerm &p : c->pairs) {
+        if (std::find(inner.begin(), inner.end(), p.f2) == inner.end()) inner.push_back(p.f2);
+        if (std::find(outer.begin(), outer.end(), p.f1) == outer.end()) outer.push_back(p.f1);
+    }
+    for (size_t i = 0; i < inner.size(); ++i) {
+        const int k = c->Fdim[inner[i]];
+        if (c->any_lattice && !fs[k].H2) {
+            fs[k].H2 = c->GF[inner[i]];
+            fs[k].dst2 = z + (int)i + 1;
+        } else {
+            fs.push_back(plain(0, GRID_CPLX, k, c->GF[inner[i]], -1, z + (int)i + 1));
+        }
+    }
+    for (int f : outer) {
+        GridFactor a = plain(1, GRID_CPLX, c->Fdim[f], c->GF[f], -1, 0);
+        a.nin = 0;
+        auto flush = [&] {
+            if (a.nin == 0) return;
+            a.scaled = a.nin == 1;  // several inputs carry their weights themselves
+            fs.push_back(a);
+            a.nin = 0;
+        };
+        for (const PairTerm &p : c->pairs) {
+            if (p.f1 != f) continue;
+            a.in[a.nin] = z + (int)(std::find(inner.begin(), inner.end(), p.f2) - inner.begin());
+            a.cre[a.nin] = p.cre;
+            a.cim[a.nin] = p.cim;
+            if (++a.nin == 4) flush();
+        }
+        flush();
+    }
+    z += (int)inner.size();
+    // longer chains and terms with diagonal factors: the coefficient and the
+    // diagonal factors scale the last factor's result
+    for (const ProdTerm &t : c->chains) {
+        int src = -1;
+        for (int f = t.nf - 1; f >= 0 || t.nf == 0; --f) {
+            const bool last = f <= 0;
+            GridFactor a = plain(t.nf ? t.nf - 1 - f : 0, t.nf ? GRID_CPLX : GRID_DIAG, t.nf ? t.k[f] : 0,
+                                 t.nf ? c->GF[t.fid[f]] : nullptr, src, last ? 0 : z + 1);
+            if (last) {
+                a.scaled = true;
+                a.cre[0] = t.cre;
+                a.cim[0] = t.cim;
+                a.use = t.use;
+                a.diag = t.use ? c->PD64[t.diag] : nullptr;
+            } else {
+                src = z++;
+            }
+            fs.push_back(a);
+            if (last) break;
+        }
+    }
+    *nz = z;
+    return fs;
+}
+
+// Whether the current set's products run on grid vectors: the default layout,
+// a grid whose vectors fit, and few enough digits in a product (a complex
+// factor's once for itself and once per input).  Above, the fiber tables'
+// passes, on the matrix cores where fibers are long, read less.  Measured, us a
+// product on fiber tables / grid vectors: 4D Morse 32^4, 52K functions (6.7M
+// digits) 52.9 / 18.3, 114K (14.6M) 47.9 / 28.6, 209K (26.7M) 28.6 / 46.6; the
+// 4D lattice, 14K (11M) 109 / 44, 36K (29M) 117 / 89, 146K (119M) 131 / 260;
+// general 3D terms, 44K (32M) 100 / 47.5, 96K (69M) 108 / 76.
+bool use_grid(const ppq_ctx *c)
+{
+    if (c->hpsi_variant != 2 || c->grid_switch == 0 || c->nact <= 0 || (int64_t)c->g.total > GRID_TOTAL_MAX) return false;
+    int nz = 0;
+    const std::vector<GridFactor> fs = grid_factors(c, &nz);
+    const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
+    if ((int64_t)c->g.total * es * (nz + 1) > GRID_BYTES_MAX) return false;
+    int64_t digits = 0;
+    bool real = true;
+    for (const GridFactor &f : fs) real = real && f.kind == GRID_REAL;
+    for (const GridFactor &f : fs)
+        digits += f.kind == GRID_DIAG ? 1 : (int64_t)c->g.n[f.k] * (f.kind == GRID_CPLX ? 1 + f.nin : 1);
+    return c->grid_switch == 2 || c->nact * digits <= (real ? GRID_REAL_MAX : GRID_CPLX_MAX);
+}
+
+// The stages of the product (one launch each): factors of one depth, up to
+// GRID_SLICES of them, their digits cut into slices of about `chunk`.
+template <class R>
+std::vector<GridStage<R>> grid_stages(const ppq_ctx *c, const std::vector<GridFactor> &fs, int chunk)
+{
+    using C = typename GridStage<R>::C;
+    std::vector<GridStage<R>> out;
+    int depth = 0;
+    for (const GridFactor &f : fs) depth = std::max(depth, f.depth);
+    for (int d = 0; d <= depth; ++d) {
+        std::vector<const GridFactor *> here;
+        for (const GridFactor &f : fs)
+            if (f.depth == d) here.push_back(&f);
+        for (size_t at = 0; at < here.size(); at += GRID_SLICES) {
+            GridStage<R> st{};
+            const size_t end = std::min(here.size(), at + GRID_SLICES);
+            st.nmax = c->pd_nmax;
+            auto result = [&](int dst) {  // 0: y, else the stage's number of the intermediate
+                if (dst == 0) {
+                    st.writes_y = 1;
+                    return 0;
+                }
+                st.out[st.nout] = (C *)c->zg[dst - 1];
+                return ++st.nout;
+            };
+            auto length = [&](const GridFactor &f) { return f.kind == GRID_DIAG ? 1 : c->g.n[f.k]; };
+            for (size_t i = at; i < end; ++i) {
+                const GridFactor &f = *here[i];
+                GridOp<R> &o = st.op[st.nop++];
+                o.H = f.H;
+                o.H2 = f.H2;
+                o.nin = f.nin;
+                for (int q = 0; q < 4; ++q) {
+                    const bool on = q < f.nin;
+                    o.x[q] = (const C *)(!on || f.in[q] < 0 ? c->xg : c->zg[f.in[q]]);
+                    o.c[q] = C{(R)(on ? f.cre[q] : 0.0), (R)(on ? f.cim[q] : 0.0)};
+                }
+                o.diag = f.diag;
+                o.use = f.use;
+                o.stride = c->g.stride[f.k];
+                o.n = c->g.n[f.k];
+                o.nb = c->nb[f.k];
+                o.kind = f.kind;
+                o.scaled = f.scaled ? 1 : 0;
+                o.dst = result(f.dst);
+                o.dst2 = f.H2 ? result(f.dst2) : -1;
+                st.second |= f.H2 != nullptr;
+                st.general |= f.kind != GRID_REAL;
+            }
+            // slices of equal length within a factor, as many as the workgroup holds
+            int len = std::max(chunk, 1), total = 0;
+            for (;; ++len) {
+                total = 0;
+                for (size_t i = at; i < end; ++i) total += (length(*here[i]) + len - 1) / len;
+                if (total <= GRID_SLICES) break;
+            }
+            for (int o = 0; o < st.nop; ++o) {
+                const int n = length(*here[at + o]), parts = (n + len - 1) / len;
+                for (int q = 0; q < parts; ++q) {
+                    st.slice_op[st.nslice] = o;
+                    st.d0[st.nslice] = (int)((int64_t)n * q / parts);
+                    st.d1[st.nslice] = (int)((int64_t)n * (q + 1) / parts);
+                    ++st.nslice;
+                }
+            }
+            for (int q = 0; q < st.nslice; ++q) {
+                const GridOp<R> &o = st.op[st.slice_op[q]];
+                st.parts_of[o.dst] |= 1u << q;
+                if (o.dst2 >= 0) st.parts_of[o.dst2] |= 1u << (st.nslice + q);
+            }
+            out.push_back(st);
+        }
+    }
+    return out;
+}
+
+// Fine slices (more wavefronts per point) fill the chip and shorten the chain
+// of loads while there are few points, coarse ones save the partial sums:
+// the stage lists of both are kept, fine first.
+constexpr int GRID_FINE = 16, GRID_COARSE = 32;
+constexpr int64_t GRID_FINE_MAX = 32768;  // points
+
+template <class R>
+void plan_grid(ppq_ctx *c, std::vector<GridStage<R>> &stages)
+{
+    int nz = 0;
+    const std::vector<GridFactor> fs = grid_factors(c, &nz);
+    stages = grid_stages<R>(c, fs, GRID_FINE);
+    const std::vector<GridStage<R>> coarse = grid_stages<R>(c, fs, GRID_COARSE);
+    stages.insert(stages.end(), coarse.begin(), coarse.end());
+    dfree(c->gst_dev);
+    c->gst_dev = upload(stages, c->stream);
+    ck(hipStreamSynchronize(c->stream), "product stages");
+}
+
+// Allocates the grid vectors, plans the stages and clears what an earlier set
+// left.  False when the memory is not there: the fiber tables serve then.
+bool ensure_grid(ppq_ctx *c)
+{
+    int nz = 0;
+    (void)grid_factors(c, &nz);
+    const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2), bytes = (int64_t)c->g.total * es;
+    try {
+        if (!c->xg) {
+            c->xg = dalloc<unsigned char>(bytes);
+            c->grid_clean = c->grid_planned = false;
+        }
+        while ((int)c->zg.size() < nz) {
+            c->zg.push_back(nullptr);
+            c->zg.back() = dalloc<unsigned char>(bytes);
+            c->grid_clean = c->grid_planned = false;
+        }
+    } catch (const std::bad_alloc &) {
+        free_grid_vectors(c);
+        return false;
+    }
+    if (!c->grid_planned) {
+        if (c->precision == PPQ_FP64) plan_grid<double>(c, c->gst64);
+        else plan_grid<float>(c, c->gst32);
+        c->grid_planned = true;
+    }
+    if (!c->grid_clean) {
+        fill_zero_bytes(c->xg, bytes, c->stream);
+        for (void *z : c->zg) fill_zero_bytes(z, bytes, c->stream);
+        c->grid_clean = true;
+    }
+    return true;
+}
+
+// Called while keys[cur] and nact are still the set that the grid vectors hold
+// values of, before the set changes: clears those values.
+void leave_set(ppq_ctx *c)
+{
+    c->fibers_valid = false;
+    if (!c->grid_clean || !c->grid_used) return;
+    c->grid_used = false;
+    const uint32_t *keys = c->keys[c->cur];
+    auto clear = [&](void *v) {
+        if (c->precision == PPQ_FP64) grid_clear<double2>(keys, c->nact, (double2 *)v, c->stream);
+        else grid_clear<float2>(keys, c->nact, (float2 *)v, c->stream);
+    };
+    clear(c->xg);
+    for (void *z : c->zg) clear(z);
+}
+
+// y = P H P x on grid vectors; x == nullptr: the input is in xg already.  With
+// dots 1 or 2 the last launch leaves <x|y>, or the dots with the nv vectors at
+// Vb, in the dots' partials (dot_nb blocks).
+template <class R>
+void apply_grid(ppq_ctx *c, const std::vector<GridStage<R>> &stages, const void *xv, void *yv, const int *skip_if,
+                int skip_j, int dots, const void *Vb, int nv)
+{
+    using C = typename GridStage<R>::C;
+    hipStream_t s = c->stream;
+    const int64_t n = c->nact;
+    const uint32_t *keys = c->keys[c->cur];
+    if (xv) grid_put<C>(keys, (const C *)xv, n, (C *)c->xg, s);
+    const size_t half = stages.size() / 2, first = n <= GRID_FINE_MAX ? 0 : half;
+    const R *V = nullptr;
+    if (!c->any_lattice) V = c->precision == PPQ_FP64 ? (const R *)c->V64 : (const R *)c->V32;
+    bool written = false;
+    for (size_t i = 0; i < half; ++i) {
+        const GridStage<R> &st = stages[first + i];
+        const bool last = i + 1 == half;
+        c->dot_nb = grid_launch<R>((const GridStage<R> *)c->gst_dev + first + i, st, c->g, keys, n, (const C *)c->xg,
+                                   written ? nullptr : V, (C *)yv, written, skip_if, skip_j, last ? dots : 0,
+                                   (const C *)Vb, c->cap, nv, c->partial + KRY_DOTS, s);
+        written = written || st.writes_y;
+    }
+    if (dots == 0) c->dot_nb = 0;
+}
+
+// Fiber tables of the current set (and the tables of the other layouts).
+void build_fibers(ppq_ctx *c)
+{
+    if (c->fibers_valid) return;
     c->plane_mode = false;
     {
         const int D = c->g.D;
@@ -1208,14 +1562,6 @@ void build_derived(ppq_ctx *c)
                          c->scan_tmp, c->small + 3 * MAXD, s);
         c->plane_mode = true;
     }
-    if (!c->any_lattice) {
-        PotDesc pd{c->pot_nterm, D, c->pot_nmax, c->pot_coef, c->pot_tab, c->pot_tabs, c->pot_ntab};
-        // flags is free once the fiber tables are built
-        potential(keys, n, c->g, pd, c->V64, c->V32, c->v_partial ? c->flags : nullptr,
-                  reinterpret_cast<unsigned *>(c->small + 2 * MAXD + 4), s);
-        c->v_valid = true;
-        c->v_partial = false;
-    }
     // The fiber counts size the H*psi launches only: the host reads them when
     // the first product is issued (ensure_nf), so the work queued in between
     // (observables, the next step's normalisation) hides the round trip.
@@ -1243,6 +1589,31 @@ void build_derived(ppq_ctx *c)
             for (int k = 0; k < c->split; ++k) build_row_major(c, k);
             ck(hipStreamSynchronize(s), "fibers");
         }
+    }
+    c->fibers_valid = true;
+}
+
+// What the products of the current set need: the operator, the fiber tables or
+// clean grid vectors, and the potential cache.
+void build_derived(ppq_ctx *c)
+{
+    if (c->derived_valid) return;
+    if (c->op_dirty) c->fibers_valid = false;  // the layouts' tables depend on the operator's terms
+    build_operator(c);
+    const int D = c->g.D;
+    const int64_t n = c->nact;
+    hipStream_t s = c->stream;
+    const uint32_t *keys = c->keys[c->cur];
+    c->grid_mode = use_grid(c) && ensure_grid(c);
+    if (c->grid_mode) c->grid_used = true;
+    else build_fibers(c);
+    if (!c->any_lattice) {
+        PotDesc pd{c->pot_nterm, D, c->pot_nmax, c->pot_coef, c->pot_tab, c->pot_tabs, c->pot_ntab};
+        // flags is free: the fiber tables are built, or will be later
+        potential(keys, n, c->g, pd, c->V64, c->V32, c->v_partial ? c->flags : nullptr,
+                  reinterpret_cast<unsigned *>(c->small + 2 * MAXD + 4), s);
+        c->v_valid = true;
+        c->v_partial = false;
     }
     c->derived_valid = true;
 }
@@ -1610,6 +1981,11 @@ void apply_products(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, in
 // y = P H P x on the current set (device vectors of the context precision)
 void apply_launches(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, int skip_j)
 {
+    if (c->grid_mode) {
+        if (c->precision == PPQ_FP64) apply_grid<double>(c, c->gst64, xv, yv, skip_if, skip_j, 0, nullptr, 0);
+        else apply_grid<float>(c, c->gst32, xv, yv, skip_if, skip_j, 0, nullptr, 0);
+        return;
+    }
     // a fused <x|y> needs the single-factor passes to write y last
     const bool want = c->dot_want;
     c->dot_want = want && c->pairs.empty() && c->chains.empty();
@@ -1694,7 +2070,12 @@ void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, doub
     C *w = (C *)c->wk;
     const int *meff = &ks->meff;
     const bool herm = c->hermitian;
-    kry_start<C>(src, n, c->partial, ks, m, dt, tol, Vb, s);
+    // on grid vectors the basis kernels write each new vector into the product's
+    // input themselves and the product leaves all its dots
+    using R = decltype(C::x);
+    const uint32_t *keys = c->keys[c->cur];
+    C *xg = c->grid_mode ? (C *)c->xg : nullptr;
+    kry_start<C>(src, n, c->partial, ks, m, dt, tol, Vb, keys, xg, s);
     // The second Gram-Schmidt pass of each vector is applied in the next step's
     // sweep: H acts on the provisional q_j in slot j, <q_j|H q_j> comes from the
     // product's last pass where it can, and one sweep per step corrects v_j and
@@ -1702,14 +2083,21 @@ void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, doub
     for (int j = 0; j < m; ++j) {
         C *qj = Vb + (int64_t)j * ld;
         mark(c, PPQ_PHASE_HPSI);
-        c->dot_want = herm;
-        apply_internal(c, qj, w, meff, j);
-        c->dot_want = false;
+        if (xg) {
+            if constexpr (std::is_same<C, double2>::value)
+                apply_grid<R>(c, c->gst64, nullptr, w, meff, j, herm ? 1 : 2, Vb, j + 1);
+            else apply_grid<R>(c, c->gst32, nullptr, w, meff, j, herm ? 1 : 2, Vb, j + 1);
+            ck(hipGetLastError(), "H*psi launch");
+        } else {
+            c->dot_want = herm;
+            apply_internal(c, qj, w, meff, j);
+            c->dot_want = false;
+        }
         int nbd = c->dot_nb;
         mark(c, PPQ_PHASE_KRYLOV);
         if (nbd == 0) nbd = kry_dots<C>(Vb, ld, w, n, c->partial, ks, j, !herm, s);
         if (j < m - 1) {
-            kry_sweep<C>(Vb, ld, w, n, c->partial, nbd, ks, j, !herm, s);
+            kry_sweep<C>(Vb, ld, w, n, c->partial, nbd, ks, j, !herm, keys, xg, s);
             continue;
         }
         kry_close(ks, m, c->partial, n, nbd, dt, herm, expv, expv, s);
@@ -1864,6 +2252,7 @@ void do_prune(ppq_ctx *c, double eps, int64_t *nabove_out)
             remap_values(c->keys[c->cur], c->Vt32, n_old, c->bm, c->prefix, c->V32, s);
         }
     }
+    leave_set(c);
     c->cur = nxt;
     c->nact = n_new;
     c->derived_valid = false;
@@ -1911,7 +2300,8 @@ void energy_into(ppq_ctx *c, int64_t r)
         // FP32 form: H acts on the FP32 copy; the inner product is accumulated in FP64
         float2 *x32 = (float2 *)c->Vk;
         KState *ks = c->ks;
-        kry_start<float2>(c->psi[c->cur], c->nact, c->partial, ks, 1, 0.0, 0.0, x32, c->stream);
+        kry_start<float2>(c->psi[c->cur], c->nact, c->partial, ks, 1, 0.0, 0.0, x32, nullptr, nullptr,
+                          c->stream);
         apply_internal(c, x32, c->wk, nullptr, 0);
         const int nbd = kry_dots<float2>(x32, c->cap, (const float2 *)c->wk, c->nact, c->partial, ks, 0, false,
                                          c->stream);
@@ -2009,6 +2399,7 @@ bool keys_valid(const ppq_ctx *c, int64_t n, const uint64_t *keys)
 void set_current_set(ppq_ctx *c, const uint32_t *keys_dev, int64_t n)
 {
     if (n > c->cap) throw std::runtime_error("set larger than the reserved capacity");
+    leave_set(c);
     if (n) ck(hipMemcpyAsync(c->keys[c->cur], keys_dev, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream),
               "set keys");
     c->nact = n;
@@ -2032,6 +2423,7 @@ void frozen_remap(ppq_ctx *c, const uint32_t *next_keys, int64_t n_next)
         ck(hipMemcpyAsync(c->keys[nxt], next_keys, n_next * sizeof(uint32_t), hipMemcpyDeviceToDevice, s), "keys");
     fill_zero_bytes(c->psi[nxt], n_next * (int64_t)sizeof(double2), s);
     remap(c->keys[c->cur], c->psi[c->cur], c->nact, c->bm, c->prefix, c->psi[nxt], s);
+    leave_set(c);
     c->cur = nxt;
     c->nact = n_next;
     c->derived_valid = false;
@@ -2300,6 +2692,10 @@ int ppq_create(ppq_ctx **out, int device, void *hip_stream, int precision)
         const int d = std::atoi(v);
         if (d >= 0 && d <= 2) c->dilate_mode = d;
     }
+    if (const char *v = std::getenv("PPQ_GRID")) {
+        const int d = std::atoi(v);
+        if (d >= 0 && d <= 2) c->grid_switch = d;
+    }
     if (const char *v = std::getenv("PPQ_BLOCK_WINDOW")) {
         const long w = std::atol(v);
         if (w >= (long)BLOCK_WINDOW && w <= (1l << 20)) c->blk_window = (uint32_t)w;
@@ -2343,6 +2739,8 @@ void ppq_destroy(ppq_ctx *c)
     free_state_buffers(c);
     free_krylov(c);
     free_operator(c);
+    free_grid_vectors(c);
+    dfree(c->gst_dev);
     dfree(c->bm);
     dfree(c->prefix);
     dfree(c->kbm);
@@ -2418,6 +2816,7 @@ int ppq_set_grid(ppq_ctx *c, int D, const int32_t *n, const double *lo, const do
         free_state_buffers(c);
         free_krylov(c);
         free_operator(c);
+        free_grid_vectors(c);
         dfree(c->bm);
         dfree(c->prefix);
         dfree(c->kbm);
@@ -2684,6 +3083,7 @@ int ppq_init_gaussian(ppq_ctx *c, const double *centre, const double *momentum, 
         ck(hipMemcpyAsync(c->h_small + MAXD, c->small + MAXD, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "n");
         ck(hipStreamSynchronize(s), "init count");
         int64_t n0 = c->h_small[MAXD];
+        leave_set(c);
         c->has_state = false;
         c->nact = 0;
         ensure_capacity(c, std::max<int64_t>(n0, 1));
@@ -2725,6 +3125,7 @@ int ppq_set_state(ppq_ctx *c, int64_t count, const uint64_t *keys, const double 
     for (int64_t i = 0; i < 2 * count; ++i)
         if (!std::isfinite(coeff[i])) return fail(c, PPQ_E_NUMERIC, "non-finite coefficient");
     PPQ_TRY(c, {
+        leave_set(c);
         c->has_state = false;
         c->nact = 0;
         ensure_capacity(c, std::max<int64_t>(count, 1));
@@ -2820,6 +3221,7 @@ int ppq_set_state_device(ppq_ctx *c, int64_t count, const uint64_t *keys, const 
             status = fail(c, PPQ_E_NUMERIC, "non-finite coefficient");
         } else {
             // the checked copy becomes the state (the previous one is dropped)
+            leave_set(c);
             c->cur = nxt;
             c->nact = count;
             c->has_state = true;
@@ -3303,7 +3705,8 @@ int ppq_time_apply(ppq_ctx *c, int nrep, double *ms_median, double *ms_mean)
         ensure_krylov(c, std::max(c->kv_m, 1));
         const void *x = c->psi[c->cur];
         if (c->precision == PPQ_FP32) {
-            kry_start<float2>(c->psi[c->cur], c->nact, c->partial, c->ks, 1, 0.0, 0.0, (float2 *)c->Vk, c->stream);
+            kry_start<float2>(c->psi[c->cur], c->nact, c->partial, c->ks, 1, 0.0, 0.0, (float2 *)c->Vk, nullptr, nullptr,
+                              c->stream);
             x = c->Vk;
         }
         apply_internal(c, x, c->wk, nullptr, 0);
@@ -3345,6 +3748,7 @@ int ppq_fiber_counts(ppq_ctx *c, int64_t *nf)
     if (!nf) return fail(c, PPQ_E_ARG, "nf is NULL");
     PPQ_TRY(c, {
         build_derived(c);
+        build_fibers(c);
         ensure_nf(c);
         for (int k = 0; k < c->g.D; ++k) nf[k] = c->nf[k];
     })

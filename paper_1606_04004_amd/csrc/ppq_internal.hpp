@@ -4,6 +4,7 @@
 
 #include <cstdint>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/ppq.h"
@@ -350,10 +351,11 @@ constexpr int64_t KRY_DOTS_VALUES = (int64_t)MAXM * RED_BLOCKS;
 constexpr int64_t PARTIAL_VALUES = KRY_DOTS + KRY_DOTS_VALUES;
 static_assert(PARTIAL_VALUES >= (int64_t)RED_BLOCKS * PSTRIDE_H, "partial sums of the other reductions");
 int kry_blocks(int64_t n);  // blocks of the Krylov kernels for n points
-// v0 = psi / |psi| and the start of KState (order limit m, |dt|, tolerance)
+// v0 = psi / |psi| and the start of KState (order limit m, |dt|, tolerance); with
+// xg, here and in kry_sweep, the new vector also at its keys in the grid vector
 template <class C>
 void kry_start(const double2 *psi, int64_t n, double2 *partial, KState *ks, int m, double dt, double tol, C *v0,
-               hipStream_t s);
+               const uint32_t *keys, C *xg, hipStream_t s);
 // Step j: the dots of z = H q_j (q_j in slot j) where the product has not left
 // them itself, <q_j|z> (Arnoldi: <v_i|z>, i < j, before it); returns the number
 // of blocks.  Then the sweep (see k_sweep), given the dots' block count.
@@ -362,7 +364,7 @@ int kry_dots(const C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, c
              hipStream_t s);
 template <class C>
 void kry_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, int nbd, KState *ks, int j, bool arnoldi,
-               hipStream_t s);
+               const uint32_t *keys, C *xg, hipStream_t s);
 // corrects the last vector (slot j > 0) of a step that ran to its full order
 template <class C>
 void kry_fix_last(C *Vb, int64_t ld, int64_t n, const KState *ks, int j, hipStream_t s);
@@ -374,6 +376,46 @@ void kry_close(KState *ks, int m, const double2 *partial, int64_t n, int nbd, do
 template <class C>
 void lincomb(const C *Vb, int64_t ld, const double2 *psi_master, int64_t n, const KState *ks, double2 *psi_out,
              hipStream_t s);
+
+// ---- products on grid vectors (ppq_grid.hip) ---------------------------------
+// One launch applies up to GRID_SLICES factors at one depth of the operator's
+// products.  A factor acts on one to four grid vectors; its result goes to y
+// (dst 0) or to the grid vector out[dst - 1], for a second factor on the same
+// input (H2) likewise with dst2.
+constexpr int GRID_SLICES = 16;   // wavefronts of a workgroup
+constexpr int GRID_BLOCKS = RED_BLOCKS;
+enum GridKind { GRID_REAL = 0, GRID_CPLX = 1, GRID_DIAG = 2 };  // GRID_DIAG: no dense factor
+template <class R>
+struct GridOp {
+    using C = typename std::conditional<sizeof(R) == 8, double2, float2>::type;
+    const void *H, *H2;   // n x n factors, column-major with nb rows per column
+    const C *x[4];
+    C c[4];               // weights of the inputs (one input: a factor of the result, with scaled)
+    const double *diag;   // diagonal factors [D][nmax] of the dimensions in use (scaled)
+    uint32_t stride;
+    unsigned use;
+    int n, nb, kind, nin, dst, dst2, scaled;
+};
+template <class R>
+struct GridStage {
+    using C = typename GridOp<R>::C;
+    GridOp<R> op[GRID_SLICES];
+    C *out[2 * GRID_SLICES];
+    int nop, nslice, nout, second, general, nmax, writes_y;
+    uint32_t parts_of[2 * GRID_SLICES + 1];  // the slices (from bit nslice on: their second results) summed into a result
+    int slice_op[GRID_SLICES], d0[GRID_SLICES], d1[GRID_SLICES];  // slice: digits [d0, d1) of a factor
+};
+// dev: the device copy of st.  dots: 0, 1 (<x|y> into dotp[block]) or 2 (<v_i|y>
+// for the nv vectors at Vb, value-major).  Returns the number of blocks.
+template <class R>
+int grid_launch(const GridStage<R> *dev, const GridStage<R> &st, const GridDesc &g, const uint32_t *keys, int64_t n,
+                const typename GridStage<R>::C *xg, const R *V, typename GridStage<R>::C *y, bool accumulate,
+                const int *skip_if, int skip_j, int dots, const typename GridStage<R>::C *Vb, int64_t ld, int nv,
+                double2 *dotp, hipStream_t s);
+template <class C>
+void grid_put(const uint32_t *keys, const C *x, int64_t n, C *xg, hipStream_t s);
+template <class C>
+void grid_clear(const uint32_t *keys, int64_t n, C *xg, hipStream_t s);
 
 // observables
 void obs_partial(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, const double2 *bra,

@@ -266,7 +266,8 @@ __global__ __launch_bounds__(TB) void k_norm0(const double2 *psi, int64_t n, dou
 // v_0 = psi / |psi| with the norm from k_norm0's partials; block 0 starts KState
 template <class C>
 __global__ __launch_bounds__(TB) void k_start(const double2 *psi, int64_t n, const double2 *partial, int nb,
-                                              KState *ks, int m, double dt, double tol, C *v0)
+                                              KState *ks, int m, double dt, double tol, C *v0,
+                                              const uint32_t *keys, C *xg)
 {
     __shared__ double2 red[RED_BLOCKS / SEG];
     reduce_tasks(partial, 1, nb, red);
@@ -285,6 +286,7 @@ __global__ __launch_bounds__(TB) void k_start(const double2 *psi, int64_t n, con
     for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
         double2 a = ld2nt(psi, p);
         st2(v0, p, make_double2(a.x * s, a.y * s));
+        if (xg) st2(xg, keys[p], make_double2(a.x * s, a.y * s));
     }
 }
 
@@ -336,7 +338,8 @@ __global__ __launch_bounds__(TB) void k_arnoldi_dots(const C *Vb, int64_t ld, co
 // small set's partials stay few.
 template <class C, int NV, bool ARN>
 __global__ __launch_bounds__(TB) void k_sweep(C *Vb, int64_t ld, const C *z, int64_t n, KState *ks, const double2 *ps,
-                                              int nbs, const double2 *pd, int nbd, double2 *pout)
+                                              int nbs, const double2 *pd, int nbd, double2 *pout,
+                                              const uint32_t *keys, C *xg)
 {
     __shared__ Scalars sc;
     if (NV >= ks->meff) return;
@@ -389,6 +392,7 @@ __global__ __launch_bounds__(TB) void k_sweep(C *Vb, int64_t ld, const C *z, int
             }
         }
         st2(qn, p, wp);
+        if (xg) st2(xg, keys[p], wp);
         const double2 ws = stored(qn, wp);
 #pragma unroll
         for (int i = 0; i < NV; ++i) cdot_acc(acc[i], vv[i], ws);
@@ -618,11 +622,12 @@ int kry_blocks(int64_t n)
 
 template <class C>
 void kry_start(const double2 *psi, int64_t n, double2 *partial, KState *ks, int m, double dt, double tol, C *v0,
-               hipStream_t s)
+               const uint32_t *keys, C *xg, hipStream_t s)
 {
     const int nb = kry_blocks(n);
     hipLaunchKernelGGL(k_norm0, dim3(nb), dim3(TB), 0, s, psi, n, partial);
-    hipLaunchKernelGGL(k_start<C>, dim3(nb), dim3(TB), 0, s, psi, n, partial, nb, ks, m, dt, tol, v0);
+    hipLaunchKernelGGL(k_start<C>, dim3(nb), dim3(TB), 0, s, psi, n, partial, nb, ks, m, dt, tol, v0, keys,
+                       xg);
 }
 
 #define PPQ_ORDERS(CALL)    \
@@ -664,19 +669,19 @@ int kry_dots(const C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, c
 
 template <class C>
 void kry_sweep(C *Vb, int64_t ld, const C *z, int64_t n, double2 *partial, int nbd, KState *ks, int j, bool arnoldi,
-               hipStream_t s)
+               const uint32_t *keys, C *xg, hipStream_t s)
 {
     const int nb = kry_blocks(n);
     const double2 *ps = sweep_partials(partial, j + 1), *pd = partial + KRY_DOTS;
     double2 *po = const_cast<double2 *>(sweep_partials(partial, j));
     if (arnoldi) {
 #define CALL(NV)                                                                                                  \
-    hipLaunchKernelGGL((k_sweep<C, NV, true>), dim3(nb), dim3(TB), 0, s, Vb, ld, z, n, ks, ps, nb, pd, nbd, po)
+    hipLaunchKernelGGL((k_sweep<C, NV, true>), dim3(nb), dim3(TB), 0, s, Vb, ld, z, n, ks, ps, nb, pd, nbd, po, keys, xg)
         PPQ_ORDERS(CALL)
 #undef CALL
     } else {
 #define CALL(NV)                                                                                                   \
-    hipLaunchKernelGGL((k_sweep<C, NV, false>), dim3(nb), dim3(TB), 0, s, Vb, ld, z, n, ks, ps, nb, pd, nbd, po)
+    hipLaunchKernelGGL((k_sweep<C, NV, false>), dim3(nb), dim3(TB), 0, s, Vb, ld, z, n, ks, ps, nb, pd, nbd, po, keys, xg)
         PPQ_ORDERS(CALL)
 #undef CALL
     }
@@ -712,10 +717,11 @@ void lincomb(const C *Vb, int64_t ld, const double2 *psi_master, int64_t n, cons
 
 #define PPQ_INST(C)                                                                                                \
     template void kry_start<C>(const double2 *, int64_t, double2 *, KState *, int, double, double, C *,            \
-                               hipStream_t);                                                                       \
+                               const uint32_t *, C *, hipStream_t);                                                \
     template int kry_dots<C>(const C *, int64_t, const C *, int64_t, double2 *, const KState *, int, bool,         \
                              hipStream_t);                                                                         \
-    template void kry_sweep<C>(C *, int64_t, const C *, int64_t, double2 *, int, KState *, int, bool, hipStream_t); \
+    template void kry_sweep<C>(C *, int64_t, const C *, int64_t, double2 *, int, KState *, int, bool,         \
+                               const uint32_t *, C *, hipStream_t);                                                \
     template void kry_fix_last<C>(C *, int64_t, int64_t, const KState *, int, hipStream_t);                        \
     template void lincomb<C>(const C *, int64_t, const double2 *, int64_t, const KState *, double2 *, hipStream_t);
 PPQ_INST(double2)
