@@ -20,7 +20,9 @@ namespace {
 //
 // No kernel reads a KState entry that its own block 0 writes: entries are
 // indexed by the order, and a prologue at order j writes order j - 1's
-// second-pass results and order j's first-pass ones.
+// second-pass results and order j's first-pass ones.  (KState's order is the
+// exception: it only ever drops to an order that every block of the writing kernel
+// finds for itself.)
 struct Scalars {
     double2 h[MAXM];   // second-pass coefficients of the provisional q_j
     double2 cc[MAXM];  // H v_j = (H q_j - sum_k cc_k v_k) / beta_{j-1}
@@ -28,19 +30,6 @@ struct Scalars {
     double alpha, ib, bm;
     int stop;
 };
-constexpr int SEG = 256;                       // blocks one wavefront sums per task
-constexpr int MAXTASK = (MAXM + 2) * 2 + 64;  // (value, segment) tasks of a prologue
-
-__device__ inline double2 wave_sum(double2 v)
-{
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) {
-        v.x += __shfl_xor(v.x, s, 64);
-        v.y += __shfl_xor(v.y, s, 64);
-    }
-    return v;
-}
-
 // Sums over groups of 16 neighbouring lanes (every lane gets its group's).
 __device__ inline double2 group16_sum(double2 v)
 {
@@ -52,37 +41,77 @@ __device__ inline double2 group16_sum(double2 v)
     return v;
 }
 
-// red[value * nseg + segment] = the sum of up to SEG blocks' partials of one
-// value; a wavefront loads four tasks' partials before it sums them
-__device__ inline void reduce_tasks(const double2 *part, int nval, int nb, double2 *red)
+// sum[value] of the partials [value][block] of nval values over nb blocks: 16
+// lanes take a value, so the 256 threads sum 16 values at once with four shuffle
+// steps (a wavefront a value takes six for every value in turn).
+__device__ inline void sum_values(const double2 *part, int nval, int nb, double2 *sum)
 {
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    const int nseg = (nb + SEG - 1) / SEG, ntask = nval * nseg;
-    for (int t0 = wv; t0 < ntask; t0 += 4 * nw) {
-        double2 v[4][SEG / 64];
+    const int l = threadIdx.x & 15;
+    for (int v = threadIdx.x >> 4; v < nval; v += TB / 16) {
+        double2 s = make_double2(0.0, 0.0);
+        for (int b0 = l; b0 < nb; b0 += 16 * 8) {
+            double2 q[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int t = t0 + u * nw;
-            const int val = t / nseg, base = (t - val * nseg) * SEG;
+            for (int u = 0; u < 8; ++u) {
+                const int b = b0 + 16 * u;
+                q[u] = b < nb ? part[(int64_t)v * RED_BLOCKS + b] : make_double2(0.0, 0.0);
+            }
 #pragma unroll
-            for (int i = 0; i < SEG / 64; ++i) {
-                const int b = base + i * 64 + lane;
-                v[u][i] = (t < ntask && b < nb) ? part[(int64_t)val * RED_BLOCKS + b] : make_double2(0.0, 0.0);
+            for (int u = 0; u < 8; ++u) {
+                s.x += q[u].x;
+                s.y += q[u].y;
             }
         }
+        s = group16_sum(s);
+        if (l == 0) sum[v] = s;
+    }
+}
+
+// One value over many blocks: the block's 256 threads share it (quarter sums).
+__device__ inline void sum_single(const double2 *part, int nb, double2 *quarter)
+{
+    double2 s = make_double2(0.0, 0.0);
+    for (int b0 = threadIdx.x; b0 < nb; b0 += TB * 4) {
+        double2 q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = b0 + TB * u < nb ? part[b0 + TB * u] : make_double2(0.0, 0.0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int t = t0 + u * nw;
-            if (t >= ntask) break;
-            double2 s = v[u][0];
-#pragma unroll
-            for (int i = 1; i < SEG / 64; ++i) {
-                s.x += v[u][i].x;
-                s.y += v[u][i].y;
-            }
-            s = wave_sum(s);
-            if (lane == 0) red[t] = s;
+            s.x += q[u].x;
+            s.y += q[u].y;
         }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        s.x += __shfl_xor(s.x, d, 64);
+        s.y += __shfl_xor(s.y, d, 64);
+    }
+    if ((threadIdx.x & 63) == 0) quarter[threadIdx.x >> 6] = s;
+}
+__device__ inline double2 four(const double2 *q)
+{
+    return make_double2((q[0].x + q[1].x) + (q[2].x + q[3].x), (q[0].y + q[1].y) + (q[2].y + q[3].y));
+}
+
+// Sums NV values over the block's threads into partial[value][block]: the
+// threads' values go through LDS, 16 threads then take a value each (as above).
+template <int NV>
+__device__ inline void block_values_store(const double2 (&acc)[NV], double2 *partial)
+{
+    __shared__ double2 red[NV][TB];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) red[i][threadIdx.x] = acc[i];
+    __syncthreads();
+    const int l = threadIdx.x & 15;
+    for (int v = threadIdx.x >> 4; v < NV; v += TB / 16) {
+        double2 s = red[v][l];
+#pragma unroll
+        for (int u = 1; u < TB / 16; ++u) {
+            s.x += red[v][l + 16 * u].x;
+            s.y += red[v][l + 16 * u].y;
+        }
+        s = group16_sum(s);
+        if (l == 0) partial[(int64_t)v * RED_BLOCKS + blockIdx.x] = s;
     }
 }
 
@@ -104,10 +133,10 @@ __device__ inline void reduce_tasks(const double2 *part, int nval, int nb, doubl
 template <bool ARN>
 __device__ void krylov_scalars(KState *ks, int j, const double2 *ps, int nbs, const double2 *pd, int nbd, Scalars &sc)
 {
-    __shared__ double2 red[MAXTASK];
-    __shared__ double2 S[MAXM + 2], R[MAXM + 1];
-    const int t = threadIdx.x, lane = t & 63;
+    __shared__ double2 S[MAXM + 2], R[MAXM + 4];
+    const int t = threadIdx.x;
     const bool store = blockIdx.x == 0;
+    const int meff = ks->meff;
     // KState entries first: their latency overlaps the partials'
     const double est0 = j > 0 ? ks->est[j - 1] : 0.0, kdt = ks->kdt, ktol = ks->ktol;
     double al = 0.0, be = 0.0;
@@ -123,35 +152,17 @@ __device__ void krylov_scalars(KState *ks, int j, const double2 *ps, int nbs, co
         }
         if (ia < j - 1) bi = ks->beta[ia];
     }
-    const int nvs = j > 0 ? j + 1 : 0, nvd = ARN ? j + 1 : 1;
-    const int ss = (nbs + SEG - 1) / SEG, sd = (nbd + SEG - 1) / SEG;
-    reduce_tasks(ps, nvs, nbs, red);
-    reduce_tasks(pd, nvd, nbd, red + nvs * ss);
-    __syncthreads();
-    if (t < nvs) {
-        double2 s = red[t * ss];
-        for (int i = 1; i < ss; ++i) {
-            s.x += red[t * ss + i].x;
-            s.y += red[t * ss + i].y;
-        }
-        S[t] = s;
-    } else if (t >= 64 && t < 64 + nvd) {
-        const double2 *r = red + nvs * ss + (t - 64) * sd;
-        double2 s = r[0];
-        for (int i = 1; i < sd; ++i) {
-            s.x += r[i].x;
-            s.y += r[i].y;
-        }
-        R[t - 64] = s;
-    }
+    sum_values(ps, j > 0 ? j + 1 : 0, nbs, S);
+    if (ARN) sum_values(pd, j + 1, nbd, R);
+    else sum_single(pd, nbd, R);
     __syncthreads();
     double b = 1.0;
     double2 h = make_double2(0.0, 0.0);
     if (t < 64) {
         if (t < j) h = S[t];
         const double hh = group16_sum(make_double2(h.x * h.x + h.y * h.y, 0.0)).x;  // lanes 0-15 hold the h_i
-        int stop = 0;
-        if (j > 0) {
+        int stop = j >= meff;
+        if (j > 0 && !stop) {
             const double b2 = S[j].x - __shfl(hh, 0, 64);
             b = sqrt(b2 > 0.0 ? b2 : 0.0);
             const double est = est0 * kdt * b / (double)j;
@@ -198,7 +209,8 @@ __device__ void krylov_scalars(KState *ks, int j, const double2 *ps, int nbs, co
             }
             if (t < MAXM) sc.cc[t] = cc;
             if (t == 0) {
-                const double alpha = j > 0 ? (R[0].x - 2.0 * s.x + s.y) / (b * b) : R[0].x;
+                const double mu = four(R).x;
+                const double alpha = j > 0 ? (mu - 2.0 * s.x + s.y) / (b * b) : mu;
                 sc.alpha = alpha;
                 if (store && !stop) {
                     ks->alpha[j] = alpha;
@@ -269,12 +281,10 @@ __global__ __launch_bounds__(TB) void k_start(const double2 *psi, int64_t n, con
                                               KState *ks, int m, double dt, double tol, C *v0,
                                               const uint32_t *keys, C *xg)
 {
-    __shared__ double2 red[RED_BLOCKS / SEG];
-    reduce_tasks(partial, 1, nb, red);
+    __shared__ double2 quarter[4];
+    sum_single(partial, nb, quarter);
     __syncthreads();
-    double s2 = red[0].x;
-    for (int i = 1; i < (nb + SEG - 1) / SEG; ++i) s2 += red[i].x;
-    const double n0 = sqrt(s2);
+    const double n0 = sqrt(four(quarter).x);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         ks->n0 = n0;
         ks->meff = m;
@@ -317,7 +327,19 @@ __global__ __launch_bounds__(TB) void k_arnoldi_dots(const C *Vb, int64_t ld, co
         for (int i = 0; i < NV; ++i) cdot_acc(acc[i], ld2nt(Vb, (int64_t)i * ld + p), zv);
         cdot_acc(acc[NV], ld2(qs, p), zv);
     }
-    block_reduce_store<NV + 1>(acc, partial);
+    block_values_store<NV + 1>(acc, partial);
+}
+
+// a value that every lane holds, in scalar registers
+__device__ inline double2 uniform(double2 v)
+{
+    int w[4];
+    __builtin_memcpy(w, &v, 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    double2 r;
+    __builtin_memcpy(&r, w, 16);
+    return r;
 }
 
 // ---- sweeps --------------------------------------------------------------------
@@ -335,37 +357,48 @@ __global__ __launch_bounds__(TB) void k_arnoldi_dots(const C *Vb, int64_t ld, co
 // one step later.
 // Bound by HBM (j + 2 vectors read, 2 written) on large sets, by its launch and
 // prologue on small ones: a block per 256 points up to KRY_BLOCKS, so that a
-// small set's partials stay few.
+// small set's partials stay few, the first points' loads issued before the
+// prologue, and reductions of 16 values at once (8.6 us to 5.7 on 660 functions,
+// 11.4 to 7.5 on a 24^4 set, 83 us or 5.4 TB/s on 4M functions as before).
 template <class C, int NV, bool ARN>
-__global__ __launch_bounds__(TB) void k_sweep(C *Vb, int64_t ld, const C *z, int64_t n, KState *ks, const double2 *ps,
+__global__ __launch_bounds__(TB, 2) void k_sweep(C *Vb, int64_t ld, const C *z, int64_t n, KState *ks, const double2 *ps,
                                               int nbs, const double2 *pd, int nbd, double2 *pout,
                                               const uint32_t *keys, C *xg)
 {
     __shared__ Scalars sc;
-    if (NV >= ks->meff) return;
-    krylov_scalars<ARN>(ks, NV, ps, nbs, pd, nbd, sc);
-    if (sc.stop) return;
     constexpr int NH = NV > 0 ? NV : 1;
-    double2 hq[NH], cc[NV + 1], g1[ARN ? NV + 1 : 1];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) hq[i] = sc.h[i];
-#pragma unroll
-    for (int k = 0; k <= NV; ++k) {
-        cc[k] = sc.cc[k];
-        if (ARN) g1[k] = sc.g[k];
-    }
-    const double ib = sc.ib, al = ARN ? 0.0 : sc.alpha, bm = sc.bm;
     C *qs = Vb + (int64_t)NV * ld;
     C *qn = Vb + (int64_t)(NV + 1) * ld;
+    // the first points' loads are on their way while the prologue sums
+    double2 qv = make_double2(0.0, 0.0), hv = qv, vv[NH];
+    uint32_t key = 0;
+    const int64_t stride = (int64_t)gridDim.x * TB;
+    auto load = [&](int64_t p) {
+        if (p >= n) return;
+        qv = ld2nt(qs, p);
+        hv = ld2nt(z, p);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) vv[i] = ld2nt(Vb, (int64_t)i * ld + p);
+        if (xg) key = keys[p];
+    };
+    load(gid());
+    krylov_scalars<ARN>(ks, NV, ps, nbs, pd, nbd, sc);
+    if (sc.stop) return;
+    double2 hq[NH], cc[NV + 1], g1[ARN ? NV + 1 : 1];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) hq[i] = uniform(sc.h[i]);
+#pragma unroll
+    for (int k = 0; k <= NV; ++k) {
+        cc[k] = uniform(sc.cc[k]);
+        if (ARN) g1[k] = uniform(sc.g[k]);
+    }
+    const double ib = sc.ib, al = ARN ? 0.0 : sc.alpha, bm = sc.bm;
     double2 acc[NV + 2];
 #pragma unroll
     for (int i = 0; i < NV + 2; ++i) acc[i] = make_double2(0.0, 0.0);
-    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * TB) {
-        double2 qv = ld2nt(qs, p), hv = ld2nt(z, p);
-        double2 vv[NH];
+    for (int64_t p = gid(); p < n; p += stride) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            vv[i] = ld2nt(Vb, (int64_t)i * ld + p);
             qv.x -= hq[i].x * vv[i].x - hq[i].y * vv[i].y;
             qv.y -= hq[i].x * vv[i].y + hq[i].y * vv[i].x;
             hv.x -= cc[i].x * vv[i].x - cc[i].y * vv[i].y;
@@ -392,14 +425,15 @@ __global__ __launch_bounds__(TB) void k_sweep(C *Vb, int64_t ld, const C *z, int
             }
         }
         st2(qn, p, wp);
-        if (xg) st2(xg, keys[p], wp);
+        if (xg) st2(xg, key, wp);
         const double2 ws = stored(qn, wp);
 #pragma unroll
         for (int i = 0; i < NV; ++i) cdot_acc(acc[i], vv[i], ws);
         cdot_acc(acc[NV], vj, ws);
         acc[NV + 1].x = fma(ws.x, ws.x, fma(ws.y, ws.y, acc[NV + 1].x));
+        load(p + stride);
     }
-    block_reduce_store<NV + 2>(acc, pout);
+    block_values_store<NV + 2>(acc, pout);
 }
 
 // v_j = (q_j - sum_{i<j} h_i v_i) / beta_{j-1} in slot j: the last vector of a
@@ -552,11 +586,10 @@ __global__ __launch_bounds__(TB) void k_close(KState *ks, int m, const double2 *
     __shared__ int s_meff;
     if (threadIdx.x == 0) s_meff = ks->meff;
     __syncthreads();
-    const int m0 = s_meff;
-    int meff = m0;
-    if (pd && m0 == m) {
+    int meff = s_meff;
+    if (pd) {
         krylov_scalars<ARN>(ks, m - 1, ps, nbs, pd, nbd, sc);
-        if (sc.stop) meff = m - 1;
+        if (sc.stop) meff = meff < m - 1 ? meff : m - 1;
         __threadfence_block();
         __syncthreads();
     }
