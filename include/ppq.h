@@ -57,6 +57,11 @@
  *               operator's factors.  On grid vectors every factor reads its
  *               fibers from a vector over the whole grid, in one launch per
  *               factor depth, and no fiber tables are built.
+ *   PPQ_BATCH=0 / 2  products of the default layout on fiber tables a pass per
+ *               factor always / batched wherever they apply (dimensions of at
+ *               most 64 points); 1 (default) batches sets of up to 1.3 million
+ *               functions.  Batched, all factors of one depth share a launch on
+ *               the matrix cores and their results are added up at the end.
  *   PPQ_DILATE=1 / 2  adaption's dilation per function (atomics) / word by
  *               word from the bitmap of the functions kept (the +-1 stencil
  *               on DVR axes only); 0 (default) chooses by the grid-to-set

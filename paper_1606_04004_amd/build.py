@@ -9,7 +9,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["ppq_kernels.hip", "ppq_hpsi.hip", "ppq_grid.hip", "ppq_krylov.hip", "ppq_model.hip", "ppq_api.hip"]
+SOURCES = ["ppq_kernels.hip", "ppq_hpsi.hip", "ppq_grid.hip", "ppq_batch.hip", "ppq_krylov.hip", "ppq_model.hip", "ppq_api.hip"]
 LIB = os.path.join(HERE, "libppq.so")
 ARCH = os.environ.get("PPQ_OFFLOAD_ARCH", "gfx950")
 

@@ -214,6 +214,15 @@ struct ppq_ctx {
     void *gst_dev = nullptr;     // device copies of the stages, fine slices then coarse ones
     void *GT[MAXD]{};            // one-dimensional factors, column-major, in the context's precision
     std::vector<void *> GF;      // dense factors of product terms, likewise
+    // batched products on fiber tables (see batch_rule)
+    int batch_switch = 1;        // 0: never, 1: by the sizes, 2: wherever they apply (PPQ_BATCH)
+    bool batch_planned = false;  // the stages match the operator and the vectors
+    std::vector<void *> ybuf;    // the factors' results
+    int64_t ybuf_cap = 0;
+    std::vector<BatchStage<double>> bst64;
+    std::vector<BatchStage<float>> bst32;
+    BatchSum<double> bsum64{};
+    BatchSum<float> bsum32{};
     bool fibers_valid = false;   // the fiber tables match the set
 
     // <x|y> of a product fused into its last pass (Hermitian Krylov steps)
@@ -394,6 +403,9 @@ void free_krylov(ppq_ctx *c)
     dfree(c->wk);
     for (auto &z : c->zbuf) dfree(z);
     c->zbuf.clear();
+    for (auto &y : c->ybuf) dfree(y);
+    c->ybuf.clear();
+    c->batch_planned = false;
     c->kv_m = 0;
     c->kv_cap = 0;
 }
@@ -414,6 +426,7 @@ void free_operator(ppq_ctx *c)
     for (auto &p : c->GF) dfree(p);
     c->GF.clear();
     c->grid_planned = false;
+    c->batch_planned = false;
     for (auto &p : c->F64) dfree(p);
     for (auto &p : c->F32) dfree(p);
     for (auto &p : c->F64p) dfree(p);
@@ -670,6 +683,7 @@ void build_operator(ppq_ctx *c)
     for (auto &p : c->GF) dfree(p);
     c->GF.clear();
     c->grid_planned = false;
+    c->batch_planned = false;
     for (auto &p : c->F64) dfree(p);
     for (auto &p : c->F32) dfree(p);
     for (auto &p : c->F64p) dfree(p);
@@ -1189,14 +1203,15 @@ PlanePass plane_pass_of(const ppq_ctx *c, int i)
 // ---- products on grid vectors -------------------------------------------------
 constexpr int64_t GRID_TOTAL_MAX = int64_t(1) << 23;  // largest grid (functions)
 constexpr int64_t GRID_BYTES_MAX = int64_t(1) << 30;  // all grid vectors of a context
-constexpr int64_t GRID_REAL_MAX = int64_t(1) << 24;   // digits summed in one product (see use_grid)
-constexpr int64_t GRID_CPLX_MAX = int64_t(1) << 25;
+constexpr int64_t GRID_WORK_MAX = int64_t(1) << 24;   // digits summed in one product (see use_grid)
+constexpr int64_t GRID_TERMS_MAX = int64_t(1) << 26;  // ... of a DVR operator with product terms
 
 // Factors of one product with their depth: those that act on the product's
 // input are at depth 0, those on the results of depth d at d + 1.
 struct GridFactor {
     int depth, kind, k;
     const void *H, *H2;
+    const void *P, *P2;  // the same, 64 x 64 padded (dimensions of at most 64 points)
     int nin;
     int in[4];         // intermediates read (-1: the input)
     double cre[4], cim[4];
@@ -1212,12 +1227,15 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
 {
     std::vector<GridFactor> fs;
     const int D = c->g.D;
-    auto plain = [](int depth, int kind, int k, const void *H, int in, int dst) {
+    const bool f64 = c->precision == PPQ_FP64;
+    auto padded = [&](int f) -> const void * { return f64 ? (const void *)c->F64p[f] : (const void *)c->F32p[f]; };
+    auto plain = [](int depth, int kind, int k, const void *H, const void *P, int in, int dst) {
         GridFactor f{};
         f.depth = depth;
         f.kind = kind;
         f.k = k;
         f.H = H;
+        f.P = P;
         f.nin = 1;
         f.in[0] = in;
         f.cre[0] = 1.0;
@@ -1225,7 +1243,11 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
         f.dst2 = -1;
         return f;
     };
-    for (int k = 0; k < D; ++k) fs.push_back(plain(0, c->any_lattice ? GRID_CPLX : GRID_REAL, k, c->GT[k], -1, 0));
+    for (int k = 0; k < D; ++k) {
+        const void *P = c->any_lattice ? (f64 ? (const void *)c->H64p[k] : (const void *)c->H32p[k])
+                                       : (f64 ? (const void *)c->T64p[k] : (const void *)c->T32p[k]);
+        fs.push_back(plain(0, c->any_lattice ? GRID_CPLX : GRID_REAL, k, c->GT[k], P, -1, 0));
+    }
     int z = 0;
     // two-factor terms: each distinct inner factor once (with the dimension's own
     // factor where there is one to share the input), each outer factor on a
@@ -1239,13 +1261,14 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
         const int k = c->Fdim[inner[i]];
         if (c->any_lattice && !fs[k].H2) {
             fs[k].H2 = c->GF[inner[i]];
+            fs[k].P2 = padded(inner[i]);
             fs[k].dst2 = z + (int)i + 1;
         } else {
-            fs.push_back(plain(0, GRID_CPLX, k, c->GF[inner[i]], -1, z + (int)i + 1));
+            fs.push_back(plain(0, GRID_CPLX, k, c->GF[inner[i]], padded(inner[i]), -1, z + (int)i + 1));
         }
     }
     for (int f : outer) {
-        GridFactor a = plain(1, GRID_CPLX, c->Fdim[f], c->GF[f], -1, 0);
+        GridFactor a = plain(1, GRID_CPLX, c->Fdim[f], c->GF[f], padded(f), -1, 0);
         a.nin = 0;
         auto flush = [&] {
             if (a.nin == 0) return;
@@ -1270,7 +1293,7 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
         for (int f = t.nf - 1; f >= 0 || t.nf == 0; --f) {
             const bool last = f <= 0;
             GridFactor a = plain(t.nf ? t.nf - 1 - f : 0, t.nf ? GRID_CPLX : GRID_DIAG, t.nf ? t.k[f] : 0,
-                                 t.nf ? c->GF[t.fid[f]] : nullptr, src, last ? 0 : z + 1);
+                                 t.nf ? c->GF[t.fid[f]] : nullptr, t.nf ? padded(t.fid[f]) : nullptr, src, last ? 0 : z + 1);
             if (last) {
                 a.scaled = true;
                 a.cre[0] = t.cre;
@@ -1290,12 +1313,13 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
 
 // Whether the current set's products run on grid vectors: the default layout,
 // a grid whose vectors fit, and few enough digits in a product (a complex
-// factor's once for itself and once per input).  Above, the fiber tables'
-// passes, on the matrix cores where fibers are long, read less.  Measured, us a
-// product on fiber tables / grid vectors: 4D Morse 32^4, 52K functions (6.7M
-// digits) 52.9 / 18.3, 114K (14.6M) 47.9 / 28.6, 209K (26.7M) 28.6 / 46.6; the
-// 4D lattice, 14K (11M) 109 / 44, 36K (29M) 117 / 89, 146K (119M) 131 / 260;
-// general 3D terms, 44K (32M) 100 / 47.5, 96K (69M) 108 / 76.
+// factor's once for itself and once per input; general terms are chains of
+// factors, where the launches saved count for more).  Above, the batched passes on
+// fiber tables read only members and use the matrix cores, once the tables are
+// built.  Measured, us a step of order 10 from a new state, grid vectors / batched:
+// 4D Morse 32^4, 52K functions (6.7M digits) 277 / 345, 114K (14.6M) 397 / 426, 209K
+// (26.7M) 603 / 502; the 4D lattice, 14K (11M) 581 / 617, 36K (29M) 1026 / 697;
+// general 3D terms, 13K (9M) 372 / 723, 96K (69M) 967 / 1075.
 bool use_grid(const ppq_ctx *c)
 {
     if (c->hpsi_variant != 2 || c->grid_switch == 0 || c->nact <= 0 || (int64_t)c->g.total > GRID_TOTAL_MAX) return false;
@@ -1304,11 +1328,9 @@ bool use_grid(const ppq_ctx *c)
     const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
     if ((int64_t)c->g.total * es * (nz + 1) > GRID_BYTES_MAX) return false;
     int64_t digits = 0;
-    bool real = true;
-    for (const GridFactor &f : fs) real = real && f.kind == GRID_REAL;
     for (const GridFactor &f : fs)
         digits += f.kind == GRID_DIAG ? 1 : (int64_t)c->g.n[f.k] * (f.kind == GRID_CPLX ? 1 + f.nin : 1);
-    return c->grid_switch == 2 || c->nact * digits <= (real ? GRID_REAL_MAX : GRID_CPLX_MAX);
+    return c->grid_switch == 2 || c->nact * digits <= (!c->any_lattice && nz > 0 ? GRID_TERMS_MAX : GRID_WORK_MAX);
 }
 
 // The stages of the product (one launch each): factors of one depth, up to
@@ -1978,12 +2000,153 @@ void apply_products(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, in
     }
 }
 
+// ---- batched products on fiber tables --------------------------------------------
+// Stages (one launch per depth and BATCH_OPS factors) and the final sum.  A
+// factor that adds to y takes a vector that no other factor of its depth takes
+// (every factor writes all of the set's functions): the first ones write, later
+// depths add.  With stages == nullptr only ts.ny is worked out.
+template <class R>
+void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, std::vector<BatchStage<R>> *stages)
+{
+    using C = typename BatchOp<R>::C;
+    ts = BatchSum<R>{};
+    ts.nmax = c->pd_nmax;
+    if (stages) stages->clear();
+    int depth = 0;
+    for (const GridFactor &f : fs) depth = std::max(depth, f.depth);
+    for (int d = 0; d <= depth; ++d) {
+        int used = 0;
+        BatchStage<R> st{};
+        st.nmax = c->pd_nmax;
+        for (const GridFactor &f : fs) {
+            if (f.depth != d) continue;
+            if (f.kind == GRID_DIAG) {
+                if (stages) {
+                    ts.c[ts.ndiag] = C{(R)f.cre[0], (R)f.cim[0]};
+                    ts.diag[ts.ndiag] = f.diag;
+                    ts.use[ts.ndiag] = f.use;
+                }
+                ++ts.ndiag;
+                continue;
+            }
+            for (int second = 0; second <= (f.H2 ? 1 : 0); ++second) {
+                const int dst = second ? f.dst2 : f.dst;
+                const int y = dst == 0 ? used++ : -1;
+                const int add = y >= 0 && y < ts.ny ? 1 : 0;
+                ts.ny = std::max(ts.ny, y + 1);
+                if (!stages) continue;
+                BatchOp<R> &o = st.op[st.nop++];
+                o.out = (C *)(y >= 0 ? c->ybuf[y] : c->zbuf[dst - 1]);
+                o.add = add;
+                o.H = second ? f.P2 : f.P;
+                o.nin = f.nin;
+                for (int q = 0; q < f.nin; ++q) {
+                    o.x[q] = (const C *)(f.in[q] < 0 ? nullptr : c->zbuf[f.in[q]]);  // nullptr: the product's input
+                    o.c[q] = C{(R)f.cre[q], (R)f.cim[q]};
+                }
+                o.diag = f.diag;
+                o.use = f.use;
+                o.n = c->g.n[f.k];
+                o.kind = f.kind | (f.k << 8);  // the dimension until the set's tables are filled in
+                o.scaled = f.scaled && !second ? 1 : 0;
+                if (st.nop == BATCH_OPS) {
+                    stages->push_back(st);
+                    st.nop = 0;
+                }
+            }
+        }
+        if (stages && st.nop) stages->push_back(st);
+    }
+    if (stages)
+        for (int i = 0; i < ts.ny; ++i) ts.y[i] = (const C *)c->ybuf[i];
+}
+
+// Whether the current set's products (on fiber tables) are batched: the default
+// layout, dimensions within a mask word, and a set that leaves a pass by itself
+// short of wavefronts.  Large sets fill the chip pass by pass, and there the vectors
+// of the factors cost more traffic than the passes' own sums.  Measured, us a
+// product pass by pass / batched: 6D quartic 5.6K functions 31.7 / 12.4, 164K 53.9 /
+// 23.0, 730K 82 / 61, 1.26M 123 / 109, 1.93M 154 / 178 (FP32 119 / 121); 4D Morse
+// 114K 47.7 / 16.5, 338K 35.8 / 25.9, 1.05M 59 / 51; the 4D lattice 146K 132 / 84,
+// 563K 318 / 230, 1.28M 376 / 382 (FP32 280 / 235), 2.1M 557 / 566 (343 / 272),
+// 3.9M 856 / 887 (477 / 481).
+constexpr int64_t BATCH_MAX = int64_t(5) << 18;
+bool use_batch(ppq_ctx *c)
+{
+    if (c->hpsi_variant != 2 || c->batch_switch == 0 || c->nact <= 0 || any_long(c)) return false;
+    const bool complex32 = c->precision == PPQ_FP32 && (c->any_lattice || !c->pairs.empty() || !c->chains.empty());
+    if (c->batch_switch == 1 && c->nact > (complex32 ? 2 * BATCH_MAX : BATCH_MAX)) return false;
+    ensure_nf(c);
+    int nz = 0, ndiag = 0;
+    if (c->batch_planned && c->ybuf_cap == c->cap) return true;
+    const std::vector<GridFactor> fs = grid_factors(c, &nz);
+    for (const GridFactor &f : fs) ndiag += f.kind == GRID_DIAG;
+    const bool f64 = c->precision == PPQ_FP64;
+    if (ndiag > BATCH_DIAGS) return false;
+    if (f64) plan_batch<double>(c, fs, c->bsum64, nullptr);
+    else plan_batch<float>(c, fs, c->bsum32, nullptr);
+    const int ny = f64 ? c->bsum64.ny : c->bsum32.ny;
+    if (ny > BATCH_SUMS) return false;
+    const int64_t es = f64 ? sizeof(double2) : sizeof(float2);
+    while ((int)c->zbuf.size() < nz) {
+        c->zbuf.push_back(nullptr);
+        c->zbuf.back() = dalloc<unsigned char>(es * c->cap);
+    }
+    while ((int)c->ybuf.size() < ny) {
+        c->ybuf.push_back(nullptr);
+        c->ybuf.back() = dalloc<unsigned char>(es * c->cap);
+    }
+    c->ybuf_cap = c->cap;
+    if (f64) plan_batch<double>(c, fs, c->bsum64, &c->bst64);
+    else plan_batch<float>(c, fs, c->bsum32, &c->bst32);
+    c->batch_planned = true;
+    return true;
+}
+
+template <class R>
+void apply_batch_t(ppq_ctx *c, const std::vector<BatchStage<R>> &stages, const BatchSum<R> &ts, const void *xv, void *yv,
+                   const int *skip_if, int skip_j, int dots, const void *Vb)
+{
+    using C = typename BatchOp<R>::C;
+    const uint32_t *keys = c->keys[c->cur];
+    for (const BatchStage<R> &plan : stages) {
+        BatchStage<R> st = plan;
+        for (int o = 0; o < st.nop; ++o) {
+            BatchOp<R> &op = st.op[o];
+            const int k = op.kind >> 8;
+            op.kind &= 255;
+            op.pi = k == c->g.D - 1 ? nullptr : c->pi[k];
+            op.off = c->off[k];
+            op.mask = c->mask[k];
+            op.nf = c->nf[k];
+            for (int q = 0; q < op.nin; ++q)
+                if (!op.x[q]) op.x[q] = (const C *)xv;
+        }
+        batch_launch<R>(st, c->g, keys, skip_if, skip_j, c->stream);
+    }
+    const R *V = nullptr;
+    if (!c->any_lattice) V = c->precision == PPQ_FP64 ? (const R *)c->V64 : (const R *)c->V32;
+    c->dot_nb = batch_combine<R>(ts, c->g, keys, c->nact, (const C *)xv, V, (C *)yv, dots, (const C *)Vb, c->cap,
+                                 c->partial + KRY_DOTS, skip_if, skip_j, c->stream);
+}
+
+// y = P H P x; dots: 0 none, else <v_i|y> for the first dots - 1 vectors at Vb and <x|y>
+void apply_batch(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, int skip_j, int dots, const void *Vb)
+{
+    if (c->precision == PPQ_FP64) apply_batch_t<double>(c, c->bst64, c->bsum64, xv, yv, skip_if, skip_j, dots, Vb);
+    else apply_batch_t<float>(c, c->bst32, c->bsum32, xv, yv, skip_if, skip_j, dots, Vb);
+}
+
 // y = P H P x on the current set (device vectors of the context precision)
 void apply_launches(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, int skip_j)
 {
     if (c->grid_mode) {
         if (c->precision == PPQ_FP64) apply_grid<double>(c, c->gst64, xv, yv, skip_if, skip_j, 0, nullptr, 0);
         else apply_grid<float>(c, c->gst32, xv, yv, skip_if, skip_j, 0, nullptr, 0);
+        return;
+    }
+    if (use_batch(c)) {
+        apply_batch(c, xv, yv, skip_if, skip_j, 0, nullptr);
         return;
     }
     // a fused <x|y> needs the single-factor passes to write y last
@@ -2072,7 +2235,6 @@ void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, doub
     const bool herm = c->hermitian;
     // on grid vectors the basis kernels write each new vector into the product's
     // input themselves and the product leaves all its dots
-    using R = decltype(C::x);
     const uint32_t *keys = c->keys[c->cur];
     C *xg = c->grid_mode ? (C *)c->xg : nullptr;
     kry_start<C>(src, n, c->partial, ks, m, dt, tol, Vb, keys, xg, s);
@@ -2085,8 +2247,11 @@ void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, doub
         mark(c, PPQ_PHASE_HPSI);
         if (xg) {
             if constexpr (std::is_same<C, double2>::value)
-                apply_grid<R>(c, c->gst64, nullptr, w, meff, j, herm ? 1 : 2, Vb, j + 1);
-            else apply_grid<R>(c, c->gst32, nullptr, w, meff, j, herm ? 1 : 2, Vb, j + 1);
+                apply_grid<double>(c, c->gst64, nullptr, w, meff, j, herm ? 1 : 2, Vb, j + 1);
+            else apply_grid<float>(c, c->gst32, nullptr, w, meff, j, herm ? 1 : 2, Vb, j + 1);
+            ck(hipGetLastError(), "H*psi launch");
+        } else if (use_batch(c)) {
+            apply_batch(c, qj, w, meff, j, herm ? 1 : j + 1, Vb);
             ck(hipGetLastError(), "H*psi launch");
         } else {
             c->dot_want = herm;
@@ -2695,6 +2860,10 @@ int ppq_create(ppq_ctx **out, int device, void *hip_stream, int precision)
     if (const char *v = std::getenv("PPQ_GRID")) {
         const int d = std::atoi(v);
         if (d >= 0 && d <= 2) c->grid_switch = d;
+    }
+    if (const char *v = std::getenv("PPQ_BATCH")) {
+        const int d = std::atoi(v);
+        if (d >= 0 && d <= 2) c->batch_switch = d;
     }
     if (const char *v = std::getenv("PPQ_BLOCK_WINDOW")) {
         const long w = std::atol(v);

@@ -95,6 +95,58 @@ __device__ inline void block_reduce_store(double2 (&acc)[NV], double2 *partial)
 
 __device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 
+template <class R>
+struct Cplx;
+template <>
+struct Cplx<double> {
+    using T = double2;
+    using V = double __attribute__((ext_vector_type(2)));
+    __device__ static T make(double x, double y) { return make_double2(x, y); }
+};
+template <>
+struct Cplx<float> {
+    using T = float2;
+    using V = float __attribute__((ext_vector_type(2)));
+    __device__ static T make(float x, float y) { return make_float2(x, y); }
+};
+
+// A launch's description in device memory is read-only and its fields are wave-uniform: constant
+// address space, so they come through the scalar cache.  The vectors and factors it
+// names are global memory: a scalar base and a 32-bit lane offset per load.
+typedef __attribute__((address_space(1))) const char gbyte;
+template <class T>
+__device__ inline T field(const T *p)
+{
+    return *(const __attribute__((address_space(4))) T *)p;
+}
+__device__ inline gbyte *global_base(const void *const *p)
+{
+    return (gbyte *)(const char *)field((const char *const *)p);
+}
+template <class T>
+__device__ inline T at_byte(gbyte *base, uint32_t off)
+{
+    return *(__attribute__((address_space(1))) const T *)(base + off);
+}
+
+template <class V>
+__device__ inline void cmul_acc(V &acc, V h, V v)
+{
+    acc.x = __builtin_elementwise_fma(h.x, v.x, __builtin_elementwise_fma(-h.y, v.y, acc.x));
+    acc.y = __builtin_elementwise_fma(h.x, v.y, __builtin_elementwise_fma(h.y, v.x, acc.y));
+}
+
+// prod_{k in use} tab[k * nmax + i_k]: the diagonal factors of a product term
+__device__ inline double diag_value(const GridDesc &g, gbyte *tab, int nmax, unsigned use, uint32_t key)
+{
+    double v = 1.0;
+    for (int k = 0; k < g.D; ++k)
+        if ((use >> k) & 1u)
+            v *= at_byte<double>(tab + (int64_t)k * nmax * sizeof(double),
+                                 ((key / g.stride[k]) % (uint32_t)g.n[k]) * (uint32_t)sizeof(double));
+    return v;
+}
+
 }  // namespace
 
 }  // namespace ppq

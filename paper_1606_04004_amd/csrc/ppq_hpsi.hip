@@ -21,7 +21,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "ppq_internal.hpp"
+#include "ppq_mfma.hpp"
 
 namespace ppq {
 namespace {
@@ -528,28 +528,8 @@ void launch_pt(const uint32_t *pi, const uint8_t *info, int64_t n, int nmax, con
 // column-major, so that the 16 lanes of a column of A read one run of memory
 // (row-major, every lane of an A load touched a cache line of its own: a
 // product of the 4D lattice model on 563K functions 286 us, 279 us now).
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int MFB = 256;  // 4 wavefronts, 64 fibers per block
 constexpr int MFP = 64;   // padded size of h
-
-template <class R>
-struct Mma;
-template <>
-struct Mma<float> {
-    using V4 = floatx4;
-    __device__ static V4 op(float a, float b, V4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    // row of the accumulator's element r in lane group kr, and the digit fed
-    // by lane group k at step kb: the same map, so a lane holds outputs at
-    // exactly the digits it feeds
-    __device__ static int row(int k, int r) { return 4 * k + r; }
-};
-template <>
-struct Mma<double> {
-    using V4 = doublex4;
-    __device__ static V4 op(double a, double b, V4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    __device__ static int row(int k, int r) { return k + 4 * r; }
-};
 
 // Inputs of a matrix-core pass: x = sum_i c_i x_i (one unweighted input for
 // real factors).

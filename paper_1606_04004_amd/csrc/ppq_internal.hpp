@@ -417,6 +417,52 @@ void grid_put(const uint32_t *keys, const C *x, int64_t n, C *xg, hipStream_t s)
 template <class C>
 void grid_clear(const uint32_t *keys, int64_t n, C *xg, hipStream_t s);
 
+// ---- batched products on fiber tables (ppq_batch.hip) --------------------------
+// Dimensions of at most 64 points.  The factors of one depth share a launch:
+// out = (or +=, with add) h (sum_i c_i x_i), each into a vector of its own.
+constexpr int BATCH_BLOCKS = 1024;
+constexpr int BATCH_OPS = 16;    // factors of a launch
+constexpr int BATCH_SUMS = 16;   // vectors a product's result is summed from
+constexpr int BATCH_DIAGS = 8;   // terms without dense factors
+template <class R>
+struct BatchOp {
+    using C = typename GridOp<R>::C;
+    const void *H;       // 64 x 64 padded, column-major
+    const uint32_t *pi;  // the dimension's fiber tables (pi: nullptr for the last)
+    const uint32_t *off;
+    const uint64_t *mask;
+    const C *x[4];
+    C c[4];
+    C *out;
+    const double *diag;
+    int64_t nf;
+    unsigned use;
+    int n, kind, nin, scaled, add;
+};
+template <class R>
+struct BatchStage {
+    BatchOp<R> op[BATCH_OPS];
+    int first[BATCH_OPS + 1];  // first workgroup of each factor
+    int nop, nmax;
+};
+template <class R>
+struct BatchSum {
+    using C = typename GridOp<R>::C;
+    int ny, ndiag, nmax;
+    const C *y[BATCH_SUMS];
+    C c[BATCH_DIAGS];
+    const double *diag[BATCH_DIAGS];
+    unsigned use[BATCH_DIAGS];
+};
+template <class R>
+void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, const int *skip_if, int skip_j, hipStream_t s);
+// y = V x + the vectors of ts.  dots: 0, or 1 + nv for the dots <v_i|y> with the nv
+// vectors at Vb and <x|y> (value-major partials); returns their blocks.
+template <class R>
+int batch_combine(const BatchSum<R> &ts, const GridDesc &g, const uint32_t *keys, int64_t n, const typename GridOp<R>::C *x,
+                  const R *V, typename GridOp<R>::C *y, int dots, const typename GridOp<R>::C *Vb, int64_t ld,
+                  double2 *partial, const int *skip_if, int skip_j, hipStream_t s);
+
 // observables
 void obs_partial(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, const double2 *bra,
                  int nmax, double eps2, double2 *partial, hipStream_t s);
