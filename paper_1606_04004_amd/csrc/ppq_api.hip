@@ -238,6 +238,7 @@ struct ppq_ctx {
     uint32_t *prefix = nullptr;
     uint64_t *kbm = nullptr;  // adaption: the functions above the threshold (word-parallel dilation)
     int64_t kbm_words = 0;
+    bool kbm_clean = false;   // ... and all clear
     int dilate_mode = 0;      // 0: by the sizes, 1: per function (atomics), 2: word by word (PPQ_DILATE)
     uint32_t *small = nullptr;            // device counters
     unsigned long long *count = nullptr;  // device counter
@@ -263,8 +264,7 @@ struct ppq_ctx {
     double krylov_tol = 0.0; // > 0: SIL order chosen per step by its error estimate
     int max_substeps = 1;    // > 1 (with krylov_tol > 0): step size control
     int nsub = 1;            // substeps the next controlled step starts with
-    double *sub_meff = nullptr;    // device: Krylov order of each substep of an attempt
-    double *h_sub_meff = nullptr;  // pinned mirror
+    double *h_sub_meff = nullptr;  // pinned: Krylov order of each substep of an attempt
     int sub_cap = 0;
     double2 *psi_save = nullptr;   // the state at the start of a controlled step
     int64_t psi_save_cap = 0;
@@ -2225,7 +2225,7 @@ void mark(ppq_ctx *c, int phase)
 // without it every basis vector is left corrected (the adjoint reads the basis).
 template <class C>
 void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, double dt = 0.0, double tol = 0.0,
-                  bool expv = false)
+                  bool expv = false, double *alpha0 = nullptr, double *order = nullptr)
 {
     hipStream_t s = c->stream;
     const int64_t n = c->nact;
@@ -2265,17 +2265,17 @@ void krylov_build(ppq_ctx *c, const double2 *src, C *Vb, KState *ks, int m, doub
             kry_sweep<C>(Vb, ld, w, n, c->partial, nbd, ks, j, !herm, keys, xg, s);
             continue;
         }
-        kry_close(ks, m, c->partial, n, nbd, dt, herm, expv, expv, s);
+        kry_close(ks, m, c->partial, n, nbd, dt, herm, expv, expv, s, alpha0, order);
         if (!expv && j > 0) kry_fix_last<C>(Vb, ld, n, ks, j, s);
     }
 }
 
 template <class C>
-void step_impl(ppq_ctx *c, double dt, int m, double tol)
+void step_impl(ppq_ctx *c, double dt, int m, double tol, double *alpha0 = nullptr, double *order = nullptr)
 {
     mark(c, PPQ_PHASE_KRYLOV);
     C *Vb = (C *)c->Vk;
-    krylov_build<C>(c, c->psi[c->cur], Vb, c->ks, m, dt, tol, true);
+    krylov_build<C>(c, c->psi[c->cur], Vb, c->ks, m, dt, tol, true, alpha0, order);
     lincomb<C>(Vb, c->cap, c->psi[c->cur], c->nact, c->ks, c->psi_tmp, c->stream);
     std::swap(c->psi[c->cur], c->psi_tmp);
 }
@@ -2287,16 +2287,17 @@ struct StepInfo {
     int nsub = 1;
 };
 
-void step_any(ppq_ctx *c, double dt, int m)
+// alpha0, order: as for kry_close
+void step_any(ppq_ctx *c, double dt, int m, double *alpha0, double *order)
 {
-    if (c->precision == PPQ_FP64) step_impl<double2>(c, dt, m, c->krylov_tol);
-    else step_impl<float2>(c, dt, m, c->krylov_tol);
+    if (c->precision == PPQ_FP64) step_impl<double2>(c, dt, m, c->krylov_tol, alpha0, order);
+    else step_impl<float2>(c, dt, m, c->krylov_tol, alpha0, order);
 }
 
 // One step of length dt on the current set (tables built).  Without step
 // control one SIL step.  With control (max_substeps > 1 and a Krylov
 // tolerance) s substeps of dt/s, s from the previous step; each substep's
-// order goes to sub_meff and the host reads them once per attempt: an order
+// order goes to pinned memory and the host reads them once per attempt: an order
 // of m means the tolerance was not met below m, and the step is redone from
 // its saved start with 2s substeps.  alpha0_dst (device, may be NULL)
 // receives alpha_0 of the first substep: the energy of the state at the start.
@@ -2306,15 +2307,12 @@ StepInfo advance(ppq_ctx *c, double dt, int m, double *alpha0_dst)
     hipStream_t s = c->stream;
     if (c->nact == 0) return info;
     if (c->max_substeps <= 1 || !(c->krylov_tol > 0.0)) {
-        step_any(c, dt, m);
-        if (alpha0_dst) copy_alpha0(c->ks, alpha0_dst, s);
+        step_any(c, dt, m, alpha0_dst, nullptr);
         return info;
     }
     if (c->sub_cap < c->max_substeps) {
-        dfree(c->sub_meff);
         if (c->h_sub_meff) (void)hipHostFree(c->h_sub_meff);
         c->h_sub_meff = nullptr;
-        c->sub_meff = dalloc<double>(c->max_substeps);
         ck(hipHostMalloc((void **)&c->h_sub_meff, sizeof(double) * c->max_substeps, hipHostMallocDefault),
            "pinned");
         c->sub_cap = c->max_substeps;
@@ -2329,11 +2327,8 @@ StepInfo advance(ppq_ctx *c, double dt, int m, double *alpha0_dst)
     for (;;) {
         const double h = dt / (double)sub;
         for (int j = 0; j < sub; ++j) {
-            step_any(c, h, m);
-            if (j == 0 && alpha0_dst) copy_alpha0(c->ks, alpha0_dst, s);
-            copy_meff(c->ks, c->sub_meff + j, s);
+            step_any(c, h, m, j == 0 ? alpha0_dst : nullptr, c->h_sub_meff + j);
         }
-        ck(hipMemcpyAsync(c->h_sub_meff, c->sub_meff, sizeof(double) * sub, hipMemcpyDeviceToHost, s), "orders");
         ck(hipStreamSynchronize(s), "orders");
         int mo = 0;
         bool ok = true;
@@ -2373,7 +2368,6 @@ void do_prune(ppq_ctx *c, double eps, int64_t *nabove_out)
     hipStream_t s = c->stream;
     const int64_t n_old = c->nact;
     double eps2 = eps * eps;
-    fill_u64((uint64_t *)c->count, 1, 0ull, s);
     // the +-1 stencil on DVR axes word by word while the grid's bitmap is not
     // much larger than the set (every word is visited); else per function
     const bool words = c->g.pairs == 0 && !c->any_lattice && c->dilate_mode != 1 &&
@@ -2383,53 +2377,52 @@ void do_prune(ppq_ctx *c, double eps, int64_t *nabove_out)
             dfree(c->kbm);
             c->kbm = dalloc<uint64_t>(c->nwords);
             c->kbm_words = c->nwords;
+            c->kbm_clean = false;
         }
+        if (!c->kbm_clean) fill_u64(c->kbm, c->nwords, 0ull, s);
+        c->kbm_clean = false;  // until the compaction has cleared it again
         dilate_words(c->keys[c->cur], c->psi[c->cur], n_old, c->g, eps2, c->kbm, c->bm, c->nwords, c->count,
-                     c->flags, s);
+                     c->flags, c->scan_tmp, s);
     } else {
+        fill_u64((uint64_t *)c->count, 1, 0ull, s);
         fill_u64(c->bm, c->nwords + 2, 0ull, s);
         dilate(c->keys[c->cur], c->psi[c->cur], n_old, c->g, eps2, c->bm, c->count, c->flags, s);
     }
     if (c->rel_excl > 0.0)
         keep_all_if_few_dropped(c->keys[c->cur], n_old, c->bm, c->rel_excl, c->flags, c->count + 1, s);
-    scan_popcount(c->bm, c->nwords, c->prefix, &c->small[MAXD], c->scan_tmp, s);
-    ck(hipMemcpyAsync(c->h_small + MAXD, c->small + MAXD, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "count");
-    ck(hipMemcpyAsync(c->h_count, c->count, sizeof(unsigned long long), hipMemcpyDeviceToHost, s), "count");
+    if (!words || c->rel_excl > 0.0) scan_reduce_popcount(c->bm, c->nwords, c->scan_tmp, s);
+    scan_top(c->scan_tmp, c->nwords, &c->small[MAXD], c->h_small + MAXD, c->count, c->h_count, s);
     ck(hipStreamSynchronize(s), "prune count");
     int64_t n_new = c->h_small[MAXD];
     if (nabove_out) *nabove_out = (int64_t)*c->h_count;
-    if (n_new > c->cap) ensure_capacity(c, n_new);  // keeps keys/psi of the current set
+    // (a growth frees the scan's tile offsets: they are formed again)
+    if (n_new > c->cap) {
+        ensure_capacity(c, n_new);  // keeps keys/psi of the current set
+        scan_reduce_popcount(c->bm, c->nwords, c->scan_tmp, s);
+        scan_top(c->scan_tmp, c->nwords, &c->small[MAXD], nullptr, nullptr, nullptr, s);
+    }
     int nxt = 1 - c->cur;
-    compact(c->bm, c->prefix, c->nwords, c->keys[nxt], s);
-    fill_zero_bytes(c->psi[nxt], n_new * (int64_t)sizeof(double2), s);
-    remap(c->keys[c->cur], c->psi[c->cur], n_old, c->bm, c->prefix, c->psi[nxt], s);
+    apply_compact(c->bm, c->nwords, c->scan_tmp, c->prefix, c->keys[nxt], words ? c->kbm : nullptr, s);
+    if (words) c->kbm_clean = true;
     // The diagonal potential of the functions that stay is carried over;
     // only the added ones are evaluated again (NaN marks them).
     const bool carry = c->v_valid && !c->any_lattice;
+    const uint32_t *okeys = c->keys[c->cur];
+    const double2 *opsi = c->psi[c->cur];
     if (carry) {
-        if (c->precision == PPQ_FP64) {
-            std::swap(c->V64, c->Vt64);
-            fill_u64(reinterpret_cast<uint64_t *>(c->V64), n_new, 0x7ff8000000000000ull, s);
-            remap_values(c->keys[c->cur], c->Vt64, n_old, c->bm, c->prefix, c->V64, s);
-        } else {
-            std::swap(c->V32, c->Vt32);
-            fill_u32(reinterpret_cast<uint32_t *>(c->V32), n_new, 0x7fc00000u, s);
-            remap_values(c->keys[c->cur], c->Vt32, n_old, c->bm, c->prefix, c->V32, s);
-        }
+        std::swap(c->V64, c->Vt64);
+        std::swap(c->V32, c->Vt32);
     }
+    if (c->precision == PPQ_FP64)
+        carry_over<double>(okeys, opsi, c->Vt64, n_old, c->bm, c->prefix, c->psi[nxt], carry ? c->V64 : nullptr, n_new, s);
+    else
+        carry_over<float>(okeys, opsi, c->Vt32, n_old, c->bm, c->prefix, c->psi[nxt], carry ? c->V32 : nullptr, n_new, s);
     leave_set(c);
     c->cur = nxt;
     c->nact = n_new;
     c->derived_valid = false;
     c->v_valid = false;
     c->v_partial = carry;
-}
-
-void set_record_host(ppq_ctx *c, int64_t r, double t, int krylov, int nsub = 1)
-{
-    // t, |A|, the Krylov dimension and the substeps are host-known: kernel
-    // arguments, no sync
-    set_record(c->rec + r * PPQ_OBS_N, t, (double)c->nact, (double)krylov, (double)nsub, c->stream);
 }
 
 void ensure_records(ppq_ctx *c, int64_t nrec)
@@ -2441,15 +2434,17 @@ void ensure_records(ppq_ctx *c, int64_t nrec)
     fill_zero_bytes(c->rec, nrec * PPQ_OBS_N * (int64_t)sizeof(double), c->stream);
 }
 
-// observables of the current set into record r (energy left to the caller)
-void observe_into(ppq_ctx *c, int64_t r, double eps)
+// observables of the current set into record r (energy left to the caller);
+// krylov < 0: the last step's order, which only the device knows
+void observe_into(ppq_ctx *c, int64_t r, double eps, double t, int krylov, int nsub)
 {
     double *rec = c->rec + r * PPQ_OBS_N;
     // without a reference packet the tables are zero and C(t) reads 0
     const double2 *bra = c->bra_tabs;
     obs_partial(c->keys[c->cur], c->psi[c->cur], c->nact, c->g, bra, c->tab_nmax, eps * eps, c->partial,
                 c->stream);
-    obs_final(c->partial, RED_BLOCKS, rec, c->stream);
+    const ObsFields f{t, (double)c->nact, (double)krylov, (double)nsub};
+    obs_final(c->partial, c->nact, rec, f, krylov < 0 ? c->ks : nullptr, c->stream);
 }
 
 // energy of the current state by one explicit application (FP64 master in, precision of the context)
@@ -2470,8 +2465,7 @@ void energy_into(ppq_ctx *c, int64_t r)
         apply_internal(c, x32, c->wk, nullptr, 0);
         const int nbd = kry_dots<float2>(x32, c->cap, (const float2 *)c->wk, c->nact, c->partial, ks, 0, false,
                                          c->stream);
-        kry_close(ks, 1, c->partial, c->nact, nbd, 0.0, true, false, false, c->stream);
-        copy_alpha0(ks, rec + PPQ_OBS_ENERGY, c->stream);
+        kry_close(ks, 1, c->partial, c->nact, nbd, 0.0, true, false, false, c->stream, rec + PPQ_OBS_ENERGY);
         return;
     }
     energy_from_dot(c->partial, RED_BLOCKS, rec, c->stream);
@@ -2640,7 +2634,7 @@ double2 overlap_with_packet(ppq_ctx *c)
 {
     ensure_records(c, 1);
     obs_partial(c->keys[c->cur], c->psi[c->cur], c->nact, c->g, c->bra_tabs, c->tab_nmax, 0.0, c->partial, c->stream);
-    obs_final(c->partial, RED_BLOCKS, c->rec, c->stream);
+    obs_final(c->partial, c->nact, c->rec, ObsFields{}, nullptr, c->stream);
     double r[PPQ_OBS_N];
     ck(hipMemcpyAsync(r, c->rec, sizeof(r), hipMemcpyDeviceToHost, c->stream), "C");
     ck(hipStreamSynchronize(c->stream), "C");
@@ -2916,7 +2910,6 @@ void ppq_destroy(ppq_ctx *c)
     dfree(c->ks);
     dfree(c->partial);
     for (auto &p : c->full) dfree(p);
-    dfree(c->sub_meff);
     if (c->h_sub_meff) (void)hipHostFree(c->h_sub_meff);
     dfree(c->small);
     dfree(c->count);
@@ -3248,15 +3241,19 @@ int ppq_init_gaussian(ppq_ctx *c, const double *centre, const double *momentum, 
         fill_u64(c->bm, c->nwords + 2, 0ull, s);
         fill_u64((uint64_t *)c->count, 1, 0ull, s);
         init_flag(c->g, c->init_tabs, nmax, eps * eps, c->bm, c->count, s);
-        scan_popcount(c->bm, c->nwords, c->prefix, &c->small[MAXD], c->scan_tmp, s);
-        ck(hipMemcpyAsync(c->h_small + MAXD, c->small + MAXD, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "n");
+        scan_reduce_popcount(c->bm, c->nwords, c->scan_tmp, s);
+        scan_top(c->scan_tmp, c->nwords, &c->small[MAXD], c->h_small + MAXD, nullptr, nullptr, s);
         ck(hipStreamSynchronize(s), "init count");
         int64_t n0 = c->h_small[MAXD];
         leave_set(c);
         c->has_state = false;
         c->nact = 0;
-        ensure_capacity(c, std::max<int64_t>(n0, 1));
-        compact(c->bm, c->prefix, c->nwords, c->keys[c->cur], s);
+        if (std::max<int64_t>(n0, 1) > c->cap) {
+            ensure_capacity(c, std::max<int64_t>(n0, 1));  // frees the scan's tile offsets
+            scan_reduce_popcount(c->bm, c->nwords, c->scan_tmp, s);
+            scan_top(c->scan_tmp, c->nwords, &c->small[MAXD], nullptr, nullptr, nullptr, s);
+        }
+        apply_compact(c->bm, c->nwords, c->scan_tmp, c->prefix, c->keys[c->cur], nullptr, s);
         product_values(c->keys[c->cur], n0, c->g, c->init_tabs, nmax, c->psi[c->cur], s);
         c->nact = n0;
         c->has_state = true;
@@ -3527,8 +3524,7 @@ int ppq_propagate(ppq_ctx *c, int nsteps, double dt, int m, double eps, double *
         mark(c, PPQ_PHASE_TABLES);
         build_derived(c);
         mark(c, PPQ_PHASE_OBS);
-        observe_into(c, 0, eps_obs);
-        set_record_host(c, 0, 0.0, 0, 0);
+        observe_into(c, 0, eps_obs, 0.0, 0, 0);
         for (int st = 1; st <= nsteps; ++st) {
             mark(c, PPQ_PHASE_TABLES);
             build_derived(c);
@@ -3540,9 +3536,7 @@ int ppq_propagate(ppq_ctx *c, int nsteps, double dt, int m, double eps, double *
             mark(c, PPQ_PHASE_TABLES);
             build_derived(c);
             mark(c, PPQ_PHASE_OBS);
-            observe_into(c, st, eps_obs);
-            set_record_host(c, st, st * dt, info.meff >= 0 ? info.meff : m, info.nsub);
-            if (had && info.meff < 0) copy_meff(c->ks, c->rec + (int64_t)st * PPQ_OBS_N + PPQ_OBS_KRYLOV, c->stream);
+            observe_into(c, st, eps_obs, st * dt, info.meff >= 0 ? info.meff : (had ? -1 : m), info.nsub);
         }
         energy_into(c, nsteps);
         mark(c, PHASE_NONE);
@@ -3565,8 +3559,7 @@ int ppq_observables(ppq_ctx *c, double eps, double *out)
         if (!c->scan_tmp) ensure_capacity(c, 1024);
         ensure_records(c, 1);
         build_derived(c);
-        observe_into(c, 0, eps);
-        set_record_host(c, 0, 0.0, 0, 0);
+        observe_into(c, 0, eps, 0.0, 0, 0);
         energy_into(c, 0);
         ck(hipStreamSynchronize(c->stream), "observables");
         ck(hipMemcpy(out, c->rec, sizeof(double) * PPQ_OBS_N, hipMemcpyDeviceToHost), "obs");

@@ -80,12 +80,25 @@ void product_values(const uint32_t *keys, int64_t n, const GridDesc &g, const do
 void dilate(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, double eps2, uint64_t *bm,
             unsigned long long *nabove, unsigned *block_counts, hipStream_t s);
 // The same dilation for the +-1 stencil on a grid without lattice axes, word
-// by word: K (nwords words of work space) gets one bit per function above the
+// by word: K (nwords words, clear) gets one bit per function above the
 // threshold, then every word of bm (nwords + 2 words) is written from K and
-// its shifts by the strides.  Costs O(nwords) instead of O(n) atomics.
+// its shifts by the strides, with the tile sums of bm's popcount scan.  Costs
+// O(nwords) instead of O(n) atomics.
 void dilate_words(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, double eps2, uint64_t *K,
-                  uint64_t *bm, int64_t nwords, unsigned long long *nabove, unsigned *block_counts, hipStream_t s);
-void compact(const uint64_t *bm, const uint32_t *prefix, int64_t nwords, uint32_t *keys_out, hipStream_t s);
+                  uint64_t *bm, int64_t nwords, unsigned long long *nabove, unsigned *block_counts, uint32_t *tile_sums,
+                  hipStream_t s);
+// The popcount scan in its parts: tile sums; their offsets and the total (with
+// pinned mirrors of the total and of *count); every word's prefix together with
+// the keys of its bits (and K, if given, cleared).
+void scan_reduce_popcount(const uint64_t *words, int64_t nwords, uint32_t *tile_sums, hipStream_t s);
+void scan_top(uint32_t *tile_sums, int64_t nwords, uint32_t *total, uint32_t *host_total,
+              const unsigned long long *count, unsigned long long *host_count, hipStream_t s);
+void apply_compact(const uint64_t *bm, int64_t nwords, const uint32_t *tile_off, uint32_t *prefix, uint32_t *keys_out,
+                   uint64_t *K, hipStream_t s);
+// npsi (and nV, optional): the old functions' values that stay, zeros (NaN) for new ones
+template <class T>
+void carry_over(const uint32_t *okeys, const double2 *opsi, const T *oV, int64_t n_old, const uint64_t *bm,
+                const uint32_t *prefix, double2 *npsi, T *nV, int64_t n_new, hipStream_t s);
 void remap(const uint32_t *okeys, const double2 *opsi, int64_t n_old, const uint64_t *bm, const uint32_t *prefix,
            double2 *npsi, hipStream_t s);
 // relative exclusion: sets the bits of all n keys when at most rel * n of them
@@ -145,11 +158,6 @@ void fib_fill(const uint32_t *flags, const uint32_t *fidx, const uint64_t *tmpma
 // (one device counter) only where V holds NaN, the rest is kept
 void potential(const uint32_t *keys, int64_t n, const GridDesc &g, const PotDesc &pd, double *V, float *Vf,
                uint32_t *list, unsigned *count, hipStream_t s);
-// nv[rank of okeys[p] in the bitmap] = ov[p] for the keys that stay
-template <class T>
-void remap_values(const uint32_t *okeys, const T *ov, int64_t n_old, const uint64_t *bm, const uint32_t *prefix,
-                  T *nv, hipStream_t s);
-
 // fiber contraction y (+)= P h_k P x along one dimension
 struct FiberPass {
     const uint32_t *pi;     // nullptr for the last dimension (identity)
@@ -371,8 +379,9 @@ void kry_fix_last(C *Vb, int64_t ld, int64_t n, const KState *ks, int j, hipStre
 // Ends a step: the scalars of order m - 1 from its dots (nbd > 0), the
 // exponential's coefficients (expv), the last vector's pending correction folded
 // into them (fold; for a recombination that reads the provisional last vector).
+// alpha0, order (device or pinned host, optional): receive alpha_0 and the order.
 void kry_close(KState *ks, int m, const double2 *partial, int64_t n, int nbd, double dt, bool hermitian, bool expv,
-               bool fold, hipStream_t s);
+               bool fold, hipStream_t s, double *alpha0 = nullptr, double *order = nullptr);
 template <class C>
 void lincomb(const C *Vb, int64_t ld, const double2 *psi_master, int64_t n, const KState *ks, double2 *psi_out,
              hipStream_t s);
@@ -466,9 +475,11 @@ int batch_combine(const BatchSum<R> &ts, const GridDesc &g, const uint32_t *keys
 // observables
 void obs_partial(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, const double2 *bra,
                  int nmax, double eps2, double2 *partial, hipStream_t s);
-void obs_final(const double2 *partial, int nblocks, double *rec, hipStream_t s);
-void copy_alpha0(const KState *ks, double *dst, hipStream_t s);
-void set_record(double *rec, double t, double nact, double krylov, double nsub, hipStream_t s);
+struct ObsFields {
+    double t, nact, krylov, nsub;  // what the host knows of a record
+};
+// ks: take the Krylov dimension from there (else f.krylov)
+void obs_final(const double2 *partial, int64_t n, double *rec, const ObsFields &f, const KState *ks, hipStream_t s);
 // *out = sum_I psi_I^2 (device), fixed-order; partials in `partial`
 void sum_of_squares(const double2 *psi, int64_t n, double2 *partial, double2 *out, hipStream_t s);
 // device state transfer: caller keys/coefficients into the context's buffers,
@@ -508,7 +519,6 @@ void adj_packet(const uint32_t *keys, int64_t n, const GridDesc &g, const double
                 int nmax, const double2 *vec, int bra, double2 *partial, hipStream_t s);
 unsigned long long count_diff(const double2 *a, const double2 *b, int64_t n, unsigned long long *dcount,
                               unsigned long long *hcount, hipStream_t s);
-void copy_meff(const KState *ks, double *dst, hipStream_t s);
 void energy_from_dot(const double2 *partial, int nblocks, double *rec, hipStream_t s);
 void dot_partial(const double2 *a, const double2 *b, int64_t n, double2 *partial, hipStream_t s);
 

@@ -2,6 +2,7 @@
 // tables, potential cache, Krylov vector work, small exponential, observables.
 // The fiber contraction kernels live in ppq_hpsi.hip.
 #include <algorithm>
+#include <limits>
 
 #include "ppq_device.hpp"
 
@@ -248,7 +249,11 @@ __global__ __launch_bounds__(SB) void k_scan_reduce(L ld, int64_t n, uint32_t *t
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_top(uint32_t *tile, int64_t ntiles, uint32_t *total)
+// (host_total, host_count: pinned mirrors of the total and of a device counter
+// for a caller that waits for them, without copies of their own)
+__global__ __launch_bounds__(1024) void k_scan_top(uint32_t *tile, int64_t ntiles, uint32_t *total,
+                                                   uint32_t *host_total, const unsigned long long *count,
+                                                   unsigned long long *host_count)
 {
     int64_t per = (ntiles + 1023) / 1024;
     int64_t lo = threadIdx.x * per, hi = lo + per < ntiles ? lo + per : ntiles;
@@ -261,7 +266,12 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint32_t *tile, int64_t ntile
         tile[i] = off;
         off += v;
     }
-    if (threadIdx.x == 0) *total = tot;
+    if (threadIdx.x == 0) {
+        *total = tot;
+        if (host_total) *host_total = tot;
+        if (host_count) *host_count = *count;
+        if (host_total || host_count) __threadfence_system();
+    }
 }
 
 // The tile's SI rows of SB consecutive elements, each row read and written by
@@ -305,7 +315,7 @@ void scan_impl(L ld, int64_t n, uint32_t *out, uint32_t *total, uint32_t *tmp, h
     int64_t ntiles = (n + STILE - 1) / STILE;
     if (ntiles < 1) ntiles = 1;
     hipLaunchKernelGGL(k_scan_reduce<L>, dim3((unsigned)ntiles), dim3(SB), 0, s, ld, n, tmp);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tmp, ntiles, total);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tmp, ntiles, total, nullptr, nullptr, nullptr);
     hipLaunchKernelGGL(k_scan_apply<L>, dim3((unsigned)ntiles), dim3(SB), 0, s, ld, n, tmp, out);
 }
 
@@ -411,13 +421,18 @@ __global__ void k_mark_kept(const uint32_t *keys, const double2 *psi, int64_t n,
 // dimension, the position of its word's first bit within the period and
 // advances it by 64 words' worth per row (no division per word).  Every word
 // is written, the grid's tail bits cleared.
+// A block's words are one tile of the popcount scan that follows: it leaves the
+// tile's sum, so the scan reads the new bitmap once less; the last block adds
+// up the block counts of the functions kept.
 constexpr int DW_ITER = 8;
-__global__ void k_dilate_words(const uint64_t *K, int64_t nwords, GridDesc g, uint64_t *bm)
+static_assert(64 * DW_ITER * (TB / 64) == STILE, "a block dilates one scan tile");
+__global__ __launch_bounds__(TB) void k_dilate_words(const uint64_t *K, int64_t nwords, GridDesc g, uint64_t *bm,
+                                                     uint32_t *tile_sums, const unsigned *block_counts, int64_t ncounts,
+                                                     unsigned long long *nabove)
 {
+    __shared__ unsigned long long s_sum[TB / 64];
     const int lane = threadIdx.x & 63;
-    const int64_t wbase = (gid() >> 6) * 64 * DW_ITER;
-    if (wbase >= nwords) return;
-    const int64_t w0 = wbase + lane;
+    const int64_t w0 = (gid() >> 6) * 64 * DW_ITER + lane;
     int64_t pos[MAXD], inc[MAXD];
 #pragma unroll
     for (int k = 0; k < MAXD; ++k) {
@@ -429,6 +444,7 @@ __global__ void k_dilate_words(const uint64_t *K, int64_t nwords, GridDesc g, ui
             inc[k] = (int64_t)(64 * 64) % P;
         }
     }
+    uint32_t bits = 0;
     for (int it = 0; it < DW_ITER; ++it) {
         const int64_t w = w0 + (int64_t)it * 64;
         if (w >= nwords) break;
@@ -452,6 +468,23 @@ __global__ void k_dilate_words(const uint64_t *K, int64_t nwords, GridDesc g, ui
         const int64_t tail = (int64_t)g.total - a;
         if (tail < 64) acc &= tail > 0 ? ((1ull << tail) - 1ull) : 0ull;
         bm[w] = acc;
+        if (w == nwords - 1) bm[nwords] = bm[nwords + 1] = 0ull;
+        bits += (uint32_t)__popcll(acc);
+    }
+    uint32_t tot;
+    block_excl_scan<TB>(bits, &tot);
+    if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
+    if (blockIdx.x != gridDim.x - 1) return;
+    unsigned long long c = 0;
+    for (int64_t i = threadIdx.x; i < ncounts; i += TB) c += block_counts[i];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+    if (lane == 0) s_sum[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int i = 0; i < TB / 64; ++i) t += s_sum[i];
+        *nabove = t;
     }
 }
 
@@ -485,17 +518,44 @@ __global__ void k_mark(const uint32_t *keys, int64_t n, uint64_t *bm)
     if (p < n) set_bit(bm, keys[p]);
 }
 
-__global__ void k_compact(const uint64_t *bm, const uint32_t *prefix, int64_t nwords, uint32_t *keys_out)
+// The scan's last pass and the compaction in one: every word's prefix (as
+// k_scan_apply) and the keys of its bits; K, with K, is cleared for the next adaption.
+__global__ __launch_bounds__(SB) void k_apply_compact(const uint64_t *bm, int64_t nwords, const uint32_t *tile_off,
+                                                      uint32_t *prefix, uint32_t *keys_out, uint64_t *K)
 {
-    int64_t w = gid();
-    if (w >= nwords) return;
-    uint64_t word = bm[w];
-    if (!word) return;
-    uint32_t q = prefix[w];
-    while (word) {
-        int b = __ffsll((unsigned long long)word) - 1;
-        keys_out[q++] = (uint32_t)(w * 64 + b);
-        word &= word - 1;
+    constexpr int NW = SB / 64;
+    __shared__ uint32_t wsum[SI * NW];
+    const int64_t base = (int64_t)blockIdx.x * STILE + threadIdx.x;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    uint64_t word[SI];
+    uint32_t inc[SI];
+#pragma unroll
+    for (int i = 0; i < SI; ++i) word[i] = (base + (int64_t)i * SB < nwords) ? bm[base + (int64_t)i * SB] : 0ull;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+        inc[i] = wave_incl_scan((uint32_t)__popcll(word[i]));
+        if (lane == 63) wsum[i * NW + w] = inc[i];
+    }
+    __syncthreads();
+    uint32_t off = tile_off[blockIdx.x];
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+        uint32_t before = 0, row = 0;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) {
+            const uint32_t t = wsum[i * NW + ww];
+            before += ww < w ? t : 0u;
+            row += t;
+        }
+        const int64_t idx = base + (int64_t)i * SB;
+        if (idx < nwords) {
+            uint32_t q = off + before + inc[i] - (uint32_t)__popcll(word[i]);
+            prefix[idx] = q;
+            if (K) K[idx] = 0ull;
+            for (uint64_t b = word[i]; b; b &= b - 1)
+                keys_out[q++] = (uint32_t)(idx * 64 + (__ffsll((unsigned long long)b) - 1));
+        }
+        off += row;
     }
 }
 
@@ -510,6 +570,36 @@ __global__ void k_remap(const uint32_t *okeys, const double2 *opsi, int64_t n_ol
     if ((word >> b) & 1ull) {
         uint32_t q = prefix[key >> 6] + (uint32_t)__popcll(word & ((1ull << b) - 1ull));
         npsi[q] = opsi[p];
+    }
+}
+
+// The carried-over values of an adaption in two launches: zeros (psi) and NaN
+// (V, optional) for every new function, then every old function's values at
+// its rank in the new set.
+template <class T>
+__global__ void k_fill_new(double2 *psi, T *V, int64_t n, T nan)
+{
+    for (int64_t p = gid(); p < n; p += (int64_t)gridDim.x * blockDim.x) {
+        psi[p] = make_double2(0.0, 0.0);
+        if (V) V[p] = nan;
+    }
+}
+
+template <class T>
+__global__ void k_remap_all(const uint32_t *okeys, const double2 *opsi, const T *oV, int64_t n_old, const uint64_t *bm,
+                            const uint32_t *prefix, double2 *npsi, T *nV)
+{
+    const int64_t p = gid();
+    if (p >= n_old) return;
+    const uint32_t key = okeys[p];
+    const uint64_t word = bm[key >> 6];
+    const uint32_t first = prefix[key >> 6], b = key & 63;
+    const double2 c = opsi[p];
+    const T v = nV ? oV[p] : T(0);
+    if ((word >> b) & 1ull) {
+        const uint32_t q = first + (uint32_t)__popcll(word & ((1ull << b) - 1ull));
+        npsi[q] = c;
+        if (nV) nV[q] = v;
     }
 }
 
@@ -921,10 +1011,10 @@ __device__ inline int select_digit(const int (&d)[MAXD], int k)
     return r;
 }
 
-// Grid-stride over the points (or over a list of them): the term
-// descriptors and tables are staged in LDS once per block.
+// Grid-stride over the points (or over a list of them, or over those whose value
+// is missing): the term descriptors and tables are staged in LDS once per block.
 __global__ __launch_bounds__(TB) void k_potential(const uint32_t *keys, int64_t n, GridDesc g, PotDesc pd, double *V,
-                                                  float *Vf, const uint32_t *list, const unsigned *count)
+                                                  float *Vf, const uint32_t *list, const unsigned *count, int missing)
 {
     __shared__ double s_coef[POT_MAX_TERMS];
     __shared__ int s_nf[POT_MAX_TERMS];
@@ -947,6 +1037,7 @@ __global__ __launch_bounds__(TB) void k_potential(const uint32_t *keys, int64_t 
     const int64_t m = list ? (int64_t)*count : n;
     for (int64_t i = gid(); i < m; i += stride) {
         const int64_t p = list ? (int64_t)list[i] : i;
+        if (missing && (V ? V[p] == V[p] : Vf[p] == Vf[p])) continue;
         uint32_t key = keys[p];
         int d[MAXD];
 #pragma unroll
@@ -1097,34 +1188,47 @@ __global__ __launch_bounds__(TB) void k_obs_partial(const uint32_t *keys, const 
     block_reduce_store<3>(acc, partial);
 }
 
-__global__ __launch_bounds__(TB) void k_obs_final(const double2 *partial, int nb, double *rec)
+// The record's sums, with the fields that the host knows (and the order from
+// KState where only the device knows it).
+__global__ __launch_bounds__(TB) void k_obs_final(const double2 *partial, int nb, double *rec, ObsFields f, const KState *ks)
 {
-    __shared__ double2 red[TB];
-    for (int i = 0; i < 3; ++i) {
-        double2 s = make_double2(0.0, 0.0);
-        for (int b = threadIdx.x; b < nb; b += TB) {
-            s.x += partial[pidx(b, i)].x;
-            s.y += partial[pidx(b, i)].y;
+    __shared__ double2 red[TB / 64][3];
+    double2 v[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = make_double2(0.0, 0.0);
+    for (int b = threadIdx.x; b < nb; b += TB) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const double2 q = partial[pidx(b, i)];
+            v[i].x += q.x;
+            v[i].y += q.y;
         }
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int st = TB / 2; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) {
-                red[threadIdx.x].x += red[threadIdx.x + st].x;
-                red[threadIdx.x].y += red[threadIdx.x + st].y;
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            if (i == 0) rec[PPQ_OBS_NORM2] = red[0].x;
-            if (i == 1) {
-                rec[PPQ_OBS_ACF_RE] = red[0].x;
-                rec[PPQ_OBS_ACF_IM] = red[0].y;
-            }
-            if (i == 2) rec[PPQ_OBS_NABOVE] = red[0].x;
-        }
-        __syncthreads();
     }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            v[i].x += __shfl_xor(v[i].x, d, 64);
+            v[i].y += __shfl_xor(v[i].y, d, 64);
+        }
+    }
+    if ((threadIdx.x & 63) == 0)
+        for (int i = 0; i < 3; ++i) red[threadIdx.x >> 6][i] = v[i];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int i = 0; i < 3; ++i)
+        for (int w = 1; w < TB / 64; ++w) {
+            red[0][i].x += red[w][i].x;
+            red[0][i].y += red[w][i].y;
+        }
+    rec[PPQ_OBS_NORM2] = red[0][0].x;
+    rec[PPQ_OBS_ACF_RE] = red[0][1].x;
+    rec[PPQ_OBS_ACF_IM] = red[0][1].y;
+    rec[PPQ_OBS_NABOVE] = red[0][2].x;
+    rec[PPQ_OBS_T] = f.t;
+    rec[PPQ_OBS_NACTIVE] = f.nact;
+    rec[PPQ_OBS_KRYLOV] = ks ? (double)ks->meff : f.krylov;
+    rec[PPQ_OBS_SUBSTEPS] = f.nsub;
 }
 
 // ---- position expectations ---------------------------------------------------------
@@ -1205,17 +1309,6 @@ __global__ void k_give_keys(const uint32_t *k32, int64_t n, uint64_t *keys)
 }
 
 // host-known fields of one observable record
-__global__ void k_set_record(double *rec, double t, double nact, double krylov, double nsub)
-{
-    rec[PPQ_OBS_T] = t;
-    rec[PPQ_OBS_NACTIVE] = nact;
-    rec[PPQ_OBS_KRYLOV] = krylov;
-    rec[PPQ_OBS_SUBSTEPS] = nsub;
-}
-
-__global__ void k_copy_alpha0(const KState *ks, double *dst) { *dst = ks->alpha[0]; }
-__global__ void k_copy_meff(const KState *ks, double *dst) { *dst = (double)ks->meff; }
-
 __global__ __launch_bounds__(TB) void k_energy_from_dot(const double2 *partial, int nb, double *rec)
 {
     __shared__ double red[TB];
@@ -1560,18 +1653,47 @@ void dilate(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc 
     hipLaunchKernelGGL(k_sum_counts, dim3(1), dim3(1024), 0, s, block_counts, (int64_t)nb, nabove);
 }
 void dilate_words(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, double eps2, uint64_t *K,
-                  uint64_t *bm, int64_t nwords, unsigned long long *nabove, unsigned *block_counts, hipStream_t s)
+                  uint64_t *bm, int64_t nwords, unsigned long long *nabove, unsigned *block_counts, uint32_t *tile_sums,
+                  hipStream_t s)
 {
-    fill_u64(K, nwords, 0ull, s);
-    if (n > 0) {
-        const unsigned nb = nblocks(n);
-        hipLaunchKernelGGL(k_mark_kept, dim3(nb), dim3(TB), 0, s, keys, psi, n, eps2, K, block_counts);
-        hipLaunchKernelGGL(k_sum_counts, dim3(1), dim3(1024), 0, s, block_counts, (int64_t)nb, nabove);
-    }
-    const int64_t waves = (nwords + 64 * DW_ITER - 1) / (64 * DW_ITER);
-    hipLaunchKernelGGL(k_dilate_words, dim3((unsigned)((waves * 64 + TB - 1) / TB)), dim3(TB), 0, s, K, nwords, g, bm);
-    fill_u64(bm + nwords, 2, 0ull, s);
+    const unsigned nb = n > 0 ? nblocks(n) : 0u;
+    if (n > 0) hipLaunchKernelGGL(k_mark_kept, dim3(nb), dim3(TB), 0, s, keys, psi, n, eps2, K, block_counts);
+    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
+    hipLaunchKernelGGL(k_dilate_words, dim3((unsigned)tiles), dim3(TB), 0, s, K, nwords, g, bm, tile_sums, block_counts,
+                       (int64_t)nb, nabove);
 }
+void scan_reduce_popcount(const uint64_t *words, int64_t nwords, uint32_t *tile_sums, hipStream_t s)
+{
+    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
+    hipLaunchKernelGGL(k_scan_reduce<PopLoad>, dim3((unsigned)tiles), dim3(SB), 0, s, PopLoad{words}, nwords, tile_sums);
+}
+void scan_top(uint32_t *tile_sums, int64_t nwords, uint32_t *total, uint32_t *host_total,
+              const unsigned long long *count, unsigned long long *host_count, hipStream_t s)
+{
+    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tile_sums, tiles, total, host_total, count, host_count);
+}
+void apply_compact(const uint64_t *bm, int64_t nwords, const uint32_t *tile_off, uint32_t *prefix, uint32_t *keys_out,
+                   uint64_t *K, hipStream_t s)
+{
+    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
+    hipLaunchKernelGGL(k_apply_compact, dim3((unsigned)tiles), dim3(SB), 0, s, bm, nwords, tile_off, prefix, keys_out, K);
+}
+template <class T>
+void carry_over(const uint32_t *okeys, const double2 *opsi, const T *oV, int64_t n_old, const uint64_t *bm,
+                const uint32_t *prefix, double2 *npsi, T *nV, int64_t n_new, hipStream_t s)
+{
+    if (n_new > 0)
+        hipLaunchKernelGGL(k_fill_new<T>, dim3(std::min<unsigned>(nblocks(n_new), 8192u)), dim3(TB), 0, s, npsi, nV, n_new,
+                           std::numeric_limits<T>::quiet_NaN());
+    if (n_old > 0)
+        hipLaunchKernelGGL(k_remap_all<T>, dim3(nblocks(n_old)), dim3(TB), 0, s, okeys, opsi, oV, n_old, bm, prefix, npsi,
+                           nV);
+}
+template void carry_over<double>(const uint32_t *, const double2 *, const double *, int64_t, const uint64_t *,
+                                 const uint32_t *, double2 *, double *, int64_t, hipStream_t);
+template void carry_over<float>(const uint32_t *, const double2 *, const float *, int64_t, const uint64_t *,
+                                const uint32_t *, double2 *, float *, int64_t, hipStream_t);
 void keep_all_if_few_dropped(const uint32_t *keys, int64_t n, uint64_t *bm, double rel, unsigned *block_counts,
                              unsigned long long *dropped, hipStream_t s)
 {
@@ -1585,10 +1707,6 @@ void mark_keys(const uint32_t *keys, int64_t n, uint64_t *bm, hipStream_t s)
 {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_mark, dim3(nblocks(n)), dim3(TB), 0, s, keys, n, bm);
-}
-void compact(const uint64_t *bm, const uint32_t *prefix, int64_t nwords, uint32_t *keys_out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_compact, dim3(nblocks(nwords)), dim3(TB), 0, s, bm, prefix, nwords, keys_out);
 }
 void remap(const uint32_t *okeys, const double2 *opsi, int64_t n_old, const uint64_t *bm, const uint32_t *prefix,
            double2 *npsi, hipStream_t s)
@@ -1705,66 +1823,41 @@ void fib_fill(const uint32_t *flags, const uint32_t *fidx, const uint64_t *tmpma
     hipLaunchKernelGGL(k_fib_fill, dim3(nblocks(n)), dim3(TB), 0, s, flags, fidx, tmpmask, n, nf, off, mask);
 }
 
+constexpr int64_t POT_DIRECT = 1 << 18;
 void potential(const uint32_t *keys, int64_t n, const GridDesc &g, const PotDesc &pd, double *V, float *Vf,
                uint32_t *list, unsigned *count, hipStream_t s)
 {
     if (n <= 0) return;
     const unsigned nb = std::min<unsigned>(nblocks(n), 2048u);
+    // a small set's missing values are evaluated where they lie: wavefronts with
+    // one run all terms, which costs less than gathering a list first (three launches)
+    if (list && n <= POT_DIRECT) {
+        hipLaunchKernelGGL(k_potential, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, nullptr, nullptr, 1);
+        return;
+    }
     if (list) {
         fill_u32(count, 1, 0u, s);
         const unsigned mb = std::min<unsigned>(nblocks(n), 1024u);
         if (V) hipLaunchKernelGGL(k_missing<double>, dim3(mb), dim3(TB), 0, s, V, n, list, count);
         else hipLaunchKernelGGL(k_missing<float>, dim3(mb), dim3(TB), 0, s, Vf, n, list, count);
     }
-    hipLaunchKernelGGL(k_potential, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, list, count);
-}
-
-template <class T>
-__global__ void k_remap_values(const uint32_t *okeys, const T *ov, int64_t n_old, const uint64_t *bm,
-                               const uint32_t *prefix, T *nv)
-{
-    int64_t p = gid();
-    if (p >= n_old) return;
-    uint32_t key = okeys[p];
-    uint64_t word = bm[key >> 6];
-    uint32_t b = key & 63;
-    if ((word >> b) & 1ull) {
-        uint32_t q = prefix[key >> 6] + (uint32_t)__popcll(word & ((1ull << b) - 1ull));
-        nv[q] = ov[p];
-    }
-}
-
-template <class T>
-void remap_values(const uint32_t *okeys, const T *ov, int64_t n_old, const uint64_t *bm, const uint32_t *prefix,
-                  T *nv, hipStream_t s)
-{
-    if (n_old <= 0) return;
-    hipLaunchKernelGGL(k_remap_values<T>, dim3(nblocks(n_old)), dim3(TB), 0, s, okeys, ov, n_old, bm, prefix, nv);
-}
-template void remap_values<double>(const uint32_t *, const double *, int64_t, const uint64_t *, const uint32_t *,
-                                   double *, hipStream_t);
-template void remap_values<float>(const uint32_t *, const float *, int64_t, const uint64_t *, const uint32_t *,
-                                  float *, hipStream_t);
-
-static unsigned red_blocks(int64_t n)
-{
-    int64_t b = (n + TB - 1) / TB;
-    if (b > RED_BLOCKS) b = RED_BLOCKS;
-    return (unsigned)(b < 1 ? 1 : b);
+    hipLaunchKernelGGL(k_potential, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, list, count, 0);
 }
 
 void dot_partial(const double2 *a, const double2 *b, int64_t n, double2 *partial, hipStream_t s)
 {
     hipLaunchKernelGGL(k_dot_partial, dim3(RED_BLOCKS), dim3(TB), 0, s, a, b, n, partial);
 }
+// a block per 256 points up to RED_BLOCKS (few partials for a small set)
+static int obs_blocks(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>((n + TB - 1) / TB, 1), RED_BLOCKS); }
 void obs_partial(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, const double2 *bra,
                  int nmax, double eps2, double2 *partial, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_obs_partial, dim3(RED_BLOCKS), dim3(TB), 0, s, keys, psi, n, g, bra, nmax, eps2, partial);
+    hipLaunchKernelGGL(k_obs_partial, dim3(obs_blocks(n)), dim3(TB), 0, s, keys, psi, n, g, bra, nmax, eps2, partial);
 }
-void obs_final(const double2 *partial, int nb, double *rec, hipStream_t s)
+void obs_final(const double2 *partial, int64_t n, double *rec, const ObsFields &f, const KState *ks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(TB), 0, s, partial, nb, rec);
+    hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(TB), 0, s, partial, obs_blocks(n), rec, f, ks);
 }
 void expect_q(const uint32_t *keys, const double2 *psi, int64_t n, const GridDesc &g, const double *q, int nmax,
               unsigned nan_mask, double2 *partial, double *out, hipStream_t s)
@@ -1791,14 +1884,6 @@ void sum_of_squares(const double2 *psi, int64_t n, double2 *partial, double2 *ou
 {
     hipLaunchKernelGGL(k_sq_partial, dim3(RED_BLOCKS), dim3(TB), 0, s, psi, n, partial);
     hipLaunchKernelGGL(k_sum_partial1, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, out);
-}
-void set_record(double *rec, double t, double nact, double krylov, double nsub, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_set_record, dim3(1), dim3(1), 0, s, rec, t, nact, krylov, nsub);
-}
-void copy_alpha0(const KState *ks, double *dst, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_copy_alpha0, dim3(1), dim3(1), 0, s, ks, dst);
 }
 void gather_remap(const uint32_t *keys, int64_t n, const uint64_t *bm, const uint32_t *prefix, const double2 *lam,
                   double2 *mu, hipStream_t s)
@@ -1932,10 +2017,6 @@ template void diag_scale<double2>(const uint32_t *, const double2 *, int64_t, co
 template void diag_scale<float2>(const uint32_t *, const float2 *, int64_t, const GridDesc &, const double *, int,
                                  unsigned, double2, float2 *, bool, const int *, int, hipStream_t);
 
-void copy_meff(const KState *ks, double *dst, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_copy_meff, dim3(1), dim3(1), 0, s, ks, dst);
-}
 void energy_from_dot(const double2 *partial, int nb, double *rec, hipStream_t s)
 {
     hipLaunchKernelGGL(k_energy_from_dot, dim3(1), dim3(TB), 0, s, partial, nb, rec);

@@ -580,7 +580,8 @@ __device__ void small_exponential(KState *ks, int meff, double dt, bool hermitia
 // the coefficients absorb the correction.
 template <bool ARN>
 __global__ __launch_bounds__(TB) void k_close(KState *ks, int m, const double2 *ps, int nbs, const double2 *pd,
-                                              int nbd, double dt, int expv, int fold)
+                                              int nbd, double dt, int expv, int fold, double *alpha0,
+                                              double *order)
 {
     __shared__ Scalars sc;
     __shared__ int s_meff;
@@ -592,6 +593,13 @@ __global__ __launch_bounds__(TB) void k_close(KState *ks, int m, const double2 *
         if (sc.stop) meff = meff < m - 1 ? meff : m - 1;
         __threadfence_block();
         __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (alpha0) *alpha0 = ks->alpha[0];
+        if (order) {
+            *order = (double)meff;
+            __threadfence_system();
+        }
     }
     if (!expv) return;
     small_exponential(ks, meff, dt, !ARN);
@@ -731,14 +739,16 @@ void kry_fix_last(C *Vb, int64_t ld, int64_t n, const KState *ks, int j, hipStre
 }
 
 void kry_close(KState *ks, int m, const double2 *partial, int64_t n, int nbd, double dt, bool hermitian, bool expv,
-               bool fold, hipStream_t s)
+               bool fold, hipStream_t s, double *alpha0, double *order)
 {
     const int nb = kry_blocks(n);
     const double2 *ps = sweep_partials(partial, m), *pd = nbd > 0 ? partial + KRY_DOTS : nullptr;
     if (hermitian)
-        hipLaunchKernelGGL(k_close<false>, dim3(1), dim3(TB), 0, s, ks, m, ps, nb, pd, nbd, dt, (int)expv, (int)fold);
+        hipLaunchKernelGGL(k_close<false>, dim3(1), dim3(TB), 0, s, ks, m, ps, nb, pd, nbd, dt, (int)expv, (int)fold,
+                           alpha0, order);
     else
-        hipLaunchKernelGGL(k_close<true>, dim3(1), dim3(TB), 0, s, ks, m, ps, nb, pd, nbd, dt, (int)expv, (int)fold);
+        hipLaunchKernelGGL(k_close<true>, dim3(1), dim3(TB), 0, s, ks, m, ps, nb, pd, nbd, dt, (int)expv, (int)fold,
+                           alpha0, order);
 }
 
 template <class C>
