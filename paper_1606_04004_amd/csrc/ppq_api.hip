@@ -91,6 +91,12 @@ T *dalloc(int64_t count)
     return (T *)p;
 }
 
+// Maps of a lattice dimension: a dense factor h acts on its coefficients as
+// G^+ h G^{-+} (padded to nb x nb, complex).
+struct LatticeMaps {
+    std::vector<std::complex<double>> G, Gadj, GinvAdj, Ginv;
+};
+
 }  // namespace
 
 struct ppq_ctx {
@@ -110,6 +116,7 @@ struct ppq_ctx {
     bool weylets[MAXD]{};   // lattice dimension built from projected Weylets (else projected von Neumann)
     bool fgh[MAXD]{};       // periodic Fourier-grid dimension (else sine-DVR)
     bool any_lattice = false;
+    LatticeMaps maps[MAXD];  // lattice dimensions' maps, formed on first use (empty: not yet)
     int64_t nwords = 0;
 
     // operator (host description)
@@ -598,14 +605,12 @@ T *upload(const std::vector<T> &h, hipStream_t s)
     return d;
 }
 
-// Dense factor on a lattice dimension: G^+ h G^{-+} (padded to nb x nb, complex).
-struct LatticeMaps {
-    std::vector<cd> G, Gadj, GinvAdj, Ginv;
-};
-
-LatticeMaps lattice_maps(const ppq_ctx *c, int k)
+// The maps depend on the dimension's grid and lattice alone: formed once (an
+// inverse of n_k x n_k, 0.2 ms at 48 points; every new packet asks for all of them).
+const LatticeMaps &lattice_maps(ppq_ctx *c, int k)
 {
-    LatticeMaps L;
+    LatticeMaps &L = c->maps[k];
+    if (!L.Ginv.empty()) return L;
     int n = c->g.n[k];
     const std::vector<double> q = dim_points(c, k);
     L.G = c->weylets[k] ? weylet_projection(q, dim_weight(c, k), c->lo[k], c->hi[k], c->g.lat_s[k], c->g.lat_l[k])
@@ -2512,7 +2517,7 @@ void set_packet_tables(ppq_ctx *c, const double *centre, const double *momentum,
         for (int i = 0; i < n; ++i) gk[i] /= nrm;
         std::vector<cd> a = gk, b = gk;
         if (c->lattice[k]) {
-            LatticeMaps L = lattice_maps(c, k);
+            const LatticeMaps &L = lattice_maps(c, k);
             a.assign(n, cd(0.0, 0.0));
             b.assign(n, cd(0.0, 0.0));
             for (int i = 0; i < n; ++i)
@@ -3003,6 +3008,7 @@ int ppq_set_grid(ppq_ctx *c, int D, const int32_t *n, const double *lo, const do
             c->hi[k] = hi[k];
             c->nb[k] = bucket(n[k]);
             c->lattice[k] = false;
+            c->maps[k] = LatticeMaps{};
             c->weylets[k] = false;
             c->fgh[k] = false;
             c->factor[k].clear();
@@ -3050,6 +3056,7 @@ static int set_lattice_kind(ppq_ctx *c, int k, int ns, int nl, bool weylets)
     c->g.lat_s[k] = ns;
     c->g.lat_l[k] = nl;
     c->lattice[k] = true;
+    c->maps[k] = LatticeMaps{};
     c->weylets[k] = weylets;
     c->any_lattice = true;
     c->block_ok = false;
@@ -3196,6 +3203,7 @@ int ppq_set_fgh(ppq_ctx *c, int k)
     if (c->lattice[k]) return fail(c, PPQ_E_STATE, "set Fourier grids before lattices");
     if (!c->terms.empty()) return fail(c, PPQ_E_STATE, "set Fourier grids before adding terms");
     c->fgh[k] = true;
+    c->maps[k] = LatticeMaps{};
     c->op_dirty = true;
     c->derived_valid = false;
     c->v_valid = false;
@@ -3239,8 +3247,7 @@ int ppq_init_gaussian(ppq_ctx *c, const double *centre, const double *momentum, 
         hipStream_t s = c->stream;
         if (!c->scan_tmp) ensure_capacity(c, 1024);
         fill_u64(c->bm, c->nwords + 2, 0ull, s);
-        fill_u64((uint64_t *)c->count, 1, 0ull, s);
-        init_flag(c->g, c->init_tabs, nmax, eps * eps, c->bm, c->count, s);
+        init_flag(c->g, c->init_tabs, nmax, eps * eps, c->bm, s);
         scan_reduce_popcount(c->bm, c->nwords, c->scan_tmp, s);
         scan_top(c->scan_tmp, c->nwords, &c->small[MAXD], c->h_small + MAXD, nullptr, nullptr, s);
         ck(hipStreamSynchronize(s), "init count");
@@ -3671,7 +3678,7 @@ int ppq_acf_doubled(ppq_ctx *c, double *c2t)
             for (int k = 0; k < c->g.D; ++k) {
                 if (!c->lattice[k]) continue;
                 const int n = c->g.n[k];
-                const LatticeMaps L = lattice_maps(c, k);
+                const LatticeMaps &L = lattice_maps(c, k);
                 std::vector<double2> B((size_t)n * n);
                 for (size_t i = 0; i < B.size(); ++i) B[i] = make_double2(L.GinvAdj[i].real(), L.GinvAdj[i].imag());
                 double2 *dB = upload(B, s);

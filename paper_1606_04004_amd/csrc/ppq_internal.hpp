@@ -72,8 +72,7 @@ void scan_popcount(const uint64_t *words, int64_t nwords, uint32_t *prefix, uint
                    hipStream_t s);
 void scan_u32(const uint32_t *in, int64_t n, uint32_t *out, uint32_t *total, uint32_t *tmp, hipStream_t s);
 
-void init_flag(const GridDesc &g, const double2 *tabs, int nmax, double eps2, uint64_t *bm,
-               unsigned long long *nabove, hipStream_t s);
+void init_flag(const GridDesc &g, const double2 *tabs, int nmax, double eps2, uint64_t *bm, hipStream_t s);
 void product_values(const uint32_t *keys, int64_t n, const GridDesc &g, const double2 *tabs, int nmax,
                     double2 *out, hipStream_t s);
 // block_counts: work space of at least n / 256 + 1 entries

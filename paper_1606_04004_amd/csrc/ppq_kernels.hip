@@ -327,8 +327,9 @@ __global__ void k_fill(T *p, int64_t n, T v)
 }
 
 // ---- adaption ----------------------------------------------------------------
-__global__ void k_init_flag(GridDesc g, const double2 *tabs, int nmax, double eps2, uint64_t *bm,
-                            unsigned long long *nabove)
+// One thread per grid function; a wavefront that keeps none (most of a large
+// grid) does not enter the stencil.
+__global__ void k_init_flag(GridDesc g, const double2 *tabs, int nmax, double eps2, uint64_t *bm)
 {
     // wave-uniform trip count: every lane runs every iteration
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < (int64_t)g.total;
@@ -342,8 +343,8 @@ __global__ void k_init_flag(GridDesc g, const double2 *tabs, int nmax, double ep
             v = cmul_rn(v, tabs[k * nmax + d]);
         }
         bool keep = inside && above_eps(v, eps2);
+        if (__ballot(keep) == 0) continue;
         set_with_neighbours(g, bm, key, keep);
-        count_ballot(keep, nabove);
     }
 }
 
@@ -1631,12 +1632,11 @@ void scan_u32(const uint32_t *in, int64_t n, uint32_t *out, uint32_t *total, uin
     scan_impl(U32Load{in}, n, out, total, tmp, s);
 }
 
-void init_flag(const GridDesc &g, const double2 *tabs, int nmax, double eps2, uint64_t *bm,
-               unsigned long long *nabove, hipStream_t s)
+void init_flag(const GridDesc &g, const double2 *tabs, int nmax, double eps2, uint64_t *bm, hipStream_t s)
 {
     unsigned b = nblocks(g.total);
     if (b > 65536) b = 65536;
-    hipLaunchKernelGGL(k_init_flag, dim3(b), dim3(TB), 0, s, g, tabs, nmax, eps2, bm, nabove);
+    hipLaunchKernelGGL(k_init_flag, dim3(b), dim3(TB), 0, s, g, tabs, nmax, eps2, bm);
 }
 void product_values(const uint32_t *keys, int64_t n, const GridDesc &g, const double2 *tabs, int nmax,
                     double2 *out, hipStream_t s)
