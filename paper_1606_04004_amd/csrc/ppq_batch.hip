@@ -185,8 +185,9 @@ __global__ __launch_bounds__(BAB, NTM <= 2 ? 3 : 2) void k_batch(BatchStage<R> s
 #pragma unroll
         for (int s = 8; s >= 1; s >>= 1)
             wm |= ((uint64_t)__shfl_xor((uint32_t)(wm >> 32), s, 64) << 32) | __shfl_xor((uint32_t)wm, s, 64);
-        wm = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(wm >> 32)) << 32) |
-             __builtin_amdgcn_readfirstlane((uint32_t)wm);
+        // (the builtin returns an int: digit 31 is not to spread over the upper half)
+        wm = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(wm >> 32)) << 32) |
+             (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)wm);
         if (wm == 0) continue;
         const int wlo = __ffsll((unsigned long long)wm) - 1, width = 64 - __clzll((long long)wm) - wlo;
 #define PPQ_TILE(CX, NT)                                                                              \
