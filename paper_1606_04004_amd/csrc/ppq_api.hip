@@ -412,6 +412,7 @@ void free_krylov(ppq_ctx *c)
     c->zbuf.clear();
     for (auto &y : c->ybuf) dfree(y);
     c->ybuf.clear();
+    c->ybuf_cap = 0;
     c->batch_planned = false;
     c->kv_m = 0;
     c->kv_cap = 0;
@@ -1445,9 +1446,9 @@ bool ensure_grid(ppq_ctx *c)
             c->xg = dalloc<unsigned char>(bytes);
             c->grid_clean = c->grid_planned = false;
         }
+        c->zg.reserve(nz);
         while ((int)c->zg.size() < nz) {
-            c->zg.push_back(nullptr);
-            c->zg.back() = dalloc<unsigned char>(bytes);
+            c->zg.push_back(dalloc<unsigned char>(bytes));
             c->grid_clean = c->grid_planned = false;
         }
     } catch (const std::bad_alloc &) {
@@ -2069,21 +2070,23 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
 // Whether the current set's products (on fiber tables) are batched: the default
 // layout, dimensions within a mask word, and a set that leaves a pass by itself
 // short of wavefronts.  Large sets fill the chip pass by pass, and there the vectors
-// of the factors cost more traffic than the passes' own sums.  Measured, us a
-// product pass by pass / batched: 6D quartic 5.6K functions 31.7 / 12.4, 164K 53.9 /
-// 23.0, 730K 82 / 61, 1.26M 123 / 109, 1.93M 154 / 178 (FP32 119 / 121); 4D Morse
-// 114K 47.7 / 16.5, 338K 35.8 / 25.9, 1.05M 59 / 51; the 4D lattice 146K 132 / 84,
-// 563K 318 / 230, 1.28M 376 / 382 (FP32 280 / 235), 2.1M 557 / 566 (343 / 272),
-// 3.9M 856 / 887 (477 / 481).
-constexpr int64_t BATCH_MAX = int64_t(5) << 18;
+// of the factors cost more traffic than the passes' own sums; complex factors are
+// bound by the contraction longer, which the batched form does over the digits
+// present only.  Measured, us a product pass by pass / batched (FP64; FP32): 6D
+// quartic 5.6K functions 33 / 15; 32 / 15, 164K 52 / 22; 47 / 21, 730K 81 / 65; 73 /
+// 43, 1.93M 155 / 155; 119 / 91, 3.97M 290 / 332; 193 / 213; 4D Morse 74K 54 / 16;
+// 46 / 16, 1.05M 58 / 50; 44 / 38; the 4D lattice 78K 123 / 54; 104 / 38, 563K 317 /
+// 177; 177 / 118, 1.14M 368 / 263; 271 / 177, 3.9M 855 / 676; 477 / 476.
+constexpr int64_t BATCH_MAX_REAL64 = int64_t(3) << 19, BATCH_MAX = int64_t(3) << 20;
 bool use_batch(ppq_ctx *c)
 {
     if (c->hpsi_variant != 2 || c->batch_switch == 0 || c->nact <= 0 || any_long(c)) return false;
-    const bool complex32 = c->precision == PPQ_FP32 && (c->any_lattice || !c->pairs.empty() || !c->chains.empty());
-    if (c->batch_switch == 1 && c->nact > (complex32 ? 2 * BATCH_MAX : BATCH_MAX)) return false;
+    const bool complex_factors = c->any_lattice || !c->pairs.empty() || !c->chains.empty();
+    const int64_t limit = c->precision == PPQ_FP64 && !complex_factors ? BATCH_MAX_REAL64 : BATCH_MAX;
+    if (c->batch_switch == 1 && c->nact > limit) return false;
     ensure_nf(c);
     int nz = 0, ndiag = 0;
-    if (c->batch_planned && c->ybuf_cap == c->cap) return true;
+    if (c->batch_planned && c->ybuf_cap >= c->nact) return true;
     const std::vector<GridFactor> fs = grid_factors(c, &nz);
     for (const GridFactor &f : fs) ndiag += f.kind == GRID_DIAG;
     const bool f64 = c->precision == PPQ_FP64;
@@ -2093,15 +2096,29 @@ bool use_batch(ppq_ctx *c)
     const int ny = f64 ? c->bsum64.ny : c->bsum32.ny;
     if (ny > BATCH_SUMS) return false;
     const int64_t es = f64 ? sizeof(double2) : sizeof(float2);
-    while ((int)c->zbuf.size() < nz) {
-        c->zbuf.push_back(nullptr);
-        c->zbuf.back() = dalloc<unsigned char>(es * c->cap);
+    c->zbuf.reserve(nz);
+    while ((int)c->zbuf.size() < nz) c->zbuf.push_back(dalloc<unsigned char>(es * c->cap));
+    // the factors' vectors hold a set of the rule, not the context's whole capacity
+    const int64_t rows = c->batch_switch == 1 ? std::min(c->cap, limit) : c->cap;
+    if (c->ybuf_cap < rows) {
+        for (auto &y : c->ybuf) dfree(y);
+        c->ybuf.clear();
+        c->ybuf_cap = rows;
     }
+    c->ybuf.reserve(ny);
     while ((int)c->ybuf.size() < ny) {
-        c->ybuf.push_back(nullptr);
-        c->ybuf.back() = dalloc<unsigned char>(es * c->cap);
+        void *p = nullptr;
+        if (hipMalloc(&p, es * c->ybuf_cap) != hipSuccess) {
+            // no memory for them: a pass per factor needs none
+            (void)hipGetLastError();
+            for (auto &y : c->ybuf) dfree(y);
+            c->ybuf.clear();
+            c->ybuf_cap = 0;
+            c->batch_planned = false;
+            return false;
+        }
+        c->ybuf.push_back(p);
     }
-    c->ybuf_cap = c->cap;
     if (f64) plan_batch<double>(c, fs, c->bsum64, &c->bst64);
     else plan_batch<float>(c, fs, c->bsum32, &c->bst32);
     c->batch_planned = true;

@@ -10,20 +10,34 @@ namespace ppq {
 namespace {
 
 // A factor's pass as in the matrix-core form of ppq_hpsi.hip (a wavefront takes 16
-// fibers, the union of their digits a window of 16 NT), with the result in a vector of
-// the factor's own instead of added to y: so all factors of a depth share one launch
+// fibers), but over the digits that the fibers' union holds, compressed to 16 NT, not
+// over a window from its first to its last (a lattice's digits count cells and
+// momenta, so its fibers have gaps: at 563K functions of 6 x 8 lattices the window
+// averages 40 digits, a fiber's members 15), and with the result in a vector of the
+// factor's own instead of added to y: so all factors of a depth share one launch
 // and none waits for another's read-modify-write.  k_combine adds the vectors up,
 // with the potential and the dots of a Krylov step.  Workgroups belong to one factor,
-// hold its columns in LDS and go over their share of its fibers; NTM is the largest
-// window of the launch's factors, which sets the registers.
+// hold its columns in LDS and go over their share of its fibers; 16 NTM is the longest
+// of the launch's factors, which sets the registers.
 // A pass by itself has 500-1400 wavefronts at 100K-600K functions, one or two per SIMD,
 // and is bound by its chain of loads (13-33 us a pass where its products take 2-5 us).
-// BATCH_NOTE
+// Here the chip holds as many workgroups as fit, each wavefront has the next group's
+// masks on their way while it contracts the current one, and what bounds a launch is
+// the gathers' latency and, with complex factors, the matrix cores.  Measured (FP64):
+// a product of the 4D lattice at 563K functions 177 us (317 in passes; 207 over windows
+// of the union, without the look ahead and with 1024 workgroups at any register count),
+// 4D Morse at 74K 16 us (54), 6D quartic at 730K 65 us (81).
 constexpr int BAB = 256;
+// wavefronts per SIMD that the registers of a window allow (workgroups per CU)
+constexpr int batch_waves(bool f64, bool general, int ntm)
+{
+    if (!f64) return ntm <= 2 ? 5 : ntm == 3 ? 4 : 3;
+    return ntm <= 2 ? 4 : ntm == 3 ? 3 : 2;
+}
 
 template <class R, bool CX, int NT>
 __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int nmax, const uint32_t *keys, int np,
-                                    const void *Hs, uint64_t m, uint32_t off, int ws, int lane)
+                                    const void *Hs, uint64_t m, uint32_t off, const uint8_t *list, int lane)
 {
     using V = typename Cplx<R>::V;
     using M = Mma<R>;
@@ -33,12 +47,16 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
     gbyte *x0 = global_base((const void *const *)&op->x[0]), *pi = global_base((const void *const *)&op->pi);
     __attribute__((address_space(1))) char *out =
         (__attribute__((address_space(1))) char *)field((char *const *)&op->out);
-    uint32_t at[NK];  // byte offsets of the members the lane holds
+    // list[i]: the i-th digit of the union, 64 past its end; the positions of the
+    // lane's entries, and which of them are members
+    uint32_t at[NK];
+    unsigned member = 0;
 #pragma unroll
     for (int kb = 0; kb < NK; ++kb) {
-        const int d = ws + 16 * (kb >> 2) + M::row(kr, kb & 3);
+        const int d = list[16 * (kb >> 2) + M::row(kr, kb & 3)];
         uint32_t pos = 0;
-        if ((m >> d) & 1ull) {
+        if (d < 64 && ((m >> d) & 1ull)) {
+            member |= 1u << kb;
             pos = off + (uint32_t)__popcll(m & ((1ull << d) - 1ull));
             if (pi) pos = at_byte<uint32_t>(pi, pos * (uint32_t)sizeof(uint32_t));
         }
@@ -47,9 +65,8 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
     V xin[NK];
 #pragma unroll
     for (int kb = 0; kb < NK; ++kb) {
-        const int d = ws + 16 * (kb >> 2) + M::row(kr, kb & 3);
         xin[kb] = V{0, 0};
-        if ((m >> d) & 1ull) xin[kb] = *(__attribute__((address_space(1))) const V *)(x0 + (uint64_t)at[kb] * sizeof(V));
+        if (member & (1u << kb)) xin[kb] = *(__attribute__((address_space(1))) const V *)(x0 + (uint64_t)at[kb] * sizeof(V));
     }
     if (CX && nin > 1) {
         auto weight = [&](int i) {
@@ -68,33 +85,38 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
         for (int q = 1; q < nin; ++q) {
             gbyte *xq = global_base((const void *const *)&op->x[q]);
             const V c = weight(q);
+            constexpr int CH = sizeof(R) == 4 ? NK : NT <= 2 ? 8 : 4;  // loads in flight that the registers allow
 #pragma unroll
-            for (int k0 = 0; k0 < NK; k0 += 4) {
-                V v[4];
+            for (int k0 = 0; k0 < NK; k0 += CH) {
+                V v[CH];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int d = ws + 16 * (k0 >> 2) + M::row(kr, u);
+                for (int u = 0; u < CH; ++u) {
+                    const int kb = k0 + u;
+                    if (kb >= NK) break;
                     v[u] = V{0, 0};
-                    if ((m >> d) & 1ull)
-                        v[u] = *(__attribute__((address_space(1))) const V *)(xq + (uint64_t)at[k0 + u] * sizeof(V));
+                    if (member & (1u << (kb % NK)))
+                        v[u] = *(__attribute__((address_space(1))) const V *)(xq + (uint64_t)at[kb] * sizeof(V));
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) cmul_acc(xin[k0 + u], c, v[u]);
+                for (int u = 0; u < CH; ++u)
+                    if (k0 + u < NK) cmul_acc(xin[k0 + u], c, v[u]);
             }
         }
     }
     typename M::V4 accr[NT], acci[NT];
+    int rowd[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
+        rowd[t] = list[16 * t + col] & 63;
         accr[t] = typename M::V4{0, 0, 0, 0};
         acci[t] = typename M::V4{0, 0, 0, 0};
     }
 #pragma unroll
     for (int kb = 0; kb < NK; ++kb) {
-        const int j = ws + 16 * (kb >> 2) + M::row(kr, kb & 3);
+        const int j = (list[16 * (kb >> 2) + M::row(kr, kb & 3)] & 63) * np;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const int hi = j * np + ws + 16 * t + col;
+            const int hi = j + rowd[t];
             if (CX) {
                 const V h = reinterpret_cast<const V *>(Hs)[hi];
                 accr[t] = M::op(h.x, xin[kb].x, accr[t]);
@@ -120,8 +142,7 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
     }
 #pragma unroll
     for (int kb = 0; kb < NK; ++kb) {
-        const int d = ws + 16 * (kb >> 2) + M::row(kr, kb & 3);
-        if (!((m >> d) & 1ull)) continue;
+        if (!(member & (1u << kb))) continue;
         V v;
         v.x = accr[kb >> 2][kb & 3];
         v.y = acci[kb >> 2][kb & 3];
@@ -145,12 +166,13 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
 // The launch's description is the kernel's first argument: read from the argument
 // segment itself, whose fields are wave-uniform.
 template <class R, bool GENERAL, int NTM>
-__global__ __launch_bounds__(BAB, NTM <= 2 ? 3 : 2) void k_batch(BatchStage<R> stage, GridDesc g, const uint32_t *__restrict__ keys,
+__global__ __launch_bounds__(BAB, batch_waves(sizeof(R) == 8, GENERAL, NTM)) void k_batch(BatchStage<R> stage, GridDesc g, const uint32_t *__restrict__ keys,
                                                                  const int *skip_if, int skip_j)
 {
     using V = typename Cplx<R>::V;
     if (skip_if && skip_j >= *skip_if) return;
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint8_t list[BAB / 64][64];
     (void)stage;
     const BatchStage<R> *st = (const BatchStage<R> *)(const char *)(__attribute__((address_space(4))) const char *)
                                   __builtin_amdgcn_kernarg_segment_ptr();
@@ -163,6 +185,19 @@ __global__ __launch_bounds__(BAB, NTM <= 2 ? 3 : 2) void k_batch(BatchStage<R> s
     const int b = bid - field(&st->first[o]), blocks = field(&st->first[o + 1]) - field(&st->first[o]);
     const int n = field(&op->n), np = (n + 15) & ~15;
     const bool cx = GENERAL && field(&op->kind) != GRID_REAL;
+    // the first fibers' tables are on their way while the factor is staged, and
+    // each next group's while its predecessor is contracted
+    gbyte *masks = global_base((const void *const *)&op->mask), *offs = global_base((const void *const *)&op->off);
+    const uint32_t nf = (uint32_t)field(&op->nf), ngroup = (nf + 15) / 16, hop = blocks * (BAB / 64);
+    uint64_t mnext = 0;
+    uint32_t onext = 0;
+    auto fetch = [&](uint32_t grp) {
+        const uint32_t f = grp * 16 + col;
+        const bool in = grp < ngroup && f < nf;
+        mnext = in ? at_byte<uint64_t>(masks, f * (uint32_t)sizeof(uint64_t)) : 0ull;
+        onext = in ? at_byte<uint32_t>(offs, f * (uint32_t)sizeof(uint32_t)) : 0u;
+    };
+    fetch(b * (BAB / 64) + w);
     // the factor's columns, np rows each, from its 64 x 64 padded form
     gbyte *H = global_base(&op->H);
     for (int i = threadIdx.x; i < np * np; i += BAB) {
@@ -170,17 +205,11 @@ __global__ __launch_bounds__(BAB, NTM <= 2 ? 3 : 2) void k_batch(BatchStage<R> s
         if (cx) reinterpret_cast<V *>(smem)[i] = at_byte<V>(H, at * (uint32_t)sizeof(V));
         else reinterpret_cast<R *>(smem)[i] = at_byte<R>(H, at * (uint32_t)sizeof(R));
     }
-    gbyte *masks = global_base((const void *const *)&op->mask), *offs = global_base((const void *const *)&op->off);
-    const uint32_t nf = (uint32_t)field(&op->nf), ngroup = (nf + 15) / 16;
     __syncthreads();
-    for (uint32_t grp = b * (BAB / 64) + w; grp < ngroup; grp += blocks * (BAB / 64)) {
-        const uint32_t f = grp * 16 + col;
-        uint64_t m = 0;
-        uint32_t off = 0;
-        if (f < nf) {
-            m = at_byte<uint64_t>(masks, f * (uint32_t)sizeof(uint64_t));
-            off = at_byte<uint32_t>(offs, f * (uint32_t)sizeof(uint32_t));
-        }
+    for (uint32_t grp = b * (BAB / 64) + w; grp < ngroup; grp += hop) {
+        const uint64_t m = mnext;
+        const uint32_t off = onext;
+        fetch(grp + hop);
         uint64_t wm = m;
 #pragma unroll
         for (int s = 8; s >= 1; s >>= 1)
@@ -189,27 +218,30 @@ __global__ __launch_bounds__(BAB, NTM <= 2 ? 3 : 2) void k_batch(BatchStage<R> s
         wm = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(wm >> 32)) << 32) |
              (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)wm);
         if (wm == 0) continue;
-        const int wlo = __ffsll((unsigned long long)wm) - 1, width = 64 - __clzll((long long)wm) - wlo;
-#define PPQ_TILE(CX, NT)                                                                              \
-    {                                                                                                 \
-        const int ws = wlo < np - 16 * (NT) ? wlo : np - 16 * (NT);                                   \
-        batch_fibers<R, CX, NT>(op, g, field(&st->nmax), keys, np, smem, m, off, ws, lane);           \
-    }
-#define PPQ_WIDTH(CX)                                       \
-    if (width <= 16) PPQ_TILE(CX, 1)                         \
-    else if (NTM == 2 || width <= 32) PPQ_TILE(CX, 2)        \
-    else if (NTM == 3 || width <= 48) PPQ_TILE(CX, NTM < 3 ? 2 : 3) \
+        // the union's digits in order, in the wavefront's own LDS: lane d writes itself at
+        // its rank among the digits present (absent: the end mark, behind them)
+        const int count = __popcll(wm), below = __popcll(wm & ((1ull << lane) - 1ull));
+        const bool here = (wm >> lane) & 1ull;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        list[w][here ? below : count + lane - below] = (uint8_t)(here ? lane : 64);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#define PPQ_TILE(CX, NT) batch_fibers<R, CX, NT>(op, g, field(&st->nmax), keys, np, smem, m, off, list[w], lane);
+#define PPQ_COUNT(CX)                                          \
+    if (count <= 16) PPQ_TILE(CX, 1)                            \
+    else if (NTM == 2 || count <= 32) PPQ_TILE(CX, 2)           \
+    else if (NTM == 3 || count <= 48) PPQ_TILE(CX, NTM < 3 ? 2 : 3) \
     else PPQ_TILE(CX, NTM)
         if constexpr (GENERAL) {
             if (cx) {
-                PPQ_WIDTH(true)
+                PPQ_COUNT(true)
             } else {
-                PPQ_WIDTH(false)
+                PPQ_COUNT(false)
             }
         } else {
-            PPQ_WIDTH(false)
+            PPQ_COUNT(false)
         }
-#undef PPQ_WIDTH
+#undef PPQ_COUNT
 #undef PPQ_TILE
     }
 }
@@ -271,8 +303,8 @@ template <class R>
 void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, const int *skip_if, int skip_j, hipStream_t s)
 {
     if (st.nop <= 0) return;
-    // BATCH_BLOCKS workgroups, shared out by the factors' fibers (at least one
-    // group of 16 per wavefront)
+    // as many workgroups as are resident at once, shared out by the factors' fibers
+    // (at least one group of 16 per wavefront)
     int nmax = 0;
     bool general = false;
     double work = 0.0;
@@ -281,15 +313,17 @@ void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, co
         general = general || st.op[o].kind != GRID_REAL;
         work += (double)st.op[o].nf * (1 + st.op[o].nin);
     }
+    const int np = (nmax + 15) & ~15;
+    const size_t lds = (size_t)np * np * (general ? 2 : 1) * sizeof(R);
+    const int per_cu = std::min<int>(batch_waves(sizeof(R) == 8, general, std::max(np / 16, 2)), (int)(LDS_BYTES / (lds + BAB)));
+    const double resident = (double)BATCH_CUS * std::max(per_cu, 1);
     st.first[0] = 0;
     for (int o = 0; o < st.nop; ++o) {
         const int64_t most = (st.op[o].nf + BAB / 4 - 1) / (BAB / 4);
-        int64_t b = (int64_t)(BATCH_BLOCKS * ((double)st.op[o].nf * (1 + st.op[o].nin) / std::max(work, 1.0)) + 0.5);
+        int64_t b = (int64_t)(resident * ((double)st.op[o].nf * (1 + st.op[o].nin) / std::max(work, 1.0)) + 0.5);
         b = std::max<int64_t>(1, std::min(b, most));
         st.first[o + 1] = st.first[o] + (int)b;
     }
-    const int np = (nmax + 15) & ~15;
-    const size_t lds = (size_t)np * np * (general ? 2 : 1) * sizeof(R);
     const dim3 grid(st.first[st.nop]), block(BAB);
 #define L(G, N) hipLaunchKernelGGL((k_batch<R, G, N>), grid, block, lds, s, st, g, keys, skip_if, skip_j)
     if (general) {

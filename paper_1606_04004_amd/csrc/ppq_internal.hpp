@@ -428,7 +428,7 @@ void grid_clear(const uint32_t *keys, int64_t n, C *xg, hipStream_t s);
 // ---- batched products on fiber tables (ppq_batch.hip) --------------------------
 // Dimensions of at most 64 points.  The factors of one depth share a launch:
 // out = (or +=, with add) h (sum_i c_i x_i), each into a vector of its own.
-constexpr int BATCH_BLOCKS = 1024;
+constexpr int BATCH_CUS = 256;   // compute units of the chip
 constexpr int BATCH_OPS = 16;    // factors of a launch
 constexpr int BATCH_SUMS = 16;   // vectors a product's result is summed from
 constexpr int BATCH_DIAGS = 8;   // terms without dense factors
