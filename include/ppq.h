@@ -48,9 +48,9 @@
  *   PPQ_HPSI=7  the last two dimensions in one pass (whole planes per
  *               workgroup), the others as in 2.
  *   PPQ_BLOCK_STATS=1  report the block layout's chunk statistics on stderr.
- *   PPQ_ACC_STAGE=1  lane-per-fiber passes (but the one with the fused
- *               <x|y>) read the permutation from each wavefront's copy of its
- *               rank range in LDS instead of scattered global loads.
+ *   PPQ_ACC_STAGE=0  lane-per-fiber passes read the permutation by scattered
+ *               global loads instead of from each wavefront's copy of its rank
+ *               range in LDS.
  *   PPQ_GRID=0 / 2  products of the default layout on fiber tables always /
  *               on grid vectors wherever they fit (grids of at most 2^23
  *               functions); 1 (default) chooses by the set's size and the
@@ -59,8 +59,9 @@
  *               factor depth, and no fiber tables are built.
  *   PPQ_BATCH=0 / 2  products of the default layout on fiber tables a pass per
  *               factor always / batched wherever they apply (dimensions of at
- *               most 64 points); 1 (default) batches sets of up to 1.3 million
- *               functions.  Batched, all factors of one depth share a launch on
+ *               most 64 points); 1 (default) batches sets of up to 3.1 million
+ *               functions, 1.6 million with real factors in double
+ *               precision.  Batched, all factors of one depth share a launch on
  *               the matrix cores and their results are added up at the end.
  *   PPQ_DILATE=1 / 2  adaption's dilation per function (atomics) / word by
  *               word from the bitmap of the functions kept (the +-1 stencil

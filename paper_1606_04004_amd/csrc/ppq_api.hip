@@ -179,8 +179,7 @@ struct ppq_ctx {
                            // 7 = the last two dimensions in one pass)
     uint32_t blk_window = BLOCK_WINDOW;  // chunk window of the block layouts (PPQ_BLOCK_WINDOW)
     int blk_unroll = 1;                  // one-lane-per-fiber block pass: row loop unrolled (PPQ_BLOCK_UNROLL)
-    bool acc_stage = false;              // lane-per-fiber passes stage pi in LDS (PPQ_ACC_STAGE;
-                                         // faster back to back in FP32, slower within steps)
+    bool acc_stage = true;               // lane-per-fiber passes stage pi in LDS (PPQ_ACC_STAGE=0: read where needed)
 
     // block-fused H*psi: outer dimensions [0, split) through the inner-first
     // frame, inner dimensions [split, D) in the row-major frame
@@ -1828,8 +1827,8 @@ void apply_single(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, int 
                 float2 *y = (float2 *)yv;
                 // the last dimension's fibers are contiguous runs, which the
                 // matrix-core pass gathers with coalesced loads: in FP32 it beats
-                // the point-parallel pass even on short fibers (25.6 against
-                // 41.2 us on the 6D snapshot; in FP64 the two are level)
+                // the point-parallel pass even on short fibers (27 against
+                // 29 us on 4M functions; in FP64 the two are level)
                 if (pair)
                     hpsi_pair_f32(pair_pass_of(c), c->T32[D - 2], c->T32[D - 1], x, c->V32, y, skip_if, skip_j, s);
                 else

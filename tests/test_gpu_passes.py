@@ -1,0 +1,62 @@
+"""The passes over one dimension at the sizes where a fiber meets the end of a
+64-entry word, a 256-entry tile or a wavefront's rank range, against the oracle."""
+import os
+
+import numpy as np
+import pytest
+
+from oracle.oracle import Oracle
+from workloads import card, random_complex
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "needs a GPU"
+    return t
+
+
+def run(cd, keys, x, prec, env, torch):
+    import paper_1606_04004_amd as ppq
+    env = {"PPQ_GRID": "0", "PPQ_BATCH": "0", **env}
+    old = {k: os.environ.get(k) for k in env}
+    os.environ.update(env)
+    try:
+        g = ppq.Propagator(cd, precision=prec, device=0, stream=torch.cuda.current_stream())
+    finally:
+        for k, v in old.items():
+            if v is None:
+                del os.environ[k]
+            else:
+                os.environ[k] = v
+    g.set_state(keys, np.where(np.isfinite(x), x, 0))
+    xt = torch.from_numpy(x.astype(np.complex64) if prec else x).cuda()
+    yt = torch.full_like(xt, 7.0)
+    g.apply_h(xt, yt)
+    torch.cuda.synchronize()
+    return yt.cpu().numpy()
+
+
+# fiber lengths that divide a word, that drift through it, that fill the halo; runs cut by gaps
+@pytest.mark.parametrize("n,fill", [([9, 64], 1.0), ([13, 63], 1.0), ([40, 33], 1.0), ([33, 32], 1.0), ([75, 31], 1.0),
+                                    ([60, 24], 0.6), ([24, 60], 0.9), ([5, 23, 24], 0.5), ([32, 8], 1.0), ([2, 2], 1.0)])
+def test_point_and_lane_passes(n, fill, torch):
+    """FP64 within 1e-13 of the oracle's largest entry, FP32 within 4e-6 (at most
+    130 products per entry); an infinite input reaches the functions coupled to it
+    and no others."""
+    cd = card("small_2d" if len(n) == 2 else "small_3d", n=n)
+    total = int(np.prod(n))
+    rng = np.random.default_rng(total)
+    keys = np.sort(rng.choice(total, size=max(1, int(fill * total)), replace=False)).astype(np.uint64)
+    x = random_complex(keys.size, 3)
+    ref = Oracle(cd).apply_def(keys, x)
+    print(f"{n}: {keys.size} functions", flush=True)
+    for prec, tol in ((0, 1e-13), (1, 4e-6)):
+        for env in ({"PPQ_HPSI": "3"}, {"PPQ_HPSI": "3", "PPQ_ACC_STAGE": "0"}, {}):
+            assert np.max(np.abs(run(cd, keys, x, prec, env, torch) - ref)) < tol * np.max(np.abs(ref))
+    bad = x.copy()
+    bad[keys.size // 2] = np.inf
+    hit = ~np.isfinite(Oracle(cd).apply_def(keys, bad))
+    assert np.array_equal(~np.isfinite(run(cd, keys, bad, 0, {"PPQ_HPSI": "3"}, torch)), hit)
