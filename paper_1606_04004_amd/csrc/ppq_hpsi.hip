@@ -419,6 +419,10 @@ __global__ __launch_bounds__(HB) void k_hpsi_cplx(const uint32_t *__restrict__ p
 // fiber has at most n_k members).  The tile and its halos are staged in LDS
 // with all their loads issued together, and each thread contracts its own
 // row of h_k with its fiber: exactly L^2 multiply-adds per fiber.
+// A fiber's bounds come from ballots of the start flags, and its members are read
+// four at a time: walking the flags and the members one by one is a chain of LDS
+// latencies (the last dimension's pass over 4M functions 50 us, 43 now; its vectors
+// and potential take 33).
 constexpr int PB = 256;
 constexpr int PH = 64;
 
@@ -433,11 +437,12 @@ __global__ __launch_bounds__(PB) void k_hpsi_pt(const uint32_t *__restrict__ pi,
     // halo: a fiber has at most NMAX members, so NMAX - 1 entries suffice
     constexpr int PHN = NMAX <= 32 ? 32 : PH;
     constexpr int NW = PB + 2 * PHN;
-    __shared__ R sT[NMAX * NMAX];
+    constexpr int TS = NMAX + 1;  // odd row stride: the rows of a fiber's digits start in different banks
+    __shared__ R sT[NMAX * TS];
     __shared__ uint8_t sinfo[NW];
     __shared__ C sx[NW];
     __shared__ uint32_t sp[NW];
-    __shared__ int sE;
+    __shared__ uint64_t sstart[NW / 64];  // a bit where a fiber begins
     const int tid = threadIdx.x;
     const int64_t B0 = (int64_t)blockIdx.x * PB;
     const int64_t W0 = B0 - PHN;
@@ -459,7 +464,7 @@ __global__ __launch_bounds__(PB) void k_hpsi_pt(const uint32_t *__restrict__ pi,
     const int64_t qo = B0 + tid;
     R vv = 0;
     if (FIRST && qo < n) vv = V[IDENT ? (uint32_t)qo : pi[qo]];
-    for (int i = tid; i < NMAX * NMAX; i += PB) sT[i] = T[i];
+    for (int i = tid; i < NMAX * NMAX; i += PB) sT[i / NMAX * TS + i % NMAX] = T[i];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int i = tid + u * PB;
@@ -469,29 +474,43 @@ __global__ __launch_bounds__(PB) void k_hpsi_pt(const uint32_t *__restrict__ pi,
             sx[i] = xw[u];
         }
     }
-    __syncthreads();
-    // end of the tile's last fiber: the first fiber start in the upper halo
-    // (one ballot of the second wavefront)
-    if ((tid >> 6) == 1) {
-        const int e = PHN + PB + (tid & 63);
-        const uint64_t b = __ballot(e >= NW || (sinfo[e] & 0x80) != 0);
-        if ((tid & 63) == 0) sE = b ? PHN + PB + (__ffsll((unsigned long long)b) - 1) : NW;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = tid + u * PB;
+        const uint64_t b = __ballot((iw[u] & 0x80) != 0);
+        if (i < NW && (i & 63) == 0) sstart[i >> 6] = b;
     }
     __syncthreads();
     if (qo >= n) return;
-    const int E = sE;
-    const int i = PHN + tid;
-    int fs = i;
-    while (!(sinfo[fs] & 0x80)) --fs;
-    int fe = i + 1;
-    while (fe < E && !(sinfo[fe] & 0x80)) ++fe;
-    const R *Tr = sT + (sinfo[i] & 63) * NMAX;
+    // the fiber's first member and its end: the nearest starts at or before the
+    // point and after it, both within 64 entries
+    const int i = PHN + tid, word = i >> 6, bit = i & 63;
+    const uint64_t here = sstart[word], before = here << (63 - bit), after = (here >> bit) >> 1;
+    int fs = i - __clzll((long long)before), fe = i + __ffsll((unsigned long long)after);
+    if (before == 0) fs = word * 64 - 1 - __clzll((long long)sstart[word > 0 ? word - 1 : 0]);
+    if (after == 0) {
+        const uint64_t next = word + 1 < NW / 64 ? sstart[word + 1] : 0;
+        fe = next ? word * 64 + 63 + __ffsll((unsigned long long)next) : NW;
+    }
+    const R *Tr = sT + (sinfo[i] & 63) * TS;
     R ar = 0, ai = 0;
-    for (int j = fs; j < fe; ++j) {
-        R t = Tr[sinfo[j] & 63];
-        C v = sx[j];
-        ar = fma(t, v.x, ar);
-        ai = fma(t, v.y, ai);
+    // several members' loads at once: one by one the loop is a chain of LDS latencies
+    constexpr int MU = 4;
+    for (int j = fs; j < fe; j += MU) {
+        R t[MU];
+        C v[MU];
+#pragma unroll
+        for (int u = 0; u < MU; ++u) {
+            const int q = j + u < fe ? j + u : fe - 1;
+            t[u] = Tr[sinfo[q] & 63];
+            v[u] = sx[q];
+        }
+#pragma unroll
+        for (int u = 0; u < MU; ++u) {
+            const bool in = j + u < fe;
+            ar = in ? fma(t[u], v[u].x, ar) : ar;
+            ai = in ? fma(t[u], v[u].y, ai) : ai;
+        }
     }
     const uint32_t p = sp[i];
     if (FIRST) {
