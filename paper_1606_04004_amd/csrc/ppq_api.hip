@@ -2734,7 +2734,7 @@ void adjoint_backward(ppq_ctx *c, double2 C_N)
             // <d psi0 / d theta | psi_N>
             adj_packet(keys_of(N), c->rec_n[N], c->g, c->init_tabs, c->dtabs, c->tab_nmax, c->psi[c->cur], 1,
                        c->partial, s);
-            adj_accumulate(c->partial, 2 * D, make_double2(1.0, 0.0), c->dC + c->nparam, s);
+            adj_accumulate(c->partial, c->rec_n[N], 2 * D, make_double2(1.0, 0.0), c->dC + c->nparam, s);
         } else {
             // the recomputation must reproduce the stored checkpoint bit for bit
             unsigned long long nd =
@@ -2763,7 +2763,7 @@ void adjoint_backward(ppq_ctx *c, double2 C_N)
                 if (c->nparam > 0) {
                     adj_reduce<C>((const C *)c->Vk, (const C *)c->Wk, c->cap, psi_n, c->mu, c->ks, c->ks_b, c->Qd,
                                   keys_of(st), nn, c->g, dd, c->partial, s);
-                    adj_accumulate(c->partial, c->nparam, make_double2(0.0, -h), c->dC, s);
+                    adj_accumulate(c->partial, nn, c->nparam, make_double2(0.0, -h), c->dC, s);
                 }
                 // lambda = exp(+i H h) mu
                 kry_close(c->ks_b, m, c->partial, nn, 0, -h, true, true, false, s);
@@ -2774,7 +2774,7 @@ void adjoint_backward(ppq_ctx *c, double2 C_N)
     }
     // <lambda_0 | d psi0 / d theta>
     adj_packet(keys_of(0), c->rec_n[0], c->g, c->init_tabs, c->dtabs, c->tab_nmax, c->lam, 0, c->partial, s);
-    adj_accumulate(c->partial, 2 * D, make_double2(1.0, 0.0), c->dC + c->nparam, s);
+    adj_accumulate(c->partial, c->rec_n[0], 2 * D, make_double2(1.0, 0.0), c->dC + c->nparam, s);
     ck(hipStreamSynchronize(s), "adjoint");
     (void)C_N;
 }

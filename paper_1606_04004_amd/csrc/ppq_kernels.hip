@@ -1004,22 +1004,35 @@ constexpr int POT_MAX_TERMS = 256;
 constexpr int POT_MAX_TAB = 2048;
 constexpr int POT_MAX_FAC = 4;
 
-__device__ inline int select_digit(const int (&d)[MAXD], int k)
+// A key's digits, digit k in byte k (a dimension has at most 256 points).
+__device__ inline uint64_t packed_digits(uint32_t key, const GridDesc &g)
 {
-    int r = d[0];
+    uint64_t digits = 0;
 #pragma unroll
-    for (int i = 1; i < MAXD; ++i) r = (k == i) ? d[i] : r;
-    return r;
+    for (int k = MAXD - 1; k >= 0; --k) {
+        if (k < g.D) {
+            const uint32_t q = key / (uint32_t)g.n[k];
+            digits |= (uint64_t)(key - q * (uint32_t)g.n[k]) << (8 * k);
+            key = q;
+        }
+    }
+    return digits;
 }
 
 // Grid-stride over the points (or over a list of them, or over those whose value
 // is missing): the term descriptors and tables are staged in LDS once per block.
+// Bound by the instructions per factor, so a thread takes P points through each
+// descriptor, which is read for the whole wavefront, and a point's digits are the
+// bytes of one word, shifted by a wave-uniform amount (picking the digit out of an
+// array by compares took 366 us over 4M functions with the 41 terms of the
+// six-dimensional quartic, this 92).
+template <int P>
 __global__ __launch_bounds__(TB) void k_potential(const uint32_t *keys, int64_t n, GridDesc g, PotDesc pd, double *V,
                                                   float *Vf, const uint32_t *list, const unsigned *count, int missing)
 {
     __shared__ double s_coef[POT_MAX_TERMS];
     __shared__ int s_nf[POT_MAX_TERMS];
-    __shared__ int s_fac[POT_MAX_TERMS][POT_MAX_FAC];  // (table index << 4) | dim
+    __shared__ int s_fac[POT_MAX_TERMS][POT_MAX_FAC];  // (first entry of the table << 6) | bit of the digit
     __shared__ double s_tab[POT_MAX_TAB];
     for (int t = threadIdx.x; t < pd.nterm; t += TB) {
         int ti[MAXD];
@@ -1029,35 +1042,55 @@ __global__ __launch_bounds__(TB) void k_potential(const uint32_t *keys, int64_t 
         int nf = 0;
 #pragma unroll
         for (int k = 0; k < MAXD; ++k)
-            if (ti[k] >= 0 && nf < POT_MAX_FAC) s_fac[t][nf++] = (ti[k] << 4) | k;
+            if (ti[k] >= 0 && nf < POT_MAX_FAC) s_fac[t][nf++] = ((ti[k] * pd.nmax) << 6) | (8 * k);
         s_nf[t] = nf;
     }
     for (int i = threadIdx.x; i < pd.ntab * pd.nmax; i += TB) s_tab[i] = pd.tabs[i];
     __syncthreads();
     const int64_t stride = (int64_t)gridDim.x * TB;
     const int64_t m = list ? (int64_t)*count : n;
-    for (int64_t i = gid(); i < m; i += stride) {
-        const int64_t p = list ? (int64_t)list[i] : i;
-        if (missing && (V ? V[p] == V[p] : Vf[p] == Vf[p])) continue;
-        uint32_t key = keys[p];
-        int d[MAXD];
+    for (int64_t i = gid(); i < m; i += P * stride) {
+        int64_t p[P];
+        uint64_t digits[P];
+        double v[P];
+        bool any = false;
 #pragma unroll
-        for (int k = 0; k < MAXD; ++k) d[k] = (k < g.D) ? (int)((key / g.stride[k]) % (uint32_t)g.n[k]) : 0;
-        double v = 0.0;
+        for (int u = 0; u < P; ++u) {
+            const int64_t j = i + u * stride;
+            p[u] = j < m ? (list ? (int64_t)list[j] : j) : -1;
+            if (missing && p[u] >= 0 && (V ? V[p[u]] == V[p[u]] : Vf[p[u]] == Vf[p[u]])) p[u] = -1;
+            any = any || p[u] >= 0;
+        }
+        if (!any) continue;
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            digits[u] = packed_digits(p[u] >= 0 ? keys[p[u]] : 0u, g);
+            v[u] = 0.0;
+        }
         for (int t = 0; t < pd.nterm; ++t) {
-            double f = s_coef[t];
-            const int nf = s_nf[t];
+            const double c = s_coef[t];
+            double f[P];
+#pragma unroll
+            for (int u = 0; u < P; ++u) f[u] = c;
+            const int nf = __builtin_amdgcn_readfirstlane(s_nf[t]);
 #pragma unroll
             for (int j = 0; j < POT_MAX_FAC; ++j) {
                 if (j < nf) {
-                    int e = s_fac[t][j];
-                    f *= s_tab[(e >> 4) * pd.nmax + select_digit(d, e & 15)];
+                    const int e = __builtin_amdgcn_readfirstlane(s_fac[t][j]);
+                    const double *tab = s_tab + (e >> 6);
+#pragma unroll
+                    for (int u = 0; u < P; ++u) f[u] *= tab[(uint32_t)(digits[u] >> (e & 63)) & 255u];
                 }
             }
-            v += f;
+#pragma unroll
+            for (int u = 0; u < P; ++u) v[u] += f[u];
         }
-        if (V) V[p] = v;
-        if (Vf) Vf[p] = (float)v;
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            if (p[u] < 0) continue;
+            if (V) V[p[u]] = v[u];
+            if (Vf) Vf[p[u]] = (float)v[u];
+        }
     }
 }
 
@@ -1365,11 +1398,12 @@ __global__ void k_mark_wave(const uint32_t *keys, int64_t n, uint64_t *bm)
 //   Q = m0 n0 [exp([[-i dt T_b, e1 e1^T], [0, -i dt T_f]])]_{12}
 // (the block-triangular exponential gives int_0^1 e^{A(1-s)} X e^{Bs} ds),
 // T_f, T_b the Lanczos matrices of psi_n (forward) and mu (adjoint), both of
-// dimension m; 1024 lanes, one per entry of the 32 x 32 block matrix.
+// dimension m; 1024 lanes, one per entry of the 32 x 32 block matrix.  Bound by the
+// products' LDS reads on one CU (57 us with 18 products and the squarings, 36 with 7).
 constexpr int M2 = 2 * MAXM;
 __global__ __launch_bounds__(1024) void k_adj_q(const KState *kf, const KState *kb, double dt, double2 *Q)
 {
-    __shared__ double2 A[M2][M2], P[M2][M2], E[M2][M2];
+    __shared__ double2 A[M2][M2], E[M2][M2];
     __shared__ double rown[M2];
     __shared__ int s_sq;
     const int mf = kf->meff, mb = kb->meff;
@@ -1410,42 +1444,61 @@ __global__ __launch_bounds__(1024) void k_adj_q(const KState *kf, const KState *
     const int sq = s_sq;
     const double scale = ldexp(1.0, -sq);
     A[r][c] = make_double2(A[r][c].x * scale, A[r][c].y * scale);
-    P[r][c] = make_double2(r == c ? 1.0 : 0.0, 0.0);
-    E[r][c] = P[r][c];
+    // the Taylor sum of degree 19 by powers of A^4: seven products (18 term by term);
+    // a lane keeps its entries of A, A^2 and A^3
+    auto product = [&](const double2(*L)[M2], const double2(*R)[M2]) {
+        double2 acc = make_double2(0.0, 0.0);
+#pragma unroll 8
+        for (int l = 0; l < M2; ++l) {
+            const double2 a = L[r][l], b = R[l][c];
+            acc.x += a.x * b.x - a.y * b.y;
+            acc.y += a.x * b.y + a.y * b.x;
+        }
+        return acc;
+    };
     __syncthreads();
-    for (int kt = 1; kt <= 18; ++kt) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int l = 0; l < M2; ++l) {
-            double2 a = P[r][l], b = A[l][c];
-            acc.x += a.x * b.x - a.y * b.y;
-            acc.y += a.x * b.y + a.y * b.x;
+    const double2 a1 = A[r][c], a2 = product(A, A);
+    E[r][c] = a2;
+    __syncthreads();
+    const double2 a3 = product(E, A), a4 = product(E, E);
+    __syncthreads();
+    A[r][c] = a4;
+    double f[20];  // 1 / k!
+    f[0] = 1.0;
+#pragma unroll
+    for (int k = 1; k < 20; ++k) f[k] = f[k - 1] / k;
+    double2 e = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int b4 = 16; b4 >= 0; b4 -= 4) {
+        if (b4 < 16) {
+            E[r][c] = e;
+            __syncthreads();
+            e = product(E, A);
+            __syncthreads();
         }
-        __syncthreads();
-        P[r][c] = make_double2(acc.x / kt, acc.y / kt);
-        E[r][c] = make_double2(E[r][c].x + acc.x / kt, E[r][c].y + acc.y / kt);
-        __syncthreads();
+        e.x += (f[b4 + 3] * a3.x + f[b4 + 2] * a2.x) + (f[b4 + 1] * a1.x + (r == c ? f[b4] : 0.0));
+        e.y += (f[b4 + 3] * a3.y + f[b4 + 2] * a2.y) + f[b4 + 1] * a1.y;
     }
+    E[r][c] = e;
+    __syncthreads();
     for (int q = 0; q < sq; ++q) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int l = 0; l < M2; ++l) {
-            double2 a = E[r][l], b = E[l][c];
-            acc.x += a.x * b.x - a.y * b.y;
-            acc.y += a.x * b.y + a.y * b.x;
-        }
+        e = product(E, E);
         __syncthreads();
-        E[r][c] = acc;
+        E[r][c] = e;
         __syncthreads();
     }
     if (r < MAXM && c >= MAXM) {
         const double s2 = kf->n0 * kb->n0;
-        double2 e = E[r][c];
         Q[r * MAXM + (c - MAXM)] = (r < mb && c - MAXM < mf) ? make_double2(s2 * e.x, s2 * e.y) : make_double2(0.0, 0.0);
     }
 }
 
 // Per point S = sum_ab Q_ab conj(W_a) V_b, then for every parameter p the
 // partial sums of S * G_p(I), G_p = dV/dtheta_p as a sum of products of 1D
-// tables (staged in LDS).  V_0 / W_0 come from the FP64 master vectors
+// tables (staged in LDS).  A block per 256 points: the blocks beyond a small set
+// would only reduce zeros (4D Morse training 72 us in 1024 blocks, 59 now; sums for
+// the parameters there are instead of ADJ_MAXP and adjoint vectors loaded four at a
+// time: 56, not kept).  V_0 / W_0 come from the FP64 master vectors
 // (psi_n / n0 and mu / m0), like the propagated vectors.
 template <class C>
 __global__ __launch_bounds__(TB) void k_adj_reduce(const C *Vb, const C *Wb, int64_t ld, const double2 *psi,
@@ -1466,7 +1519,7 @@ __global__ __launch_bounds__(TB) void k_adj_reduce(const C *Vb, const C *Wb, int
         int nf = 0;
         for (int k = 0; k < g.D; ++k) {
             int ti = dd.tab[t * g.D + k];
-            if (ti >= 0 && nf < POT_MAX_FAC) s_fac[t][nf++] = (ti << 4) | k;
+            if (ti >= 0 && nf < POT_MAX_FAC) s_fac[t][nf++] = ((ti * dd.nmax) << 6) | (8 * k);
         }
         s_nf[t] = nf;
     }
@@ -1501,21 +1554,18 @@ __global__ __launch_bounds__(TB) void k_adj_reduce(const C *Vb, const C *Wb, int
             }
             cdot_acc(S, wa, t);
         }
-        uint32_t key = keys[p];
-        int d[MAXD];
-#pragma unroll
-        for (int k = 0; k < MAXD; ++k) d[k] = (k < g.D) ? (int)((key / g.stride[k]) % (uint32_t)g.n[k]) : 0;
+        const uint64_t digits = packed_digits(keys[p], g);
         for (int t = 0; t < dd.nterm; ++t) {
             double f = s_coef[t];
-            const int nf = s_nf[t];
+            const int nf = __builtin_amdgcn_readfirstlane(s_nf[t]);
 #pragma unroll
             for (int j = 0; j < POT_MAX_FAC; ++j) {
                 if (j < nf) {
-                    int e = s_fac[t][j];
-                    f *= s_tab[(e >> 4) * dd.nmax + select_digit(d, e & 15)];
+                    const int e = __builtin_amdgcn_readfirstlane(s_fac[t][j]);
+                    f *= s_tab[(e >> 6) + ((uint32_t)(digits >> (e & 63)) & 255u)];
                 }
             }
-            const int pp = s_par[t];
+            const int pp = __builtin_amdgcn_readfirstlane(s_par[t]);
 #pragma unroll
             for (int i = 0; i < ADJ_MAXP; ++i) {
                 if (i == pp) {
@@ -1528,32 +1578,29 @@ __global__ __launch_bounds__(TB) void k_adj_reduce(const C *Vb, const C *Wb, int
     block_reduce_store<ADJ_MAXP>(acc, partial);
 }
 
-// dC[p] += coef * sum over blocks (fixed order), coef = -i dt
-__global__ __launch_bounds__(TB) void k_adj_accumulate(const double2 *partial, int nb, int nparam,
-                                                       double2 coef, double2 *dC)
+// dC[i] += coef * sum over blocks (fixed order), coef = -i dt; a block per parameter
+__global__ __launch_bounds__(TB) void k_adj_accumulate(const double2 *partial, int nb, double2 coef, double2 *dC)
 {
     __shared__ double2 red[TB];
-    for (int i = 0; i < nparam; ++i) {
-        double2 s = make_double2(0.0, 0.0);
-        for (int b = threadIdx.x; b < nb; b += TB) {
-            s.x += partial[pidx(b, i)].x;
-            s.y += partial[pidx(b, i)].y;
-        }
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int st = TB / 2; st >= 1; st >>= 1) {
-            if ((int)threadIdx.x < st) {
-                red[threadIdx.x].x += red[threadIdx.x + st].x;
-                red[threadIdx.x].y += red[threadIdx.x + st].y;
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            double2 r = red[0];
-            dC[i].x += coef.x * r.x - coef.y * r.y;
-            dC[i].y += coef.x * r.y + coef.y * r.x;
+    const int i = blockIdx.x;
+    double2 s = make_double2(0.0, 0.0);
+    for (int b = threadIdx.x; b < nb; b += TB) {
+        s.x += partial[pidx(b, i)].x;
+        s.y += partial[pidx(b, i)].y;
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int st = TB / 2; st >= 1; st >>= 1) {
+        if ((int)threadIdx.x < st) {
+            red[threadIdx.x].x += red[threadIdx.x + st].x;
+            red[threadIdx.x].y += red[threadIdx.x + st].y;
         }
         __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const double2 r = red[0];
+        dC[i].x += coef.x * r.x - coef.y * r.y;
+        dC[i].y += coef.x * r.y + coef.y * r.x;
     }
 }
 
@@ -1832,7 +1879,7 @@ void potential(const uint32_t *keys, int64_t n, const GridDesc &g, const PotDesc
     // a small set's missing values are evaluated where they lie: wavefronts with
     // one run all terms, which costs less than gathering a list first (three launches)
     if (list && n <= POT_DIRECT) {
-        hipLaunchKernelGGL(k_potential, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, nullptr, nullptr, 1);
+        hipLaunchKernelGGL(k_potential<1>, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, nullptr, nullptr, 1);
         return;
     }
     if (list) {
@@ -1841,7 +1888,13 @@ void potential(const uint32_t *keys, int64_t n, const GridDesc &g, const PotDesc
         if (V) hipLaunchKernelGGL(k_missing<double>, dim3(mb), dim3(TB), 0, s, V, n, list, count);
         else hipLaunchKernelGGL(k_missing<float>, dim3(mb), dim3(TB), 0, s, Vf, n, list, count);
     }
-    hipLaunchKernelGGL(k_potential, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, list, count, 0);
+    // several points per thread where that leaves every SIMD its wavefronts (a list is a
+    // few per cent of the set)
+    if (list || n <= POT_DIRECT)
+        hipLaunchKernelGGL(k_potential<1>, dim3(nb), dim3(TB), 0, s, keys, n, g, pd, V, Vf, list, count, 0);
+    else
+        hipLaunchKernelGGL(k_potential<4>, dim3(std::min<unsigned>(nblocks((n + 3) / 4), 2048u)), dim3(TB), 0, s, keys, n,
+                           g, pd, V, Vf, list, count, 0);
 }
 
 void dot_partial(const double2 *a, const double2 *b, int64_t n, double2 *partial, hipStream_t s)
@@ -1914,7 +1967,7 @@ void adj_reduce(const C *Vb, const C *Wb, int64_t ld, const double2 *psi, const 
                 const KState *kb, const double2 *Q, const uint32_t *keys, int64_t n, const GridDesc &g,
                 const DerivDesc &dd, double2 *partial, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adj_reduce<C>, dim3(RED_BLOCKS), dim3(TB), 0, s, Vb, Wb, ld, psi, mu, kf, kb, Q, keys, n, g,
+    hipLaunchKernelGGL(k_adj_reduce<C>, dim3(obs_blocks(n)), dim3(TB), 0, s, Vb, Wb, ld, psi, mu, kf, kb, Q, keys, n, g,
                        dd, partial);
 }
 template void adj_reduce<double2>(const double2 *, const double2 *, int64_t, const double2 *, const double2 *,
@@ -1923,14 +1976,15 @@ template void adj_reduce<double2>(const double2 *, const double2 *, int64_t, con
 template void adj_reduce<float2>(const float2 *, const float2 *, int64_t, const double2 *, const double2 *,
                                  const KState *, const KState *, const double2 *, const uint32_t *, int64_t,
                                  const GridDesc &, const DerivDesc &, double2 *, hipStream_t);
-void adj_accumulate(const double2 *partial, int nparam, double2 coef, double2 *dC, hipStream_t s)
+void adj_accumulate(const double2 *partial, int64_t n, int nparam, double2 coef, double2 *dC, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adj_accumulate, dim3(1), dim3(TB), 0, s, partial, RED_BLOCKS, nparam, coef, dC);
+    if (nparam <= 0) return;
+    hipLaunchKernelGGL(k_adj_accumulate, dim3(nparam), dim3(TB), 0, s, partial, obs_blocks(n), coef, dC);
 }
 void adj_packet(const uint32_t *keys, int64_t n, const GridDesc &g, const double2 *tabs, const double2 *dtabs,
                 int nmax, const double2 *vec, int bra, double2 *partial, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adj_packet, dim3(RED_BLOCKS), dim3(TB), 0, s, keys, n, g, tabs, dtabs, nmax, vec, bra,
+    hipLaunchKernelGGL(k_adj_packet, dim3(obs_blocks(n)), dim3(TB), 0, s, keys, n, g, tabs, dtabs, nmax, vec, bra,
                        partial);
 }
 

@@ -60,3 +60,20 @@ def test_point_and_lane_passes(n, fill, torch):
     bad[keys.size // 2] = np.inf
     hit = ~np.isfinite(Oracle(cd).apply_def(keys, bad))
     assert np.array_equal(~np.isfinite(run(cd, keys, bad, 0, {"PPQ_HPSI": "3"}, torch)), hit)
+
+
+@pytest.mark.parametrize("count", [2 ** 18, 2 ** 18 + 1, 256 * 33 * 35 - 3])
+def test_potential_of_large_sets(count, torch):
+    """Sets at and past the size where a thread evaluates several functions, with
+    digits up to 255 and terms of one to three factors: the product at sampled
+    functions within 1e-13 of the largest (FP32: 2e-5, 324 products of 2^-24)."""
+    cd = card("small_3d", n=[256, 33, 35])
+    cd["terms"] = cd["terms"] + [{"coef": 0.02, "factors": [{"dim": k, "kind": "power", "p": p} for k, p in ((0, 1), (1, 3), (2, 2))]}]
+    rng = np.random.default_rng(count)
+    keys = np.sort(rng.choice(256 * 33 * 35, size=count, replace=False)).astype(np.uint64)
+    x = random_complex(count, 5)
+    at = np.unique(np.concatenate([rng.choice(count, size=400), [0, 1, 255, 256, count - 1]])).astype(np.int64)
+    ref = Oracle(cd).apply_def_at(keys, x, at)
+    for prec, tol in ((0, 1e-13), (1, 2e-5)):
+        got = run(cd, keys, x, prec, {}, torch)[at]
+        assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
