@@ -279,8 +279,7 @@ struct ppq_ctx {
     // fiber tables of all non-last dimensions at once (see fiber_tables_all)
     uint64_t *bmB = nullptr;
     uint32_t *pfxB = nullptr, *scanB = nullptr, *cntB = nullptr;
-    uint64_t *occB = nullptr;  // fiber-slot bitmaps of the non-last dimensions
-    uint32_t *opfxB = nullptr;
+    uint32_t *tcntB = nullptr, *toffB = nullptr;  // the tiles' counts and their prefix
     int64_t bat_cap = 0;     // capacity the batched work space was sized for (0: not allocated)
 
     // records
@@ -377,8 +376,8 @@ void free_state_buffers(ppq_ctx *c)
     dfree(c->pfxB);
     dfree(c->scanB);
     dfree(c->cntB);
-    dfree(c->occB);
-    dfree(c->opfxB);
+    dfree(c->tcntB);
+    dfree(c->toffB);
     c->bat_cap = 0;
     for (int i = 0; i < MAXD; ++i) {
         dfree(c->plP[i]);
@@ -1111,27 +1110,26 @@ void build_inner_first(ppq_ctx *c)
 // Device memory the one-pass tables of all non-last dimensions need, or 0 if
 // they do not apply (one dimension; concatenated ranks beyond 32 bits).
 constexpr int64_t BATCH_BYTES_MAX = 8ll << 30;
-// Words of the fiber-slot bitmaps of the non-last dimensions, concatenated
-// (offsets in owoff[0..nd]): one bit per key with digit k removed.
-int64_t occ_words(const ppq_ctx *c, int64_t *owoff)
+TileAll tiles_of(const ppq_ctx *c)
 {
-    const int nd = c->g.D - 1;
-    int64_t w = 0;
-    for (int k = 0; k < nd; ++k) {
-        if (owoff) owoff[k] = w;
-        w += ((int64_t)c->g.total / c->g.n[k] + 63) / 64;
+    TileAll r{};
+    r.nd = c->g.D - 1;
+    for (int k = 0; k < r.nd; ++k) {
+        r.sk[k] = c->g.stride[k];
+        r.nk[k] = (uint32_t)c->g.n[k];
+        r.per[k] = (r.sk[k] + 63) / 64;
+        r.first[k + 1] = r.first[k] + (uint32_t)(c->g.total / ((uint64_t)r.sk[k] * r.nk[k])) * r.per[k];
     }
-    if (owoff) owoff[nd] = w;
-    return w;
+    return r;
 }
 
 int64_t batched_bytes(const ppq_ctx *c)
 {
     const int64_t nd = c->g.D - 1;
-    // ranks of the concatenated bitmaps are offset by k |A| in 32 bits
+    // the dimensions' points are counted up in 32 bits
     if (nd < 1 || (nd + 1) * c->cap >= (1ll << 32)) return 0;
-    const int64_t words = (nd + 1) * c->nwords + 2, owords = occ_words(c, nullptr) + 2;
-    return (words + owords) * 12 + scan_tmp_words(std::max(words, owords)) * 4;
+    const int64_t words = c->nwords + 2, tiles = 2 * (int64_t)tiles_of(c).first[nd];
+    return words * 12 + tiles * 8 + scan_tmp_words(std::max(words, tiles)) * 4;
 }
 
 bool ensure_batched(ppq_ctx *c)
@@ -1141,19 +1139,19 @@ bool ensure_batched(ppq_ctx *c)
     const int64_t bytes = batched_bytes(c);
     if (bytes == 0 || bytes > BATCH_BYTES_MAX) return false;
     if (c->bat_cap == c->cap) return true;
-    const int64_t nd = c->g.D - 1, words = (nd + 1) * c->nwords + 2, owords = occ_words(c, nullptr) + 2;
+    const int64_t words = c->nwords + 2, tiles = 2 * (int64_t)tiles_of(c).first[c->g.D - 1];
     dfree(c->bmB);
     dfree(c->pfxB);
     dfree(c->scanB);
     dfree(c->cntB);
-    dfree(c->occB);
-    dfree(c->opfxB);
+    dfree(c->tcntB);
+    dfree(c->toffB);
     c->bat_cap = 0;
     c->bmB = dalloc<uint64_t>(words);
     c->pfxB = dalloc<uint32_t>(words);
-    c->occB = dalloc<uint64_t>(owords);
-    c->opfxB = dalloc<uint32_t>(owords);
-    c->scanB = dalloc<uint32_t>(scan_tmp_words(std::max(words, owords)));
+    c->tcntB = dalloc<uint32_t>(tiles);
+    c->toffB = dalloc<uint32_t>(tiles);
+    c->scanB = dalloc<uint32_t>(scan_tmp_words(std::max(words, tiles)));
     c->cntB = dalloc<uint32_t>(2 + MAXD);
     c->bat_cap = c->cap;
     return true;
@@ -1553,19 +1551,14 @@ void build_fibers(ppq_ctx *c)
     // the per-point fiber info of dimensions other than the last is read only
     // by the point-parallel-everywhere layout, which takes the per-dimension path
     if (!try_block && c->hpsi_variant != 1 && n > 0 && D > 1 && ensure_batched(c)) {
-        RotAll r{};
         TabPtrs t{};
-        r.nd = D - 1;
-        r.nwords = c->nwords;
-        occ_words(c, r.owoff);
         for (int k = 0; k < D - 1; ++k) {
-            r.sk[k] = c->g.stride[k];
-            r.nk[k] = (uint32_t)c->g.n[k];
             t.pi[k] = c->pi[k];
             t.off[k] = c->off[k];
             t.mask[k] = c->mask[k];
         }
-        fiber_tables_all(keys, n, r, c->bmB, c->pfxB, c->occB, c->opfxB, t, c->scanB, c->cntB, c->small, s);
+        fiber_tables_all(keys, n, tiles_of(c), c->nwords, c->bmB, c->pfxB, c->tcntB, c->toffB, t, c->scanB, c->cntB,
+                         c->small, s);
     } else {
         for (int k = try_block ? c->split : 0; k < D - 1; ++k) {
             build_row_major(c, k);

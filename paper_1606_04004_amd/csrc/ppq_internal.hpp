@@ -118,25 +118,25 @@ struct RotFrame {
     uint32_t rin, rout;  // inner-first frame (S_in, total / S_in); rin == 0: row-major frame
 };
 inline RotFrame row_major_rot(const GridDesc &g, int k) { return RotFrame{g.stride[k], (uint32_t)g.n[k], 0u, 0u}; }
-// fiber tables of dimensions 0..nd-1 (row-major frames) in one set of launches
-struct RotAll {
-    int nd;                 // dimensions 0..nd-1 (all but the last)
-    uint32_t sk[MAXD];      // stride of the digit moved last
-    uint32_t nk[MAXD];      // its size
-    int64_t nwords;         // words per rotated bitmap
-    int64_t owoff[MAXD + 1];  // word offsets of the fiber-slot bitmaps (one bit per key without digit k)
-};
 struct TabPtrs {
     uint32_t *pi[MAXD];
     uint32_t *off[MAXD];
     uint64_t *mask[MAXD];
 };
-// bm, prefix: (nd+1)*nwords + 2 words (nd rotated segments, then the row-major
-// one); occ, oprefix: owoff[nd] + 2 words (per dimension a bit for every
-// fiber slot that holds a point; their ranks number the fibers); counters: 2
-// entries of scratch; nf[k] receives dimension k's fiber count.
-void fiber_tables_all(const uint32_t *keys, int64_t n, const RotAll &r, uint64_t *bm, uint32_t *prefix,
-                      uint64_t *occ, uint32_t *oprefix, const TabPtrs &t, uint32_t *scan_tmp, uint32_t *counters,
+// Fiber tables of dimensions 0..nd-1 (row-major frames) in one set of launches, tile
+// by tile: a tile is the fibers of up to 64 consecutive keys below digit k (all n_k
+// digits).
+struct TileAll {
+    int nd;                   // dimensions 0..nd-1
+    uint32_t sk[MAXD];        // stride of the dimension's digit
+    uint32_t nk[MAXD];        // its size (at most 64)
+    uint32_t per[MAXD];       // tiles per value of the digits above it
+    uint32_t first[MAXD + 1]; // first tile of each dimension
+};
+// bm, prefix: nwords + 2 words; cnt, offs: 2 first[nd] words; counters: 2 entries
+// of scratch; nf[k] receives dimension k's fiber count
+void fiber_tables_all(const uint32_t *keys, int64_t n, const TileAll &r, int64_t nwords, uint64_t *bm, uint32_t *prefix,
+                      uint32_t *cnt, uint32_t *offs, const TabPtrs &t, uint32_t *scan_tmp, uint32_t *counters,
                       uint32_t *nf, hipStream_t s);
 void rot_set(const uint32_t *keys, int64_t n, const RotFrame &f, uint64_t *bm, hipStream_t s);
 void rot_rank(const uint32_t *keys, int64_t n, const RotFrame &f, const uint64_t *bm, const uint32_t *prefix,

@@ -734,136 +734,120 @@ __global__ void k_rot_rank(const uint32_t *keys, int64_t n, uint32_t sk, uint32_
 }
 
 // ---- fiber tables of every non-last dimension in one set of launches ----------
-// The D-1 rotated bitmaps (digit k moved last, k < D-1) and the row-major
-// bitmap of the set are concatenated, each nwords long.  Every bitmap holds
-// exactly n bits (rotation permutes the keys), so one exclusive prefix over the
-// concatenation gives bitmap k's ranks offset by k n, and one scan over the
-// concatenated fiber-start flags gives dimension k's fiber numbers offset by
-// the count of the earlier dimensions.
-__global__ void k_rot_set_all(const uint32_t *keys, int64_t n, RotAll r, uint64_t *bm, uint64_t *occ)
+// From the set's row-major bitmap and its prefix, tile by tile.
+// A tile of dimension k: the fibers of up to 64 consecutive keys below digit k, so
+// digit d of all of them is a run of bits, and n_k runs hold the tile.  No rotated
+// bitmap is formed: a first pass counts each tile's points and fibers (a thread per
+// tile, neighbours read neighbouring words), one scan numbers them, and a second
+// pass writes the tiles that hold points.  There a lane is a fiber: the runs, loaded
+// a digit per lane, are read from lane to lane, a point's position is its run's rank
+// plus the run's bits below the lane, and the permutation leaves through LDS in
+// contiguous stores.  Bound by the instructions of the second pass.  Measured, 4M
+// functions of a 24^6 grid (830K tiles): 15 us for the bitmap, 40 for the counts, 112
+// for the tiles (rotated bitmaps and a walk over them in rank order, before: 173 and
+// 236); 108K of 48^4 (5K tiles) 18 and 11 (38 the walk); 33K of 24^3 x 8, a build
+// with its waits 134 (173).
+__device__ inline void tile_of(const TileAll &r, uint32_t tile, int &k, uint32_t &base, int &len)
 {
-    int64_t p = gid();
-    const bool valid = p < n;
-    const uint32_t key = valid ? keys[p] : 0u;
-    for (int k = 0; k < r.nd; ++k) {
-        uint32_t d, rk = 0;
-        if (valid) rk = rotate_key(key, r.sk[k], r.nk[k], &d);
-        set_bit_wave(bm + (int64_t)k * r.nwords, rk, valid);
-        // the point's fiber slot (the rotated key without its last digit)
-        set_bit_wave(occ + r.owoff[k], rk / r.nk[k], valid);
-    }
-    // segment nd: the row-major bitmap of the set itself (point positions)
-    set_bit_wave(bm + (int64_t)r.nd * r.nwords, key, valid);
+    k = 0;
+    while (tile >= r.first[k + 1]) ++k;
+    const uint32_t i = tile - r.first[k], hi = i / r.per[k], lo = (i - hi * r.per[k]) * 64u;
+    base = hi * r.nk[k] * r.sk[k] + lo;
+    len = (int)(r.sk[k] - lo < 64u ? r.sk[k] - lo : 64u);
 }
 
-// The r-th (0-based) set bit of v (r < popcount(v)): six halving steps.
-__device__ inline int select_bit(uint64_t v, int r)
+__global__ __launch_bounds__(TB) void k_tile_count(TileAll r, const uint64_t *bm, uint32_t *cnt)
 {
-    int pos = 0;
-#pragma unroll
-    for (int sh = 32; sh >= 1; sh >>= 1) {
-        const int c = __popcll(v & ((1ull << sh) - 1ull));
-        if (r >= c) {
-            r -= c;
-            v >>= sh;
-            pos += sh;
-        }
+    const uint32_t nt = r.first[r.nd], tile = (uint32_t)gid();
+    if (tile >= nt) return;
+    int k, len;
+    uint32_t base;
+    tile_of(r, tile, k, base, len);
+    uint64_t any = 0;
+    uint32_t points = 0;
+    const uint32_t nk = r.nk[k], sk = r.sk[k];
+#pragma unroll 16
+    for (uint32_t d = 0; d < nk; ++d) {
+        const uint64_t v = extract_bits(bm, base + d * sk, len);
+        any |= v;
+        points += (uint32_t)__popcll(v);
     }
-    return pos;
+    cnt[tile] = points;
+    cnt[nt + tile] = (uint32_t)__popcll(any);
 }
 
-// Rank order gather: the rotated bitmaps are walked word by word, so the
-// points of dimension k come out in rank order q and every table write is
-// contiguous.  A wavefront takes 64 consecutive words of the concatenated
-// rotated segments; their set bits are dealt out to the lanes 64 at a time
-// (a dense word's bits spread over the wavefront instead of one lane).  For
-// the bit of rotated key rk: q from the segment's prefix, the point's
-// position p from the row-major segment (rank of the un-rotated key), the
-// fiber start and mask from the n_k-bit window holding rk, and the fiber's
-// number from the rank of its slot among the occupied ones.
-__global__ __launch_bounds__(TB) void k_rank_gather(int64_t n, RotAll r, const uint64_t *bm, const uint32_t *prefix,
-                                                    const uint64_t *occ, const uint32_t *oprefix, TabPtrs t)
+__device__ inline uint64_t readlane64(uint64_t v, int l)
 {
-    __shared__ uint64_t s_word[TB];
-    __shared__ uint32_t s_off[TB];
-    __shared__ uint32_t s_q0[TB];
-    __shared__ uint32_t s_w[TB];
-    const int lane = threadIdx.x & 63, wbase = threadIdx.x & ~63;
-    const int64_t nw = (int64_t)r.nd * r.nwords;
-    const int64_t w = (int64_t)blockIdx.x * TB + threadIdx.x;
-    uint64_t word = 0;
-    uint32_t q0 = 0;
-    if (w < nw) {
-        word = bm[w];
-        const int k = (int)(w / r.nwords);
-        q0 = prefix[w] - (uint32_t)((int64_t)k * n);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+}
+__device__ inline uint32_t bits_below_lane(uint64_t v)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(v >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)v, 0u));
+}
+
+// smem: 64 max(n_k) positions per wavefront
+__global__ __launch_bounds__(TB) void k_tile_fill(TileAll r, uint32_t n, int nmax, int group, const uint64_t *bm, const uint32_t *prefix,
+                                                  const uint32_t *cnt, const uint32_t *offs, const uint32_t *total,
+                                                  TabPtrs t, uint32_t *nf)
+{
+    extern __shared__ uint32_t s_pos[];
+    const uint32_t nt = r.first[r.nd];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t *sl = s_pos + wave * 64 * nmax;
+    if (blockIdx.x == 0 && (int)threadIdx.x < r.nd) {
+        // the dimension's fibers and the end of its last one
+        const int k = threadIdx.x;
+        const uint32_t end = k + 1 < r.nd ? offs[nt + r.first[k + 1]] : *total;
+        nf[k] = end - offs[nt + r.first[k]];
+        t.off[k][nf[k]] = n;
     }
-    const uint32_t cnt = (uint32_t)__popcll(word);
-    // exclusive prefix of the counts over the wavefront
-    uint32_t incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
-    const uint32_t total = __shfl(incl, 63, 64);
-    s_word[threadIdx.x] = word;
-    s_off[threadIdx.x] = incl - cnt;
-    s_q0[threadIdx.x] = q0;
-    s_w[threadIdx.x] = (uint32_t)(w < nw ? w % r.nwords : 0);
-    __syncthreads();
-    const uint64_t *rowm = bm + nw;            // row-major segment
-    const uint32_t *rowp = prefix + nw;
-    const uint32_t rbase = (uint32_t)((int64_t)r.nd * n);
-    for (uint32_t b0 = 0; b0 < total; b0 += 64) {
-        const uint32_t b = b0 + lane;
-        if (b >= total) break;
-        // source lane: the last lane whose offset is <= b (offsets ascend)
-        int lo = 0, hi = 63;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_off[wbase + mid] <= b) lo = mid;
-            else hi = mid - 1;
-        }
-        const int src = wbase + lo;
-        const int rr = (int)(b - s_off[src]);
-        const uint64_t sw = s_word[src];
-        const int pos = select_bit(sw, rr);
-        const int64_t wg = (int64_t)blockIdx.x * TB + src;  // global word index
-        const int k = (int)(wg / r.nwords);
-        const uint32_t rk = s_w[src] * 64u + (uint32_t)pos;
-        const uint32_t q = s_q0[src] + (uint32_t)rr;
-        // un-rotate: rk = (hi * sk + lo) * nk + d  ->  key = (hi * nk + d) * sk + lo
+    const uint32_t t0 = ((uint32_t)blockIdx.x * (TB / 64) + (uint32_t)wave) * (uint32_t)group;
+    uint64_t todo = __ballot(lane < group && t0 + lane < nt && cnt[t0 + lane] != 0);
+    for (; todo; todo &= todo - 1) {
+        const uint32_t tile = t0 + (uint32_t)(__ffsll((unsigned long long)todo) - 1);
+        int k, len;
+        uint32_t base;
+        tile_of(r, tile, k, base, len);
         const uint32_t nk = r.nk[k], sk = r.sk[k];
-        const uint32_t d = rk % nk, tq = rk / nk;
-        const uint32_t khi = tq / sk, klo = tq - khi * sk;
-        const uint32_t key = (khi * nk + d) * sk + klo;
-        const uint32_t p = rowp[key >> 6] - rbase +
-                           (uint32_t)__popcll(rowm[key >> 6] & ((1ull << (key & 63)) - 1ull));
-        t.pi[k][q] = p;
-        const uint64_t *seg = bm + (int64_t)k * r.nwords;
-        const uint64_t m = extract_bits(seg, rk - d, (int)nk);
-        if ((m & ((1ull << d) - 1ull)) == 0) {
-            // the fiber's first point: its slot tq's rank among the occupied slots
-            const int64_t o0 = r.owoff[k], ow = o0 + (tq >> 6);
-            const uint32_t f = oprefix[ow] - oprefix[o0] + (uint32_t)__popcll(occ[ow] & ((1ull << (tq & 63)) - 1ull));
-            t.off[k][f] = q;
+        // (the counts before the tile's dimension: n points each)
+        const uint32_t q0 = offs[tile] - (uint32_t)k * n, f0 = offs[nt + tile] - offs[nt + r.first[k]];
+        uint64_t run = 0;
+        uint32_t rank = 0;
+        if ((uint32_t)lane < nk) {
+            const uint32_t at = base + (uint32_t)lane * sk, w = at >> 6, sh = at & 63;
+            const uint64_t lo = bm[w], hi = bm[w + 1];
+            run = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
+            if (len < 64) run &= (1ull << len) - 1ull;
+            rank = prefix[w] + (uint32_t)__popcll(lo & ((1ull << sh) - 1ull));
+        }
+        const uint64_t digits = __ballot(run != 0);
+        uint64_t m = 0;
+        for (uint64_t x = digits; x; x &= x - 1) {
+            const int d = __ffsll((unsigned long long)x) - 1;
+            if (__builtin_amdgcn_inverse_ballot_w64(readlane64(run, d))) m |= 1ull << d;
+        }
+        const uint32_t c = (uint32_t)__popcll(m), incl = wave_incl_scan(c), points = __shfl(incl, 63, 64);
+        const uint64_t fibers = __ballot(m != 0);
+        if (m) {
+            const uint32_t f = f0 + bits_below_lane(fibers);
+            t.off[k][f] = q0 + incl - c;
             t.mask[k][f] = m;
         }
+        uint32_t at = incl - c;
+        for (uint64_t x = digits; x; x &= x - 1) {
+            const int d = __ffsll((unsigned long long)x) - 1;
+            const uint64_t v = readlane64(run, d);
+            const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)rank, d) + bits_below_lane(v);
+            if (__builtin_amdgcn_inverse_ballot_w64(v)) sl[at++] = pos;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t i = (uint32_t)lane; i < points; i += 64) t.pi[k][q0 + i] = sl[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
-}
-
-// Per dimension: the fiber count (occupied slots) and the end sentinel
-// off_k[nf_k] = n.  `total` is the occupancy scan's total over all dimensions.
-__global__ void k_occ_counts(const uint32_t *oprefix, int64_t n, RotAll r, const uint32_t *total, TabPtrs t,
-                             uint32_t *nf)
-{
-    const int k = threadIdx.x;
-    if (k >= r.nd) return;
-    const uint32_t b0 = oprefix[r.owoff[k]];
-    const uint32_t b1 = (k + 1 < r.nd) ? oprefix[r.owoff[k + 1]] : *total;
-    nf[k] = b1 - b0;
-    t.off[k][b1 - b0] = (uint32_t)n;
 }
 
 // Chunks of whole blocks for the block-fused H*psi.  A block is a maximal run
@@ -1816,21 +1800,28 @@ void last_info(const uint32_t *keys, int64_t n, int nlast, uint8_t *info, hipStr
     if (n <= 0) return;
     hipLaunchKernelGGL(k_last_info, dim3(nblocks(n)), dim3(TB), 0, s, keys, n, nlast, info);
 }
-void fiber_tables_all(const uint32_t *keys, int64_t n, const RotAll &r, uint64_t *bm, uint32_t *prefix,
-                      uint64_t *occ, uint32_t *oprefix, const TabPtrs &t, uint32_t *scan_tmp, uint32_t *counters,
+void fiber_tables_all(const uint32_t *keys, int64_t n, const TileAll &r, int64_t nwords, uint64_t *bm, uint32_t *prefix,
+                      uint32_t *cnt, uint32_t *offs, const TabPtrs &t, uint32_t *scan_tmp, uint32_t *counters,
                       uint32_t *nf, hipStream_t s)
 {
     if (n <= 0 || r.nd <= 0) return;
-    const int64_t words = (int64_t)(r.nd + 1) * r.nwords;  // nd rotated segments + the row-major one
-    const int64_t owords = r.owoff[r.nd];
-    fill_u64(bm, words + 2, 0ull, s);
-    fill_u64(occ, owords + 2, 0ull, s);
-    hipLaunchKernelGGL(k_rot_set_all, dim3(nblocks(n)), dim3(TB), 0, s, keys, n, r, bm, occ);
-    scan_popcount(bm, words, prefix, &counters[0], scan_tmp, s);
-    scan_popcount(occ, owords, oprefix, &counters[1], scan_tmp, s);
-    hipLaunchKernelGGL(k_occ_counts, dim3(1), dim3(64), 0, s, oprefix, n, r, &counters[1], t, nf);
-    hipLaunchKernelGGL(k_rank_gather, dim3(nblocks((int64_t)r.nd * r.nwords)), dim3(TB), 0, s, n, r, bm, prefix, occ,
-                       oprefix, t);
+    const int64_t nt = r.first[r.nd];
+    int nmax = 0;
+    for (int k = 0; k < r.nd; ++k) nmax = std::max<int>(nmax, (int)r.nk[k]);
+    fill_u64(bm, nwords + 2, 0ull, s);
+    mark_keys_wave(keys, n, bm, s);
+    scan_popcount(bm, nwords, prefix, &counters[0], scan_tmp, s);
+    hipLaunchKernelGGL(k_tile_count, dim3(nblocks(nt)), dim3(TB), 0, s, r, bm, cnt);
+    scan_u32(cnt, 2 * nt, offs, &counters[1], scan_tmp, s);
+    // tiles a wavefront goes through: most hold nothing on a large grid, and a wavefront
+    // of its own for each costs more than finding the next (163 us with 1, 120 with 4,
+    // 115 with 8, 126 with 16 over 830K tiles); few tiles are spread over the chip (11 us
+    // with 1, 40 with 8 over 5K)
+    const int group = (int)std::min<int64_t>(std::max<int64_t>(nt / 8192, 1), 8);
+    const int64_t per = (int64_t)(TB / 64) * group;
+    hipLaunchKernelGGL(k_tile_fill, dim3((unsigned)((nt + per - 1) / per)), dim3(TB),
+                       (size_t)(TB / 64) * 64 * nmax * sizeof(uint32_t), s, r, (uint32_t)n, nmax, group, bm, prefix, cnt, offs,
+                       &counters[1], t, nf);
 }
 void plane_tables(const uint32_t *keys, int64_t n, const GridDesc &g, int a, uint64_t *bm, uint32_t *prefix,
                   int64_t nwords, uint32_t *P, uint16_t *dig, uint32_t *tstart, uint32_t *poff, uint32_t *pkey,

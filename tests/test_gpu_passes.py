@@ -77,3 +77,31 @@ def test_potential_of_large_sets(count, torch):
     for prec, tol in ((0, 1e-13), (1, 2e-5)):
         got = run(cd, keys, x, prec, {}, torch)[at]
         assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
+
+
+# the tables' tiles: fibers below a digit in runs of less than, exactly and more than 64, runs that start
+# anywhere in a word, dimensions of 2 to 64 digits; a last dimension of 15 takes the other form
+@pytest.mark.parametrize("n,count", [([2, 16], 32), ([64, 64], 4096), ([5, 7, 17], 300), ([9, 4, 16], 576), ([3, 40, 31], 1),
+                                     ([3, 64, 48], 4000), ([12, 5, 3, 33], 2500), ([12, 5, 3, 33], 7), ([7, 6, 5, 15], 900),
+                                     ([2, 3, 2, 4, 3, 20], 1000)])
+def test_fiber_tables(n, count, torch):
+    """The products on the tables within 1e-13 of the oracle's largest entry, and
+    the fibers of every dimension as many as the oracle's."""
+    import paper_1606_04004_amd as ppq
+    cd = card(f"small_{len(n)}d", n=n)
+    total = int(np.prod(n))
+    rng = np.random.default_rng(count)
+    keys = np.sort(rng.choice(total, size=count, replace=False)).astype(np.uint64)
+    x = random_complex(count, 9)
+    o = Oracle(cd)
+    ref = o.apply_def(keys, x)
+    got = run(cd, keys, x, 0, {}, torch)
+    assert np.max(np.abs(got - ref)) < 1e-13 * np.max(np.abs(ref))
+    os.environ["PPQ_GRID"] = "0"
+    try:
+        g = ppq.Propagator(cd, precision=0, device=0, stream=torch.cuda.current_stream())
+    finally:
+        del os.environ["PPQ_GRID"]
+    for ks in (keys, keys[::3].copy()):
+        g.set_state(ks, random_complex(ks.size, 2))
+        assert g.fiber_counts().tolist() == [len(o.fiber_ranges(ks, k)) for k in range(len(n))]
