@@ -130,7 +130,8 @@ enum {
 };
 
 /* Creates a context on HIP device `device`.  `hip_stream` is a hipStream_t to
-   run on (NULL: the library creates its own).  `precision` is a ppq_precision. */
+   run on (NULL: the library creates its own; hipStreamLegacy: one of its own in
+   order with the default stream).  `precision` is a ppq_precision. */
 int ppq_create(ppq_ctx **out, int device, void *hip_stream, int precision);
 void ppq_destroy(ppq_ctx *ctx);
 /* Message of the last error on this context; valid until the next call. */

@@ -43,7 +43,8 @@ class Propagator:
         self.n = [int(v) for v in card["n"]]
         handle = None
         if stream is not None:
-            handle = getattr(stream, "cuda_stream", stream)
+            # the default stream's handle is 0, which the library takes for "none": hipStreamLegacy
+            handle = getattr(stream, "cuda_stream", stream) or 1
         ctx = ctypes.c_void_p()
         _ppq.check(None, self.lib.ppq_create(ctypes.byref(ctx), int(device),
                                              ctypes.c_void_p(handle) if handle else None, int(precision)))

@@ -2880,10 +2880,13 @@ int ppq_create(ppq_ctx **out, int device, void *hip_stream, int precision)
     try {
         ck(hipSetDevice(device), "hipSetDevice");
         scratch_setup(device);  // once per device; a failure is reported by the entry point that needs it
-        if (hip_stream) {
+        // the default stream: a stream of the library's own in order with it (so a caller's
+        // work there is done before ours begins)
+        const bool legacy = (hipStream_t)hip_stream == hipStreamLegacy;
+        if (hip_stream && !legacy) {
             c->stream = (hipStream_t)hip_stream;
         } else {
-            ck(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking), "stream");
+            ck(hipStreamCreateWithFlags(&c->stream, legacy ? hipStreamDefault : hipStreamNonBlocking), "stream");
             c->own_stream = true;
         }
         void *p = nullptr;
