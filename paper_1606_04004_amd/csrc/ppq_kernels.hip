@@ -191,8 +191,17 @@ __global__ __launch_bounds__(1024) void k_sum_counts(const unsigned *bc, int64_t
 
 // ---- scan ------------------------------------------------------------------
 constexpr int SB = 256;
+// Elements a thread takes: eight, or one while that makes at most as many tiles as the
+// top scan has threads (fewer blocks than CUs would each be a chain of eight: a 4D
+// bitmap of 16K words dilated, scanned and compacted in 8 blocks 29 + 21 us, 8 + 6 in 64).
 constexpr int SI = 8;
-constexpr int STILE = SB * SI;
+constexpr int64_t SCAN_ONE = (int64_t)SB * 1024;
+static int scan_items(int64_t n) { return n <= SCAN_ONE ? 1 : SI; }
+static int64_t scan_tiles(int64_t n)
+{
+    const int64_t t = (int64_t)SB * scan_items(n);
+    return std::max<int64_t>((n + t - 1) / t, 1);
+}
 
 __device__ inline uint32_t wave_incl_scan(uint32_t v)
 {
@@ -234,13 +243,13 @@ struct U32Load {
     __device__ uint32_t operator()(int64_t i) const { return a[i]; }
 };
 
-template <class L>
+template <class L, int I>
 __global__ __launch_bounds__(SB) void k_scan_reduce(L ld, int64_t n, uint32_t *tile_sums)
 {
-    int64_t base = (int64_t)blockIdx.x * STILE;
+    int64_t base = (int64_t)blockIdx.x * (SB * I);
     uint32_t s = 0;
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
+    for (int i = 0; i < I; ++i) {
         int64_t idx = base + (int64_t)i * SB + threadIdx.x;
         if (idx < n) s += ld(idx);
     }
@@ -274,28 +283,28 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint32_t *tile, int64_t ntile
     }
 }
 
-// The tile's SI rows of SB consecutive elements, each row read and written by
+// The tile's I rows of SB consecutive elements, each row read and written by
 // the whole block (coalesced): a wavefront scan per row and wave, then every
 // thread adds the totals of the (row, wave) pieces before its own.
-template <class L>
+template <class L, int I>
 __global__ __launch_bounds__(SB) void k_scan_apply(L ld, int64_t n, const uint32_t *tile_off, uint32_t *out)
 {
     constexpr int NW = SB / 64;
-    __shared__ uint32_t wsum[SI * NW];
-    const int64_t base = (int64_t)blockIdx.x * STILE + threadIdx.x;
+    __shared__ uint32_t wsum[I * NW];
+    const int64_t base = (int64_t)blockIdx.x * (SB * I) + threadIdx.x;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint32_t v[SI], inc[SI];
+    uint32_t v[I], inc[I];
 #pragma unroll
-    for (int i = 0; i < SI; ++i) v[i] = (base + (int64_t)i * SB < n) ? ld(base + (int64_t)i * SB) : 0u;
+    for (int i = 0; i < I; ++i) v[i] = (base + (int64_t)i * SB < n) ? ld(base + (int64_t)i * SB) : 0u;
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
+    for (int i = 0; i < I; ++i) {
         inc[i] = wave_incl_scan(v[i]);
         if (lane == 63) wsum[i * NW + w] = inc[i];
     }
     __syncthreads();
     uint32_t off = tile_off[blockIdx.x];
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
+    for (int i = 0; i < I; ++i) {
         uint32_t before = 0, row = 0;
 #pragma unroll
         for (int ww = 0; ww < NW; ++ww) {
@@ -309,14 +318,19 @@ __global__ __launch_bounds__(SB) void k_scan_apply(L ld, int64_t n, const uint32
     }
 }
 
+template <class L, int I>
+void scan_launch(L ld, int64_t n, uint32_t *out, uint32_t *total, uint32_t *tmp, hipStream_t s)
+{
+    const unsigned tiles = (unsigned)scan_tiles(n);
+    hipLaunchKernelGGL((k_scan_reduce<L, I>), dim3(tiles), dim3(SB), 0, s, ld, n, tmp);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tmp, (int64_t)tiles, total, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL((k_scan_apply<L, I>), dim3(tiles), dim3(SB), 0, s, ld, n, tmp, out);
+}
 template <class L>
 void scan_impl(L ld, int64_t n, uint32_t *out, uint32_t *total, uint32_t *tmp, hipStream_t s)
 {
-    int64_t ntiles = (n + STILE - 1) / STILE;
-    if (ntiles < 1) ntiles = 1;
-    hipLaunchKernelGGL(k_scan_reduce<L>, dim3((unsigned)ntiles), dim3(SB), 0, s, ld, n, tmp);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tmp, ntiles, total, nullptr, nullptr, nullptr);
-    hipLaunchKernelGGL(k_scan_apply<L>, dim3((unsigned)ntiles), dim3(SB), 0, s, ld, n, tmp, out);
+    if (scan_items(n) == 1) scan_launch<L, 1>(ld, n, out, total, tmp, s);
+    else scan_launch<L, SI>(ld, n, out, total, tmp, s);
 }
 
 // ---- fills -----------------------------------------------------------------
@@ -418,35 +432,36 @@ __global__ void k_mark_kept(const uint32_t *keys, const double2 *psi, int64_t n,
 // below are K read s_k bits earlier, kept where the key's digit k is not 0
 // (one stride above: not n_k - 1).  With P = s_k n_k, digit k is 0 on the
 // runs [m P, m P + s_k) and n_k - 1 on [(m + 1) P - s_k, (m + 1) P).  A
-// wavefront takes DW_ITER rows of 64 consecutive words; each lane keeps, per
+// wavefront takes I rows of 64 consecutive words; each lane keeps, per
 // dimension, the position of its word's first bit within the period and
 // advances it by 64 words' worth per row (no division per word).  Every word
 // is written, the grid's tail bits cleared.
 // A block's words are one tile of the popcount scan that follows: it leaves the
 // tile's sum, so the scan reads the new bitmap once less; the last block adds
 // up the block counts of the functions kept.
-constexpr int DW_ITER = 8;
-static_assert(64 * DW_ITER * (TB / 64) == STILE, "a block dilates one scan tile");
+static_assert(TB == SB, "a block dilates one scan tile");
+template <int I>
 __global__ __launch_bounds__(TB) void k_dilate_words(const uint64_t *K, int64_t nwords, GridDesc g, uint64_t *bm,
                                                      uint32_t *tile_sums, const unsigned *block_counts, int64_t ncounts,
                                                      unsigned long long *nabove)
 {
     __shared__ unsigned long long s_sum[TB / 64];
     const int lane = threadIdx.x & 63;
-    const int64_t w0 = (gid() >> 6) * 64 * DW_ITER + lane;
+    const int64_t w0 = (gid() >> 6) * 64 * I + lane;
     int64_t pos[MAXD], inc[MAXD];
 #pragma unroll
     for (int k = 0; k < MAXD; ++k) {
         pos[k] = 0;
         inc[k] = 0;
         if (k < g.D) {
-            const int64_t P = (int64_t)g.stride[k] * g.n[k];
-            pos[k] = (w0 * 64) % P;
-            inc[k] = (int64_t)(64 * 64) % P;
+            // (keys are below 2^32; lanes past the end are not used)
+            const uint32_t P = g.stride[k] * (uint32_t)g.n[k];
+            pos[k] = w0 < nwords ? (int64_t)((uint32_t)(w0 * 64) % P) : 0;
+            inc[k] = I > 1 ? (int64_t)((uint32_t)(64 * 64) % P) : 0;
         }
     }
     uint32_t bits = 0;
-    for (int it = 0; it < DW_ITER; ++it) {
+    for (int it = 0; it < I; ++it) {
         const int64_t w = w0 + (int64_t)it * 64;
         if (w >= nwords) break;
         const int64_t a = w * 64;
@@ -521,26 +536,27 @@ __global__ void k_mark(const uint32_t *keys, int64_t n, uint64_t *bm)
 
 // The scan's last pass and the compaction in one: every word's prefix (as
 // k_scan_apply) and the keys of its bits; K, with K, is cleared for the next adaption.
+template <int I>
 __global__ __launch_bounds__(SB) void k_apply_compact(const uint64_t *bm, int64_t nwords, const uint32_t *tile_off,
                                                       uint32_t *prefix, uint32_t *keys_out, uint64_t *K)
 {
     constexpr int NW = SB / 64;
-    __shared__ uint32_t wsum[SI * NW];
-    const int64_t base = (int64_t)blockIdx.x * STILE + threadIdx.x;
+    __shared__ uint32_t wsum[I * NW];
+    const int64_t base = (int64_t)blockIdx.x * (SB * I) + threadIdx.x;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint64_t word[SI];
-    uint32_t inc[SI];
+    uint64_t word[I];
+    uint32_t inc[I];
 #pragma unroll
-    for (int i = 0; i < SI; ++i) word[i] = (base + (int64_t)i * SB < nwords) ? bm[base + (int64_t)i * SB] : 0ull;
+    for (int i = 0; i < I; ++i) word[i] = (base + (int64_t)i * SB < nwords) ? bm[base + (int64_t)i * SB] : 0ull;
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
+    for (int i = 0; i < I; ++i) {
         inc[i] = wave_incl_scan((uint32_t)__popcll(word[i]));
         if (lane == 63) wsum[i * NW + w] = inc[i];
     }
     __syncthreads();
     uint32_t off = tile_off[blockIdx.x];
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
+    for (int i = 0; i < I; ++i) {
         uint32_t before = 0, row = 0;
 #pragma unroll
         for (int ww = 0; ww < NW; ++ww) {
@@ -745,7 +761,7 @@ __global__ void k_rot_rank(const uint32_t *keys, int64_t n, uint32_t sk, uint32_
 // contiguous stores.  Bound by the instructions of the second pass.  Measured, 4M
 // functions of a 24^6 grid (830K tiles): 15 us for the bitmap, 40 for the counts, 112
 // for the tiles (rotated bitmaps and a walk over them in rank order, before: 173 and
-// 236); 108K of 48^4 (5K tiles) 18 and 11 (38 the walk); 33K of 24^3 x 8, a build
+// 236); 108K of 48^4 (5K tiles) 5 and 11 (38 the walk); 33K of 24^3 x 8, a build
 // with its waits 134 (173).
 __device__ inline void tile_of(const TileAll &r, uint32_t tile, int &k, uint32_t &base, int &len)
 {
@@ -756,9 +772,11 @@ __device__ inline void tile_of(const TileAll &r, uint32_t tile, int &k, uint32_t
     len = (int)(r.sk[k] - lo < 64u ? r.sk[k] - lo : 64u);
 }
 
+// S lanes share a tile's digits: one while there are tiles enough for every SIMD.
+template <int S>
 __global__ __launch_bounds__(TB) void k_tile_count(TileAll r, const uint64_t *bm, uint32_t *cnt)
 {
-    const uint32_t nt = r.first[r.nd], tile = (uint32_t)gid();
+    const uint32_t nt = r.first[r.nd], tile = (uint32_t)(gid() / S), sub = (uint32_t)(gid() % S);
     if (tile >= nt) return;
     int k, len;
     uint32_t base;
@@ -767,13 +785,20 @@ __global__ __launch_bounds__(TB) void k_tile_count(TileAll r, const uint64_t *bm
     uint32_t points = 0;
     const uint32_t nk = r.nk[k], sk = r.sk[k];
 #pragma unroll 16
-    for (uint32_t d = 0; d < nk; ++d) {
+    for (uint32_t d = sub; d < nk; d += S) {
         const uint64_t v = extract_bits(bm, base + d * sk, len);
         any |= v;
         points += (uint32_t)__popcll(v);
     }
-    cnt[tile] = points;
-    cnt[nt + tile] = (uint32_t)__popcll(any);
+#pragma unroll
+    for (int x = 1; x < S; x <<= 1) {
+        points += __shfl_xor(points, x, 64);
+        any |= ((uint64_t)__shfl_xor((uint32_t)(any >> 32), x, 64) << 32) | __shfl_xor((uint32_t)any, x, 64);
+    }
+    if (sub == 0) {
+        cnt[tile] = points;
+        cnt[nt + tile] = (uint32_t)__popcll(any);
+    }
 }
 
 __device__ inline uint64_t readlane64(uint64_t v, int l)
@@ -1651,7 +1676,8 @@ void fill_zero_bytes(void *p, int64_t nbytes, hipStream_t s)
     fill_u64((uint64_t *)p, nbytes / 8, 0ull, s);
 }
 
-int64_t scan_tmp_words(int64_t n) { return (n + STILE - 1) / STILE + 16; }
+// (for every size up to n)
+int64_t scan_tmp_words(int64_t n) { return std::max(scan_tiles(n), scan_tiles(std::min(n, SCAN_ONE))) + 16; }
 
 void scan_popcount(const uint64_t *words, int64_t nwords, uint32_t *prefix, uint32_t *total, uint32_t *tmp,
                    hipStream_t s)
@@ -1689,26 +1715,36 @@ void dilate_words(const uint32_t *keys, const double2 *psi, int64_t n, const Gri
 {
     const unsigned nb = n > 0 ? nblocks(n) : 0u;
     if (n > 0) hipLaunchKernelGGL(k_mark_kept, dim3(nb), dim3(TB), 0, s, keys, psi, n, eps2, K, block_counts);
-    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
-    hipLaunchKernelGGL(k_dilate_words, dim3((unsigned)tiles), dim3(TB), 0, s, K, nwords, g, bm, tile_sums, block_counts,
-                       (int64_t)nb, nabove);
+    const int64_t tiles = scan_tiles(nwords);
+#define L(I)                                                                                                            \
+    hipLaunchKernelGGL(k_dilate_words<I>, dim3((unsigned)tiles), dim3(TB), 0, s, K, nwords, g, bm, tile_sums, block_counts, \
+                       (int64_t)nb, nabove)
+    if (scan_items(nwords) == 1) L(1);
+    else L(SI);
+#undef L
 }
 void scan_reduce_popcount(const uint64_t *words, int64_t nwords, uint32_t *tile_sums, hipStream_t s)
 {
-    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
-    hipLaunchKernelGGL(k_scan_reduce<PopLoad>, dim3((unsigned)tiles), dim3(SB), 0, s, PopLoad{words}, nwords, tile_sums);
+    const int64_t tiles = scan_tiles(nwords);
+    if (scan_items(nwords) == 1)
+        hipLaunchKernelGGL((k_scan_reduce<PopLoad, 1>), dim3((unsigned)tiles), dim3(SB), 0, s, PopLoad{words}, nwords, tile_sums);
+    else
+        hipLaunchKernelGGL((k_scan_reduce<PopLoad, SI>), dim3((unsigned)tiles), dim3(SB), 0, s, PopLoad{words}, nwords, tile_sums);
 }
 void scan_top(uint32_t *tile_sums, int64_t nwords, uint32_t *total, uint32_t *host_total,
               const unsigned long long *count, unsigned long long *host_count, hipStream_t s)
 {
-    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
+    const int64_t tiles = scan_tiles(nwords);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tile_sums, tiles, total, host_total, count, host_count);
 }
 void apply_compact(const uint64_t *bm, int64_t nwords, const uint32_t *tile_off, uint32_t *prefix, uint32_t *keys_out,
                    uint64_t *K, hipStream_t s)
 {
-    const int64_t tiles = std::max<int64_t>((nwords + STILE - 1) / STILE, 1);
-    hipLaunchKernelGGL(k_apply_compact, dim3((unsigned)tiles), dim3(SB), 0, s, bm, nwords, tile_off, prefix, keys_out, K);
+    const int64_t tiles = scan_tiles(nwords);
+    if (scan_items(nwords) == 1)
+        hipLaunchKernelGGL(k_apply_compact<1>, dim3((unsigned)tiles), dim3(SB), 0, s, bm, nwords, tile_off, prefix, keys_out, K);
+    else
+        hipLaunchKernelGGL(k_apply_compact<SI>, dim3((unsigned)tiles), dim3(SB), 0, s, bm, nwords, tile_off, prefix, keys_out, K);
 }
 template <class T>
 void carry_over(const uint32_t *okeys, const double2 *opsi, const T *oV, int64_t n_old, const uint64_t *bm,
@@ -1811,7 +1847,8 @@ void fiber_tables_all(const uint32_t *keys, int64_t n, const TileAll &r, int64_t
     fill_u64(bm, nwords + 2, 0ull, s);
     mark_keys_wave(keys, n, bm, s);
     scan_popcount(bm, nwords, prefix, &counters[0], scan_tmp, s);
-    hipLaunchKernelGGL(k_tile_count, dim3(nblocks(nt)), dim3(TB), 0, s, r, bm, cnt);
+    if (nt <= 1 << 16) hipLaunchKernelGGL(k_tile_count<8>, dim3(nblocks(8 * nt)), dim3(TB), 0, s, r, bm, cnt);
+    else hipLaunchKernelGGL(k_tile_count<1>, dim3(nblocks(nt)), dim3(TB), 0, s, r, bm, cnt);
     scan_u32(cnt, 2 * nt, offs, &counters[1], scan_tmp, s);
     // tiles a wavefront goes through: most hold nothing on a large grid, and a wavefront
     // of its own for each costs more than finding the next (163 us with 1, 120 with 4,
