@@ -1113,12 +1113,14 @@ constexpr int64_t BATCH_BYTES_MAX = 8ll << 30;
 TileAll tiles_of(const ppq_ctx *c)
 {
     TileAll r{};
-    r.nd = c->g.D - 1;
+    r.nd = c->g.D;
+    const int last = r.nd - 1;
+    r.fibers = (uint32_t)(c->g.total / (uint64_t)c->g.n[last]);
     for (int k = 0; k < r.nd; ++k) {
         r.sk[k] = c->g.stride[k];
         r.nk[k] = (uint32_t)c->g.n[k];
-        r.per[k] = (r.sk[k] + 63) / 64;
-        r.first[k + 1] = r.first[k] + (uint32_t)(c->g.total / ((uint64_t)r.sk[k] * r.nk[k])) * r.per[k];
+        r.per[k] = ((k < last ? r.sk[k] : r.fibers) + 63) / 64;
+        r.first[k + 1] = r.first[k] + (k < last ? (uint32_t)(c->g.total / ((uint64_t)r.sk[k] * r.nk[k])) : 1u) * r.per[k];
     }
     return r;
 }
@@ -1128,7 +1130,7 @@ int64_t batched_bytes(const ppq_ctx *c)
     const int64_t nd = c->g.D - 1;
     // the dimensions' points are counted up in 32 bits
     if (nd < 1 || (nd + 1) * c->cap >= (1ll << 32)) return 0;
-    const int64_t words = c->nwords + 2, tiles = 2 * (int64_t)tiles_of(c).first[nd];
+    const int64_t words = c->nwords + 2, tiles = 2 * (int64_t)tiles_of(c).first[c->g.D];
     return words * 12 + tiles * 8 + scan_tmp_words(std::max(words, tiles)) * 4;
 }
 
@@ -1139,7 +1141,7 @@ bool ensure_batched(ppq_ctx *c)
     const int64_t bytes = batched_bytes(c);
     if (bytes == 0 || bytes > BATCH_BYTES_MAX) return false;
     if (c->bat_cap == c->cap) return true;
-    const int64_t words = c->nwords + 2, tiles = 2 * (int64_t)tiles_of(c).first[c->g.D - 1];
+    const int64_t words = c->nwords + 2, tiles = 2 * (int64_t)tiles_of(c).first[c->g.D];
     dfree(c->bmB);
     dfree(c->pfxB);
     dfree(c->scanB);
@@ -1206,8 +1208,10 @@ PlanePass plane_pass_of(const ppq_ctx *c, int i)
 // ---- products on grid vectors -------------------------------------------------
 constexpr int64_t GRID_TOTAL_MAX = int64_t(1) << 23;  // largest grid (functions)
 constexpr int64_t GRID_BYTES_MAX = int64_t(1) << 30;  // all grid vectors of a context
-constexpr int64_t GRID_WORK_MAX = int64_t(1) << 24;   // digits summed in one product (see use_grid)
-constexpr int64_t GRID_TERMS_MAX = int64_t(1) << 26;  // ... of a DVR operator with product terms
+// digits summed in one product (see use_grid): dimensions longer than a mask word, a DVR
+// operator, one with product terms, lattices
+constexpr int64_t GRID_LONG_MAX = int64_t(1) << 24, GRID_WORK_MAX = 14'000'000, GRID_TERMS_MAX = int64_t(1) << 26,
+                  GRID_LATTICE_MAX = int64_t(1) << 22;
 
 // Factors of one product with their depth: those that act on the product's
 // input are at depth 0, those on the results of depth d at d + 1.
@@ -1319,10 +1323,13 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
 // factor's once for itself and once per input; general terms are chains of
 // factors, where the launches saved count for more).  Above, the batched passes on
 // fiber tables read only members and use the matrix cores, once the tables are
-// built.  Measured, us a step of order 10 from a new state, grid vectors / batched:
-// 4D Morse 32^4, 52K functions (6.7M digits) 277 / 345, 114K (14.6M) 397 / 426, 209K
-// (26.7M) 603 / 502; the 4D lattice, 14K (11M) 581 / 617, 36K (29M) 1026 / 697;
-// general 3D terms, 13K (9M) 372 / 723, 96K (69M) 967 / 1075.
+// built (about 60 us of small launches).  Measured, us a step of order 10 from a new
+// state, grid vectors / batched (FP64; FP32): 4D Morse 32^4, 52K functions (6.7M
+// digits) 276 / 293; 245 / 291, 114K (14.6M) 396 / 360; 336 / 333, 209K (26.7M) 597 /
+// 427; the 3D anharmonic 48^3, 44K (6.3M) 236 / 313, 96K (13.9M) 328 / 357; the 4D
+// lattice, 2.3K (1.8M) 485 / 437; 411 / 427, 10K (7.7M) 509 / 460; 441 / 451, 36K (28M)
+// 1025 / 583; a 2D Weylet lattice, 1.0K (0.2M) 273 / 515; general 3D terms, 13K (9M)
+// 369 / 645, 96K (69M) 959 / 942.  Dimensions of more than 64 points are not batched.
 bool use_grid(const ppq_ctx *c)
 {
     if (c->hpsi_variant != 2 || c->grid_switch == 0 || c->nact <= 0 || (int64_t)c->g.total > GRID_TOTAL_MAX) return false;
@@ -1333,7 +1340,9 @@ bool use_grid(const ppq_ctx *c)
     int64_t digits = 0;
     for (const GridFactor &f : fs)
         digits += f.kind == GRID_DIAG ? 1 : (int64_t)c->g.n[f.k] * (f.kind == GRID_CPLX ? 1 + f.nin : 1);
-    return c->grid_switch == 2 || c->nact * digits <= (!c->any_lattice && nz > 0 ? GRID_TERMS_MAX : GRID_WORK_MAX);
+    const int64_t limit = any_long(c) ? (!c->any_lattice && nz > 0 ? GRID_TERMS_MAX : GRID_LONG_MAX)
+                          : c->any_lattice ? GRID_LATTICE_MAX : nz > 0 ? GRID_TERMS_MAX : GRID_WORK_MAX;
+    return c->grid_switch == 2 || c->nact * digits <= limit;
 }
 
 // The stages of the product (one launch each): factors of one depth, up to
@@ -1542,17 +1551,21 @@ void build_fibers(ppq_ctx *c)
         make_chunks(keys, nullptr, n, c->g.stride[c->split - 1], false, c->blk_window, cap_s,
                     c->chunk[0], c->big[0], c->small + 2 * MAXD, s);
     }
-    // last dimension: contiguous runs
-    last_flags(keys, n, c->g.n[D - 1], c->flags, s);
-    scan_u32(c->flags, n, c->fidx, &c->small[D - 1], c->scan_tmp, s);
-    last_fill(keys, n, c->g.n[D - 1], c->flags, c->fidx, &c->small[D - 1], c->off[D - 1], c->mask[D - 1], s);
-    last_info(keys, n, c->g.n[D - 1], c->info[D - 1], s);
-    if (try_block) chunk_fibers(c->chunk[0], n, c->blk_window, c->fidx, &c->small[D - 1], c->fch[D - 1], s);
     // the per-point fiber info of dimensions other than the last is read only
     // by the point-parallel-everywhere layout, which takes the per-dimension path
-    if (!try_block && c->hpsi_variant != 1 && n > 0 && D > 1 && ensure_batched(c)) {
+    const bool all = !try_block && c->hpsi_variant != 1 && n > 0 && D > 1 && ensure_batched(c);
+    if (!all) {
+        // last dimension: contiguous runs
+        last_flags(keys, n, c->g.n[D - 1], c->flags, s);
+        scan_u32(c->flags, n, c->fidx, &c->small[D - 1], c->scan_tmp, s);
+        last_fill(keys, n, c->g.n[D - 1], c->flags, c->fidx, &c->small[D - 1], c->off[D - 1], c->mask[D - 1], s);
+        last_info(keys, n, c->g.n[D - 1], c->info[D - 1], s);
+    }
+    if (try_block) chunk_fibers(c->chunk[0], n, c->blk_window, c->fidx, &c->small[D - 1], c->fch[D - 1], s);
+    if (all) {
         TabPtrs t{};
-        for (int k = 0; k < D - 1; ++k) {
+        t.info = c->info[D - 1];
+        for (int k = 0; k < D; ++k) {
             t.pi[k] = c->pi[k];
             t.off[k] = c->off[k];
             t.mask[k] = c->mask[k];

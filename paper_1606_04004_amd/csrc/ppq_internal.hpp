@@ -122,15 +122,17 @@ struct TabPtrs {
     uint32_t *pi[MAXD];
     uint32_t *off[MAXD];
     uint64_t *mask[MAXD];
+    uint8_t *info;  // of the last dimension, which has no pi
 };
-// Fiber tables of dimensions 0..nd-1 (row-major frames) in one set of launches, tile
-// by tile: a tile is the fibers of up to 64 consecutive keys below digit k (all n_k
-// digits).
+// Fiber tables of every dimension (row-major frames) in one set of launches, tile by
+// tile: a tile is the fibers of up to 64 consecutive keys below digit k (all n_k
+// digits), or up to 64 consecutive fibers of the last dimension.
 struct TileAll {
-    int nd;                   // dimensions 0..nd-1
+    int nd;                   // dimensions
     uint32_t sk[MAXD];        // stride of the dimension's digit
     uint32_t nk[MAXD];        // its size (at most 64)
     uint32_t per[MAXD];       // tiles per value of the digits above it
+    uint32_t fibers;          // slots for fibers of the last dimension
     uint32_t first[MAXD + 1]; // first tile of each dimension
 };
 // bm, prefix: nwords + 2 words; cnt, offs: 2 first[nd] words; counters: 2 entries

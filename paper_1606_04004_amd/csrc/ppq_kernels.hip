@@ -470,13 +470,16 @@ __global__ __launch_bounds__(TB) void k_dilate_words(const uint64_t *K, int64_t 
         for (int k = 0; k < MAXD; ++k) {
             if (k < g.D) {
                 const int64_t st = g.stride[k], P = st * g.n[k];
-                uint64_t zm = 0ull, tm = 0ull;
-                for (int64_t r0 = -pos[k]; r0 < 64; r0 += P) {
-                    if (r0 + st > 0) zm |= bit_range((int)i64max(r0, 0), (int)i64min(r0 + st, 64));
-                    const int64_t ts = r0 + P - st;
-                    if (r0 + P > 0 && ts < 64) tm |= bit_range((int)i64max(ts, 0), (int)i64min(r0 + P, 64));
+                const uint64_t below = bit_window(K, nwords, a - st), above = bit_window(K, nwords, a + st);
+                if (below | above) {  // (most of a large grid is empty)
+                    uint64_t zm = 0ull, tm = 0ull;
+                    for (int64_t r0 = -pos[k]; r0 < 64; r0 += P) {
+                        if (r0 + st > 0) zm |= bit_range((int)i64max(r0, 0), (int)i64min(r0 + st, 64));
+                        const int64_t ts = r0 + P - st;
+                        if (r0 + P > 0 && ts < 64) tm |= bit_range((int)i64max(ts, 0), (int)i64min(r0 + P, 64));
+                    }
+                    acc |= (below & ~zm) | (above & ~tm);
                 }
-                acc |= (bit_window(K, nwords, a - st) & ~zm) | (bit_window(K, nwords, a + st) & ~tm);
                 pos[k] += inc[k];
                 if (pos[k] >= P) pos[k] -= P;
             }
@@ -749,7 +752,7 @@ __global__ void k_rot_rank(const uint32_t *keys, int64_t n, uint32_t sk, uint32_
     if (info) info[q] = (uint8_t)(d | (start ? 0x80u : 0u));
 }
 
-// ---- fiber tables of every non-last dimension in one set of launches ----------
+// ---- fiber tables of every dimension in one set of launches --------------------
 // From the set's row-major bitmap and its prefix, tile by tile.
 // A tile of dimension k: the fibers of up to 64 consecutive keys below digit k, so
 // digit d of all of them is a run of bits, and n_k runs hold the tile.  No rotated
@@ -759,27 +762,48 @@ __global__ void k_rot_rank(const uint32_t *keys, int64_t n, uint32_t sk, uint32_
 // a digit per lane, are read from lane to lane, a point's position is its run's rank
 // plus the run's bits below the lane, and the permutation leaves through LDS in
 // contiguous stores.  Bound by the instructions of the second pass.  Measured, 4M
-// functions of a 24^6 grid (830K tiles): 15 us for the bitmap, 40 for the counts, 112
-// for the tiles (rotated bitmaps and a walk over them in rank order, before: 173 and
-// 236); 108K of 48^4 (5K tiles) 5 and 11 (38 the walk); 33K of 24^3 x 8, a build
+// functions of a 24^6 grid (950K tiles): 15 us for the bitmap, 58 for the counts, 124
+// for the tiles (rotated bitmaps, a walk over them in rank order and four passes over
+// the points for the last dimension, before: 173, 236 and 50); 108K of 48^4 6 and 11
+// (38 the walk); 33K of 24^3 x 8, a build
 // with its waits 134 (173).
+// Of the last dimension `base` is the first fiber's first key, `len` the fibers.
 __device__ inline void tile_of(const TileAll &r, uint32_t tile, int &k, uint32_t &base, int &len)
 {
     k = 0;
     while (tile >= r.first[k + 1]) ++k;
     const uint32_t i = tile - r.first[k], hi = i / r.per[k], lo = (i - hi * r.per[k]) * 64u;
-    base = hi * r.nk[k] * r.sk[k] + lo;
-    len = (int)(r.sk[k] - lo < 64u ? r.sk[k] - lo : 64u);
+    const uint32_t row = k + 1 < r.nd ? r.sk[k] : r.fibers;
+    base = k + 1 < r.nd ? hi * r.nk[k] * r.sk[k] + lo : lo * r.nk[k];
+    len = (int)(row - lo < 64u ? row - lo : 64u);
 }
 
 // S lanes share a tile's digits: one while there are tiles enough for every SIMD.
+// The blocks from `wide` on take the last dimension, a wavefront LAST_TILES of its
+// tiles, a lane per fiber (only the fibers are counted: its points are in key order).
+constexpr int LAST_TILES = 4;
 template <int S>
-__global__ __launch_bounds__(TB) void k_tile_count(TileAll r, const uint64_t *bm, uint32_t *cnt)
+__global__ __launch_bounds__(TB) void k_tile_count(TileAll r, unsigned wide, const uint64_t *bm, uint32_t *cnt)
 {
-    const uint32_t nt = r.first[r.nd], tile = (uint32_t)(gid() / S), sub = (uint32_t)(gid() % S);
-    if (tile >= nt) return;
+    const uint32_t nt = r.first[r.nd], end = r.first[r.nd - 1];
     int k, len;
     uint32_t base;
+    if (blockIdx.x >= wide) {
+        const int lane = threadIdx.x & 63;
+        const uint32_t wave = (blockIdx.x - wide) * (TB / 64) + (threadIdx.x >> 6);
+#pragma unroll
+        for (int u = 0; u < LAST_TILES; ++u) {
+            const uint32_t tile = end + wave * LAST_TILES + u;
+            if (tile >= nt) break;
+            tile_of(r, tile, k, base, len);
+            const uint64_t v = lane < len ? extract_bits(bm, base + (uint32_t)lane * r.nk[k], (int)r.nk[k]) : 0ull;
+            const uint32_t c = (uint32_t)__popcll(__ballot(v != 0));
+            if (lane == 0) cnt[tile] = cnt[nt + tile] = c;
+        }
+        return;
+    }
+    const uint32_t tile = (uint32_t)(gid() / S), sub = (uint32_t)(gid() % S);
+    if (tile >= end) return;
     tile_of(r, tile, k, base, len);
     uint64_t any = 0;
     uint32_t points = 0;
@@ -838,6 +862,36 @@ __global__ __launch_bounds__(TB) void k_tile_fill(TileAll r, uint32_t n, int nma
         const uint32_t nk = r.nk[k], sk = r.sk[k];
         // (the counts before the tile's dimension: n points each)
         const uint32_t q0 = offs[tile] - (uint32_t)k * n, f0 = offs[nt + tile] - offs[nt + r.first[k]];
+        if (k + 1 == r.nd) {
+            // the fibers' windows lie one after the other, their points in key order
+            uint64_t m = 0;
+            uint32_t q = 0;
+            if (lane < len) {
+                const uint32_t at = base + (uint32_t)lane * nk;
+                m = extract_bits(bm, at, (int)nk);
+                q = prefix[at >> 6] + (uint32_t)__popcll(bm[at >> 6] & ((1ull << (at & 63)) - 1ull));
+            }
+            const uint64_t fibers = __ballot(m != 0);
+            if (m) {
+                const uint32_t f = f0 + bits_below_lane(fibers);
+                t.off[k][f] = q;
+                t.mask[k][f] = m;
+            }
+            uint8_t *si = reinterpret_cast<uint8_t *>(sl);
+            const int first = __ffsll((unsigned long long)fibers) - 1, last = 63 - __clzll((long long)fibers);
+            const uint32_t p0 = __shfl(q, first, 64), points = __shfl(q + (uint32_t)__popcll(m), last, 64) - p0;
+            uint32_t at = q - p0, start = 0x80u;
+            for (uint64_t x = m; x; x &= x - 1) {
+                si[at++] = (uint8_t)((uint32_t)(__ffsll((unsigned long long)x) - 1) | start);
+                start = 0;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t i = (uint32_t)lane; i < points; i += 64) t.info[p0 + i] = si[i];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            continue;
+        }
         uint64_t run = 0;
         uint32_t rank = 0;
         if ((uint32_t)lane < nk) {
@@ -1847,8 +1901,11 @@ void fiber_tables_all(const uint32_t *keys, int64_t n, const TileAll &r, int64_t
     fill_u64(bm, nwords + 2, 0ull, s);
     mark_keys_wave(keys, n, bm, s);
     scan_popcount(bm, nwords, prefix, &counters[0], scan_tmp, s);
-    if (nt <= 1 << 16) hipLaunchKernelGGL(k_tile_count<8>, dim3(nblocks(8 * nt)), dim3(TB), 0, s, r, bm, cnt);
-    else hipLaunchKernelGGL(k_tile_count<1>, dim3(nblocks(nt)), dim3(TB), 0, s, r, bm, cnt);
+    const int64_t head = r.first[r.nd - 1], tail = nt - head;
+    const int lanes = nt <= 1 << 16 ? 8 : 1;
+    const unsigned wide = nblocks(head * lanes), last = nblocks((tail + LAST_TILES - 1) / LAST_TILES * 64);
+    if (lanes == 8) hipLaunchKernelGGL(k_tile_count<8>, dim3(wide + last), dim3(TB), 0, s, r, wide, bm, cnt);
+    else hipLaunchKernelGGL(k_tile_count<1>, dim3(wide + last), dim3(TB), 0, s, r, wide, bm, cnt);
     scan_u32(cnt, 2 * nt, offs, &counters[1], scan_tmp, s);
     // tiles a wavefront goes through: most hold nothing on a large grid, and a wavefront
     // of its own for each costs more than finding the next (163 us with 1, 120 with 4,
