@@ -145,9 +145,8 @@ __global__ __launch_bounds__(HB) void k_hpsi_real(const uint32_t *__restrict__ p
 #undef PPQ_BODY
 }
 
-// Accumulating pass with every memory access of the wavefront issued up
-// front: positions, x and the old y of all window digits are loaded before the
-// contraction, so the output loop has no dependent loads.
+// Accumulating pass: the x of all window digits are loaded before the contraction,
+// and the y of the next rows before their sums, so no row waits for its own loads.
 // DOT: also returns sum_p conj(x_p) y_p over the fiber (the stored y), the
 // lane's share of <x|y> when this pass writes y last.
 // STAGE: the positions come from the wavefront's copy of its rank range of
@@ -159,46 +158,60 @@ __device__ __forceinline__ double2 body_real_acc(uint32_t o, uint64_t m, int ws,
                                                  uint32_t r0 = 0)
 {
     using C = typename Cx<R>::T;
-    C xw[W], yw[W];
-    uint32_t pw[W];
+    // STAGE: rows whose y is held at a time; else all, with their positions
+    constexpr int YC = !STAGE ? W : W % 8 == 0 ? 8 : W;
+    C xw[W];
+    uint32_t pw[STAGE ? 1 : W];
+    auto position = [&](int jj) {
+        if constexpr (STAGE) return sp[o + (uint32_t)__popcll(m & ((1ull << (ws + jj)) - 1ull)) - r0];
+        else return pw[jj];
+    };
+    if constexpr (!STAGE) {
 #pragma unroll
-    for (int jj = 0; jj < W; ++jj) {
-        int j = ws + jj;
-        pw[jj] = 0;
-        if ((m >> j) & 1ull) {
-            uint32_t pos = o + (uint32_t)__popcll(m & ((1ull << j) - 1ull));
-            pw[jj] = IDENT ? pos : (STAGE ? sp[pos - r0] : pi[pos]);
+        for (int jj = 0; jj < W; ++jj) {
+            int j = ws + jj;
+            pw[jj] = 0;
+            if ((m >> j) & 1ull) {
+                uint32_t pos = o + (uint32_t)__popcll(m & ((1ull << j) - 1ull));
+                pw[jj] = IDENT ? pos : pi[pos];
+            }
         }
     }
 #pragma unroll
     for (int jj = 0; jj < W; ++jj) {
         xw[jj] = Cx<R>::make(0, 0);
-        yw[jj] = Cx<R>::make(0, 0);
-        if ((m >> (ws + jj)) & 1ull) {
-            xw[jj] = x[pw[jj]];
-            yw[jj] = y[pw[jj]];
-        }
+        if ((m >> (ws + jj)) & 1ull) xw[jj] = x[position(jj)];
     }
     const R *Tw = T + ws * NMAX + ws;
     double2 dot = make_double2(0.0, 0.0);
 #pragma unroll
-    for (int ll = 0; ll < W; ++ll) {
-        R ar = yw[ll].x, ai = yw[ll].y;
-        const R *Tr = Tw + ll * NMAX;
+    for (int l0 = 0; l0 < W; l0 += YC) {
+        C yw[YC];
 #pragma unroll
-        for (int jj = 0; jj < W; ++jj) {
-            R t = Tr[jj];
-            ar = fma(t, xw[jj].x, ar);
-            ai = fma(t, xw[jj].y, ai);
+        for (int u = 0; u < YC; ++u) {
+            yw[u] = Cx<R>::make(0, 0);
+            if ((m >> (ws + l0 + u)) & 1ull) yw[u] = y[position(l0 + u)];
         }
-        if ((m >> (ws + ll)) & 1ull) {
-            uint32_t p = pw[ll];
-            if constexpr (STAGE) p = sp[o + (uint32_t)__popcll(m & ((1ull << (ws + ll)) - 1ull)) - r0];
-            y[p] = Cx<R>::make(ar, ai);
-            if (DOT) {
-                const double xr = (double)xw[ll].x, xi = (double)xw[ll].y;
-                dot.x = fma(xr, (double)ar, fma(xi, (double)ai, dot.x));
-                dot.y = fma(xr, (double)ai, fma(-xi, (double)ar, dot.y));
+#pragma unroll
+        for (int u = 0; u < YC; ++u) {
+            const int ll = l0 + u;
+            R ar = 0, ai = 0;
+            const R *Tr = Tw + ll * NMAX;
+#pragma unroll
+            for (int jj = 0; jj < W; ++jj) {
+                R t = Tr[jj];
+                ar = fma(t, xw[jj].x, ar);
+                ai = fma(t, xw[jj].y, ai);
+            }
+            if ((m >> (ws + ll)) & 1ull) {
+                ar += yw[u].x;
+                ai += yw[u].y;
+                y[position(ll)] = Cx<R>::make(ar, ai);
+                if (DOT) {
+                    const double xr = (double)xw[ll].x, xi = (double)xw[ll].y;
+                    dot.x = fma(xr, (double)ar, fma(xi, (double)ai, dot.x));
+                    dot.y = fma(xr, (double)ai, fma(-xi, (double)ar, dot.y));
+                }
             }
         }
     }
@@ -213,11 +226,13 @@ __device__ __forceinline__ double2 body_real_acc(uint32_t o, uint64_t m, int ws,
 // lane's lookups otherwise touch a cache line of their own for every window
 // digit, and the passes are bound by the lines a CU can look up: 28 us a pass
 // over 4M functions in FP32 where the vectors take 20).  The positions are read
-// again at the stores, which leaves registers for a fourth wavefront per SIMD in
-// FP32.  Six-dimensional quartic product on 3.97M functions: FP64 290 -> 268 us,
-// FP32 193 -> 167 us; a copy loop that waits for each load was slower than none.
+// again where they are needed, and y is held for eight rows at a time, so three
+// wavefronts fit a SIMD in FP64 and five in FP32 (two and three with both windows
+// in registers).  Six-dimensional quartic product on 3.97M functions: FP64 290 us
+// with scattered lookups, 268 staged, 242 with eight rows; FP32 193, 167, 158; a copy
+// loop that waits for each load was slower than none.
 template <class R, int NMAX, bool IDENT, bool DOT, bool STAGE = false>
-__global__ __launch_bounds__(HB, !STAGE || NMAX > 24 ? 1 : sizeof(R) == 4 ? 4 : 2) void k_hpsi_acc(const uint32_t *__restrict__ pi, const uint32_t *__restrict__ off,
+__global__ __launch_bounds__(HB, !STAGE || NMAX > 24 ? 1 : sizeof(R) == 4 ? 5 : 3) void k_hpsi_acc(const uint32_t *__restrict__ pi, const uint32_t *__restrict__ off,
                                                  const uint64_t *__restrict__ mask, int64_t nf,
                                                  const R *__restrict__ T, const typename Cx<R>::T *__restrict__ x,
                                                  typename Cx<R>::T *__restrict__ y, const int *skip_if, int skip_j,
