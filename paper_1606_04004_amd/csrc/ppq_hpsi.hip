@@ -159,7 +159,7 @@ __device__ __forceinline__ double2 body_real_acc(uint32_t o, uint64_t m, int ws,
 {
     using C = typename Cx<R>::T;
     // STAGE: rows whose y is held at a time; else all, with their positions
-    constexpr int YC = !STAGE ? W : W % 8 == 0 ? 8 : W;
+    constexpr int YC = !STAGE ? W : W % 4 == 0 ? 4 : W;
     C xw[W];
     uint32_t pw[STAGE ? 1 : W];
     auto position = [&](int jj) {
@@ -226,13 +226,14 @@ __device__ __forceinline__ double2 body_real_acc(uint32_t o, uint64_t m, int ws,
 // lane's lookups otherwise touch a cache line of their own for every window
 // digit, and the passes are bound by the lines a CU can look up: 28 us a pass
 // over 4M functions in FP32 where the vectors take 20).  The positions are read
-// again where they are needed, and y is held for eight rows at a time, so three
-// wavefronts fit a SIMD in FP64 and five in FP32 (two and three with both windows
-// in registers).  Six-dimensional quartic product on 3.97M functions: FP64 290 us
-// with scattered lookups, 268 staged, 242 with eight rows; FP32 193, 167, 158; a copy
-// loop that waits for each load was slower than none.
+// again where they are needed, and y is held for four rows at a time, so four
+// wavefronts fit a SIMD in FP64 and six (all that LDS holds) in FP32, where both
+// windows in registers left two and three.  Six-dimensional quartic product on 3.97M
+// functions: FP64 290 us with scattered lookups, 268 staged; on another card 237
+// staged, 215 with eight rows, 208 with four and a bucket of 20 digits; FP32 193 and
+// 167; 159, 153 and 137.  A copy loop that waits for each load was slower than none.
 template <class R, int NMAX, bool IDENT, bool DOT, bool STAGE = false>
-__global__ __launch_bounds__(HB, !STAGE || NMAX > 24 ? 1 : sizeof(R) == 4 ? 5 : 3) void k_hpsi_acc(const uint32_t *__restrict__ pi, const uint32_t *__restrict__ off,
+__global__ __launch_bounds__(HB, !STAGE || NMAX > 24 ? 1 : sizeof(R) == 4 ? (DOT ? 5 : 6) : DOT ? 3 : 4) void k_hpsi_acc(const uint32_t *__restrict__ pi, const uint32_t *__restrict__ off,
                                                  const uint64_t *__restrict__ mask, int64_t nf,
                                                  const R *__restrict__ T, const typename Cx<R>::T *__restrict__ x,
                                                  typename Cx<R>::T *__restrict__ y, const int *skip_if, int skip_j,
@@ -294,6 +295,9 @@ __global__ __launch_bounds__(HB, !STAGE || NMAX > 24 ? 1 : sizeof(R) == 4 ? 5 : 
         }
         if constexpr (NMAX >= 16) {
             if (width <= 16) PPQ_BODY(16)
+        }
+        if constexpr (NMAX >= 24 && STAGE) {
+            if (width <= 20) PPQ_BODY(20)
         }
         if constexpr (NMAX >= 24) {
             if (width <= 24) PPQ_BODY(24)
