@@ -130,3 +130,29 @@ def test_default_stream_is_in_order(torch):
         torch.cuda.synchronize()
     ref = Oracle(cd).apply_def(keys, x)
     assert np.max(np.abs(yt.cpu().numpy() - ref)) < 1e-13 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("n", [[64, 64, 64, 64], [2, 2, 64, 64, 64, 17]])
+def test_bitmaps_at_the_scan_limit(n, torch):
+    """Bitmaps of exactly 2^18 words (one word per thread of the scans) and of more:
+    the same sets after an adaption as the oracle's, coefficients carried over bit
+    for bit, and products on their tables within 1e-13 of the largest entry."""
+    import paper_1606_04004_amd as ppq
+    cd = card(f"small_{len(n)}d", n=n)
+    total = int(np.prod(n))
+    rng = np.random.default_rng(3)
+    keys = np.unique(np.concatenate([rng.choice(total, size=1500), np.arange(total // 2, total // 2 + 600), [0, 63, 64, total - 1]])).astype(np.uint64)
+    x = random_complex(keys.size, 4)
+    o = Oracle(cd)
+    o.set_state(keys, x)
+    g = ppq.Propagator(cd, precision=0, device=0, stream=torch.cuda.current_stream())
+    g.set_state(keys, x)
+    eps = float(np.median(np.abs(x)))
+    for turn in range(2):
+        o.prune(eps)
+        g.prune(eps)
+        (ko, co), (kg, cg) = o.state(), g.state()
+        assert np.array_equal(kg, ko) and np.array_equal(cg, co)
+        z = random_complex(ko.size, 6)
+        got, ref = run(cd, ko, z, 0, {}, torch), o.apply_def(ko, z)
+        assert np.max(np.abs(got - ref)) < 1e-13 * np.max(np.abs(ref))
