@@ -1380,7 +1380,7 @@ std::vector<GridStage<R>> grid_stages(const ppq_ctx *c, const std::vector<GridFa
                 for (int q = 0; q < 4; ++q) {
                     const bool on = q < f.nin;
                     o.x[q] = (const C *)(!on || f.in[q] < 0 ? c->xg : c->zg[f.in[q]]);
-                    o.c[q] = C{(R)(on ? f.cre[q] : 0.0), (R)(on ? f.cim[q] : 0.0)};
+                    o.c[q] = make_double2(on ? f.cre[q] : 0.0, on ? f.cim[q] : 0.0);
                 }
                 o.diag = f.diag;
                 o.use = f.use;
@@ -2033,7 +2033,7 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
             if (f.depth != d) continue;
             if (f.kind == GRID_DIAG) {
                 if (stages) {
-                    ts.c[ts.ndiag] = C{(R)f.cre[0], (R)f.cim[0]};
+                    ts.c[ts.ndiag] = make_double2(f.cre[0], f.cim[0]);
                     ts.diag[ts.ndiag] = f.diag;
                     ts.use[ts.ndiag] = f.use;
                 }
@@ -2053,7 +2053,7 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
                 o.nin = f.nin;
                 for (int q = 0; q < f.nin; ++q) {
                     o.x[q] = (const C *)(f.in[q] < 0 ? nullptr : c->zbuf[f.in[q]]);  // nullptr: the product's input
-                    o.c[q] = C{(R)f.cre[q], (R)f.cim[q]};
+                    o.c[q] = make_double2(f.cre[q], f.cim[q]);
                 }
                 o.diag = f.diag;
                 o.use = f.use;

@@ -71,8 +71,8 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
     if (CX && nin > 1) {
         auto weight = [&](int i) {
             V c;
-            c.x = field((const R *)&op->c[i].x);
-            c.y = field((const R *)&op->c[i].y);
+            c.x = (R)field(&op->c[i].x);
+            c.y = (R)field(&op->c[i].y);
             return c;
         };
         const V c0 = weight(0);
@@ -131,12 +131,12 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
         }
     }
     const int scaled = CX ? field(&op->scaled) : 0;
-    V cs = V{1, 0};
+    double2 cs = make_double2(1.0, 0.0);
     unsigned use = 0;
     gbyte *diag = nullptr;
     if (scaled) {
-        cs.x = field((const R *)&op->c[0].x);
-        cs.y = field((const R *)&op->c[0].y);
+        cs.x = field(&op->c[0].x);
+        cs.y = field(&op->c[0].y);
         use = field(&op->use);
         diag = global_base((const void *const *)&op->diag);
     }
@@ -146,15 +146,21 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
         V v;
         v.x = accr[kb >> 2][kb & 3];
         v.y = acci[kb >> 2][kb & 3];
-        if (scaled) {
-            // the term's coefficient and its diagonal factors (see ppq_grid.hip)
-            const R w = use ? (R)diag_value(g, diag, nmax, use, keys[at[kb]]) : R(1);
-            const V a = v;
-            v.x = (cs.x * a.x - cs.y * a.y) * w;
-            v.y = (cs.x * a.y + cs.y * a.x) * w;
-        }
         __attribute__((address_space(1))) V *o = (__attribute__((address_space(1))) V *)(out + (uint64_t)at[kb] * sizeof(V));
-        if (add) {
+        if (scaled) {
+            // the term's coefficient and its diagonal factors (see ppq_grid.hip): in FP64,
+            // rounded once, with the sum
+            const double w = use ? diag_value(g, diag, nmax, use, keys[at[kb]]) : 1.0;
+            const double ax = v.x, ay = v.y;
+            double tx = (cs.x * ax - cs.y * ay) * w, ty = (cs.x * ay + cs.y * ax) * w;
+            if (add) {
+                const V q = *o;
+                tx += q.x;
+                ty += q.y;
+            }
+            v.x = (R)tx;
+            v.y = (R)ty;
+        } else if (add) {
             const V q = *o;
             v.x += q.x;
             v.y += q.y;
@@ -248,7 +254,8 @@ __global__ __launch_bounds__(BAB, batch_waves(sizeof(R) == 8, GENERAL, NTM)) voi
 
 // y_p = V_p x_p + the factors' vectors at the point (+ the terms without dense
 // factors).  NV >= 0: with the partial sums of <v_i|y> for i < NV and <q|y> (q the
-// product's input); NV < 0: none.  Streams ny + 3 + NV vectors.
+// product's input); NV < 0: none.  Streams ny + 3 + NV vectors.  The sum is formed in
+// FP64 and rounded once.
 template <class R, int NV>
 __global__ __launch_bounds__(TB, 2) void k_combine(BatchSum<R> ts, GridDesc g, const uint32_t *__restrict__ keys, int64_t n,
                                                    const typename Cplx<R>::T *x, const R *V, typename Cplx<R>::T *y,
@@ -268,7 +275,8 @@ __global__ __launch_bounds__(TB, 2) void k_combine(BatchSum<R> ts, GridDesc g, c
         for (int i = 0; i < BATCH_SUMS; ++i)
             if (i < ts.ny) v[i] = ts.y[i][p];
         const C xv = x[p];
-        C s = v[0];
+        const double2 xd = make_double2((double)xv.x, (double)xv.y);
+        double2 s = make_double2((double)v[0].x, (double)v[0].y);
 #pragma unroll
         for (int i = 1; i < BATCH_SUMS; ++i) {
             if (i < ts.ny) {
@@ -277,21 +285,22 @@ __global__ __launch_bounds__(TB, 2) void k_combine(BatchSum<R> ts, GridDesc g, c
             }
         }
         if (V) {
-            const R pot = V[p];
-            s.x = fma(pot, xv.x, s.x);
-            s.y = fma(pot, xv.y, s.y);
+            const double pot = V[p];
+            s.x = fma(pot, xd.x, s.x);
+            s.y = fma(pot, xd.y, s.y);
         }
         for (int i = 0; i < ts.ndiag; ++i) {
-            const R w = ts.use[i] ? (R)diag_value(g, (gbyte *)(const char *)ts.diag[i], ts.nmax, ts.use[i], key) : R(1);
-            s.x += (ts.c[i].x * xv.x - ts.c[i].y * xv.y) * w;
-            s.y += (ts.c[i].x * xv.y + ts.c[i].y * xv.x) * w;
+            const double w = ts.use[i] ? diag_value(g, (gbyte *)(const char *)ts.diag[i], ts.nmax, ts.use[i], key) : 1.0;
+            s.x += (ts.c[i].x * xd.x - ts.c[i].y * xd.y) * w;
+            s.y += (ts.c[i].x * xd.y + ts.c[i].y * xd.x) * w;
         }
-        y[p] = s;
+        const C r = Cplx<R>::make(s.x, s.y);
+        y[p] = r;
         if constexpr (NV >= 0) {
-            const double2 sd = make_double2((double)s.x, (double)s.y);
+            const double2 sd = make_double2((double)r.x, (double)r.y);  // as stored
 #pragma unroll
             for (int i = 0; i < NV; ++i) cdot_acc(acc[i], ld2(Vb, (int64_t)i * ld + p), sd);
-            cdot_acc(acc[NA - 1], make_double2((double)xv.x, (double)xv.y), sd);
+            cdot_acc(acc[NA - 1], xd, sd);
         }
     }
     if constexpr (NV >= 0) block_reduce_store<NA>(acc, partial);

@@ -25,12 +25,16 @@ namespace {
 // of 32^4 (50), 25 us with three general terms on 12K functions of a 3D grid (76).
 constexpr int GU = 8;  // digits in flight per lane
 
-// A wavefront's slice: digits [d0, d1) of one factor.
+// A wavefront's slice: digits [d0, d1) of one factor.  With product terms (GENERAL)
+// its sum is returned in FP64, whatever the vectors: a term's coefficient and diagonal
+// factors act in FP64 and a result is rounded once, when it is stored.
 template <class R, bool GENERAL>
 struct Slice {
     using V = typename Cplx<R>::V;
+    using S = typename Cplx<typename std::conditional<GENERAL, double, R>::type>::V;
     gbyte *x[GENERAL ? 4 : 1], *H, *H2, *diag;
     V c[GENERAL ? 4 : 1];
+    double2 c0;
     uint32_t st;
     unsigned use;
     int n, nb, kind, nin, scaled, d0, d1, nmax;
@@ -49,10 +53,9 @@ struct Slice {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 x[i % (GENERAL ? 4 : 1)] = global_base((const void *const *)&op->x[i]);
-                V ci;
-                ci.x = field((const R *)&op->c[i].x);
-                ci.y = field((const R *)&op->c[i].y);
-                c[i % (GENERAL ? 4 : 1)] = ci;
+                const double2 w = make_double2(field(&op->c[i].x), field(&op->c[i].y));
+                if (i == 0) c0 = w;
+                c[i % (GENERAL ? 4 : 1)] = V{(R)w.x, (R)w.y};
             }
             H2 = global_base(&op->H2);
             diag = global_base((const void *const *)&op->diag);
@@ -64,11 +67,10 @@ struct Slice {
         }
     }
 
-    // the slice's sum for the point (acc), and the second factor's (acc2)
-    __device__ void sum(const GridDesc &g, uint32_t key, V &acc, V &acc2) const
+    // the slice's sum for the point (out), and the second factor's (out2)
+    __device__ void sum(const GridDesc &g, uint32_t key, S &out, S &out2) const
     {
-        acc = V{0, 0};
-        acc2 = acc;
+        V acc = V{0, 0}, acc2 = acc;
         if (GENERAL && kind == GRID_DIAG) {
             acc = at_byte<V>(x[0], key * (uint32_t)sizeof(V));
         } else {
@@ -143,11 +145,16 @@ struct Slice {
         if (GENERAL && scaled) {
             // the term's coefficient and its diagonal factors, which commute with the
             // dense factors of the other dimensions and with the truncation
-            const R w = use ? (R)diag_value(g, diag, nmax, use, key) : R(1);
-            const V v = acc;
-            acc.x = (c[0].x * v.x - c[0].y * v.y) * w;
-            acc.y = (c[0].x * v.y + c[0].y * v.x) * w;
+            const double w = use ? diag_value(g, diag, nmax, use, key) : 1.0;
+            const double vx = acc.x, vy = acc.y;
+            out.x = (c0.x * vx - c0.y * vy) * w;
+            out.y = (c0.x * vy + c0.y * vx) * w;
+        } else {
+            out.x = acc.x;
+            out.y = acc.y;
         }
+        out2.x = acc2.x;
+        out2.y = acc2.y;
     }
 };
 
@@ -163,7 +170,8 @@ __global__ __launch_bounds__(1024) void k_grid(const GridStage<R> *stp, GridDesc
     using C = typename Cplx<R>::T;
     if (skip_if && skip_j >= *skip_if) return;
     extern __shared__ __align__(16) unsigned char smem[];
-    using Vec = typename Cplx<R>::V;
+    using Vec = typename Slice<R, GENERAL>::S;
+    using S = decltype(Vec{}.x);
     const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ns = field(&stp->nslice), second = GENERAL ? field(&stp->second) : 0, nout = GENERAL ? field(&stp->nout) : 0;
@@ -204,16 +212,20 @@ __global__ __launch_bounds__(1024) void k_grid(const GridStage<R> *stp, GridDesc
             if (valid) {
                 const C xv = xg[key];
                 if (V) {
-                    const R pot = V[p];
-                    v.x = fma(pot, xv.x, v.x);
-                    v.y = fma(pot, xv.y, v.y);
+                    const S pot = V[p];
+                    v.x = fma(pot, (S)xv.x, v.x);
+                    v.y = fma(pot, (S)xv.y, v.y);
                 }
                 if (accumulate) {
                     const C o = y[p];
                     v.x += o.x;
                     v.y += o.y;
                 }
-                y[p] = Cplx<R>::make(v.x, v.y);
+                const C r = Cplx<R>::make(v.x, v.y);
+                y[p] = r;
+                // the dots are those of the result as it is stored
+                v.x = r.x;
+                v.y = r.y;
                 if (DOTS == 1)
                     cdot_acc(acc[0], make_double2((double)xv.x, (double)xv.y), make_double2((double)v.x, (double)v.y));
             }
@@ -283,7 +295,8 @@ int grid_launch(const GridStage<R> *dev, const GridStage<R> &st, const GridDesc 
     const int64_t tiles = (n + 63) / 64, per = (tiles + GRID_BLOCKS - 1) / GRID_BLOCKS;
     const unsigned nb = (unsigned)((tiles + per - 1) / per);
     const int W = std::max(st.nslice, 4);
-    const size_t lds = (size_t)st.nslice * (st.second ? 2 : 1) * 64 * sizeof(typename GridStage<R>::C) +
+    const size_t lds = (size_t)st.nslice * (st.second ? 2 : 1) * 64 *
+                           (st.general ? sizeof(double2) : sizeof(typename GridStage<R>::C)) +
                        (dots == 2 ? 64 * sizeof(double2) : 0);
 #define L(G, DT)                                                                                                \
     hipLaunchKernelGGL((k_grid<R, G, DT>), dim3(nb), dim3(64 * W), lds, s, dev, g, keys, n, xg, V, y, (int)accumulate, \

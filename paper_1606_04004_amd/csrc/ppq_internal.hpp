@@ -400,7 +400,7 @@ struct GridOp {
     using C = typename std::conditional<sizeof(R) == 8, double2, float2>::type;
     const void *H, *H2;   // n x n factors, column-major with nb rows per column
     const C *x[4];
-    C c[4];               // weights of the inputs (one input: a factor of the result, with scaled)
+    double2 c[4];         // weights of the inputs (one input: a factor of the result, with scaled)
     const double *diag;   // diagonal factors [D][nmax] of the dimensions in use (scaled)
     uint32_t stride;
     unsigned use;
@@ -442,7 +442,7 @@ struct BatchOp {
     const uint32_t *off;
     const uint64_t *mask;
     const C *x[4];
-    C c[4];
+    double2 c[4];
     C *out;
     const double *diag;
     int64_t nf;
@@ -460,7 +460,7 @@ struct BatchSum {
     using C = typename GridOp<R>::C;
     int ny, ndiag, nmax;
     const C *y[BATCH_SUMS];
-    C c[BATCH_DIAGS];
+    double2 c[BATCH_DIAGS];
     const double *diag[BATCH_DIAGS];
     unsigned use[BATCH_DIAGS];
 };
