@@ -89,9 +89,10 @@ struct Slice {
                     }
 #pragma unroll
                     for (int u = 0; u < GU; ++u) {
-                        const R tu = d + u < d1 ? t[u] : R(0);
-                        acc.x = __builtin_elementwise_fma(tu, xv[u].x, acc.x);
-                        acc.y = __builtin_elementwise_fma(tu, xv[u].y, acc.y);
+                        // past the slice's end the entry is another digit's, which may be infinite
+                        const V v = d + u < d1 ? xv[u] : V{0, 0};
+                        acc.x = __builtin_elementwise_fma(t[u], v.x, acc.x);
+                        acc.y = __builtin_elementwise_fma(t[u], v.y, acc.y);
                     }
                 }
             } else if (GENERAL) {

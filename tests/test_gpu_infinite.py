@@ -1,0 +1,62 @@
+"""Infinite inputs: an infinite coefficient reaches the functions coupled to it as the
+products make it, infinite or NaN, in every form of the product."""
+import os
+
+import numpy as np
+import pytest
+
+from oracle.oracle import Oracle
+from workloads import card, random_complex
+
+pytestmark = pytest.mark.gpu
+
+# (PPQ_GRID, PPQ_BATCH): a pass per factor, batched passes, grid vectors
+PASSES, BATCH, GRID = ("0", "0"), ("0", "2"), ("2", "0")
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "needs a GPU"
+    return t
+
+
+# slices of digits with and without a remainder of the digits in flight; grids of up to 256 points a dimension
+@pytest.mark.parametrize("n", [[16, 14], [9, 11, 10], [48, 47], [3, 2], [256, 17], [70, 65]])
+@pytest.mark.parametrize("form", [PASSES, BATCH, GRID])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_infinite_input(n, form, prec, torch):
+    """Kinetic factors and a potential, all real and finite: the real and the
+    imaginary part of every result are finite, infinite of either sign or NaN where
+    the oracle's are."""
+    import paper_1606_04004_amd as ppq
+    if form == BATCH and max(n) > 64:
+        pytest.skip("batched passes take dimensions of at most 64 points")
+    cd = card(f"small_{len(n)}d", n=n)
+    total = int(np.prod(n))
+    keys = np.arange(total, dtype=np.uint64)
+    if total > 1000:
+        # half the functions, those of the first digits among them
+        keys = np.unique(np.concatenate([np.random.default_rng(2).choice(total, size=total // 2, replace=False),
+                                         np.arange(n[-1]), np.arange(n[0]) * (total // n[0])])).astype(np.uint64)
+    os.environ["PPQ_GRID"], os.environ["PPQ_BATCH"] = form
+    try:
+        g = ppq.Propagator(cd, precision=prec, device=0, stream=torch.cuda.current_stream())
+    finally:
+        del os.environ["PPQ_GRID"], os.environ["PPQ_BATCH"]
+    x = random_complex(keys.size, 3)
+    g.set_state(keys, x)
+    o = Oracle(cd)
+    for at, value in ((0, complex(np.inf, 0.5)), (keys.size // 2, complex(0.25, -np.inf)), (keys.size - 1, complex(-np.inf, np.inf))):
+        bad = x.copy()
+        bad[at] = value
+        xt = torch.from_numpy(bad.astype(np.complex64) if prec else bad).cuda()
+        yt = torch.zeros_like(xt)
+        g.apply_h(xt, yt)
+        torch.cuda.synchronize()
+        got = yt.cpu().numpy()
+        # part by part: complex products would spread an infinite part's 0 * inf over the other one
+        for a, part in ((got.real, bad.real), (got.imag, bad.imag)):
+            b = o.apply_def(keys, part.astype(np.complex128)).real
+            assert np.array_equal(np.isnan(a), np.isnan(b))
+            assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(b), np.sign(b), 0))
