@@ -67,6 +67,8 @@
  *               word from the bitmap of the functions kept (the +-1 stencil
  *               on DVR axes only); 0 (default) chooses by the grid-to-set
  *               size ratio.  Both give the same set.
+ *   PPQ_ALLOC_FAIL=k  the k-th allocation of a context's work memory (from 0)
+ *               is refused, as when the device has none left.
  *   Every layout computes the same product; only the summation order of
  *   the dimensions' contributions differs.
  */
@@ -239,8 +241,9 @@ int ppq_clear_potential(ppq_ctx *ctx);
 /* Capacity of the active set (number of functions).  Grows automatically when
    adaption needs more, doubling each time (never past the grid size); each
    growth reallocates every per-point buffer, so reserving ahead avoids
-   reallocation inside a run.  PPQ_E_ARG unless 1 <= max_active <= the grid
-   size; PPQ_E_STATE without a grid. */
+   reallocation inside a run.  A growth that fails (PPQ_E_OOM, from whichever
+   call needed it) keeps the state, and the call may be made again.
+   PPQ_E_ARG unless 1 <= max_active <= the grid size; PPQ_E_STATE without a grid. */
 int ppq_reserve(ppq_ctx *ctx, int64_t max_active);
 
 /* Initial state: product Gaussian psi0(q) = prod_k g_k(q_k),

@@ -87,7 +87,11 @@ T *dalloc(int64_t count)
     void *p = nullptr;
     if (count <= 0) count = 1;
     hipError_t e = hipMalloc(&p, (size_t)count * sizeof(T));
-    if (e != hipSuccess) throw std::bad_alloc();
+    if (e != hipSuccess) {
+        // reported by the exception: not left behind for the next launch check
+        (void)hipGetLastError();
+        throw std::bad_alloc();
+    }
     return (T *)p;
 }
 
@@ -101,6 +105,7 @@ struct LatticeMaps {
 
 struct ppq_ctx {
     int device = 0;
+    int64_t alloc_fail = -1, alloc_count = 0;  // the work allocation that is refused (PPQ_ALLOC_FAIL), those made
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int precision = PPQ_FP64;
@@ -453,18 +458,35 @@ void free_operator(ppq_ctx *c)
     c->op_dirty = true;
 }
 
+// Memory for a context's work: what its sets, basis vectors and products need.
+// The request that PPQ_ALLOC_FAIL names is made one that no device can meet.
+template <class T>
+T *walloc(ppq_ctx *c, int64_t count)
+{
+    constexpr int64_t NO_DEVICE = int64_t(1) << 46;  // bytes
+    return dalloc<T>(c->alloc_count++ == c->alloc_fail ? NO_DEVICE / (int64_t)sizeof(T) : count);
+}
+
 // (Re)allocates every per-point buffer for at least n points, keeping the
 // current keys and coefficients. A growing set doubles the capacity (never
 // past the grid size, which bounds the active set): each growth frees and
 // allocates every table, so a set that spreads over a few steps should pay
-// for that once or twice, not at every step.
+// for that once or twice, not at every step.  Without the memory the state
+// stays (in buffers of its own, capacity 0) and the next call that needs the
+// others asks for them again.
 void ensure_capacity(ppq_ctx *c, int64_t n)
 {
     if (n <= c->cap) return;
     int64_t nc = std::max<int64_t>(n, std::min<int64_t>(2 * c->cap, (int64_t)c->g.total));
-    nc = std::max<int64_t>(nc, 1024);
-    uint32_t *nk = dalloc<uint32_t>(nc);
-    double2 *np = dalloc<double2>(nc);
+    nc = std::max<int64_t>(nc, std::max<int64_t>(1024, c->has_state ? c->nact : 0));
+    uint32_t *nk = walloc<uint32_t>(c, nc);
+    double2 *np = nullptr;
+    try {
+        np = walloc<double2>(c, nc);
+    } catch (...) {
+        dfree(nk);
+        throw;
+    }
     if (c->has_state && c->nact > 0) {
         ck(hipMemcpyAsync(nk, c->keys[c->cur], c->nact * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream),
            "copy keys");
@@ -473,54 +495,58 @@ void ensure_capacity(ppq_ctx *c, int64_t n)
     }
     ck(hipStreamSynchronize(c->stream), "sync");
     free_state_buffers(c);
-    c->cap = nc;
     c->cur = 0;
-    c->keys[0] = nk;
-    c->psi[0] = np;
-    c->keys[1] = dalloc<uint32_t>(nc);
-    c->psi[1] = dalloc<double2>(nc);
-    c->psi_tmp = dalloc<double2>(nc);
-    if (c->precision == PPQ_FP64) {
-        c->V64 = dalloc<double>(nc);
-        c->Vt64 = dalloc<double>(nc);
-    } else {
-        c->V32 = dalloc<float>(nc);
-        c->Vt32 = dalloc<float>(nc);
-    }
-    for (int k = 0; k < c->g.D; ++k) {
-        if (k < c->g.D - 1) c->pi[k] = dalloc<uint32_t>(nc);
-        c->off[k] = dalloc<uint32_t>(nc + 1);
-        c->mask[k] = dalloc<uint64_t>(nc);
-        c->info[k] = dalloc<uint8_t>(nc);
-    }
-    c->flags = dalloc<uint32_t>(nc);
-    c->fidx = dalloc<uint32_t>(nc);
-    c->tmpmask = dalloc<uint64_t>(nc);
-    c->scan_tmp_n = std::max(scan_tmp_words(nc), scan_tmp_words(c->nwords));
-    c->scan_tmp = dalloc<uint32_t>(c->scan_tmp_n);
-    c->P_R = dalloc<uint32_t>(nc);
-    c->inv_R = dalloc<uint32_t>(nc);
-    for (int i = 0; i < 2; ++i) {
-        c->chunk[i] = dalloc<uint32_t>(nc / BLOCK_WINDOW + 2);
-        c->big[i] = dalloc<uint32_t>(nc / BLOCK_WINDOW + 2);
-    }
-    for (int k = 0; k < c->g.D; ++k) c->fch[k] = dalloc<uint32_t>(nc / BLOCK_WINDOW + 2);
     c->derived_valid = false;
     c->v_valid = false;
     c->v_partial = false;
     free_krylov(c);
+    try {
+        c->keys[1] = walloc<uint32_t>(c, nc);
+        c->psi[1] = walloc<double2>(c, nc);
+        c->psi_tmp = walloc<double2>(c, nc);
+        if (c->precision == PPQ_FP64) {
+            c->V64 = walloc<double>(c, nc);
+            c->Vt64 = walloc<double>(c, nc);
+        } else {
+            c->V32 = walloc<float>(c, nc);
+            c->Vt32 = walloc<float>(c, nc);
+        }
+        for (int k = 0; k < c->g.D; ++k) {
+            if (k < c->g.D - 1) c->pi[k] = walloc<uint32_t>(c, nc);
+            c->off[k] = walloc<uint32_t>(c, nc + 1);
+            c->mask[k] = walloc<uint64_t>(c, nc);
+            c->info[k] = walloc<uint8_t>(c, nc);
+        }
+        c->flags = walloc<uint32_t>(c, nc);
+        c->fidx = walloc<uint32_t>(c, nc);
+        c->tmpmask = walloc<uint64_t>(c, nc);
+        c->scan_tmp_n = std::max(scan_tmp_words(nc), scan_tmp_words(c->nwords));
+        c->scan_tmp = walloc<uint32_t>(c, c->scan_tmp_n);
+        c->P_R = walloc<uint32_t>(c, nc);
+        c->inv_R = walloc<uint32_t>(c, nc);
+        for (int i = 0; i < 2; ++i) {
+            c->chunk[i] = walloc<uint32_t>(c, nc / BLOCK_WINDOW + 2);
+            c->big[i] = walloc<uint32_t>(c, nc / BLOCK_WINDOW + 2);
+        }
+        for (int k = 0; k < c->g.D; ++k) c->fch[k] = walloc<uint32_t>(c, nc / BLOCK_WINDOW + 2);
+    } catch (...) {
+        free_state_buffers(c);
+        c->keys[0] = nk;
+        c->psi[0] = np;
+        throw;
+    }
+    c->keys[0] = nk;
+    c->psi[0] = np;
+    c->cap = nc;
 }
 
 void ensure_krylov(ppq_ctx *c, int m)
 {
     if (c->Vk && c->kv_m >= m && c->kv_cap == c->cap) return;
     free_krylov(c);
-    size_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
-    void *p = nullptr;
-    if (hipMalloc(&p, es * (size_t)(m + 1) * (size_t)c->cap) != hipSuccess) throw std::bad_alloc();
-    c->Vk = p;
-    if (hipMalloc(&p, es * (size_t)c->cap) != hipSuccess) throw std::bad_alloc();
-    c->wk = p;
+    const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
+    c->Vk = walloc<unsigned char>(c, es * (m + 1) * c->cap);
+    c->wk = walloc<unsigned char>(c, es * c->cap);
     c->kv_m = m;
     c->kv_cap = c->cap;
 }
@@ -529,12 +555,9 @@ void ensure_zbuf(ppq_ctx *c)
 {
     size_t need = std::max(c->F64.size(), c->chains.empty() ? (size_t)0 : (size_t)3);
     if (c->zbuf.size() >= need && c->kv_cap == c->cap && c->Vk) return;
-    size_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
-    while (c->zbuf.size() < need) {
-        void *p = nullptr;
-        if (hipMalloc(&p, es * (size_t)c->cap) != hipSuccess) throw std::bad_alloc();
-        c->zbuf.push_back(p);
-    }
+    const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
+    c->zbuf.reserve(need);
+    while (c->zbuf.size() < need) c->zbuf.push_back(walloc<unsigned char>(c, es * c->cap));
 }
 
 // ---- operator assembly -------------------------------------------------------
@@ -1149,12 +1172,12 @@ bool ensure_batched(ppq_ctx *c)
     dfree(c->tcntB);
     dfree(c->toffB);
     c->bat_cap = 0;
-    c->bmB = dalloc<uint64_t>(words);
-    c->pfxB = dalloc<uint32_t>(words);
-    c->tcntB = dalloc<uint32_t>(tiles);
-    c->toffB = dalloc<uint32_t>(tiles);
-    c->scanB = dalloc<uint32_t>(scan_tmp_words(std::max(words, tiles)));
-    c->cntB = dalloc<uint32_t>(2 + MAXD);
+    c->bmB = walloc<uint64_t>(c, words);
+    c->pfxB = walloc<uint32_t>(c, words);
+    c->tcntB = walloc<uint32_t>(c, tiles);
+    c->toffB = walloc<uint32_t>(c, tiles);
+    c->scanB = walloc<uint32_t>(c, scan_tmp_words(std::max(words, tiles)));
+    c->cntB = walloc<uint32_t>(c, 2 + MAXD);
     c->bat_cap = c->cap;
     return true;
 }
@@ -1164,16 +1187,17 @@ void ensure_planes(ppq_ctx *c)
 {
     if (c->pl_cap == c->cap) return;
     const int64_t nc = c->cap;
+    c->pl_cap = 0;
     for (int i = 0; i < c->npl; ++i) {
         dfree(c->plP[i]);
         dfree(c->pltask[i]);
         dfree(c->pldig[i]);
-        if (c->pl_a[i] + 2 < c->g.D) c->plP[i] = dalloc<uint32_t>(nc);
-        c->pldig[i] = dalloc<uint16_t>(nc);
-        c->pltask[i] = dalloc<uint32_t>(nc / PLANE_WINDOW + 2);
+        if (c->pl_a[i] + 2 < c->g.D) c->plP[i] = walloc<uint32_t>(c, nc);
+        c->pldig[i] = walloc<uint16_t>(c, nc);
+        c->pltask[i] = walloc<uint32_t>(c, nc / PLANE_WINDOW + 2);
     }
     dfree(c->pl_poff);
-    c->pl_poff = dalloc<uint32_t>(nc + 1);
+    c->pl_poff = walloc<uint32_t>(c, nc + 1);
     c->pl_cap = nc;
 }
 
@@ -1449,12 +1473,12 @@ bool ensure_grid(ppq_ctx *c)
     const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2), bytes = (int64_t)c->g.total * es;
     try {
         if (!c->xg) {
-            c->xg = dalloc<unsigned char>(bytes);
+            c->xg = walloc<unsigned char>(c, bytes);
             c->grid_clean = c->grid_planned = false;
         }
         c->zg.reserve(nz);
         while ((int)c->zg.size() < nz) {
-            c->zg.push_back(dalloc<unsigned char>(bytes));
+            c->zg.push_back(walloc<unsigned char>(c, bytes));
             c->grid_clean = c->grid_planned = false;
         }
     } catch (const std::bad_alloc &) {
@@ -1631,6 +1655,7 @@ void build_fibers(ppq_ctx *c)
 void build_derived(ppq_ctx *c)
 {
     if (c->derived_valid) return;
+    ensure_capacity(c, std::max<int64_t>(c->nact, 1));  // (after a growth that failed)
     if (c->op_dirty) c->fibers_valid = false;  // the layouts' tables depend on the operator's terms
     build_operator(c);
     const int D = c->g.D;
@@ -2102,7 +2127,7 @@ bool use_batch(ppq_ctx *c)
     if (ny > BATCH_SUMS) return false;
     const int64_t es = f64 ? sizeof(double2) : sizeof(float2);
     c->zbuf.reserve(nz);
-    while ((int)c->zbuf.size() < nz) c->zbuf.push_back(dalloc<unsigned char>(es * c->cap));
+    while ((int)c->zbuf.size() < nz) c->zbuf.push_back(walloc<unsigned char>(c, es * c->cap));
     // the factors' vectors hold a set of the rule, not the context's whole capacity
     const int64_t rows = c->batch_switch == 1 ? std::min(c->cap, limit) : c->cap;
     if (c->ybuf_cap < rows) {
@@ -2113,9 +2138,10 @@ bool use_batch(ppq_ctx *c)
     c->ybuf.reserve(ny);
     while ((int)c->ybuf.size() < ny) {
         void *p = nullptr;
-        if (hipMalloc(&p, es * c->ybuf_cap) != hipSuccess) {
+        try {
+            p = walloc<unsigned char>(c, es * c->ybuf_cap);
+        } catch (const std::bad_alloc &) {
             // no memory for them: a pass per factor needs none
-            (void)hipGetLastError();
             for (auto &y : c->ybuf) dfree(y);
             c->ybuf.clear();
             c->ybuf_cap = 0;
@@ -2340,13 +2366,15 @@ StepInfo advance(ppq_ctx *c, double dt, int m, double *alpha0_dst)
     if (c->sub_cap < c->max_substeps) {
         if (c->h_sub_meff) (void)hipHostFree(c->h_sub_meff);
         c->h_sub_meff = nullptr;
+        c->sub_cap = 0;
         ck(hipHostMalloc((void **)&c->h_sub_meff, sizeof(double) * c->max_substeps, hipHostMallocDefault),
            "pinned");
         c->sub_cap = c->max_substeps;
     }
     if (c->psi_save_cap < c->cap) {
         dfree(c->psi_save);
-        c->psi_save = dalloc<double2>(c->cap);
+        c->psi_save_cap = 0;
+        c->psi_save = walloc<double2>(c, c->cap);
         c->psi_save_cap = c->cap;
     }
     ck(hipMemcpyAsync(c->psi_save, c->psi[c->cur], c->nact * sizeof(double2), hipMemcpyDeviceToDevice, s), "save");
@@ -2402,7 +2430,8 @@ void do_prune(ppq_ctx *c, double eps, int64_t *nabove_out)
     if (words) {
         if (c->kbm_words != c->nwords) {
             dfree(c->kbm);
-            c->kbm = dalloc<uint64_t>(c->nwords);
+            c->kbm_words = 0;
+            c->kbm = walloc<uint64_t>(c, c->nwords);
             c->kbm_words = c->nwords;
             c->kbm_clean = false;
         }
@@ -2456,7 +2485,8 @@ void ensure_records(ppq_ctx *c, int64_t nrec)
 {
     if (c->rec_cap >= nrec) return;
     dfree(c->rec);
-    c->rec = dalloc<double>(nrec * PPQ_OBS_N);
+    c->rec_cap = 0;
+    c->rec = walloc<double>(c, nrec * PPQ_OBS_N);
     c->rec_cap = nrec;
     fill_zero_bytes(c->rec, nrec * PPQ_OBS_N * (int64_t)sizeof(double), c->stream);
 }
@@ -2622,7 +2652,7 @@ void record_append(ppq_ctx *c)
     int64_t used = c->rec_off.empty() ? 0 : c->rec_off.back() + c->rec_n.back();
     if (used + c->nact > c->rec_keys_cap) {
         int64_t nc = std::max<int64_t>(2 * c->rec_keys_cap, used + c->nact + (1 << 20));
-        uint32_t *nb = dalloc<uint32_t>(nc);
+        uint32_t *nb = walloc<uint32_t>(c, nc);
         if (used) ck(hipMemcpyAsync(nb, c->rec_keys, used * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream),
                      "record grow");
         ck(hipStreamSynchronize(c->stream), "record grow");
@@ -2650,7 +2680,7 @@ void clear_record(ppq_ctx *c)
 
 void checkpoint_now(ppq_ctx *c)
 {
-    double2 *b = dalloc<double2>(std::max<int64_t>(c->nact, 1));
+    double2 *b = walloc<double2>(c, std::max<int64_t>(c->nact, 1));
     if (c->nact)
         ck(hipMemcpyAsync(b, c->psi[c->cur], c->nact * sizeof(double2), hipMemcpyDeviceToDevice, c->stream), "ckpt");
     c->ckpt.push_back(b);
@@ -2671,31 +2701,27 @@ double2 overlap_with_packet(ppq_ctx *c)
 // K: the most states one recomputed segment holds (its steps' substeps)
 void ensure_adjoint_buffers(ppq_ctx *c, int m, int K)
 {
-    const size_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
+    const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
     if (!c->Wk || c->wk_cap != c->cap) {
         dfree(c->Wk);
-        void *p = nullptr;
-        if (hipMalloc(&p, es * (size_t)(m + 1) * (size_t)c->cap) != hipSuccess) throw std::bad_alloc();
-        c->Wk = p;
+        c->Wk = walloc<unsigned char>(c, es * (m + 1) * c->cap);
         c->wk_cap = c->cap;
     }
-    if (!c->ks_b) {
-        void *p = nullptr;
-        ck(hipMalloc(&p, sizeof(KState)), "kstate");
-        c->ks_b = (KState *)p;
-        c->Qd = dalloc<double2>(MAXM * MAXM);
-        c->dC = dalloc<double2>(ADJ_MAXP + 2 * MAXD);
-    }
+    if (!c->ks_b) c->ks_b = walloc<KState>(c, 1);
+    if (!c->Qd) c->Qd = walloc<double2>(c, MAXM * MAXM);
+    if (!c->dC) c->dC = walloc<double2>(c, ADJ_MAXP + 2 * MAXD);
     if (c->adj_cap != c->cap || !c->lam) {
         dfree(c->lam);
         dfree(c->mu);
-        c->lam = dalloc<double2>(c->cap);
-        c->mu = dalloc<double2>(c->cap);
+        c->adj_cap = 0;
+        c->lam = walloc<double2>(c, c->cap);
+        c->mu = walloc<double2>(c, c->cap);
         c->adj_cap = c->cap;
     }
     if (c->seg_cap < (int64_t)K * c->cap) {
         dfree(c->seg);
-        c->seg = dalloc<double2>((int64_t)K * c->cap);
+        c->seg_cap = 0;
+        c->seg = walloc<double2>(c, (int64_t)K * c->cap);
         c->seg_cap = (int64_t)K * c->cap;
     }
 }
@@ -2886,6 +2912,7 @@ int ppq_create(ppq_ctx **out, int device, void *hip_stream, int precision)
         const int d = std::atoi(v);
         if (d >= 0 && d <= 2) c->batch_switch = d;
     }
+    if (const char *v = std::getenv("PPQ_ALLOC_FAIL")) c->alloc_fail = std::atoll(v);
     if (const char *v = std::getenv("PPQ_BLOCK_WINDOW")) {
         const long w = std::atol(v);
         if (w >= (long)BLOCK_WINDOW && w <= (1l << 20)) c->blk_window = (uint32_t)w;
@@ -3692,8 +3719,9 @@ int ppq_acf_doubled(ppq_ctx *c, double *c2t)
             const int64_t total = c->g.total;
             if (c->full_cap < total) {
                 for (auto &p : c->full) dfree(p);
-                c->full[0] = dalloc<double2>(total);
-                c->full[1] = dalloc<double2>(total);
+                c->full_cap = 0;
+                c->full[0] = walloc<double2>(c, total);
+                c->full[1] = walloc<double2>(c, total);
                 c->full_cap = total;
             }
             hipStream_t s = c->stream;
