@@ -218,6 +218,7 @@ struct ppq_ctx {
     bool grid_clean = false;     // the grid vectors are zero outside the current set
     bool grid_used = false;      // ... and hold values on it
     bool grid_planned = false;   // stages match the operator and the grid vectors
+    bool grid_denied = false;    // no memory for them (until the operator changes)
     void *xg = nullptr;          // grid vector of a product's input
     std::vector<void *> zg;      // grid vectors of the products' intermediates
     std::vector<GridStage<double>> gst64;
@@ -696,6 +697,7 @@ std::vector<cd> factor_matrix(const ppq_ctx *c, const Factor &f)
 void build_operator(ppq_ctx *c)
 {
     if (!c->op_dirty) return;
+    c->grid_denied = false;
     for (int k = 0; k < MAXD; ++k) {
         dfree(c->T64[k]);
         dfree(c->T32[k]);
@@ -1465,9 +1467,12 @@ void plan_grid(ppq_ctx *c, std::vector<GridStage<R>> &stages)
 }
 
 // Allocates the grid vectors, plans the stages and clears what an earlier set
-// left.  False when the memory is not there: the fiber tables serve then.
+// left.  False when the memory is not there: the fiber tables serve then, for
+// every set until the operator changes (no request of a gigabyte per set, and a
+// recorded run's steps are recomputed by the form that recorded them).
 bool ensure_grid(ppq_ctx *c)
 {
+    if (c->grid_denied) return false;
     int nz = 0;
     (void)grid_factors(c, &nz);
     const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2), bytes = (int64_t)c->g.total * es;
@@ -1481,14 +1486,15 @@ bool ensure_grid(ppq_ctx *c)
             c->zg.push_back(walloc<unsigned char>(c, bytes));
             c->grid_clean = c->grid_planned = false;
         }
+        if (!c->grid_planned) {
+            if (c->precision == PPQ_FP64) plan_grid<double>(c, c->gst64);
+            else plan_grid<float>(c, c->gst32);
+            c->grid_planned = true;
+        }
     } catch (const std::bad_alloc &) {
         free_grid_vectors(c);
+        c->grid_denied = true;
         return false;
-    }
-    if (!c->grid_planned) {
-        if (c->precision == PPQ_FP64) plan_grid<double>(c, c->gst64);
-        else plan_grid<float>(c, c->gst32);
-        c->grid_planned = true;
     }
     if (!c->grid_clean) {
         fill_zero_bytes(c->xg, bytes, c->stream);

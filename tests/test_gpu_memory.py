@@ -148,3 +148,15 @@ def refuse_each_of_a_gradient(grid, torch):
 def test_adjoint_allocations(torch):
     """The recorded run and its gradient likewise (1e-10: the gradient's own bound)."""
     refuse_each_of_a_gradient("0", torch)
+
+
+@pytest.mark.parametrize("name", ["single", "terms"])
+def test_grid_vectors_are_done_without(name, torch):
+    """No product fails for want of grid vectors: there the fiber tables serve."""
+    assert "product" not in refuse_each(name, GRID, torch)
+
+
+def test_adjoint_keeps_its_form(torch):
+    """A recorded run's steps are recomputed by the form of the product that
+    recorded them, with and without its grid vectors."""
+    refuse_each_of_a_gradient("2", torch)
