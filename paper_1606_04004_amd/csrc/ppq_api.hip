@@ -328,6 +328,7 @@ struct ppq_ctx {
     int64_t seg_cap = 0;
     void *Wk = nullptr;
     int64_t wk_cap = 0;
+    int wk_m = 0;  // the order it holds
     KState *ks_b = nullptr;
     double2 *Qd = nullptr, *dC = nullptr, *lam = nullptr, *mu = nullptr;
     int64_t adj_cap = 0;
@@ -2708,10 +2709,11 @@ double2 overlap_with_packet(ppq_ctx *c)
 void ensure_adjoint_buffers(ppq_ctx *c, int m, int K)
 {
     const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
-    if (!c->Wk || c->wk_cap != c->cap) {
+    if (!c->Wk || c->wk_cap != c->cap || c->wk_m < m) {
         dfree(c->Wk);
         c->Wk = walloc<unsigned char>(c, es * (m + 1) * c->cap);
         c->wk_cap = c->cap;
+        c->wk_m = m;
     }
     if (!c->ks_b) c->ks_b = walloc<KState>(c, 1);
     if (!c->Qd) c->Qd = walloc<double2>(c, MAXM * MAXM);

@@ -160,3 +160,22 @@ def test_adjoint_keeps_its_form(torch):
     """A recorded run's steps are recomputed by the form of the product that
     recorded them, with and without its grid vectors."""
     refuse_each_of_a_gradient("2", torch)
+
+
+def test_adjoint_of_a_higher_order(torch):
+    """A gradient of a higher order than the context's first one: the basis of the
+    adjoint vectors grows with it, and the gradient is a new context's bit for bit."""
+    from paper_1606_04004_amd.adjoint import declare_trainable
+    cd = card("small_adjoint4d")
+
+    def gradient(g, m):
+        j = g.adjoint_record(nsteps=3, m=m, every=2)
+        return [np.array([j]), *g.adjoint_gradient()]
+
+    g, fresh = propagator(cd, torch), propagator(cd, torch)
+    for h in (g, fresh):
+        declare_trainable(h, cd)
+        h.reserve(10 ** 4)
+    gradient(g, 8)
+    for a, b in zip(gradient(g, 16), gradient(fresh, 16)):
+        assert np.array_equal(a, b)
