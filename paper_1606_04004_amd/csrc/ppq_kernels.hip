@@ -1497,7 +1497,7 @@ __global__ __launch_bounds__(1024) void k_adj_q(const KState *kf, const KState *
         double nrm = 0.0;
         for (int i = 0; i < M2; ++i) nrm = rown[i] > nrm ? rown[i] : nrm;
         int sq = 0;
-        while (nrm > 0.125) {
+        while (nrm > 0.125 && sq < 1100) {  // (an infinite norm ends it too)
             nrm *= 0.5;
             ++sq;
         }

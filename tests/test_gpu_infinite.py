@@ -60,3 +60,21 @@ def test_infinite_input(n, form, prec, torch):
             b = o.apply_def(keys, part.astype(np.complex128)).real
             assert np.array_equal(np.isnan(a), np.isnan(b))
             assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(b), np.sign(b), 0))
+
+
+def test_gradient_of_an_overflowing_potential(torch):
+    """A potential whose values overflow in H psi: the recorded run's scalars are
+    infinite or NaN, and the gradient's small exponential ends all the same.  The calls
+    return, with a PPQ error or results that are not finite."""
+    import paper_1606_04004_amd as ppq
+    from paper_1606_04004_amd.adjoint import declare_trainable
+    cd = card("small_adjoint4d")
+    cd = dict(cd, terms=[dict(t, coef=1e308 if i == 0 else t["coef"]) for i, t in enumerate(cd["terms"])])
+    g = ppq.Propagator(cd, device=0, stream=torch.cuda.current_stream())
+    declare_trainable(g, cd)
+    try:
+        j = g.adjoint_record(nsteps=1, m=4, every=1)
+        dp, dc, dm = g.adjoint_gradient()
+    except ppq.PPQError:
+        return
+    assert not np.all(np.isfinite(np.concatenate([[j], dp, dc, dm])))
