@@ -229,8 +229,9 @@ struct ppq_ctx {
     // batched products on fiber tables (see batch_rule)
     int batch_switch = 1;        // 0: never, 1: by the sizes, 2: wherever they apply (PPQ_BATCH)
     bool batch_planned = false;  // the stages match the operator and the vectors
-    std::vector<void *> ybuf;    // the factors' results
-    int64_t ybuf_cap = 0;
+    bool batch_denied = false;   // too many vectors, or no memory for them (until the operator changes)
+    std::vector<void *> ybuf;    // the factors' results, then the intermediates
+    int64_t ybuf_cap = 0;        // functions each holds
     std::vector<BatchStage<double>> bst64;
     std::vector<BatchStage<float>> bst32;
     BatchSum<double> bsum64{};
@@ -699,6 +700,7 @@ void build_operator(ppq_ctx *c)
 {
     if (!c->op_dirty) return;
     c->grid_denied = false;
+    c->batch_denied = false;
     for (int k = 0; k < MAXD; ++k) {
         dfree(c->T64[k]);
         dfree(c->T32[k]);
@@ -2047,11 +2049,12 @@ void apply_products(ppq_ctx *c, const void *xv, void *yv, const int *skip_if, in
 // Stages (one launch per depth and BATCH_OPS factors) and the final sum.  A
 // factor that adds to y takes a vector that no other factor of its depth takes
 // (every factor writes all of the set's functions): the first ones write, later
-// depths add.  With stages == nullptr only ts.ny is worked out.
+// depths add.  With stages == nullptr only ts.ny is worked out, which the stages need.
 template <class R>
 void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, std::vector<BatchStage<R>> *stages)
 {
     using C = typename BatchOp<R>::C;
+    const int ny = ts.ny;
     ts = BatchSum<R>{};
     ts.nmax = c->pd_nmax;
     if (stages) stages->clear();
@@ -2079,12 +2082,12 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
                 ts.ny = std::max(ts.ny, y + 1);
                 if (!stages) continue;
                 BatchOp<R> &o = st.op[st.nop++];
-                o.out = (C *)(y >= 0 ? c->ybuf[y] : c->zbuf[dst - 1]);
+                o.out = (C *)c->ybuf[y >= 0 ? y : ny + dst - 1];
                 o.add = add;
                 o.H = second ? f.P2 : f.P;
                 o.nin = f.nin;
                 for (int q = 0; q < f.nin; ++q) {
-                    o.x[q] = (const C *)(f.in[q] < 0 ? nullptr : c->zbuf[f.in[q]]);  // nullptr: the product's input
+                    o.x[q] = (const C *)(f.in[q] < 0 ? nullptr : c->ybuf[ny + f.in[q]]);  // nullptr: the product's input
                     o.c[q] = make_double2(f.cre[q], f.cim[q]);
                 }
                 o.diag = f.diag;
@@ -2104,6 +2107,47 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
         for (int i = 0; i < ts.ny; ++i) ts.y[i] = (const C *)c->ybuf[i];
 }
 
+// The batched product's vectors and stages.  The vectors hold a set of the rule
+// (`limit`), not the context's whole capacity, and no more than BATCH_VECTORS_MAX
+// together.  False where the operator takes more factors than a launch sums, or
+// where there is no memory: a pass per factor serves then, for every set until the
+// operator changes (as with the grid vectors).
+constexpr int64_t BATCH_VECTORS_MAX = int64_t(2) << 30;     // bytes
+constexpr int64_t BATCH_SET_MAX = int64_t(1) << 29;         // the tables' 32-bit byte offsets (8 bytes an entry)
+bool ensure_batch(ppq_ctx *c, int64_t limit)
+{
+    int nz = 0, ndiag = 0;
+    const std::vector<GridFactor> fs = grid_factors(c, &nz);
+    for (const GridFactor &f : fs) ndiag += f.kind == GRID_DIAG;
+    if (ndiag > BATCH_DIAGS) return false;
+    const bool f64 = c->precision == PPQ_FP64;
+    if (f64) plan_batch<double>(c, fs, c->bsum64, nullptr);
+    else plan_batch<float>(c, fs, c->bsum32, nullptr);
+    const int ny = f64 ? c->bsum64.ny : c->bsum32.ny;
+    if (ny > BATCH_SUMS) return false;
+    const int64_t es = f64 ? sizeof(double2) : sizeof(float2);
+    int64_t rows = std::min(c->cap, BATCH_SET_MAX);
+    if (c->batch_switch == 1) rows = std::min(rows, std::min(limit, BATCH_VECTORS_MAX / (es * (ny + nz))));
+    if (c->ybuf_cap != rows) {
+        for (auto &y : c->ybuf) dfree(y);
+        c->ybuf.clear();
+        c->ybuf_cap = rows;
+    }
+    try {
+        c->ybuf.reserve(ny + nz);
+        while ((int)c->ybuf.size() < ny + nz) c->ybuf.push_back(walloc<unsigned char>(c, es * rows));
+    } catch (const std::bad_alloc &) {
+        for (auto &y : c->ybuf) dfree(y);
+        c->ybuf.clear();
+        c->ybuf_cap = 0;
+        return false;
+    }
+    if (f64) plan_batch<double>(c, fs, c->bsum64, &c->bst64);
+    else plan_batch<float>(c, fs, c->bsum32, &c->bst32);
+    c->batch_planned = true;
+    return true;
+}
+
 // Whether the current set's products (on fiber tables) are batched: the default
 // layout, dimensions within a mask word, and a set that leaves a pass by itself
 // short of wavefronts.  Large sets fill the chip pass by pass, and there the vectors
@@ -2117,49 +2161,16 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
 constexpr int64_t BATCH_MAX_REAL64 = int64_t(3) << 19, BATCH_MAX = int64_t(3) << 20;
 bool use_batch(ppq_ctx *c)
 {
-    if (c->hpsi_variant != 2 || c->batch_switch == 0 || c->nact <= 0 || any_long(c)) return false;
+    if (c->hpsi_variant != 2 || c->batch_switch == 0 || c->batch_denied || c->nact <= 0 || any_long(c)) return false;
     const bool complex_factors = c->any_lattice || !c->pairs.empty() || !c->chains.empty();
     const int64_t limit = c->precision == PPQ_FP64 && !complex_factors ? BATCH_MAX_REAL64 : BATCH_MAX;
     if (c->batch_switch == 1 && c->nact > limit) return false;
+    if (!c->batch_planned && !ensure_batch(c, limit)) {
+        c->batch_denied = true;
+        return false;
+    }
+    if (c->nact > c->ybuf_cap) return false;
     ensure_nf(c);
-    int nz = 0, ndiag = 0;
-    if (c->batch_planned && c->ybuf_cap >= c->nact) return true;
-    const std::vector<GridFactor> fs = grid_factors(c, &nz);
-    for (const GridFactor &f : fs) ndiag += f.kind == GRID_DIAG;
-    const bool f64 = c->precision == PPQ_FP64;
-    if (ndiag > BATCH_DIAGS) return false;
-    if (f64) plan_batch<double>(c, fs, c->bsum64, nullptr);
-    else plan_batch<float>(c, fs, c->bsum32, nullptr);
-    const int ny = f64 ? c->bsum64.ny : c->bsum32.ny;
-    if (ny > BATCH_SUMS) return false;
-    const int64_t es = f64 ? sizeof(double2) : sizeof(float2);
-    c->zbuf.reserve(nz);
-    while ((int)c->zbuf.size() < nz) c->zbuf.push_back(walloc<unsigned char>(c, es * c->cap));
-    // the factors' vectors hold a set of the rule, not the context's whole capacity
-    const int64_t rows = c->batch_switch == 1 ? std::min(c->cap, limit) : c->cap;
-    if (c->ybuf_cap < rows) {
-        for (auto &y : c->ybuf) dfree(y);
-        c->ybuf.clear();
-        c->ybuf_cap = rows;
-    }
-    c->ybuf.reserve(ny);
-    while ((int)c->ybuf.size() < ny) {
-        void *p = nullptr;
-        try {
-            p = walloc<unsigned char>(c, es * c->ybuf_cap);
-        } catch (const std::bad_alloc &) {
-            // no memory for them: a pass per factor needs none
-            for (auto &y : c->ybuf) dfree(y);
-            c->ybuf.clear();
-            c->ybuf_cap = 0;
-            c->batch_planned = false;
-            return false;
-        }
-        c->ybuf.push_back(p);
-    }
-    if (f64) plan_batch<double>(c, fs, c->bsum64, &c->bst64);
-    else plan_batch<float>(c, fs, c->bsum32, &c->bst32);
-    c->batch_planned = true;
     return true;
 }
 

@@ -179,3 +179,57 @@ def test_adjoint_of_a_higher_order(torch):
     gradient(g, 8)
     for a, b in zip(gradient(g, 16), gradient(fresh, 16)):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("name", ["single", "terms"])
+def test_batched_vectors_are_done_without(name, torch):
+    """With the fiber tables there, no product fails for want of the batched form's
+    vectors: a pass per factor serves, and goes on serving (the same bits)."""
+    cd = card("small_4d") if name == "single" else terms_card()
+    keys = np.arange(0, 10 ** 4, 3, dtype=np.uint64)
+    x = random_complex(keys.size, 3)
+    results = []
+    for k in [-1, *range(60)]:
+        g = propagator(cd, torch, PPQ_GRID="0", PPQ_ALLOC_FAIL=str(k))
+        call = Twice()
+        call("set_state", lambda: g.set_state(keys, x))
+        call("tables", g.fiber_counts)
+        xt = torch.from_numpy(x).cuda()
+        ys = []
+        for _ in range(3):
+            yt = torch.zeros_like(xt)
+            call("product", lambda: g.apply_h(xt, yt))
+            torch.cuda.synchronize()
+            ys.append(yt.cpu().numpy())
+        assert "product" not in call.failed, f"allocation {k}"
+        assert np.array_equal(ys[0], ys[1]) and np.array_equal(ys[0], ys[2]), f"allocation {k}"
+        results.append(ys[0])
+        assert np.max(np.abs(ys[0] - results[0])) < 1e-12 * np.max(np.abs(results[0]))
+    # some of the refusals led to the other form, whose sums round differently
+    assert any(not np.array_equal(r, results[0]) for r in results)
+
+
+def test_batched_vectors_have_the_size_of_the_rule(torch):
+    """Fifteen three-factor terms with 30 vectors between their factors, on a context
+    that reserves eight million functions: the batched product takes at most 2 GiB."""
+    n = [64, 64, 64, 64]
+    cd = card("small_4d", n=n)
+    rng = np.random.default_rng(2)
+    m = [(0.1 * rng.standard_normal((64, 64))).tolist() for _ in range(4)]
+    cd["terms"] = cd["terms"] + [{"coef": 0.1 + 0.01 * i, "factors": [{"dim": k, "kind": "dense", "re": m[k]} for k in range(4) if k != i % 4]}
+                                 for i in range(15)]
+    g = propagator(cd, torch, PPQ_GRID="0")
+    g.reserve(8_000_000)
+    keys = np.arange(0, 64 ** 4, 9973, dtype=np.uint64)
+    x = random_complex(keys.size, 3)
+    g.set_state(keys, x)
+    g.fiber_counts()
+    xt = torch.from_numpy(x).cuda()
+    yt = torch.zeros_like(xt)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    g.apply_h(xt, yt)
+    torch.cuda.synchronize()
+    taken = free - torch.cuda.mem_get_info()[0]
+    print(f"{taken / 2 ** 30:.2f} GiB", flush=True)
+    assert taken < 2.1 * 2 ** 30
