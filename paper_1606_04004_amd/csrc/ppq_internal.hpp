@@ -210,8 +210,8 @@ int hpsi_acc_f64(const FiberPass &fp, const double *T, const double2 *x, double2
                  hipStream_t s, double2 *dotp = nullptr);
 int hpsi_acc_f32(const FiberPass &fp, const float *T, const float2 *x, float2 *y, const int *skip_if, int skip_j,
                  hipStream_t s, double2 *dotp = nullptr);
-// blocks of a fused <x|y> the next kernel's prologue sums
-constexpr int64_t DOT_BLOCKS_MAX = 4096;
+// blocks of a fused <x|y> that the next kernel's prologue sums (dimension 0's fibers / 256)
+constexpr int64_t DOT_BLOCKS_MAX = (int64_t)RED_BLOCKS * PSTRIDE_H;
 // matrix-core forms (v_mfma_*_16x16x4); T64 / H64 are h zero-padded to 64 x 64, column-major
 void hpsi_mfma_f32(const FiberPass &fp, const float *T64, const float2 *x, const float *V, float2 *y, bool first,
                    const int *skip_if, int skip_j, hipStream_t s);
@@ -356,7 +356,7 @@ void diag_scale(const uint32_t *keys, const C *x, int64_t n, const GridDesc &g, 
 constexpr int KRY_BLOCKS = 512;      // blocks of a sweep or dot kernel at most
 constexpr int KRY_SLOTS = MAXM + 2;
 constexpr int64_t KRY_DOTS = (int64_t)2 * KRY_SLOTS * RED_BLOCKS;
-constexpr int64_t KRY_DOTS_VALUES = (int64_t)MAXM * RED_BLOCKS;
+constexpr int64_t KRY_DOTS_VALUES = (int64_t)MAXM * RED_BLOCKS > DOT_BLOCKS_MAX ? (int64_t)MAXM * RED_BLOCKS : DOT_BLOCKS_MAX;
 constexpr int64_t PARTIAL_VALUES = KRY_DOTS + KRY_DOTS_VALUES;
 static_assert(PARTIAL_VALUES >= (int64_t)RED_BLOCKS * PSTRIDE_H, "partial sums of the other reductions");
 int kry_blocks(int64_t n);  // blocks of the Krylov kernels for n points
