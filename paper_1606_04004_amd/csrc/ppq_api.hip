@@ -1409,8 +1409,9 @@ std::vector<GridStage<R>> grid_stages(const ppq_ctx *c, const std::vector<GridFa
                 for (int q = 0; q < 4; ++q) {
                     const bool on = q < f.nin;
                     o.x[q] = (const C *)(!on || f.in[q] < 0 ? c->xg : c->zg[f.in[q]]);
-                    o.c[q] = make_double2(on ? f.cre[q] : 0.0, on ? f.cim[q] : 0.0);
+                    o.c[q] = C{(R)(on ? f.cre[q] : 0.0), (R)(on ? f.cim[q] : 0.0)};
                 }
+                o.scale = make_double2(f.cre[0], f.cim[0]);
                 o.diag = f.diag;
                 o.use = f.use;
                 o.stride = c->g.stride[f.k];
@@ -2088,8 +2089,9 @@ void plan_batch(ppq_ctx *c, const std::vector<GridFactor> &fs, BatchSum<R> &ts, 
                 o.nin = f.nin;
                 for (int q = 0; q < f.nin; ++q) {
                     o.x[q] = (const C *)(f.in[q] < 0 ? nullptr : c->ybuf[ny + f.in[q]]);  // nullptr: the product's input
-                    o.c[q] = make_double2(f.cre[q], f.cim[q]);
+                    o.c[q] = C{(R)f.cre[q], (R)f.cim[q]};
                 }
+                o.scale = make_double2(f.cre[0], f.cim[0]);
                 o.diag = f.diag;
                 o.use = f.use;
                 o.n = c->g.n[f.k];

@@ -71,8 +71,8 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
     if (CX && nin > 1) {
         auto weight = [&](int i) {
             V c;
-            c.x = (R)field(&op->c[i].x);
-            c.y = (R)field(&op->c[i].y);
+            c.x = field((const R *)&op->c[i].x);
+            c.y = field((const R *)&op->c[i].y);
             return c;
         };
         const V c0 = weight(0);
@@ -135,8 +135,8 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
     unsigned use = 0;
     gbyte *diag = nullptr;
     if (scaled) {
-        cs.x = field(&op->c[0].x);
-        cs.y = field(&op->c[0].y);
+        cs.x = field(&op->scale.x);
+        cs.y = field(&op->scale.y);
         use = field(&op->use);
         diag = global_base((const void *const *)&op->diag);
     }

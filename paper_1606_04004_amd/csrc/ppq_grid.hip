@@ -34,7 +34,7 @@ struct Slice {
     using S = typename Cplx<typename std::conditional<GENERAL, double, R>::type>::V;
     gbyte *x[GENERAL ? 4 : 1], *H, *H2, *diag;
     V c[GENERAL ? 4 : 1];
-    double2 c0;
+    double2 scale;
     uint32_t st;
     unsigned use;
     int n, nb, kind, nin, scaled, d0, d1, nmax;
@@ -53,10 +53,12 @@ struct Slice {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 x[i % (GENERAL ? 4 : 1)] = global_base((const void *const *)&op->x[i]);
-                const double2 w = make_double2(field(&op->c[i].x), field(&op->c[i].y));
-                if (i == 0) c0 = w;
-                c[i % (GENERAL ? 4 : 1)] = V{(R)w.x, (R)w.y};
+                V ci;
+                ci.x = field((const R *)&op->c[i].x);
+                ci.y = field((const R *)&op->c[i].y);
+                c[i % (GENERAL ? 4 : 1)] = ci;
             }
+            scale = make_double2(field(&op->scale.x), field(&op->scale.y));
             H2 = global_base(&op->H2);
             diag = global_base((const void *const *)&op->diag);
             use = field(&op->use);
@@ -148,8 +150,8 @@ struct Slice {
             // dense factors of the other dimensions and with the truncation
             const double w = use ? diag_value(g, diag, nmax, use, key) : 1.0;
             const double vx = acc.x, vy = acc.y;
-            out.x = (c0.x * vx - c0.y * vy) * w;
-            out.y = (c0.x * vy + c0.y * vx) * w;
+            out.x = (scale.x * vx - scale.y * vy) * w;
+            out.y = (scale.x * vy + scale.y * vx) * w;
         } else {
             out.x = acc.x;
             out.y = acc.y;

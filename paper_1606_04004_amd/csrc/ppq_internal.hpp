@@ -400,7 +400,8 @@ struct GridOp {
     using C = typename std::conditional<sizeof(R) == 8, double2, float2>::type;
     const void *H, *H2;   // n x n factors, column-major with nb rows per column
     const C *x[4];
-    double2 c[4];         // weights of the inputs (one input: a factor of the result, with scaled)
+    C c[4];               // weights of several inputs
+    double2 scale;        // a factor of the result (scaled)
     const double *diag;   // diagonal factors [D][nmax] of the dimensions in use (scaled)
     uint32_t stride;
     unsigned use;
@@ -442,7 +443,8 @@ struct BatchOp {
     const uint32_t *off;
     const uint64_t *mask;
     const C *x[4];
-    double2 c[4];
+    C c[4];
+    double2 scale;
     C *out;
     const double *diag;
     int64_t nf;
