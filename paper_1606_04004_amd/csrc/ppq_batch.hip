@@ -150,9 +150,13 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
         if (scaled) {
             // the term's coefficient and its diagonal factors (see ppq_grid.hip): in FP64,
             // rounded once, with the sum
-            const double w = use ? diag_value(g, diag, nmax, use, keys[at[kb]]) : 1.0;
             const double ax = v.x, ay = v.y;
-            double tx = (cs.x * ax - cs.y * ay) * w, ty = (cs.x * ay + cs.y * ax) * w;
+            double tx = cs.x * ax - cs.y * ay, ty = cs.x * ay + cs.y * ax;
+            if (use) {
+                const double w = diag_value(g, diag, nmax, use, keys[at[kb]]);
+                tx *= w;
+                ty *= w;
+            }
             if (add) {
                 const V q = *o;
                 tx += q.x;
@@ -254,9 +258,11 @@ __global__ __launch_bounds__(BAB, batch_waves(sizeof(R) == 8, GENERAL, NTM)) voi
 
 // y_p = V_p x_p + the factors' vectors at the point (+ the terms without dense
 // factors).  NV >= 0: with the partial sums of <v_i|y> for i < NV and <q|y> (q the
-// product's input); NV < 0: none.  Streams ny + 3 + NV vectors.  The sum is formed in
-// FP64 and rounded once.
-template <class R, int NV>
+// product's input); NV < 0: none.  Streams ny + 3 + NV vectors.  With terms without dense
+// factors (WIDE) the sum is formed in FP64 and rounded once; for the factors' vectors alone
+// that would cost 2-3% of an FP32 step (684 us and 702 on 1M functions in 4D) and spare
+// a rounding each.
+template <class R, int NV, bool WIDE>
 __global__ __launch_bounds__(TB, 2) void k_combine(BatchSum<R> ts, GridDesc g, const uint32_t *__restrict__ keys, int64_t n,
                                                    const typename Cplx<R>::T *x, const R *V, typename Cplx<R>::T *y,
                                                    const typename Cplx<R>::T *Vb, int64_t ld, double2 *partial,
@@ -276,28 +282,44 @@ __global__ __launch_bounds__(TB, 2) void k_combine(BatchSum<R> ts, GridDesc g, c
             if (i < ts.ny) v[i] = ts.y[i][p];
         const C xv = x[p];
         const double2 xd = make_double2((double)xv.x, (double)xv.y);
-        double2 s = make_double2((double)v[0].x, (double)v[0].y);
+        C s = v[0];
+        if constexpr (!WIDE) {
 #pragma unroll
-        for (int i = 1; i < BATCH_SUMS; ++i) {
-            if (i < ts.ny) {
-                s.x += v[i].x;
-                s.y += v[i].y;
+            for (int i = 1; i < BATCH_SUMS; ++i) {
+                if (i < ts.ny) {
+                    s.x += v[i].x;
+                    s.y += v[i].y;
+                }
             }
+            if (V) {
+                const R pot = V[p];
+                s.x = fma(pot, xv.x, s.x);
+                s.y = fma(pot, xv.y, s.y);
+            }
+        } else {
+            double2 t = make_double2((double)s.x, (double)s.y);
+#pragma unroll
+            for (int i = 1; i < BATCH_SUMS; ++i) {
+                if (i < ts.ny) {
+                    t.x += v[i].x;
+                    t.y += v[i].y;
+                }
+            }
+            if (V) {
+                const double pot = V[p];
+                t.x = fma(pot, xd.x, t.x);
+                t.y = fma(pot, xd.y, t.y);
+            }
+            for (int i = 0; i < ts.ndiag; ++i) {
+                const double w = ts.use[i] ? diag_value(g, (gbyte *)(const char *)ts.diag[i], ts.nmax, ts.use[i], key) : 1.0;
+                t.x += (ts.c[i].x * xd.x - ts.c[i].y * xd.y) * w;
+                t.y += (ts.c[i].x * xd.y + ts.c[i].y * xd.x) * w;
+            }
+            s = Cplx<R>::make(t.x, t.y);
         }
-        if (V) {
-            const double pot = V[p];
-            s.x = fma(pot, xd.x, s.x);
-            s.y = fma(pot, xd.y, s.y);
-        }
-        for (int i = 0; i < ts.ndiag; ++i) {
-            const double w = ts.use[i] ? diag_value(g, (gbyte *)(const char *)ts.diag[i], ts.nmax, ts.use[i], key) : 1.0;
-            s.x += (ts.c[i].x * xd.x - ts.c[i].y * xd.y) * w;
-            s.y += (ts.c[i].x * xd.y + ts.c[i].y * xd.x) * w;
-        }
-        const C r = Cplx<R>::make(s.x, s.y);
-        y[p] = r;
+        y[p] = s;
         if constexpr (NV >= 0) {
-            const double2 sd = make_double2((double)r.x, (double)r.y);  // as stored
+            const double2 sd = make_double2((double)s.x, (double)s.y);
 #pragma unroll
             for (int i = 0; i < NV; ++i) cdot_acc(acc[i], ld2(Vb, (int64_t)i * ld + p), sd);
             cdot_acc(acc[NA - 1], xd, sd);
@@ -354,9 +376,14 @@ int batch_combine(const BatchSum<R> &ts, const GridDesc &g, const uint32_t *keys
 {
     if (n <= 0) return 0;
     const int nb = kry_blocks(n);
-#define CALL(NV)                                                                                                      \
-    hipLaunchKernelGGL((k_combine<R, NV>), dim3(nb), dim3(TB), 0, s, ts, g, keys, n, x, V, y, Vb, ld, partial, skip_if, \
-                       skip_j)
+    const bool wide = ts.ndiag > 0;
+#define CALL(NV)                                                                                                       \
+    if (wide)                                                                                                          \
+        hipLaunchKernelGGL((k_combine<R, NV, true>), dim3(nb), dim3(TB), 0, s, ts, g, keys, n, x, V, y, Vb, ld, partial, \
+                           skip_if, skip_j);                                                                           \
+    else                                                                                                               \
+        hipLaunchKernelGGL((k_combine<R, NV, false>), dim3(nb), dim3(TB), 0, s, ts, g, keys, n, x, V, y, Vb, ld, partial, \
+                           skip_if, skip_j)
     switch (dots) {
     case 0: CALL(-1); break;
     case 1: CALL(0); break;
