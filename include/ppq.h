@@ -59,10 +59,10 @@
  *               factor depth, and no fiber tables are built.
  *   PPQ_BATCH=0 / 2  products of the default layout on fiber tables a pass per
  *               factor always / batched wherever they apply (dimensions of at
- *               most 64 points); 1 (default) batches sets of up to 3.1 million
- *               functions, 1.6 million with real factors in double
- *               precision.  Batched, all factors of one depth share a launch on
- *               the matrix cores and their results are added up at the end.
+ *               most 64 points); 1 (default) chooses by the set's size, its
+ *               fibers and the operator's factors (up to one to four million
+ *               functions).  Batched, all factors of one depth share a launch
+ *               on the matrix cores and their results are added up at the end.
  *   PPQ_DILATE=1 / 2  adaption's dilation per function (atomics) / word by
  *               word from the bitmap of the functions kept (the +-1 stencil
  *               on DVR axes only); 0 (default) chooses by the grid-to-set
@@ -241,7 +241,9 @@ int ppq_clear_potential(ppq_ctx *ctx);
 /* Capacity of the active set (number of functions).  Grows automatically when
    adaption needs more, doubling each time (never past the grid size); each
    growth reallocates every per-point buffer, so reserving ahead avoids
-   reallocation inside a run.  A growth that fails (PPQ_E_OOM, from whichever
+   reallocation inside a run.  (The vectors of the products' grid and batched
+   forms, at most 1 and 2 GiB, are allocated when a set first takes the form and
+   kept until the capacity or the operator changes.)  A growth that fails (PPQ_E_OOM, from whichever
    call needed it) keeps the state, and the call may be made again.
    PPQ_E_ARG unless 1 <= max_active <= the grid size; PPQ_E_STATE without a grid. */
 int ppq_reserve(ppq_ctx *ctx, int64_t max_active);

@@ -1237,11 +1237,6 @@ PlanePass plane_pass_of(const ppq_ctx *c, int i)
 // ---- products on grid vectors -------------------------------------------------
 constexpr int64_t GRID_TOTAL_MAX = int64_t(1) << 23;  // largest grid (functions)
 constexpr int64_t GRID_BYTES_MAX = int64_t(1) << 30;  // all grid vectors of a context
-// digits summed in one product (see use_grid): dimensions longer than a mask word, a DVR
-// operator, one with product terms, lattices
-constexpr int64_t GRID_LONG_MAX = int64_t(1) << 24, GRID_WORK_MAX = 14'000'000, GRID_TERMS_MAX = int64_t(1) << 26,
-                  GRID_LATTICE_MAX = int64_t(1) << 22;
-
 // Factors of one product with their depth: those that act on the product's
 // input are at depth 0, those on the results of depth d at d + 1.
 struct GridFactor {
@@ -1349,16 +1344,32 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
 
 // Whether the current set's products run on grid vectors: the default layout,
 // a grid whose vectors fit, and few enough digits in a product (a complex
-// factor's once for itself and once per input; general terms are chains of
-// factors, where the launches saved count for more).  Above, the batched passes on
-// fiber tables read only members and use the matrix cores, once the tables are
-// built (about 60 us of small launches).  Measured, us a step of order 10 from a new
-// state, grid vectors / batched (FP64; FP32): 4D Morse 32^4, 52K functions (6.7M
-// digits) 276 / 293; 245 / 291, 114K (14.6M) 396 / 360; 336 / 333, 209K (26.7M) 597 /
-// 427; the 3D anharmonic 48^3, 44K (6.3M) 236 / 313, 96K (13.9M) 328 / 357; the 4D
-// lattice, 2.3K (1.8M) 485 / 437; 411 / 427, 10K (7.7M) 509 / 460; 441 / 451, 36K (28M)
-// 1025 / 583; a 2D Weylet lattice, 1.0K (0.2M) 273 / 515; general 3D terms, 13K (9M)
-// 369 / 645, 96K (69M) 959 / 942.  Dimensions of more than 64 points are not batched.
+// factor's once for itself and once per input).  Above, the batched passes on fiber
+// tables read only members and use the matrix cores, once the tables are built
+// (60-100 us of small launches), and the more so the wider the grid: its entries
+// share fewer lines and caches.  Measured, us a step of order 10 from a new state,
+// grid vectors / batched (FP64; FP32), and the crossing:
+//   real, 64^3 10M digits 295 / 337, 14M 378 / 372; 14M 307 / 357, 20M 355 / 350
+//   real, 32^4 4M 233 / 269, 7M 269 / 266, 14M 410 / 330; 7M 240 / 290, 10M 303 / 282
+//   real, 48^4 4M 259 / 257, 10M 342 / 293; 10M 275 / 286, 14M 341 / 298
+//   lattice 24^4 4M 338 / 378, 8M 409 / 405; 8M 347 / 379, 16M 439 / 439
+//   lattice 48^4 1.2M 394 / 353; 4M 371 / 390, 10M 394 / 400, 16M 495 / 361
+//   terms in 3D, 48^3 16M 536 / 578, 41M 769 / 671; 16M 501 / 556, 41M 703 / 574
+//   terms in 4D, 32^4 17M 469 / 451; 17M 436 / 461, 46M 736 / 526
+// Dimensions of more than 64 points are not batched: grid vectors against passes,
+// 90x40x40x20 19M 651 / 942, 57M 1426 / 1376; 57M 921 / 1256; 100x100x60 104M 2205 / 2372;
+// 1579 / 1792; 256^2 31M 543 / 1292; terms on 70x66x80, 245M 3155 / 3224; 2720 / 2884.
+int64_t grid_limit(const ppq_ctx *c, bool general)
+{
+    const bool f64 = c->precision == PPQ_FP64;
+    const double near = double(1 << 20) / (double)c->g.total;
+    if (any_long(c)) return general ? 250'000'000 : f64 ? 60'000'000 : 120'000'000;
+    if (c->any_lattice) return (int64_t)(f64 ? 3.5e6 * near : std::max(5e6 * near, 6e6));
+    if (general) return (int64_t)(f64 ? std::min(14e6 * std::sqrt(near), 28e6) : std::min(20e6 * std::sqrt(near), 36e6));
+    return (int64_t)(f64 ? std::min(std::max(8e6 * std::sqrt(near), 4e6), 14e6)
+                         : std::min(std::max(11e6 * std::sqrt(near), 9e6), 18e6));
+}
+
 bool use_grid(const ppq_ctx *c)
 {
     if (c->hpsi_variant != 2 || c->grid_switch == 0 || c->nact <= 0 || (int64_t)c->g.total > GRID_TOTAL_MAX) return false;
@@ -1367,11 +1378,12 @@ bool use_grid(const ppq_ctx *c)
     const int64_t es = c->precision == PPQ_FP64 ? sizeof(double2) : sizeof(float2);
     if ((int64_t)c->g.total * es * (nz + 1) > GRID_BYTES_MAX) return false;
     int64_t digits = 0;
-    for (const GridFactor &f : fs)
+    bool general = false;
+    for (const GridFactor &f : fs) {
         digits += f.kind == GRID_DIAG ? 1 : (int64_t)c->g.n[f.k] * (f.kind == GRID_CPLX ? 1 + f.nin : 1);
-    const int64_t limit = any_long(c) ? (!c->any_lattice && nz > 0 ? GRID_TERMS_MAX : GRID_LONG_MAX)
-                          : c->any_lattice ? GRID_LATTICE_MAX : nz > 0 ? GRID_TERMS_MAX : GRID_WORK_MAX;
-    return c->grid_switch == 2 || c->nact * digits <= limit;
+        general = general || f.kind == GRID_CPLX;
+    }
+    return c->grid_switch == 2 || c->nact * digits <= grid_limit(c, general);
 }
 
 // The stages of the product (one launch each): factors of one depth, up to
@@ -2153,27 +2165,60 @@ bool ensure_batch(ppq_ctx *c, int64_t limit)
 // Whether the current set's products (on fiber tables) are batched: the default
 // layout, dimensions within a mask word, and a set that leaves a pass by itself
 // short of wavefronts.  Large sets fill the chip pass by pass, and there the vectors
-// of the factors cost more traffic than the passes' own sums; complex factors are
-// bound by the contraction longer, which the batched form does over the digits
-// present only.  Measured, us a product pass by pass / batched (FP64; FP32): 6D
-// quartic 5.6K functions 33 / 15; 32 / 15, 164K 52 / 22; 47 / 21, 730K 81 / 65; 73 /
-// 43, 1.93M 155 / 155; 119 / 91, 3.97M 290 / 332; 193 / 213; 4D Morse 74K 54 / 16;
-// 46 / 16, 1.05M 58 / 50; 44 / 38; the 4D lattice 78K 123 / 54; 104 / 38, 563K 317 /
-// 177; 177 / 118, 1.14M 368 / 263; 271 / 177, 3.9M 855 / 676; 477 / 476.
-constexpr int64_t BATCH_MAX_REAL64 = int64_t(3) << 19, BATCH_MAX = int64_t(3) << 20;
+// of the factors cost more traffic than the passes' own sums, the sooner the more
+// dimensions write one and the shorter the fibers in their tiles of 16 digits.
+// Complex factors are bound by the contraction longer, which the batched form does
+// over the digits present only, with two wavefronts per SIMD above 48 points; a
+// pass stages less of the permutation, and waits less, below 24.
+// The limit is on functions times dimensions.  Measured, us a step of order 10, pass
+// by pass / batched (FP64; FP32):
+//   6D, 24^6 0.66M 974 / 705; 830 / 574, 1.13M 1229 / 1051; 1024 / 827, 1.33M 1338 / 1231;
+//     1074 / 895, 1.49M 1443 / 1480; 1118 / 996, 2.05M 1807 / 2111; 1307 / 1272, 2.34M 2027 /
+//     2426; 1390 / 1452
+//   6D, 12^6 0.8M 935 / 893; 814 / 629, 1.2M 1180 / 1238; 918 / 789, 2.2M 1752 / 2347; 1260 / 1231
+//   8D, 6^8 0.6M 925 / 866; 795 / 764, 0.8M 1016 / 1072; 882 / 891, 1.2M 1317 / 1595; 1027 / 1164
+//   4D, 48^4 1M 1072 / 888; 760 / 692, 2M 1684 / 1541; 1200 / 1083, 3M 2333 / 2430; 1569 / 1526
+//   4D, 64^4 2M 1805 / 1718; 1173 / 1124, 2.5M 2192 / 2357; 1447 / 1414, 3M 2526 / 2831; 1613 / 1616
+//   4D lattice, 48^4 0.6M 2133 / 1681; 1674 / 1113, 1.8M 4483 / 4389; 3156 / 2442, 3M 7144 / 7242;
+//     4394 / 3692
+//   4D lattice, 64^4 1M 3199 / 2970; 2095 / 1904, 1.5M 4112 / 4303; 2827 / 2661, 3M 8044 / 9647;
+//     4871 / 5202
+//   terms in 4D, 48^4 1.5M 4163 / 3873; 2809 / 2635, 2M 4910 / 5148; 3538 / 3212, 3M 7416 / 7633;
+//     4548 / 4819; 64^4 1.5M 4168 / 4865; 2816 / 2914
+// `fiber`: the mean fiber's functions, or 0 for the largest limit of any.
+int64_t batch_limit(const ppq_ctx *c, double fiber)
+{
+    const bool f64 = c->precision == PPQ_FP64;
+    int n = 0;
+    for (int k = 0; k < c->g.D; ++k) n = std::max(n, c->g.n[k]);
+    double limit;
+    if (c->any_lattice || !c->pairs.empty() || !c->chains.empty()) {
+        if (f64) limit = n <= 48 ? 7.5e6 : 5e6;
+        else if (c->any_lattice) limit = n <= 48 ? 16e6 : 9e6;
+        else limit = n <= 48 ? 10.5e6 : 5e6;
+    } else if (f64) {
+        limit = fiber == 0.0 || fiber > 16.0 ? 9.5e6 : n > 16 ? 8e6 : 6.5e6;
+    } else {
+        limit = n > 8 ? 12e6 : 6.5e6;
+    }
+    return (int64_t)(limit / c->g.D);
+}
+
 bool use_batch(ppq_ctx *c)
 {
     if (c->hpsi_variant != 2 || c->batch_switch == 0 || c->batch_denied || c->nact <= 0 || any_long(c)) return false;
-    const bool complex_factors = c->any_lattice || !c->pairs.empty() || !c->chains.empty();
-    const int64_t limit = c->precision == PPQ_FP64 && !complex_factors ? BATCH_MAX_REAL64 : BATCH_MAX;
-    if (c->batch_switch == 1 && c->nact > limit) return false;
-    if (!c->batch_planned && !ensure_batch(c, limit)) {
+    const int64_t most = batch_limit(c, 0.0);
+    if (c->batch_switch == 1 && c->nact > most) return false;
+    if (!c->batch_planned && !ensure_batch(c, most)) {
         c->batch_denied = true;
         return false;
     }
     if (c->nact > c->ybuf_cap) return false;
     ensure_nf(c);
-    return true;
+    if (c->batch_switch == 2) return true;
+    int64_t fibers = 0;
+    for (int k = 0; k < c->g.D; ++k) fibers += c->nf[k];
+    return c->nact <= batch_limit(c, (double)c->nact * c->g.D / (double)fibers);
 }
 
 template <class R>
