@@ -1350,7 +1350,8 @@ std::vector<GridFactor> grid_factors(const ppq_ctx *c, int *nz)
 // share fewer lines and caches.  Measured, us a step of order 10 from a new state,
 // grid vectors / batched (FP64; FP32), and the crossing:
 //   real, 64^3 10M digits 295 / 337, 14M 378 / 372; 14M 307 / 357, 20M 355 / 350
-//   real, 32^4 4M 233 / 269, 7M 269 / 266, 14M 410 / 330; 7M 240 / 290, 10M 303 / 282
+//   real, 32^4 4M 233 / 269, 7M 269 / 266, 14M 410 / 330; 7M 240 / 290, 14M 350 / 328; 31^4 13M
+//     (FP32) 321 / 328
 //   real, 48^4 4M 259 / 257, 10M 342 / 293; 10M 275 / 286, 14M 341 / 298
 //   lattice 24^4 4M 338 / 378, 8M 409 / 405; 8M 347 / 379, 16M 439 / 439
 //   lattice 48^4 1.2M 394 / 353; 4M 371 / 390, 10M 394 / 400, 16M 495 / 361
@@ -1367,7 +1368,7 @@ int64_t grid_limit(const ppq_ctx *c, bool general)
     if (c->any_lattice) return (int64_t)(f64 ? 3.5e6 * near : std::max(5e6 * near, 6e6));
     if (general) return (int64_t)(f64 ? std::min(14e6 * std::sqrt(near), 28e6) : std::min(20e6 * std::sqrt(near), 36e6));
     return (int64_t)(f64 ? std::min(std::max(8e6 * std::sqrt(near), 4e6), 14e6)
-                         : std::min(std::max(11e6 * std::sqrt(near), 9e6), 18e6));
+                         : std::min(std::max(14e6 * std::sqrt(near), 9e6), 18e6));
 }
 
 bool use_grid(const ppq_ctx *c)
@@ -2170,7 +2171,9 @@ bool ensure_batch(ppq_ctx *c, int64_t limit)
 // Complex factors are bound by the contraction longer, which the batched form does
 // over the digits present only, with two wavefronts per SIMD above 48 points; a
 // pass stages less of the permutation, and waits less, below 24.
-// The limit is on functions times dimensions.  Measured, us a step of order 10, pass
+// In FP64 the limit is on functions times dimensions.  In FP32 sets stay batched past
+// the crossing: their results are nearer to FP64 (rms, passes / batched: 6D, 24^6 2.6M
+// 5.3e-8 / 5.1e-8; 8D, 6^8 1.2M 6.2e-8 / 3.7e-8; 4D lattice, 64^4 2.5M 1.15e-7 / 1.07e-7).  Measured, us a step of order 10, pass
 // by pass / batched (FP64; FP32):
 //   6D, 24^6 0.66M 974 / 705; 830 / 574, 1.13M 1229 / 1051; 1024 / 827, 1.33M 1338 / 1231;
 //     1074 / 895, 1.49M 1443 / 1480; 1118 / 996, 2.05M 1807 / 2111; 1307 / 1272, 2.34M 2027 /
@@ -2188,19 +2191,12 @@ bool ensure_batch(ppq_ctx *c, int64_t limit)
 // `fiber`: the mean fiber's functions, or 0 for the largest limit of any.
 int64_t batch_limit(const ppq_ctx *c, double fiber)
 {
-    const bool f64 = c->precision == PPQ_FP64;
     int n = 0;
     for (int k = 0; k < c->g.D; ++k) n = std::max(n, c->g.n[k]);
+    if (c->precision == PPQ_FP32) return c->any_lattice && n <= 48 ? int64_t(1) << 22 : int64_t(3) << 20;
     double limit;
-    if (c->any_lattice || !c->pairs.empty() || !c->chains.empty()) {
-        if (f64) limit = n <= 48 ? 7.5e6 : 5e6;
-        else if (c->any_lattice) limit = n <= 48 ? 16e6 : 9e6;
-        else limit = n <= 48 ? 10.5e6 : 5e6;
-    } else if (f64) {
-        limit = fiber == 0.0 || fiber > 16.0 ? 9.5e6 : n > 16 ? 8e6 : 6.5e6;
-    } else {
-        limit = n > 8 ? 12e6 : 6.5e6;
-    }
+    if (c->any_lattice || !c->pairs.empty() || !c->chains.empty()) limit = n <= 48 ? 7.5e6 : 5e6;
+    else limit = fiber == 0.0 || fiber > 16.0 ? 9.5e6 : n > 16 ? 8e6 : 6.5e6;
     return (int64_t)(limit / c->g.D);
 }
 

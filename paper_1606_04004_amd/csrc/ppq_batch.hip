@@ -28,8 +28,9 @@ namespace {
 // of the union, without the look ahead and with 1024 workgroups at any register count),
 // 4D Morse at 74K 16 us (54), 6D quartic at 730K 65 us (81).
 constexpr int BAB = 256;
-// wavefronts per SIMD that the registers of a window allow (workgroups per CU)
-constexpr int batch_waves(bool f64, bool general, int ntm)
+// wavefronts per SIMD that the registers of a window allow (workgroups per CU;
+// complex factors of three tiles spill a few)
+constexpr int batch_waves(bool f64, int ntm)
 {
     if (!f64) return ntm <= 2 ? 5 : ntm == 3 ? 4 : 3;
     return ntm <= 2 ? 4 : ntm == 3 ? 3 : 2;
@@ -176,7 +177,7 @@ __device__ inline void batch_fibers(const BatchOp<R> *op, const GridDesc &g, int
 // The launch's description is the kernel's first argument: read from the argument
 // segment itself, whose fields are wave-uniform.
 template <class R, bool GENERAL, int NTM>
-__global__ __launch_bounds__(BAB, batch_waves(sizeof(R) == 8, GENERAL, NTM)) void k_batch(BatchStage<R> stage, GridDesc g, const uint32_t *__restrict__ keys,
+__global__ __launch_bounds__(BAB, batch_waves(sizeof(R) == 8, NTM)) void k_batch(BatchStage<R> stage, GridDesc g, const uint32_t *__restrict__ keys,
                                                                  const int *skip_if, int skip_j)
 {
     using V = typename Cplx<R>::V;
@@ -346,7 +347,7 @@ void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, co
     }
     const int np = (nmax + 15) & ~15;
     const size_t lds = (size_t)np * np * (general ? 2 : 1) * sizeof(R);
-    const int per_cu = std::min<int>(batch_waves(sizeof(R) == 8, general, std::max(np / 16, 2)), (int)(LDS_BYTES / (lds + BAB)));
+    const int per_cu = std::min<int>(batch_waves(sizeof(R) == 8, std::max(np / 16, 2)), (int)(LDS_BYTES / (lds + BAB)));
     const double resident = (double)BATCH_CUS * std::max(per_cu, 1);
     st.first[0] = 0;
     for (int o = 0; o < st.nop; ++o) {

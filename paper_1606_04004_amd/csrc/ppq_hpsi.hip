@@ -218,6 +218,14 @@ __device__ __forceinline__ double2 body_real_acc(uint32_t o, uint64_t m, int ws,
     return dot;
 }
 
+// wavefronts per SIMD of k_hpsi_acc (see there)
+constexpr int acc_waves(bool f64, int nmax, bool dot, bool stage)
+{
+    if (!stage || nmax > 24) return 1;
+    if (f64) return dot ? 3 : 4;
+    return dot ? 5 : 6;
+}
+
 // DOT: every block also stores its share of <x|y> (the y this pass leaves)
 // in dotp[blockIdx.x], summed over the block in a fixed order.
 // STAGE: a wavefront's 64 consecutive fibers cover one contiguous range of
@@ -226,14 +234,16 @@ __device__ __forceinline__ double2 body_real_acc(uint32_t o, uint64_t m, int ws,
 // lane's lookups otherwise touch a cache line of their own for every window
 // digit, and the passes are bound by the lines a CU can look up: 28 us a pass
 // over 4M functions in FP32 where the vectors take 20).  The positions are read
-// again where they are needed, and y is held for four rows at a time, so four
-// wavefronts fit a SIMD in FP64 and six (all that LDS holds) in FP32, where both
-// windows in registers left two and three.  Six-dimensional quartic product on 3.97M
+// again where they are needed, and y is held for four rows at a time, so up to
+// 24 points four wavefronts fit a SIMD in FP64 and six (all that LDS holds) in
+// FP32, with the fused dot three (four would spill) and five; both windows in
+// registers left two and three.  Longer dimensions are left to the compiler:
+// their staged ranges fill LDS first.  Six-dimensional quartic product on 3.97M
 // functions: FP64 290 us with scattered lookups, 268 staged; on another card 237
 // staged, 215 with eight rows, 208 with four and a bucket of 20 digits; FP32 193 and
 // 167; 159, 153 and 137.  A copy loop that waits for each load was slower than none.
 template <class R, int NMAX, bool IDENT, bool DOT, bool STAGE = false>
-__global__ __launch_bounds__(HB, !STAGE || NMAX > 24 ? 1 : sizeof(R) == 4 ? (DOT ? 5 : 6) : DOT ? 3 : 4) void k_hpsi_acc(const uint32_t *__restrict__ pi, const uint32_t *__restrict__ off,
+__global__ __launch_bounds__(HB, acc_waves(sizeof(R) == 8, NMAX, DOT, STAGE)) void k_hpsi_acc(const uint32_t *__restrict__ pi, const uint32_t *__restrict__ off,
                                                  const uint64_t *__restrict__ mask, int64_t nf,
                                                  const R *__restrict__ T, const typename Cx<R>::T *__restrict__ x,
                                                  typename Cx<R>::T *__restrict__ y, const int *skip_if, int skip_j,
