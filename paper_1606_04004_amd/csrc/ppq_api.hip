@@ -2173,8 +2173,8 @@ bool ensure_batch(ppq_ctx *c, int64_t limit)
 // pass stages less of the permutation, and waits less, below 24.
 // In FP64 the limit is on functions times dimensions.  In FP32 sets stay batched past
 // the crossing: their results are nearer to FP64 (rms, passes / batched: 6D, 24^6 2.6M
-// 5.3e-8 / 5.1e-8; 8D, 6^8 1.2M 6.2e-8 / 3.7e-8; 4D lattice, 64^4 2.5M 1.15e-7 / 1.07e-7).  Measured, us a step of order 10, pass
-// by pass / batched (FP64; FP32):
+// 5.3e-8 / 5.1e-8; 8D, 6^8 1.2M 6.2e-8 / 3.7e-8; 4D lattice, 64^4 2.5M 1.15e-7 /
+// 1.07e-7).  Measured, us a step of order 10, pass by pass / batched (FP64; FP32):
 //   6D, 24^6 0.66M 974 / 705; 830 / 574, 1.13M 1229 / 1051; 1024 / 827, 1.33M 1338 / 1231;
 //     1074 / 895, 1.49M 1443 / 1480; 1118 / 996, 2.05M 1807 / 2111; 1307 / 1272, 2.34M 2027 /
 //     2426; 1390 / 1452

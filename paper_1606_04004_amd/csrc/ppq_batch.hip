@@ -24,7 +24,7 @@ namespace {
 // Here the chip holds as many workgroups as fit, each wavefront has the next group's
 // masks on their way while it contracts the current one, and what bounds a launch is
 // the gathers' latency and, with complex factors, the matrix cores.  Measured (FP64):
-// a product of the 4D lattice at 563K functions 177 us (317 in passes; 207 over windows
+// a product of the 4D lattice at 563K functions 169 us (281-319 in passes; 207 over windows
 // of the union, without the look ahead and with 1024 workgroups at any register count),
 // 4D Morse at 74K 16 us (54), 6D quartic at 730K 65 us (81).
 constexpr int BAB = 256;
