@@ -2237,19 +2237,22 @@ bool ensure_batch(ppq_ctx *c, int64_t limit)
 // the crossing: their results are nearer to FP64 (rms, passes / batched: 6D, 24^6 2.6M
 // 5.3e-8 / 5.1e-8; 8D, 6^8 1.2M 6.2e-8 / 3.7e-8; 4D lattice, 64^4 2.5M 1.15e-7 /
 // 1.07e-7).  Measured, us a step of order 10, pass by pass / batched (FP64; FP32):
-//   6D, 24^6 0.66M 974 / 705; 830 / 574, 1.13M 1229 / 1051; 1024 / 827, 1.33M 1338 / 1231;
-//     1074 / 895, 1.49M 1443 / 1480; 1118 / 996, 2.05M 1807 / 2111; 1307 / 1272, 2.34M 2027 /
-//     2426; 1390 / 1452
-//   6D, 12^6 0.8M 935 / 893; 814 / 629, 1.2M 1180 / 1238; 918 / 789, 2.2M 1752 / 2347; 1260 / 1231
-//   8D, 6^8 0.6M 925 / 866; 795 / 764, 0.8M 1016 / 1072; 882 / 891, 1.2M 1317 / 1595; 1027 / 1164
-//   4D, 48^4 1M 1072 / 888; 760 / 692, 2M 1684 / 1541; 1200 / 1083, 3M 2333 / 2430; 1569 / 1526
-//   4D, 64^4 2M 1805 / 1718; 1173 / 1124, 2.5M 2192 / 2357; 1447 / 1414, 3M 2526 / 2831; 1613 / 1616
-//   4D lattice, 48^4 0.6M 2133 / 1681; 1674 / 1113, 1.8M 4483 / 4389; 3156 / 2442, 3M 7144 / 7242;
-//     4394 / 3692
-//   4D lattice, 64^4 1M 3199 / 2970; 2095 / 1904, 1.5M 4112 / 4303; 2827 / 2661, 3M 8044 / 9647;
-//     4871 / 5202
-//   terms in 4D, 48^4 1.5M 4163 / 3873; 2809 / 2635, 2M 4910 / 5148; 3538 / 3212, 3M 7416 / 7633;
-//     4548 / 4819; 64^4 1.5M 4168 / 4865; 2816 / 2914
+//   6D, 24^6 1.33M 1346 / 1235; 1083 / 931, 1.72M 1616 / 1749; 1196 / 1088, 2.05M 1816 / 2104;
+//     1313 / 1247, 2.34M 2038 / 2430; 1409 / 1398, 2.89M 2425 / 3099; 1622 / 1836
+//   6D, 12^6 0.8M 927 / 787; 811 / 627, 1.2M 1195 / 1073; 922 / 812, 2.2M 1761 / 2090; 1241 / 1231
+//   8D, 6^8 0.6M 929 / 872; 805 / 768, 0.8M 1021 / 1070; 887 / 942, 1.2M 1320 / 1619; 1028 / 1169
+//   5D, 20^5 1.5M 1356 / 1250; 1027 / 945, 2M 1584 / 1703; 1148 / 1129
+//   4D, 48^4 1M 1076 / 896; 766 / 691, 2M 1690 / 1519; 1193 / 1075, 3M 2322 / 2464; 1573 / 1473
+//   4D, 64^4 2M 1804 / 1716; 1176 / 1114, 2.5M 2183 / 2347; 1436 / 1372, 3M 2523 / 2874; 1618 / 1601
+//   6D, 64^4 x 3^2 0.76M 1255 / 1121; 1221 / 882, 1.4M 1828 / 1864; 1306 / 1458, 2.8M 3285 / 3988;
+//     2134 / 2792
+//   6D, 48^4 x 6^2 1.46M 1555 / 1432; 1345 / 1079, 3M 3132 / 3639; 2252 / 2485
+//   4D lattice, 48^4 0.6M 2124 / 1522; 1681 / 1113, 1.8M 4490 / 3893; 3147 / 2484, 3M 7142 / 6272;
+//     4388 / 3744
+//   4D lattice, 64^4 1M 3187 / 2632; 2076 / 1872, 1.5M 4115 / 3775; 2841 / 2519, 2.2M 6340 /
+//     5875; 3928 / 3573, 3M 8110 / 8785; 4877 / 4921
+//   terms in 4D, 48^4 1.5M 4171 / 3890; 2807 / 2599, 2M 4903 / 5076; 3533 / 3238, 3M 7364 / 7498;
+//     4534 / 4822; 64^4 1M 3193 / 3176; 2151 / 2249, 1.5M 4180 / 4469; 2823 / 3081
 // `fiber`: the mean fiber's functions, or 0 for the largest limit of any.
 int64_t batch_limit(const ppq_ctx *c, double fiber)
 {
@@ -2257,7 +2260,8 @@ int64_t batch_limit(const ppq_ctx *c, double fiber)
     for (int k = 0; k < c->g.D; ++k) n = std::max(n, c->g.n[k]);
     if (c->precision == PPQ_FP32) return c->any_lattice && n <= 48 ? int64_t(1) << 22 : int64_t(3) << 20;
     double limit;
-    if (c->any_lattice || !c->pairs.empty() || !c->chains.empty()) limit = n <= 48 ? 7.5e6 : 5e6;
+    if (c->any_lattice) limit = n <= 48 ? 12e6 : 9e6;
+    else if (!c->pairs.empty() || !c->chains.empty()) limit = n <= 48 ? 7.5e6 : 5e6;
     else limit = fiber == 0.0 || fiber > 16.0 ? 9.5e6 : n > 16 ? 8e6 : 6.5e6;
     return (int64_t)(limit / c->g.D);
 }
@@ -2298,7 +2302,7 @@ void apply_batch_t(ppq_ctx *c, const std::vector<BatchStage<R>> &stages, const B
             for (int q = 0; q < op.nin; ++q)
                 if (!op.x[q]) op.x[q] = (const C *)xv;
         }
-        batch_launch<R>(st, c->g, keys, skip_if, skip_j, c->stream);
+        batch_launch<R>(st, c->g, keys, c->nact, skip_if, skip_j, c->stream);
     }
     const R *V = nullptr;
     if (!c->any_lattice) V = c->precision == PPQ_FP64 ? (const R *)c->V64 : (const R *)c->V32;

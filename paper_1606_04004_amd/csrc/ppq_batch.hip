@@ -24,9 +24,9 @@ namespace {
 // Here the chip holds as many workgroups as fit, each wavefront has the next group's
 // masks on their way while it contracts the current one, and what bounds a launch is
 // the gathers' latency and, with complex factors, the matrix cores.  Measured (FP64):
-// a product of the 4D lattice at 563K functions 169 us (281-319 in passes; 207 over windows
+// a product of the 4D lattice at 563K functions 158 us (281-319 in passes; 207 over windows
 // of the union, without the look ahead and with 1024 workgroups at any register count),
-// 4D Morse at 74K 16 us (54), 6D quartic at 730K 65 us (81).
+// 4D at 74K 15 us (61), 6D quartic at 781K 57 us (81).
 constexpr int BAB = 256;
 // wavefronts per SIMD that the registers of a window allow (workgroups per CU;
 // complex factors of three tiles spill a few)
@@ -332,18 +332,24 @@ __global__ __launch_bounds__(TB, 2) void k_combine(BatchSum<R> ts, GridDesc g, c
 }  // namespace
 
 template <class R>
-void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, const int *skip_if, int skip_j, hipStream_t s)
+void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, int64_t n, const int *skip_if, int skip_j,
+                  hipStream_t s)
 {
     if (st.nop <= 0) return;
-    // as many workgroups as are resident at once, shared out by the factors' fibers
-    // (at least one group of 16 per wavefront)
+    // as many workgroups as are resident at once (no more: the one too many would start
+    // when the others end), at least one group of 16 fibers per wavefront, shared out by
+    // what the factors take.  A fiber takes its own time and its digits': by fibers alone
+    // a short dimension, which has many, kept the long ones short of workgroups (a product
+    // in FP64, us: 64^4 x 3^2 756K 131, now 91; 64^2 x 8^3 793K 128, 70; shares rounded up
+    // past the chip: 12^6 1.2M 95, 77, a 48^4 lattice 1.8M 374, 324)
+    auto weight = [&](const BatchOp<R> &op) { return (6.0 * op.nf + (double)n) * (1 + op.nin); };
     int nmax = 0;
     bool general = false;
     double work = 0.0;
     for (int o = 0; o < st.nop; ++o) {
         nmax = std::max(nmax, st.op[o].n);
         general = general || st.op[o].kind != GRID_REAL;
-        work += (double)st.op[o].nf * (1 + st.op[o].nin);
+        work += weight(st.op[o]);
     }
     const int np = (nmax + 15) & ~15;
     const size_t lds = (size_t)np * np * (general ? 2 : 1) * sizeof(R);
@@ -352,7 +358,7 @@ void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, co
     st.first[0] = 0;
     for (int o = 0; o < st.nop; ++o) {
         const int64_t most = (st.op[o].nf + BAB / 4 - 1) / (BAB / 4);
-        int64_t b = (int64_t)(resident * ((double)st.op[o].nf * (1 + st.op[o].nin) / std::max(work, 1.0)) + 0.5);
+        int64_t b = (int64_t)(resident * (weight(st.op[o]) / std::max(work, 1.0)));
         b = std::max<int64_t>(1, std::min(b, most));
         st.first[o + 1] = st.first[o] + (int)b;
     }
@@ -409,7 +415,8 @@ int batch_combine(const BatchSum<R> &ts, const GridDesc &g, const uint32_t *keys
 }
 
 #define PPQ_INST(R)                                                                                                   \
-    template void batch_launch<R>(BatchStage<R> &, const GridDesc &, const uint32_t *, const int *, int, hipStream_t); \
+    template void batch_launch<R>(BatchStage<R> &, const GridDesc &, const uint32_t *, int64_t, const int *, int,     \
+                                  hipStream_t);                                                                       \
     template int batch_combine<R>(const BatchSum<R> &, const GridDesc &, const uint32_t *, int64_t,                   \
                                   const typename GridOp<R>::C *, const R *, typename GridOp<R>::C *, int,             \
                                   const typename GridOp<R>::C *, int64_t, double2 *, const int *, int, hipStream_t);

@@ -482,7 +482,8 @@ struct BatchSum {
     unsigned use[BATCH_DIAGS];
 };
 template <class R>
-void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, const int *skip_if, int skip_j, hipStream_t s);
+void batch_launch(BatchStage<R> &st, const GridDesc &g, const uint32_t *keys, int64_t n, const int *skip_if, int skip_j,
+                  hipStream_t s);
 // y = V x + the vectors of ts.  dots: 0, or 1 + nv for the dots <v_i|y> with the nv
 // vectors at Vb and <x|y> (value-major partials); returns their blocks.
 template <class R>
