@@ -24,8 +24,9 @@ namespace {
 // Here the chip holds as many workgroups as fit, each wavefront has the next group's
 // masks on their way while it contracts the current one, and what bounds a launch is
 // the gathers' latency and, with complex factors, the matrix cores.  Measured (FP64):
-// a product of the 4D lattice at 563K functions 158 us (281-319 in passes; 207 over windows
-// of the union, without the look ahead and with 1024 workgroups at any register count),
+// a product of the 4D lattice at 563K functions 150-170 us by card (268-319 in passes; 207
+// over windows of the union, without the look ahead and with 1024 workgroups at any
+// register count),
 // 4D at 74K 15 us (61), 6D quartic at 781K 57 us (81).
 constexpr int BAB = 256;
 // wavefronts per SIMD that the registers of a window allow (workgroups per CU;
